@@ -735,6 +735,7 @@ etc_status etc_moe_layer_create(const etc_model_desc *m, const etc_tile_desc *t,
     const size_t r_max = (size_t)moe_max_row_tiles(m->n_experts, m->top_k, s->max_batch, d.tile_m);
     P.n_layers = 1; P.H = m->hidden; P.E = m->n_experts; P.topk = m->top_k; P.moeF = m->moe_ffn; P.page = 1;
     P.eps = m->rms_eps; P.tile_m = d.tile_m; P.moel = 1; P.max_batch = s->max_batch;
+    P.row_merge = moe_row_merge(d.tile_m, d.H);
     P.col_stride = (int32_t)Tp;
     auto A = [&](auto **p, size_t n) -> bool {
         hipError_t e = dev_alloc(p, n, c->owned);
@@ -742,7 +743,7 @@ etc_status etc_moe_layer_create(const etc_model_desc *m, const etc_tile_desc *t,
         return true;
     };
     bool okk = A(&P.x, T * H) && A(&P.x_mid, T * H) && A(&P.xmg_hi, Tp * H) && A(&P.xmg_lo, Tp * H) &&
-               A(&P.ssq_xmid, (H / 16) * Tp) && A(&c->d_weights, 1) &&
+               A(&P.ssq_xmid, Tp) && A(&c->d_weights, 1) &&
                A(&P.router_logits, Tp * E) && A(&P.topk_ids, rows) && A(&P.topk_w, rows) &&
                A(&P.tok_indptr, E + 1) && A(&P.exp_indptr, E + 1) && A(&P.exp_event, E) && A(&P.perm, rows) && A(&P.inv_perm, rows) &&
                A(&P.perm_tok, rows) && A(&P.tile_expert, r_max) && A(&P.tile_row0, r_max) && A(&P.tile_n, r_max) &&

@@ -10,6 +10,7 @@ constexpr int kMaxBatch = 64;
 constexpr int kMaxLayers = 128;
 constexpr int kMaxExperts = 256;
 constexpr int kMaxTopK = 16;
+constexpr int kMaxBufLd = 131072;         // longest operand row the buffer-descriptor paths take: 4096 gathered rows stay below 2 GB
 constexpr int kLdsBytes = 148 * 1024;    // of the 160 KB LDS per CU: exactly one persistent workgroup per CU
 constexpr int kRsFloats = 64;                     // LDS: RMSNorm factors of the columns
 constexpr int kStagedMaxCols = 16;                // widest batch the staged (latency-critical) projection path takes
@@ -159,6 +160,7 @@ struct Params {
     uint16_t *eact_hi, *eact_lo;       // expert activations, split [maxB*topk, moeF]
     float *ey;                         // expert outputs fp32 [maxB*topk, H]
     int32_t moel;                      // 1: stand-alone MoE layer over a block of B tokens
+    int32_t row_merge;                 // stand-alone MoE layer: row tiles a GroupGEMM row block takes at most
     int32_t *moel_hist;                // [token blocks of 64][E] pairs of the block routed to the expert
     int32_t *moel_base;                // [token blocks][E] first grouped row of the block's pairs of the expert
     int32_t *moel_count;               // [E] pairs routed to the expert

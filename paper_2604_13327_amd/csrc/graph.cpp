@@ -2,6 +2,7 @@
 #include "graph.h"
 
 #include <algorithm>
+#include <cmath>
 #include <sstream>
 
 namespace etc {
@@ -191,6 +192,26 @@ std::string instantiate(const GraphDecl &g, const int *sym, int n_queues, bool u
     return "";
 }
 
+int moe_tiles_per_task(const ModelDims &m, int tokens, int row_block, int per_slot, int K, int n_queues)
+{
+    const double pairs = (double)tokens * m.topk, per_expert = pairs / m.E;
+    const double routed = m.E * (1.0 - std::pow(1.0 - (double)m.topk / m.E, tokens));
+    // an expert with more rows than a block has its full blocks and, half a block on average, one more
+    const double blocks = per_expert <= 0.75 * row_block ? routed : m.E * (per_expert / row_block + 0.5);
+    const double cols = std::min((double)row_block, pairs / blocks);
+    const double tile_bytes = 32.0 * K, operand_bytes = cols * K * 4.0;
+    double best = -1;
+    int best_r = 1;
+    for (int r = 1; r <= per_slot; ++r) {
+        if (per_slot % r) continue;
+        const double rounds = std::ceil(std::floor(blocks + 0.5) * (per_slot / r) / n_queues);
+        const double passes = cols <= 16 ? 1 : (r + 15) / 16;
+        const double cost = rounds * (384.0 * 1024 + r * tile_bytes + passes * operand_bytes);
+        if (best < 0 || cost < best) { best = cost; best_r = r; }
+    }
+    return best_r;
+}
+
 std::string build_decoder_graph(const ModelDims &m, int Bs, int n_queues, bool moe_static_coarse, GraphDecl *out)
 {
     (void)moe_static_coarse;
@@ -272,7 +293,8 @@ std::string build_decoder_graph(const ModelDims &m, int Bs, int n_queues, bool m
     const bool slice_d = g.k_slices_d > 0 && n_ht % pass_d == 0;
     if (!slice_o) g.k_slices_o = 0;
     if (!slice_d) g.k_slices_d = 0;
-    g.all_staged = m.E == 0 && staged_fits(r_qkv, Bs, m.H) && staged_fits(r_gu, Bs, m.H) &&
+    // (the staged-only kernel instances carry one group of 8 columns)
+    g.all_staged = m.E == 0 && Bs <= 8 && staged_fits(r_qkv, Bs, m.H) && staged_fits(r_gu, Bs, m.H) &&
                    (slice_o ? staged_fits(pass_tiles, Bs, m.nq * m.d / g.k_slices_o) : staged_fits(1, Bs, m.nq * m.d)) &&
                    (slice_d ? staged_fits(pass_tiles, Bs, m.F / g.k_slices_d) : staged_fits(1, Bs, m.F));
 
@@ -392,26 +414,8 @@ std::string build_decoder_graph(const ModelDims &m, int Bs, int n_queues, bool m
             // GroupGEMM-2 stays fine-grained: one event per slot.
             const int r_max = moe_max_row_tiles(m.E, m.topk, Bs, m.tile_m);
             const int n_ft = m.moeF / 8;
-            // Row tiles per GroupGEMM task: what a queue takes longest over, in bytes: rounds x (fixed cost of a task +
-            // tiles x bytes of a tile).  The fixed cost (slot look-up, operand gather, first chunk, epilogue, drain:
-            // about 15 us) is worth 384 KB of streaming; rounds = tasks per queue, rounded up (the stage ends with
-            // the queue that holds most).  Against "about three tasks per queue": Qwen3-30B-A3B shape, batch 4 9.4 -> 7.6 ms
-            // per step, batch 8 12.0 -> 11.1, batch 16 .. 64 unchanged.
-            auto tiles_per_task = [&](int per_slot, long long tile_bytes) {
-                long long best = -1;
-                int best_r = 1;
-                const long long cap = 1LL << 20;      // a task streams at most 1 MB (measured on the Qwen3-30B-A3B shape, batch 4 .. 64:
-                                                      // above that the rounds the model saves cost more in passes and imbalance)
-                for (int r = 1; r <= per_slot; ++r) {
-                    if (per_slot % r) continue;
-                    if (r > 1 && r * tile_bytes > cap) continue;
-                    const long long tasks = (long long)r_max * (per_slot / r), rounds = (tasks + n_queues - 1) / n_queues;
-                    const long long cost = rounds * (384LL * 1024 + r * tile_bytes);
-                    if (best < 0 || cost < best) { best = cost; best_r = r; }
-                }
-                return best_r;
-            };
-            const int r_g = tiles_per_task(n_ft, 16LL * m.H * 2), r_d = tiles_per_task(n_ht, 16LL * m.moeF * 2);
+            const int r_g = moe_tiles_per_task(m, Bs, m.tile_m, n_ft, m.H, n_queues);
+            const int r_d = moe_tiles_per_task(m, Bs, m.tile_m, n_ht, m.moeF, n_queues);
             const int e_logits = g.add_event({one});
             const int e_group = g.add_event({one});
             const int e_eact = g.add_event({dim_const(r_max)});
@@ -516,21 +520,9 @@ std::string build_moe_layer_graph(const ModelDims &m, int Ts, int n_queues, Grap
     const DimExpr one = dim_const(1);
     const int n_blk = (Ts + 63) / 64, n_ht = m.H / 16, n_ft = m.moeF / 8;
     const int r_max = moe_max_row_tiles(m.E, m.topk, Ts, m.tile_m);
-    auto tiles_per_task = [&](int per_slot) {
-        const long long total = (long long)r_max * per_slot;
-        const long long want = total <= 4LL * n_queues ? n_queues : 3LL * n_queues;
-        int cand = (int)std::max(1LL, total / std::max(1LL, want));
-        cand = std::min(cand, per_slot);
-        while (cand > 1 && per_slot % cand) --cand;
-        // full row tiles of more than 32 tokens take the wide path, whose pass is 16 row tiles: whole passes, if any
-        if (m.tile_m > 32 && Ts >= 512 && cand >= 16) {
-            int c16 = cand / 16 * 16;
-            while (c16 >= 16 && per_slot % c16) c16 -= 16;
-            if (c16 >= 16) cand = c16;
-        }
-        return std::max(1, cand);
-    };
-    const int r_g = tiles_per_task(n_ft), r_d = tiles_per_task(n_ht);
+    const int row_block = m.tile_m * moe_row_merge(m.tile_m, m.H);
+    const int r_g = moe_tiles_per_task(m, Ts, row_block, n_ft, m.H, n_queues);
+    const int r_d = moe_tiles_per_task(m, Ts, row_block, n_ht, m.moeF, n_queues);
     const int e_x = g.add_event({one});
     const int e_logits = g.add_event({dim_const(n_blk)});
     const int e_hist = g.add_event({one});

@@ -100,6 +100,19 @@ inline int moe_max_row_tiles(int n_experts, int top_k, int batch, int tile_m)
     return (n + nonempty * (tile_m - 1)) / tile_m;
 }
 
+// Row tiles of one expert that a GroupGEMM task of the stand-alone MoE layer takes as one row block: row tiles of more
+// than 32 tokens in pairs, up to the 128 columns of the widest task body.  (Smaller row tiles are the caller's choice for
+// small blocks, where an expert rarely has a second one.)
+inline int moe_row_merge(int tile_m, int hidden) { return tile_m > 32 && hidden <= kMaxBufLd ? 128 / tile_m : 1; }
+
+// Row tiles of the weights a GroupGEMM task streams, of `per_slot` in all (K elements each): what a queue takes longest
+// over, in bytes: rounds x (fixed cost of a task + weights + operand).  The fixed cost (slot look-up, operand, epilogue,
+// drain, hand-over: about 15 us) is worth 384 KB of streaming; rounds = live tasks per queue, rounded up.  The live row
+// blocks are those uniform routing would give: the grid has a slot for every block any routing can produce, but at 100
+// tokens over 128 experts (top-8) 128 blocks live in 138 slots, and two tasks each are one round of 256 queues.  Blocks
+// of more than 16 columns pass over their operand once per 16 tiles.
+int moe_tiles_per_task(const ModelDims &m, int tokens, int row_block, int per_slot, int K, int n_queues);
+
 // Keys per split-KV attention task for one sampled batch size.  `min_chunk` is the caller's tile shape; it
 // is enlarged (in whole pages) until a layer has at most one attention task per queue: every chunk costs a
 // partial result the merge reads back, and a second task per queue only adds such chunks (half a task per

@@ -224,7 +224,7 @@ __device__ __forceinline__ bool setup_gemm(const Params &P, const Task &t, GemmT
         g.rowsB = g.rowsA + (size_t)8 * P.H;
         g.ldw = P.H; g.K = P.H;
         g.b_hi = P.xmg_hi + (size_t)cb * P.H; g.b_lo = P.xmg_lo + (size_t)cb * P.H; g.ldb = P.H;
-        g.ssq_parts = P.ssq_xmid; g.n_parts = P.H / 16; g.eps = P.eps; g.ssq_stride = MOE ? P.col_stride : kMaxBatch;
+        g.ssq_parts = P.ssq_xmid; g.n_parts = P.moel ? 1 : P.H / 16; g.eps = P.eps; g.ssq_stride = MOE ? P.col_stride : kMaxBatch;
         g.ssq_parts += cb;
         g.n_cols = P.B - cb < 64 ? P.B - cb : 64;      // <= 0: a block beyond the bound tokens (the caller skips the tile)
         e.kind = EPI_STORE_F32; e.layer = t.layer; e.row0 = r0; e.outf = P.router_logits + (size_t)cb * P.E; e.ld = P.E;
@@ -267,7 +267,7 @@ __device__ __forceinline__ void setup_moe_gemm(const Params &P, const Task &t, c
         g.ldw = P.H; g.K = P.H;
         g.b_hi = P.xmg_hi; g.b_lo = P.xmg_lo; g.ldb = P.H;
         g.col_rows = P.perm_tok + rt.row0;             // column n reads the hidden state of the row's token
-        g.ssq_parts = P.ssq_xmid; g.n_parts = P.H / 16; g.eps = P.eps; g.ssq_stride = P.col_stride;
+        g.ssq_parts = P.ssq_xmid; g.n_parts = P.moel ? 1 : P.H / 16; g.eps = P.eps; g.ssq_stride = P.col_stride;
         e.kind = EPI_MOE_ACT; e.row0 = f0; e.out_hi = P.eact_hi; e.out_lo = P.eact_lo; e.ld = P.moeF;
     } else {
         const int h0 = t.c1 * 16;
@@ -307,7 +307,8 @@ __device__ __noinline__ WgState staged_task_out_of_line(const Params &PL, Task t
         setup_gemm<MOE, LM>(PL, t, g, e);
         if (mode == 2) slice_of_k(PL, t, t.fn == FN_OPROJ ? PL.k_slices_o : PL.k_slices_d, g, e);
     }
-    gemm_tiles_staged<PF, LM>(PL, g, e, tw, sm, st, t.id);
+    if (g.n_cols <= 8) gemm_tiles_staged<PF / 2, 1, LM>(PL, g, e, tw, sm, st, t.id);
+    else gemm_tiles_staged<PF / 2, 2, LM>(PL, g, e, tw, sm, st, t.id);
     return st;
 }
 
@@ -316,7 +317,7 @@ template <bool MOE, bool LM>
 __device__ __forceinline__ void dispatch_projection(const Params &PL, const Task &t, const TaskWaits &tw, const RowTile &rt, int mode,
                                                     const GemmTile &g, const Epilogue &e, float *sm, WgState &st)
 {
-    if (staged_fits(g.n_tiles, g.n_cols, g.K)) st = staged_task_out_of_line<MOE, LM>(PL, t, tw, rt, mode, sm, st);
+    if (staged_fits(g.n_tiles, g.n_cols, g.K) && !(MOE && mode == 1 && stream_fits(g.n_tiles, g.n_cols, g.K, g.ldb))) st = staged_task_out_of_line<MOE, LM>(PL, t, tw, rt, mode, sm, st);
     else gemm_chunked_dispatch<MOE>(PL, g, e, tw, sm, st, t.id);
 }
 
@@ -373,7 +374,7 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
                 slice_of_k(P, t, t.fn == FN_OPROJ ? P.k_slices_o : P.k_slices_d, g, e);
                 if (w0 >= 0) tw.op_key = w0 + ((t.c1 + 1) << 20);
             }
-            gemm_tiles_staged<10, LM>(P, g, e, tw, sm, st, t.id);
+            gemm_tiles_staged<5, 1, LM>(P, g, e, tw, sm, st, t.id);
         } else {
             dispatch_projection<MOE, LM>(PL, t, tw, RowTile{}, 0, g, e, sm, st);
         }

@@ -20,6 +20,8 @@
 // up rows, plain tiles take 16 consecutive rows.  Partial tiles of the 8 waves are reduced through LDS
 // in a fixed order (deterministic), then the epilogue runs on 8 x columns threads.
 #pragma once
+#include <type_traits>
+
 #include "device_rt.hip.h"
 
 namespace etc {
@@ -73,6 +75,7 @@ __device__ __forceinline__ EpiPre epilogue_preload(const Params &P, const Epilog
 template <bool LM>
 __device__ __forceinline__ void apply_epilogue(const Params &P, const Epilogue &e, int col, int mp, float lo, float hi,
                                                const EpiPre &pre);
+__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 
 constexpr int PF = 16;                            // weight loads in flight per lane (16 KB per wave)
 
@@ -102,12 +105,37 @@ __device__ __forceinline__ void wg_state_init(WgState &st)
 
 __device__ __forceinline__ bool event_known_zero(const WgState &st, int ev) { return ev < 0 || ev == st.zero0 || ev == st.zero1; }
 
-__device__ __forceinline__ const uint16_t *lane_weight_row(const GemmTile &g)
+// Whole lines of weights per load.  The A fragment of the 16x16x32 product is 16 rows x 64 bytes: loaded as it stands, every
+// load touches 16 half lines, and streamed non-temporally that costs a fifth of the rate (256 workgroups, 16 loads in
+// flight per lane: 5.6 - 5.9 TB/s; 8 rows x 128 bytes per load 6.9, contiguous memory 7.0).  So a load takes 8 rows x one
+// UNIT of 64 elements of K: lane (x = lane % 16, kg = lane / 16) the 16-byte piece 2 kg + x % 2 of row x / 2.  In the
+// product, rows x of one parity then hold the pieces of that parity, so the operand is given in the same way: its column
+// n holds the pieces 2 kg + n % 2 of batch column n / 2, and the product of equal parities is the sum over those pieces
+// (the other half of the product is not used).  8 batch columns per product instead of 16: the matrix pipe has room for
+// that up to 16 columns or so, and the operand fragment serves both 8-row groups of a tile.
+constexpr int kUnitK = 64;
+__device__ __forceinline__ const uint16_t *unit_row(const uint16_t *rows, int ldw)
 {
-    const int wave = wave_id(), lane = lane_id();
-    const int m = lane & 15, kg = lane >> 4;
-    const int kbase = wave * (g.K / kWaves) + kg * 8;
-    return (m < 8 ? g.rowsA + (size_t)m * (size_t)g.ldw : g.rowsB + (size_t)(m - 8) * (size_t)g.ldw) + kbase;
+    const int x = lane_id() & 15, kg = lane_id() >> 4;
+    return rows + (size_t)(x >> 1) * (size_t)ldw + (kg * 2 + (x & 1)) * 8;
+}
+// Sums of the two parities: lane (n, kg) gets rows 2 kg and 2 kg + 1 of group n % 2 (0: rowsA, 1: rowsB) for batch column
+// n / 2 of the group of 8.  acc register i of lane (n, kg) is product row 4 kg + i: row 2 kg + i / 2 of its 8, parity i % 2.
+__device__ __forceinline__ void unit_sums(const f32x4 &accA, const f32x4 &accB, float (&v)[2])
+{
+    const bool odd = (lane_id() & 1) != 0;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const float give = odd ? accA[2 * j + 1] : accB[2 * j], keep = odd ? accB[2 * j + 1] : accA[2 * j];
+        v[j] = keep + dpp_f32<0xB1>(give);               // neighbouring lane (quad_perm [1,0,3,2])
+    }
+}
+// Units of K a wavefront takes when the 8 of them split K / 64 units: [first, first + count).
+__device__ __forceinline__ void wave_units(int K, int wave, int &first, int &count)
+{
+    const int n = K / kUnitK;
+    first = n * wave / kWaves;
+    count = n * (wave + 1) / kWaves - first;
 }
 
 // Workgroup wait with a two-entry cache of events already known to have fired.
@@ -146,16 +174,17 @@ __device__ __forceinline__ void wg_wait_cached(const Params &P, WgState &st, int
 //     registers: refilled in front of them it needs other registers, and the copy back at the loop's end
 //     waits for every load of the revolution.
 // With both, every step waits for exactly the oldest of the PF loads (4.08 -> 3.94 ms per 8B step).
-template <int PRE, bool LM>
+template <int PRE, int NG, bool LM>
 __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTile &g, const Epilogue &e, const TaskWaits &w,
                                                   float *sm, WgState &st, int task_id)
 {
-    static_assert(PRE >= 1 && PRE <= PF, "ring slots requested before the wait");
-    const int wave = wave_id(), lane = lane_id();
-    const int m = lane & 15, kg = lane >> 4;
-    const int Kw = g.K / kWaves, n_it = Kw >> 5;
-    const int kbase = wave * Kw + kg * 8;
-    const uint16_t *wcur = lane_weight_row(g);
+    // PRE: ring units requested before the wait; NG: groups of 8 columns (1 or 2)
+    constexpr int PU = PF / 2;                        // a ring unit is two loads: rows A and rows B
+    static_assert(PRE >= 1 && PRE <= PU && (NG == 1 || NG == 2), "ring units requested before the wait, column groups");
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id()), lane = lane_id();
+    const int n16 = lane & 15, kg = lane >> 4;
+    int unit0, n_it;                                  // this wavefront's units of K
+    wave_units(g.K, wave, unit0, n_it);
     const size_t tile_step = (size_t)g.tile_rows * (size_t)g.ldw;
 
     ETC_AS_LDS float *red = as_lds(sm);               // [tile][wave][col][16 rows]
@@ -166,39 +195,42 @@ __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTil
 
     const int key = w.op_key;
     const bool restage = key < 0 || key != st.staged_key;
-    // The task's weights are one linear stream of (tile, step) pairs: step s of tile t sits at wcur + t * tile_step +
-    // 32 s.  The issue cursor runs PF steps ahead of the consume cursor through that stream.
+    // The task's weights are one linear stream of (tile, unit) pairs: unit s of tile t sits t * tile_step + 64 s behind the
+    // first one.  The issue cursor runs PU units ahead of the consume cursor through that stream.
     const int total = g.n_tiles * n_it;
-    const long long tile_jump = (long long)tile_step - (long long)n_it * 32;
-    const uint16_t *ip = wcur;                        // address of the next step to request
-    int is = 0;                                       // its step inside its tile
+    const long long tile_jump = (long long)tile_step - (long long)n_it * kUnitK;
+    const uint16_t *ipA = unit_row(g.rowsA, g.ldw) + unit0 * kUnitK;      // next unit to request
+    const uint16_t *ipB = unit_row(g.rowsB, g.ldw) + unit0 * kUnitK;
+    int is = 0;                                       // its place inside its tile
     auto advance_issue = [&]() {
         ++is;
-        ip += 32;
         const bool wrap = is == n_it;
-        ip += wrap ? tile_jump : 0;
+        const long long by = kUnitK + (wrap ? tile_jump : 0);
+        ipA += by;
+        ipB += by;
         is = wrap ? 0 : is;
     };
     u32x4 wr[PF];
-    // Of the PF ring slots, PRE are requested before the task waits on its events and the rest behind the
-    // operand once the events have fired: the poll and the operand queue behind whatever was prefetched, which
-    // costs the workgroup that arrives last (and sets the stage's end) what it gains the early ones.  Measured:
-    // 8B step (staged-only instance) 8 / 10 / 12 / 14 / 16 slots = 3.95 / 3.88 / 3.88 / 3.95 / 3.92 ms; the MoE
-    // step is 5 % faster with all 16 (its tasks are small and many), so the count is a parameter of the instance.
+    // Of the PU ring units, PRE are requested before the task waits on its events and the rest behind the operand once the
+    // events have fired: the poll and the operand queue behind whatever was prefetched, which costs the workgroup that
+    // arrives last (and sets the stage's end) what it gains the early ones.  Measured: 8B step (staged-only instance)
+    // 4 / 5 / 6 / 7 / 8 units = 3.95 / 3.88 / 3.88 / 3.95 / 3.92 ms; the MoE step is 5 % faster with all 8 (its tasks are
+    // small and many), so the count is a parameter of the instance.
     auto prefetch_range = [&](int j0, int j1) {
 #pragma unroll
-        for (int j = 0; j < PF; ++j) {
+        for (int j = 0; j < PU; ++j) {
             if (j >= j0 && j < j1) {
                 if (j < total) {
-                    wr[j] = load16_nt(ip);
+                    wr[2 * j] = load16_nt(ipA);
+                    wr[2 * j + 1] = load16_nt(ipB);
                     advance_issue();
                 } else {
-                    wr[j] = u32x4{0, 0, 0, 0};
+                    wr[2 * j] = wr[2 * j + 1] = u32x4{0, 0, 0, 0};
                 }
             }
         }
     };
-    auto prefetch = [&]() { prefetch_range(0, PF); };
+    auto prefetch = [&]() { prefetch_range(0, PU); };
     // A task that has nothing to wait for (its events are already known to have fired, or it runs without
     // events in the kernel-by-kernel comparator) issues its operand loads first and the weight stream right
     // behind them: loads return in order, so the operand would otherwise arrive a full round trip under load
@@ -239,25 +271,13 @@ __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTil
         }
         trace_mark(P, task_id, 1);
         // ---- stage the operand: all loads of a thread in flight at once ---------------------------
-        constexpr int U = 8;
-        const int quads = g.K >> 2;                         // 8-byte pieces per column
-        const int total = g.n_cols * quads;
+        constexpr int U = 4;
+        const int ppc = g.K >> 3;                           // 16-byte pieces per column
+        const int total_p = g.n_cols * ppc;
+        const __amdgpu_buffer_rsrc_t hi_b = buf_of(g.b_hi), lo_b = buf_of(g.b_lo);
         float sq[8];                                        // RMSNorm: this lane's partial sums of squares of column `wave`
         const bool one_col_per_wave = g.ssq_parts != nullptr && g.n_cols <= kWaves && g.n_parts <= 512;
-        if (total <= kWgThreads * U) {
-            uint64_t vh[U], vl[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int idx = (int)threadIdx.x + u * kWgThreads;
-                vh[u] = vl[u] = 0;
-                if (idx < total) {
-                    const int col = idx / quads, q = idx - col * quads;
-                    int row = g.col_rows ? ld_i32(g.col_rows + col) : col;
-                    if (row < 0) row = 0;
-                    vh[u] = ld_u64(g.b_hi + (size_t)row * (size_t)g.ldb + q * 4);
-                    vl[u] = ld_u64(g.b_lo + (size_t)row * (size_t)g.ldb + q * 4);
-                }
-            }
+        auto request_norm = [&]() {
             if (one_col_per_wave && wave < g.n_cols) {
                 const int row = g.col_rows ? ld_i32(g.col_rows + wave) : wave;
 #pragma unroll
@@ -266,38 +286,43 @@ __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTil
                     sq[j] = (pt < g.n_parts && row >= 0) ? ld_f32(g.ssq_parts + (size_t)pt * (size_t)g.ssq_stride + row) : 0.f;
                 }
             }
-            request_epilogue_inputs();
-            if (fired) prefetch(); else prefetch_range(PRE, PF);   // right behind the operand loads
+        };
+        u32x4 vh[U], vl[U];
+        uint32_t at[U];
+        int i0 = threadIdx.x;
+        auto load_pieces = [&]() {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int idx = (int)threadIdx.x + u * kWgThreads;
-                if (idx < total) {
-                    const int col = idx / quads, q = idx - col * quads;
-                    *reinterpret_cast<ETC_AS_LDS uint64_t *>(op_hi + (size_t)col * Kp + q * 4) = vh[u];
-                    *reinterpret_cast<ETC_AS_LDS uint64_t *>(op_lo + (size_t)col * Kp + q * 4) = vl[u];
-                }
-            }
-        } else {
-            for (int idx = threadIdx.x; idx < total; idx += kWgThreads) {
-                const int col = idx / quads, q = idx - col * quads;
-                int row = g.col_rows ? ld_i32(g.col_rows + col) : col;
+                const int idx = i0 + u * kWgThreads;
+                const int col = idx < total_p ? idx / ppc : 0, q = idx - col * ppc;
+                int row = col;
+                if (g.col_rows) row = ld_i32(g.col_rows + col);
                 if (row < 0) row = 0;
-                const uint64_t vh = ld_u64(g.b_hi + (size_t)row * (size_t)g.ldb + q * 4);
-                const uint64_t vl = ld_u64(g.b_lo + (size_t)row * (size_t)g.ldb + q * 4);
-                *reinterpret_cast<ETC_AS_LDS uint64_t *>(op_hi + (size_t)col * Kp + q * 4) = vh;
-                *reinterpret_cast<ETC_AS_LDS uint64_t *>(op_lo + (size_t)col * Kp + q * 4) = vl;
+                at[u] = (uint32_t)(col * Kp + q * 8);
+                const uint32_t off = idx < total_p ? ((uint32_t)row * (uint32_t)g.ldb + (uint32_t)q * 8u) * 2u : kBufNone;
+                vh[u] = buf_ld_16B(hi_b, off, 0);
+                vl[u] = buf_ld_16B(lo_b, off, 0);
             }
-            if (one_col_per_wave && wave < g.n_cols) {
-                const int row = g.col_rows ? ld_i32(g.col_rows + wave) : wave;
+        };
+        auto store_pieces = [&]() {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int pt = lane + 64 * j;
-                    sq[j] = (pt < g.n_parts && row >= 0) ? ld_f32(g.ssq_parts + (size_t)pt * (size_t)g.ssq_stride + row) : 0.f;
+            for (int u = 0; u < U; ++u) {
+                if (i0 + u * kWgThreads < total_p) {
+                    *reinterpret_cast<ETC_AS_LDS u32x4 *>(op_hi + at[u]) = vh[u];
+                    *reinterpret_cast<ETC_AS_LDS u32x4 *>(op_lo + at[u]) = vl[u];
                 }
             }
-            request_epilogue_inputs();
-            if (fired) prefetch(); else prefetch_range(PRE, PF);
+        };
+        for (int left = total_p; left > U * kWgThreads; left -= U * kWgThreads) {
+            load_pieces();
+            store_pieces();
+            i0 += U * kWgThreads;
         }
+        load_pieces();       // everything else the task needs is requested behind its last pieces, without a branch around it
+        request_norm();
+        request_epilogue_inputs();
+        if (fired) prefetch(); else prefetch_range(PRE, PU);
+        store_pieces();
         if (g.ssq_parts) {       // RMSNorm factor of every column: fixed-order sum of the producers' partial sums of squares
             if (one_col_per_wave) {
                 if (wave < g.n_cols) {
@@ -326,67 +351,94 @@ __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTil
         } else {
             wg_wait_cached(P, st, w.ev1, -1, w.fn);
             request_epilogue_inputs();
-            prefetch_range(PRE, PF);
+            prefetch_range(PRE, PU);
         }
     }
     trace_mark(P, task_id, 2);
 
-    const bool valid = m < g.n_cols;
-    ETC_AS_LDS const uint16_t *sh = op_hi + (size_t)(valid ? m : 0) * (size_t)Kp + kbase;
-    ETC_AS_LDS const uint16_t *sl = op_lo + (size_t)(valid ? m : 0) * (size_t)Kp + kbase;
-    // Consume cursor: step sc of tile tc.  Columns beyond n_cols read column 0's operand (never stored).
-    f32x4 acc = f32x4{0, 0, 0, 0};
+    // operand fragments: column n16 / 2 of each group of 8, pieces 2 kg + n16 % 2; columns beyond n_cols read column 0's
+    // operand (never stored)
+    ETC_AS_LDS const uint16_t *sh[NG], *sl[NG];
+#pragma unroll
+    for (int ng = 0; ng < NG; ++ng) {
+        const int col = ng * 8 + (n16 >> 1), c = col < g.n_cols ? col : 0;
+        sh[ng] = op_hi + (size_t)c * (size_t)Kp + unit0 * kUnitK + (kg * 2 + (n16 & 1)) * 8;
+        sl[ng] = op_lo + (size_t)c * (size_t)Kp + unit0 * kUnitK + (kg * 2 + (n16 & 1)) * 8;
+    }
+    // Consume cursor: unit sc of tile tc.
+    f32x4 accA[NG], accB[NG];
+#pragma unroll
+    for (int ng = 0; ng < NG; ++ng) accA[ng] = accB[ng] = f32x4{0, 0, 0, 0};
     int sc = 0, tc = 0;
-#define ETC_STAGED_STEP(j, RELOAD)                                                                               \
+    auto store_tile = [&](int t) {      // rows 2 kg, 2 kg + 1 of group n16 % 2, this wavefront's share of K
+#pragma unroll
+        for (int ng = 0; ng < NG; ++ng) {
+            float v[2];
+            unit_sums(accA[ng], accB[ng], v);
+            const int col = ng * 8 + (n16 >> 1);
+            if (col < g.n_cols) {
+                ETC_AS_LDS float *dst = red + ((size_t)(t * kWaves + wave) * g.n_cols + col) * 16 + (n16 & 1) * 8 + 2 * kg;
+                dst[0] = v[0];
+                dst[1] = v[1];
+            }
+            accA[ng] = accB[ng] = f32x4{0, 0, 0, 0};
+        }
+    };
+#define ETC_STAGED_UNIT(j, RELOAD)                                                                               \
     {                                                                                                             \
-        const bf16x8 a = __builtin_bit_cast(bf16x8, wr[j]);                                                       \
-        const u32x4 bh = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(sh + sc * 32);                               \
-        const u32x4 bl = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(sl + sc * 32);                               \
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, bh), acc, 0, 0, 0);           \
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, bl), acc, 0, 0, 0);           \
-        if (RELOAD) {           /* behind the MFMAs that read the slot: the load can land in the same registers */ \
-            wr[j] = load16_nt(ip);                                                                                \
+        const bf16x8 a0 = __builtin_bit_cast(bf16x8, wr[2 * (j)]), a1 = __builtin_bit_cast(bf16x8, wr[2 * (j) + 1]); \
+        _Pragma("unroll") for (int ng = 0; ng < NG; ++ng) {                                                       \
+            const bf16x8 bh = __builtin_bit_cast(bf16x8, *reinterpret_cast<ETC_AS_LDS const u32x4 *>(sh[ng] + sc * kUnitK)); \
+            const bf16x8 bl = __builtin_bit_cast(bf16x8, *reinterpret_cast<ETC_AS_LDS const u32x4 *>(sl[ng] + sc * kUnitK)); \
+            accA[ng] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bh, accA[ng], 0, 0, 0);                        \
+            accB[ng] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bh, accB[ng], 0, 0, 0);                        \
+            accA[ng] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bl, accA[ng], 0, 0, 0);                        \
+            accB[ng] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bl, accB[ng], 0, 0, 0);                        \
+        }                                                                                                         \
+        if (RELOAD) {           /* behind the MFMAs that read the slots: the loads can land in the same registers */ \
+            wr[2 * (j)] = load16_nt(ipA);                                                                         \
+            wr[2 * (j) + 1] = load16_nt(ipB);                                                                     \
             advance_issue();                                                                                      \
         }                                                                                                         \
-        if (++sc == n_it) {     /* tile done: lane holds rows 4*kg .. 4*kg+3 of column m */                       \
-            if (valid)                                                                                            \
-                *reinterpret_cast<ETC_AS_LDS f32x4 *>(red + ((size_t)(tc * kWaves + wave) * g.n_cols + m) * 16 + 4 * kg) = acc; \
-            acc = f32x4{0, 0, 0, 0};                                                                              \
+        if (++sc == n_it) {     /* tile done */                                                                   \
+            store_tile(tc);                                                                                       \
             sc = 0;                                                                                               \
             ++tc;                                                                                                 \
         }                                                                                                         \
     }
-    // Steady state: whole ring revolutions whose look-ahead steps all exist.  No branch around a load here: the
+    // Steady state: whole ring revolutions whose look-ahead units all exist.  No branch around a load here: the
     // compiler places its wait counts per basic block, and a conditional load turns the waits behind it into full
     // drains of the ring.
     int q = 0;
-    for (; q + 2 * PF <= total; q += PF) {
+    for (; q + 2 * PU <= total; q += PU) {
 #pragma unroll
-        for (int j = 0; j < PF; ++j) ETC_STAGED_STEP(j, true)
+        for (int j = 0; j < PU; ++j) ETC_STAGED_UNIT(j, true)
     }
-    if (total - q == PF) {                           // one whole revolution left: nothing to request, nothing to test
+    if (total - q == PU) {                           // one whole revolution left: nothing to request, nothing to test
 #pragma unroll
-        for (int j = 0; j < PF; ++j) ETC_STAGED_STEP(j, false)
+        for (int j = 0; j < PU; ++j) ETC_STAGED_UNIT(j, false)
         q = total;
-    } else if (total - q == PF + PF / 2) {           // one and a half (K = 3.5 revolutions per tile, one tile)
+    } else if (total - q == PU + PU / 2) {           // one and a half (K = 3.5 revolutions per tile, one tile)
 #pragma unroll
-        for (int j = 0; j < PF / 2; ++j) ETC_STAGED_STEP(j, true)
+        for (int j = 0; j < PU / 2; ++j) ETC_STAGED_UNIT(j, true)
 #pragma unroll
-        for (int j = PF / 2; j < PF; ++j) ETC_STAGED_STEP(j, false)
+        for (int j = PU / 2; j < PU; ++j) ETC_STAGED_UNIT(j, false)
 #pragma unroll
-        for (int j = 0; j < PF / 2; ++j) ETC_STAGED_STEP(j, false)
+        for (int j = 0; j < PU / 2; ++j) ETC_STAGED_UNIT(j, false)
         q = total;
     }
-    for (; q < total; q += PF) {                     // the last revolutions of any other length
+    for (; q < total; q += PU) {                     // the last revolutions of any other length
 #pragma unroll
-        for (int j = 0; j < PF; ++j) {
+        for (int j = 0; j < PU; ++j) {
             if (q + j < total) {
-                if (q + j + PF < total) ETC_STAGED_STEP(j, true)
-                else ETC_STAGED_STEP(j, false)
+                if (q + j + PU < total) ETC_STAGED_UNIT(j, true)
+                else ETC_STAGED_UNIT(j, false)
             }
         }
     }
-#undef ETC_STAGED_STEP
+#undef ETC_STAGED_UNIT
+    if (n_it == 0)                                   // K of fewer units than wavefronts: this one has none
+        for (int t = 0; t < g.n_tiles; ++t) store_tile(t);
 
     // ---- one reduction (fixed wave order) and one epilogue for all tiles of the task -------------
     trace_mark(P, task_id, 3);
@@ -460,7 +512,7 @@ __device__ __forceinline__ ChunkedArgs *chunked_args_slot()
 // on every call: 112 registers per lane here, at batch 64 twenty times the bytes the tasks produce.  A callee whose
 // call sites all hand it a piece of the caller's frame cannot be tail-called; the compiler then tells the callers
 // what the callee clobbers instead, and the callers (the task loop) have next to nothing live across the call.
-template <int NB, int T>
+template <int NB, int T, bool BUF16>
 __device__ __noinline__ void gemm_tiles_chunked(const Params &P, const ChunkedArgs *args, float *sm, int *frame_anchor)
 {
     const ChunkedArgs a = lds_get_uniform(args);
@@ -475,8 +527,9 @@ __device__ __noinline__ void gemm_tiles_chunked(const Params &P, const ChunkedAr
     constexpr int S = (4 / NB) < (PFC / T) ? (4 / NB) : (PFC / T);   // MFMA steps per wavefront, chunk and tile
     constexpr int KC = 256 * S;                    // K elements per chunk
     constexpr int STRIDE = KC + 8;                 // LDS column stride in elements: 16 columns cover all banks
-    constexpr int PPC = KC / 4;                    // 8-byte pieces per column and half
-    constexpr int U = COLS * PPC / kWgThreads;     // 8-byte pieces per thread, chunk and half
+    constexpr int PE = BUF16 ? 8 : 4;              // elements of a piece
+    constexpr int PPC = KC / PE;                   // pieces per column and half
+    constexpr int U = COLS * PPC / kWgThreads;     // pieces per thread, chunk and half
     constexpr int BUF = 2 * COLS * STRIDE;         // elements of one buffer: hi columns, then lo columns
     constexpr int CPR = PFC / (T * S);              // chunks per revolution of the ring
     static_assert(COLS * PPC == U * kWgThreads, "every thread moves U pieces of each half");
@@ -512,7 +565,7 @@ __device__ __noinline__ void gemm_tiles_chunked(const Params &P, const ChunkedAr
 #pragma unroll
     for (int j = 0; j < PFC; ++j) {
         const int c = j / (S * T), sidx = (j / T) % S, ti = j % T;
-        if (step_live(c, sidx)) wr[j] = load16_nt(wbase + toff[ti] + c * KC + sidx * 256);
+        if (step_live(c, sidx)) wr[j] = gld_16B(wbase + toff[ti] + c * KC + sidx * 256);
         else wr[j] = u32x4{0, 0, 0, 0};
     }
     // ---- E.wait(): the operand is needed in full, so every K slice event is waited for ---------------
@@ -526,7 +579,9 @@ __device__ __noinline__ void gemm_tiles_chunked(const Params &P, const ChunkedAr
     }
     trace_mark(P, task_id, 1);
 
-    // this thread's pieces of every chunk: piece tid + 512u = (column, 8-byte piece of the column's chunk)
+    // this thread's pieces of every chunk: piece tid + 512u = (column, piece of the column's chunk)
+    using Piece = typename std::conditional<BUF16, u32x4, uint64_t>::type;
+    const __amdgpu_buffer_rsrc_t hi_b = buf_of(g.b_hi), lo_b = buf_of(g.b_lo);
     int rows[U], pcs[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -536,26 +591,31 @@ __device__ __noinline__ void gemm_tiles_chunked(const Params &P, const ChunkedAr
         rows[u] = 0;
         if (col < g.n_cols) rows[u] = g.col_rows ? ld_i32(g.col_rows + col) : col;
         if (rows[u] < 0) rows[u] = 0;
+        if (BUF16)                                 // byte offset from here on; a column beyond n_cols loads nothing
+            rows[u] = col < g.n_cols ? (int)(((uint32_t)rows[u] * (uint32_t)g.ldb + (uint32_t)pcs[u] * PE) * 2u) : (int)kBufNone;
     }
-    uint64_t vh[U], vl[U];
-    auto fetch_chunk = [&](int c) {                // any chunk: pieces beyond K are left out
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            vh[u] = vl[u] = 0;
-            if (c * KC + pcs[u] * 4 < K) {
-                const size_t off = (size_t)rows[u] * (size_t)g.ldb + (size_t)c * KC + pcs[u] * 4;
-                vh[u] = ld_u64(g.b_hi + off);
-                vl[u] = ld_u64(g.b_lo + off);
-            }
-        }
-    };
-    auto fetch_full_chunk = [&](int c) {           // a chunk inside K: no conditions
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const size_t off = (size_t)rows[u] * (size_t)g.ldb + (size_t)c * KC + pcs[u] * 4;
+    Piece vh[U], vl[U];
+    auto fetch_piece = [&](int u, int c) {
+        if constexpr (BUF16) {
+            vh[u] = buf_ld_16B(hi_b, (uint32_t)rows[u], (uint32_t)c * (KC * 2));
+            vl[u] = buf_ld_16B(lo_b, (uint32_t)rows[u], (uint32_t)c * (KC * 2));
+        } else {
+            const size_t off = (size_t)rows[u] * (size_t)g.ldb + (size_t)c * KC + pcs[u] * PE;
             vh[u] = ld_u64(g.b_hi + off);
             vl[u] = ld_u64(g.b_lo + off);
         }
+    };
+    auto fetch_chunk = [&](int c) {                // any chunk: pieces beyond K are left out
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            vh[u] = vl[u] = Piece{};
+            if (c * KC + pcs[u] * PE < K) fetch_piece(u, c);
+        }
+    };
+    auto fetch_full_chunk = [&](int c) {           // a chunk inside K: no conditions, and not sunk towards its use
+#pragma unroll
+        for (int u = 0; u < U; ++u) fetch_piece(u, c);
+        __builtin_amdgcn_sched_barrier(0);
     };
     auto park_chunk = [&](int b) {
         ETC_AS_LDS uint16_t *hi = buf0 + b * BUF, *lo = hi + COLS * STRIDE;
@@ -563,8 +623,8 @@ __device__ __noinline__ void gemm_tiles_chunked(const Params &P, const ChunkedAr
         for (int u = 0; u < U; ++u) {
             const int idx = (int)threadIdx.x + kWgThreads * u;
             const int col = idx / PPC;
-            *reinterpret_cast<ETC_AS_LDS uint64_t *>(hi + col * STRIDE + pcs[u] * 4) = vh[u];
-            *reinterpret_cast<ETC_AS_LDS uint64_t *>(lo + col * STRIDE + pcs[u] * 4) = vl[u];
+            *reinterpret_cast<ETC_AS_LDS Piece *>(hi + col * STRIDE + pcs[u] * PE) = vh[u];
+            *reinterpret_cast<ETC_AS_LDS Piece *>(lo + col * STRIDE + pcs[u] * PE) = vl[u];
         }
     };
     fetch_chunk(0);
@@ -619,7 +679,7 @@ __device__ __noinline__ void gemm_tiles_chunked(const Params &P, const ChunkedAr
         _Pragma("unroll") for (int ti = 0; ti < T; ++ti) {                                                        \
             const int j = ((cc) * S + (sidx)) * T + ti;                                                           \
             const bf16x8 a = __builtin_bit_cast(bf16x8, wr[j]);                                                   \
-            if (RELOAD) wr[j] = load16_nt(wbase + toff[ti] + (size_t)(cn) * KC + (sidx) * 256);                   \
+            if (RELOAD) wr[j] = gld_16B(wbase + toff[ti] + (size_t)(cn) * KC + (sidx) * 256);                   \
             _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) acc[ti][nb] =                                       \
                 __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, fb[nb]), acc[ti][nb], 0, 0, 0); \
         }                                                                                                         \
@@ -701,171 +761,156 @@ __device__ __noinline__ void gemm_tiles_chunked(const Params &P, const ChunkedAr
         __hip_atomic_fetch_max(as_global(P.best + threadIdx.x), lbest[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Wide path: tasks of 5 or more row tiles at any column count (16 * NB columns).  The chunked path splits K over the 8
-// wavefronts, so every wavefront holds accumulators for all tiles of the pass (at 64 columns a pass is 4 tiles: the
-// operand, hi and lo, is read again for every 256 KB of weights) and the tiles meet in a reduction across wavefronts.
-// Here the wavefronts split the OUTPUT instead: each owns TW row tiles of the pass and runs over all of K, the operand
-// chunk in LDS is shared by all of them, and a pass is 8 x TW tiles.  No reduction across wavefronts; the accumulators
-// go through LDS once, into the layout the epilogue threads read.  Measured against the chunked path on whole decode
-// steps (8B shape): batch 16 7.30 -> 6.45 ms, batch 32 8.59 -> 7.57 ms, batch 64 14.0 -> 10.9 ms; 70B shape, batch 32,
-// with 14 - 16 tiles per task (TW = 2, one task per queue instead of two): 58.1 -> 48.4 ms.
-template <int TW, int NB>
-__device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs *args, float *sm, int *frame_anchor)
+// Waits of the task's events (with the weights of its first steps already requested), as in the paths above.
+__device__ __forceinline__ void gemm_wait(const Params &P, const TaskWaits &w)
 {
-    const ChunkedArgs a = lds_get_uniform(args);
-    if (a.task_id == -0x7FFFFFFF) *frame_anchor = 1;      // never true; see gemm_tiles_chunked
-    const GemmTile &g = a.g;
-    const Epilogue &e = a.e;
-    const TaskWaits &w = a.w;
-    const int task_id = a.task_id;
-    constexpr int COLS = 16 * NB, KC = 256, STRIDE = KC + 8, PPC = KC / 4, U = COLS * PPC / kWgThreads;
-    constexpr int BUF = 2 * COLS * STRIDE;         // elements of one operand buffer: hi columns, then lo columns
-    constexpr int PASS = kWaves * TW;              // row tiles per pass
-    constexpr int RING = 8 * TW;                   // weight fragments of one chunk per wavefront = loads in flight per lane
-    static_assert((TW == 1 || TW == 2) && (NB == 1 || NB == 2 || NB == 4), "tiles per wavefront, column blocks");
-    static_assert((size_t)2 * BUF * 2 + (64 + 512) * 4 <= (size_t)kLdsBytes, "two operand buffers and the norm scratch fit");
-    static_assert((size_t)PASS * NB * 256 * 4 <= (size_t)2 * BUF * 2, "the tiles' accumulators alias the operand buffers");
-    const int wave = wave_id(), lane = lane_id();
-    const int m = lane & 15, kg = lane >> 4;
-    const int K = __builtin_amdgcn_readfirstlane(g.K);
-    const int n_chunks = K / KC;                   // K is a multiple of 256
-    const int n_tiles = __builtin_amdgcn_readfirstlane(g.n_tiles);      // <= PASS
-    const size_t tile_step = (size_t)g.tile_rows * (size_t)g.ldw;
-    const uint16_t *wbase = (m < 8 ? g.rowsA + (size_t)m * (size_t)g.ldw : g.rowsB + (size_t)(m - 8) * (size_t)g.ldw) + kg * 8;
-    // a wavefront whose tile lies beyond n_tiles streams the last live tile again and never stores it: no branch in the loop
-    uint32_t toff[TW];
-#pragma unroll
-    for (int t = 0; t < TW; ++t) {
-        const int ti = wave * TW + t;
-        toff[t] = __builtin_amdgcn_readfirstlane((uint32_t)((size_t)(ti < n_tiles ? ti : n_tiles - 1) * tile_step));
-    }
-    ETC_AS_LDS uint16_t *buf0 = reinterpret_cast<ETC_AS_LDS uint16_t *>(as_lds(sm));
-    ETC_AS_LDS float *tb = as_lds(sm);                                    // after the last chunk: [PASS][NB][64 lanes][4]
-    ETC_AS_LDS float *rs = reinterpret_cast<ETC_AS_LDS float *>(buf0 + 2 * BUF);
-    ETC_AS_LDS float *rs_part = rs + 64;                                  // [8][64]
-
-    // ---- weight prefetch before the wait: the fragments of chunk 0 -----------------------------------------
-    u32x4 wr[RING];
-#pragma unroll
-    for (int j = 0; j < RING; ++j) wr[j] = gld_16B(wbase + toff[j % TW] + (j / TW) * 32);
     if (w.per_wave) {
-        if (wave == 0 && lane < kWaves) spin_until_zero(P, w.ev0 + lane, w.fn);
+        if (wave_id() == 0 && lane_id() < kWaves) spin_until_zero(P, w.ev0 + lane_id(), w.fn);
         if (threadIdx.x == 0 && w.ev1 >= 0) spin_until_zero(P, w.ev1, w.fn);
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     } else {
         wg_wait(P, w.ev0, w.ev1, w.fn);
     }
-    trace_mark(P, task_id, 1);
+}
 
-    int rows[U], pcs[U];
+// RMSNorm factors of the columns, first half: thread (column, group) leaves its share of the column's sum of squares in
+// rs_part [512 / NCOL][NCOL].  Behind a barrier norm_factors() adds the shares.
+template <int NCOL>
+__device__ __forceinline__ void norm_shares(const GemmTile &g, ETC_AS_LDS float *rs_part)
+{
+    constexpr int GRPS = kWgThreads / NCOL;
+    const int col = (int)threadIdx.x % NCOL, grp = (int)threadIdx.x / NCOL;
+    int row = -1;
+    if (col < g.n_cols) row = g.col_rows ? ld_i32(g.col_rows + col) : col;
+    float s = 0.f;
+    for (int p0 = grp; p0 < g.n_parts; p0 += GRPS * 16) {
+        float t[16];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int idx = (int)threadIdx.x + kWgThreads * u;
-        const int col = idx / PPC;
-        pcs[u] = idx - col * PPC;
-        rows[u] = 0;
-        if (col < g.n_cols) rows[u] = g.col_rows ? ld_i32(g.col_rows + col) : col;
-        if (rows[u] < 0) rows[u] = 0;
+        for (int j = 0; j < 16; ++j) {
+            const int pt = p0 + GRPS * j;
+            t[j] = (pt < g.n_parts && row >= 0) ? ld_f32(g.ssq_parts + (size_t)pt * (size_t)g.ssq_stride + row) : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) s += t[j];
     }
-    uint64_t vh[U], vl[U];
-    auto fetch_chunk = [&](int c) {
+    rs_part[grp * NCOL + col] = s;
+}
+template <int NCOL>
+__device__ __forceinline__ void norm_factors(const GemmTile &g, ETC_AS_LDS float *rs, const ETC_AS_LDS float *rs_part)
+{
+    if (threadIdx.x >= NCOL) return;
+    float s = 0.f;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const size_t off = (size_t)rows[u] * (size_t)g.ldb + (size_t)c * KC + pcs[u] * 4;
-            vh[u] = ld_u64(g.b_hi + off);
-            vl[u] = ld_u64(g.b_lo + off);
-        }
-    };
-    auto park_chunk = [&](int b) {
-        ETC_AS_LDS uint16_t *hi = buf0 + b * BUF, *lo = hi + COLS * STRIDE;
+    for (int gq = 0; gq < kWgThreads / NCOL; ++gq) s += rs_part[gq * NCOL + threadIdx.x];
+    rs[threadIdx.x] = 1.0f / sqrtf(s / (float)g.K + g.eps);
+}
+
+// Four gate rows and the four matching up rows of a column -> silu(gate) * up, split, 8 bytes each to hi and lo.
+__device__ __forceinline__ void store_swiglu4(__amdgpu_buffer_rsrc_t hi_b, __amdgpu_buffer_rsrc_t lo_b, uint32_t off, const f32x4 &gate,
+                                              const f32x4 &up, float r)
+{
+    uint16_t h[4], l[4];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int idx = (int)threadIdx.x + kWgThreads * u;
-            const int col = idx / PPC;
-            *reinterpret_cast<ETC_AS_LDS uint64_t *>(hi + col * STRIDE + pcs[u] * 4) = vh[u];
-            *reinterpret_cast<ETC_AS_LDS uint64_t *>(lo + col * STRIDE + pcs[u] * 4) = vl[u];
-        }
-    };
-    fetch_chunk(0);
-    if (g.ssq_parts) {       // RMSNorm factors, as in the chunked path
-        const int col = threadIdx.x & 63;
-        int row = -1;
-        if (col < g.n_cols) row = g.col_rows ? ld_i32(g.col_rows + col) : col;
-        float s = 0.f;
-        for (int p0 = wave; p0 < g.n_parts; p0 += 8 * 16) {
-            float t[16];
+    for (int i = 0; i < 4; ++i) split_bf16(silu_f(gate[i] * r) * (up[i] * r), h[i], l[i]);
+    buf_st_8B(hi_b, off, u32x2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)});
+    buf_st_8B(lo_b, off, u32x2{(uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16)});
+}
+
+// Epilogues that need no other thread's rows run straight from the accumulators of a 16-row tile: a lane holds rows
+// 4 kg .. 4 kg + 3 of column nb * 16 + m.  SwiGLU pairs gate row r with up row r + 8, two lane groups further: lanes
+// kg < 2 finish the even column blocks and lanes kg >= 2 the odd ones, after one exchange.
+__device__ __forceinline__ constexpr bool epilogue_is_direct(int kind)
+{
+    return kind == EPI_SWIGLU || kind == EPI_MOE_ACT || kind == EPI_PARTIAL || kind == EPI_MOE_Y;
+}
+template <int NB>
+__device__ __forceinline__ void epilogue_direct(const Epilogue &e, int row0, int n_cols, const f32x4 (&acc)[NB],
+                                                const ETC_AS_LDS float *rs, bool normed)
+{
+    const int lane = lane_id(), m = lane & 15, kg = lane >> 4;
+    if (e.kind == EPI_SWIGLU || e.kind == EPI_MOE_ACT) {
+        const size_t first = e.kind == EPI_MOE_ACT ? (size_t)e.col0 * e.ld : 0;
+        const __amdgpu_buffer_rsrc_t hi_b = buf_of(e.out_hi + first), lo_b = buf_of(e.out_lo + first);
+        const bool lower = kg < 2;
+        const uint32_t f = (uint32_t)(row0 + (kg & 1) * 4);
+        if constexpr (NB == 1) {
+            f32x4 up;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int pt = p0 + 8 * j;
-                t[j] = (pt < g.n_parts && row >= 0) ? ld_f32(g.ssq_parts + (size_t)pt * (size_t)g.ssq_stride + row) : 0.f;
+            for (int i = 0; i < 4; ++i) up[i] = __shfl_xor(acc[0][i], 32, 64);
+            if (lower && m < n_cols) store_swiglu4(hi_b, lo_b, ((uint32_t)m * (uint32_t)e.ld + f) * 2u, acc[0], up, normed ? rs[m] : 1.f);
+        } else {
+#pragma unroll
+            for (int nb = 0; nb < NB; nb += 2) {
+                f32x4 gate, up;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float got = __shfl_xor(lower ? acc[nb + 1][i] : acc[nb][i], 32, 64);
+                    gate[i] = lower ? acc[nb][i] : got;
+                    up[i] = lower ? got : acc[nb + 1][i];
+                }
+                const int col = (lower ? nb : nb + 1) * 16 + m;
+                if (col < n_cols) store_swiglu4(hi_b, lo_b, ((uint32_t)col * (uint32_t)e.ld + f) * 2u, gate, up, normed ? rs[col] : 1.f);
             }
-#pragma unroll
-            for (int j = 0; j < 16; ++j) s += t[j];
         }
-        rs_part[wave * 64 + col] = s;
-    }
-    park_chunk(0);
-    __syncthreads();
-    if (g.ssq_parts && threadIdx.x < 64) {
-        float s = 0.f;
+    } else {
+        const bool partial = e.kind == EPI_PARTIAL;
+        const __amdgpu_buffer_rsrc_t out_b = buf_of(partial ? e.outf : e.outf + (size_t)e.col0 * e.ld);
 #pragma unroll
-        for (int gq = 0; gq < 8; ++gq) s += rs_part[gq * 64 + threadIdx.x];
-        rs[threadIdx.x] = 1.0f / sqrtf(s / (float)g.K + g.eps);
-    }
-    trace_mark(P, task_id, 2);
-
-    f32x4 acc[TW][NB];
-#pragma unroll
-    for (int t = 0; t < TW; ++t)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[t][nb] = f32x4{0, 0, 0, 0};
-    // one chunk: 8 steps of 32 elements of K; RELOAD: ring slots are refilled for the next chunk behind their use
-#define ETC_WIDE_CHUNK(c, RELOAD)                                                                                 \
-    {                                                                                                             \
-        ETC_AS_LDS const uint16_t *hi = buf0 + ((c) & 1) * BUF + m * STRIDE + kg * 8;                             \
-        ETC_AS_LDS const uint16_t *lo = hi + COLS * STRIDE;                                                       \
-        _Pragma("unroll") for (int kk = 0; kk < 8; ++kk) {                                                        \
-            u32x4 fb[NB];                                                                                         \
-            _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                     \
-                fb[nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(hi + nb * 16 * STRIDE + kk * 32);             \
-            _Pragma("unroll") for (int t = 0; t < TW; ++t) {                                                      \
-                const bf16x8 av = __builtin_bit_cast(bf16x8, wr[kk * TW + t]);                                    \
-                _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) acc[t][nb] =                                    \
-                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, fb[nb]), acc[t][nb], 0, 0, 0); \
-            }                                                                                                     \
-            _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                     \
-                fb[nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(lo + nb * 16 * STRIDE + kk * 32);             \
-            _Pragma("unroll") for (int t = 0; t < TW; ++t) {                                                      \
-                const bf16x8 av = __builtin_bit_cast(bf16x8, wr[kk * TW + t]);                                    \
-                if (RELOAD) wr[kk * TW + t] = gld_16B(wbase + toff[t] + (size_t)((c) + 1) * KC + kk * 32);      \
-                _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) acc[t][nb] =                                    \
-                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, fb[nb]), acc[t][nb], 0, 0, 0); \
-            }                                                                                                     \
-        }                                                                                                         \
-    }
-    int c = 0;
-    for (; c + 1 < n_chunks; ++c) {                // every chunk but the last: the next chunk is fetched and the ring refilled
-        fetch_chunk(c + 1);
-        ETC_WIDE_CHUNK(c, true)
-        park_chunk((c + 1) & 1);
-        __syncthreads();
-    }
-    ETC_WIDE_CHUNK(c, false)
-#undef ETC_WIDE_CHUNK
-    __syncthreads();                               // every wavefront is done with the operand buffers
-
-    // ---- accumulators through LDS into the layout of the epilogue threads, then the epilogue tile by tile ----
-    trace_mark(P, task_id, 3);
-#pragma unroll
-    for (int t = 0; t < TW; ++t) {
-        const int ti = wave * TW + t;
-        if (ti < n_tiles) {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                *reinterpret_cast<ETC_AS_LDS f32x4 *>(tb + ((size_t)(ti * NB + nb) * 64 + lane) * 4) = acc[t][nb];
+        for (int nb = 0; nb < NB; ++nb) {
+            const int col = nb * 16 + m;
+            const uint32_t o = partial ? (uint32_t)(((row0 >> 4) * kMaxBatch + col) * 16 + 4 * kg)
+                                       : (uint32_t)col * (uint32_t)e.ld + (uint32_t)(row0 + 4 * kg);
+            if (col < n_cols) buf_st_16B(out_b, o * 4u, __builtin_bit_cast(u32x4, acc[nb]));
         }
     }
+}
+
+// The same from the sums of unit_sums(): lane (n16, kg) has rows 2 kg, 2 kg + 1 of group n16 % 2 of column ng * 8 + n16 / 2;
+// SwiGLU pairs them with the neighbouring lane's, the same rows of the other group.
+template <int NG>
+__device__ __forceinline__ void epilogue_direct_units(const Epilogue &e, int row0, int n_cols, const float (&sums)[NG][2],
+                                                      const ETC_AS_LDS float *rs, bool normed)
+{
+    const int lane = lane_id(), n16 = lane & 15, kg = lane >> 4;
+    if (e.kind == EPI_SWIGLU || e.kind == EPI_MOE_ACT) {
+        const size_t first = e.kind == EPI_MOE_ACT ? (size_t)e.col0 * e.ld : 0;
+        const __amdgpu_buffer_rsrc_t hi_b = buf_of(e.out_hi + first), lo_b = buf_of(e.out_lo + first);
+#pragma unroll
+        for (int ng = 0; ng < NG; ++ng) {
+            const int col = ng * 8 + (n16 >> 1);
+            const float r = normed ? rs[col] : 1.f;
+            const float v0 = sums[ng][0] * r, v1 = sums[ng][1] * r;
+            const float u0 = dpp_f32<0xB1>(v0), u1 = dpp_f32<0xB1>(v1);
+            if ((n16 & 1) == 0 && col < n_cols) {
+                uint16_t h0, l0, h1, l1;
+                split_bf16(silu_f(v0) * u0, h0, l0);
+                split_bf16(silu_f(v1) * u1, h1, l1);
+                const uint32_t o = ((uint32_t)col * (uint32_t)e.ld + (uint32_t)(row0 + 2 * kg)) * 2u;
+                buf_st_4B(hi_b, o, (uint32_t)h0 | ((uint32_t)h1 << 16));
+                buf_st_4B(lo_b, o, (uint32_t)l0 | ((uint32_t)l1 << 16));
+            }
+        }
+    } else {
+        const bool partial = e.kind == EPI_PARTIAL;
+        const __amdgpu_buffer_rsrc_t out_b = buf_of(partial ? e.outf : e.outf + (size_t)e.col0 * e.ld);
+        const int r = (n16 & 1) * 8 + 2 * kg;
+#pragma unroll
+        for (int ng = 0; ng < NG; ++ng) {
+            const int col = ng * 8 + (n16 >> 1);
+            const uint32_t o = partial ? (uint32_t)(((row0 >> 4) * kMaxBatch + col) * 16 + r) : (uint32_t)col * (uint32_t)e.ld + (uint32_t)(row0 + r);
+            if (col < n_cols) buf_st_8B(out_b, o * 4u, u32x2{__float_as_uint(sums[ng][0]), __float_as_uint(sums[ng][1])});
+        }
+    }
+}
+
+// The epilogues that need other threads' rows, tile by tile out of LDS (the caller has written the tiles, no barrier yet).
+template <int NB>
+__device__ __forceinline__ void tiles_epilogue(const Params &P, const ChunkedArgs &a, const ETC_AS_LDS float *tb, const ETC_AS_LDS float *rs,
+                                               ETC_AS_LDS float *rs_part, int n_tiles)
+{
+    const GemmTile &g = a.g;
+    const Epilogue &e = a.e;
     ETC_AS_LDS unsigned long long *lbest = reinterpret_cast<ETC_AS_LDS unsigned long long *>(rs_part);
     const bool to_best = e.kind == EPI_LOGITS;
     if (to_best && (int)threadIdx.x < g.n_cols) lbest[threadIdx.x] = 0ull;
@@ -895,11 +940,787 @@ __device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs 
         __hip_atomic_fetch_max(as_global(P.best + threadIdx.x), lbest[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Passes of the wide path: 8 x TW row tiles each.
-template <int TW, int NB>
+// Wide path: tasks of 5 or more row tiles at any column count (16 * NB columns, up to 128).  The chunked path splits K
+// over the 8 wavefronts, so every wavefront holds accumulators for all tiles of the pass (at 64 columns a pass is 4
+// tiles: the operand, hi and lo, is read again for every 256 KB of weights) and the tiles meet in a reduction across
+// wavefronts.  Here the wavefronts split the OUTPUT instead: each owns TW row tiles of the pass and runs over all of K,
+// the operand chunk in LDS (double buffered) is shared by all of them, and a pass is 8 x TW tiles.  No reduction across
+// wavefronts, and the epilogues that allow it run straight from the accumulators.
+// What bounds it is bytes in flight per compute unit: the ring holds RD chunks of weights per wavefront (128 KB per unit)
+// next to one chunk of the operand in registers.  128 columns (a GroupGEMM row block) halve the chunk, so that two
+// buffers still fit: a block of 128 columns x 256 rows moves 1 KB per element of K for 131 kflop.
+template <int TW, int NB, int KH>
+__device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs *args, float *sm, int *frame_anchor)
+{
+    const ChunkedArgs a = lds_get_uniform(args);
+    if (a.task_id == -0x7FFFFFFF) *frame_anchor = 1;      // never true; see gemm_tiles_chunked
+    const GemmTile &g = a.g;
+    const Epilogue &e = a.e;
+    const TaskWaits &w = a.w;
+    const int task_id = a.task_id;
+    constexpr int COLS = 16 * NB, KC = NB == 8 ? 128 : 256, KS = KC / 32, STRIDE = KC + 8;
+    constexpr int PPC = KC / 8;                    // 16-byte pieces per column and half
+    constexpr int U = COLS * PPC / kWgThreads;     // pieces per thread, chunk and half
+    constexpr int BUF = 2 * COLS * STRIDE;         // elements of one operand buffer: hi columns, then lo columns
+    constexpr int PASS = kWaves / KH * TW;         // row tiles per pass
+    constexpr int KSW = KS / KH;                   // k steps of a chunk that one wavefront takes: kh * KSW on (whole 128-byte lines)
+    constexpr int RD = KSW * TW >= 16 || NB == 8 ? 1 : 16 / (KSW * TW);      // chunks of weights in flight
+    constexpr int RING = KSW * TW * RD;            // weight fragments in flight per lane
+    constexpr int FD = KH == 2 && NB < 4 ? 2 : 1;   // chunks of the operand in flight, as the registers allow
+    constexpr int NCOL = COLS < 64 ? 64 : COLS, GRPS = kWgThreads / NCOL;      // norm factors: threads (column, group)
+    static_assert((KH == 1 || (KH == 2 && TW % 2 == 0)) && (NB == 1 || NB == 2 || NB == 4 || NB == 8), "wavefronts per row group, column blocks");
+    static_assert(U >= 1 && COLS * PPC == U * kWgThreads && RD <= 2, "every thread moves U pieces of each half");
+    static_assert((size_t)2 * BUF * 2 + (NCOL + kWgThreads) * 4 <= (size_t)kLdsBytes, "two operand buffers and the norm scratch fit");
+    static_assert((size_t)PASS * NB * 256 * 4 <= (size_t)2 * BUF * 2, "the tiles' accumulators alias the operand buffers");
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id()), lane = lane_id();
+    const int rg = wave / KH, kh = wave % KH;      // row group and share of K of this wavefront
+    const int m = lane & 15, kg = lane >> 4;
+    const int K = __builtin_amdgcn_readfirstlane(g.K);
+    const int n_chunks = K / KC;                   // K is a multiple of 256
+    const int n_tiles = __builtin_amdgcn_readfirstlane(g.n_tiles);      // <= PASS
+    const size_t tile_step = (size_t)g.tile_rows * (size_t)g.ldw;
+    const uint16_t *wbase = (m < 8 ? g.rowsA + (size_t)m * (size_t)g.ldw : g.rowsB + (size_t)(m - 8) * (size_t)g.ldw) + kg * 8 + kh * (KSW * 32);
+    // a wavefront whose tile lies beyond n_tiles streams the last live tile again and never stores it: no branch in the loop
+    uint32_t toff[TW];
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+        const int ti = rg * TW + t;
+        toff[t] = __builtin_amdgcn_readfirstlane((uint32_t)((size_t)(ti < n_tiles ? ti : n_tiles - 1) * tile_step));
+    }
+    ETC_AS_LDS uint16_t *buf0 = reinterpret_cast<ETC_AS_LDS uint16_t *>(as_lds(sm));
+    ETC_AS_LDS float *tb = as_lds(sm);                                    // after the last chunk: [PASS][NB][64 lanes][4]
+    ETC_AS_LDS float *rs = reinterpret_cast<ETC_AS_LDS float *>(buf0 + 2 * BUF);
+    ETC_AS_LDS float *rs_part = rs + NCOL;                                // [GRPS][NCOL]
+
+    // ---- weight prefetch before the wait: the fragments of the first RD chunks -------------------------------
+    u32x4 wr[RING];
+#pragma unroll
+    for (int j = 0; j < RING; ++j) {
+        const int k = (j / TW / KSW) * KC + (j / TW % KSW) * 32;               // beyond K (one chunk, two in the ring): the last one again, never used
+        wr[j] = gld_16B(wbase + toff[j % TW] + (RD == 1 || k < K ? k : 0));
+    }
+    if (w.per_wave) {
+        if (wave == 0 && lane < kWaves) spin_until_zero(P, w.ev0 + lane, w.fn);
+        if (threadIdx.x == 0 && w.ev1 >= 0) spin_until_zero(P, w.ev1, w.fn);
+        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    } else {
+        wg_wait(P, w.ev0, w.ev1, w.fn);
+    }
+    trace_mark(P, task_id, 1);
+
+    const __amdgpu_buffer_rsrc_t hi_b = buf_of(g.b_hi), lo_b = buf_of(g.b_lo);
+    uint32_t off[U];                               // byte offset of this thread's pieces in chunk 0
+    const int pc = (int)threadIdx.x % PPC;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int col = ((int)threadIdx.x + kWgThreads * u) / PPC;
+        int row = 0;
+        if (col < g.n_cols) row = g.col_rows ? ld_i32(g.col_rows + col) : col;
+        if (row < 0) row = 0;
+        off[u] = col < g.n_cols ? ((uint32_t)row * (uint32_t)g.ldb + (uint32_t)pc * 8u) * 2u : kBufNone;
+    }
+    u32x4 vh[FD][U], vl[FD][U];                    // pieces in flight: set c % FD holds chunk c
+    auto fetch_chunk = [&](int c, u32x4 (&h)[U], u32x4 (&l)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            h[u] = buf_ld_16B(hi_b, off[u], (uint32_t)c * (KC * 2));
+            l[u] = buf_ld_16B(lo_b, off[u], (uint32_t)c * (KC * 2));
+        }
+    };
+    auto park_chunk = [&](int b, const u32x4 (&h)[U], const u32x4 (&l)[U]) {
+        ETC_AS_LDS uint16_t *hi = buf0 + b * BUF, *lo = hi + COLS * STRIDE;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int col = ((int)threadIdx.x + kWgThreads * u) / PPC;
+            *reinterpret_cast<ETC_AS_LDS u32x4 *>(hi + col * STRIDE + pc * 8) = h[u];
+            *reinterpret_cast<ETC_AS_LDS u32x4 *>(lo + col * STRIDE + pc * 8) = l[u];
+        }
+    };
+    fetch_chunk(0, vh[0], vl[0]);
+    if (FD == 2 && n_chunks > 1) fetch_chunk(1, vh[FD - 1], vl[FD - 1]);
+    if (g.ssq_parts) {       // RMSNorm factors, as in the chunked path
+        const int col = (int)threadIdx.x % NCOL, grp = (int)threadIdx.x / NCOL;
+        int row = -1;
+        if (col < g.n_cols) row = g.col_rows ? ld_i32(g.col_rows + col) : col;
+        float s = 0.f;
+        for (int p0 = grp; p0 < g.n_parts; p0 += GRPS * 16) {
+            float t[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int pt = p0 + GRPS * j;
+                t[j] = (pt < g.n_parts && row >= 0) ? ld_f32(g.ssq_parts + (size_t)pt * (size_t)g.ssq_stride + row) : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < 16; ++j) s += t[j];
+        }
+        rs_part[grp * NCOL + col] = s;
+    }
+    park_chunk(0, vh[0], vl[0]);
+    __syncthreads();
+    if (g.ssq_parts && threadIdx.x < NCOL) {
+        float s = 0.f;
+#pragma unroll
+        for (int gq = 0; gq < GRPS; ++gq) s += rs_part[gq * NCOL + threadIdx.x];
+        rs[threadIdx.x] = 1.0f / sqrtf(s / (float)g.K + g.eps);
+    }
+    trace_mark(P, task_id, 2);
+
+    f32x4 acc[TW][NB];
+#pragma unroll
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[t][nb] = f32x4{0, 0, 0, 0};
+    // Chunk c out of ring part r: KS steps of 32 elements of K, hi and lo products in turn.  RELOAD: a slot is refilled for
+    // chunk c + RD behind its use.  The scheduling barriers keep the order as written: left to itself the compiler sinks
+    // the loads of the next chunk to the end of this one, next to their use, and the LDS reads to the products that need
+    // them; here the fragments of the next half step are read while the products of this one run.
+#define ETC_WIDE_CHUNK(c, r, RELOAD)                                                                              \
+    {                                                                                                             \
+        ETC_AS_LDS const uint16_t *hi = buf0 + ((c) & 1) * BUF + m * STRIDE + kg * 8 + kh * (KSW * 32);                             \
+        ETC_AS_LDS const uint16_t *lo = hi + COLS * STRIDE;                                                       \
+        u32x4 fh[NB], fl[NB];                                                                                     \
+        _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                         \
+            fh[nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(hi + nb * 16 * STRIDE);                          \
+        __builtin_amdgcn_sched_barrier(0);                                                                        \
+        _Pragma("unroll") for (int kk = 0; kk < KSW; ++kk) {                                                       \
+            _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                     \
+                fl[nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(lo + nb * 16 * STRIDE + kk * 32);             \
+            _Pragma("unroll") for (int t = 0; t < TW; ++t) {                                                      \
+                const bf16x8 av = __builtin_bit_cast(bf16x8, wr[((r) * KSW + kk) * TW + t]);                       \
+                _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) acc[t][nb] =                                    \
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, fh[nb]), acc[t][nb], 0, 0, 0); \
+            }                                                                                                     \
+            __builtin_amdgcn_sched_barrier(0);                                                                    \
+            if (kk + 1 < KSW) {                                                                                    \
+                _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                 \
+                    fh[nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(hi + nb * 16 * STRIDE + (kk + 1) * 32);   \
+            }                                                                                                     \
+            _Pragma("unroll") for (int t = 0; t < TW; ++t) {                                                      \
+                const int j = ((r) * KSW + kk) * TW + t;                                                           \
+                const bf16x8 av = __builtin_bit_cast(bf16x8, wr[j]);                                              \
+                _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) acc[t][nb] =                                    \
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, fl[nb]), acc[t][nb], 0, 0, 0); \
+            }                                                                                                     \
+            __builtin_amdgcn_sched_barrier(0);                                                                    \
+            if (RELOAD) {                                                                                         \
+                _Pragma("unroll") for (int t = 0; t < TW; ++t) wr[((r) * KSW + kk) * TW + t] =                     \
+                    gld_16B(wbase + toff[t] + (size_t)((c) + RD) * KC + kk * 32);                                \
+            }                                                                                                     \
+        }                                                                                                         \
+        __builtin_amdgcn_sched_barrier(0);                                                                        \
+    }
+    // one chunk of parity p: request the operand FD chunks ahead, compute, park the next chunk's operand
+#define ETC_WIDE_STEP(c, p, FETCH, RELOAD, PARK)                                                                  \
+    {                                                                                                             \
+        if (FETCH) fetch_chunk((c) + FD, vh[(p) % FD], vl[(p) % FD]);                                             \
+        ETC_WIDE_CHUNK(c, (p) % RD, RELOAD)                                                                       \
+        if (PARK) {                                                                                               \
+            park_chunk(((p) + 1) & 1, vh[((p) + 1) % FD], vl[((p) + 1) % FD]);                                    \
+            __syncthreads();                                                                                      \
+        }                                                                                                         \
+    }
+    int c = 0;
+    if constexpr (RD == 1 && FD == 1) {
+        for (; c + 1 < n_chunks; ++c) {            // steady state: the next chunk exists
+            fetch_chunk(c + 1, vh[0], vl[0]);
+            ETC_WIDE_CHUNK(c, 0, true)
+            park_chunk((c + 1) & 1, vh[0], vl[0]);
+            __syncthreads();
+        }
+        ETC_WIDE_CHUNK(c, 0, false)
+    } else {
+        for (; c + 4 <= n_chunks; c += 2) {        // steady state: everything ahead exists; c is even
+            ETC_WIDE_STEP(c, 0, true, true, true)
+            ETC_WIDE_STEP(c + 1, 1, true, true, true)
+        }
+        if (n_chunks - c == 3) {
+            ETC_WIDE_STEP(c, 0, true, true, true)
+            ETC_WIDE_STEP(c + 1, 1, FD == 1, RD == 1, true)
+            ETC_WIDE_STEP(c + 2, 0, false, false, false)
+        } else if (n_chunks - c == 2) {
+            ETC_WIDE_STEP(c, 0, FD == 1, RD == 1, true)
+            ETC_WIDE_STEP(c + 1, 1, false, false, false)
+        } else {
+            ETC_WIDE_STEP(c, 0, false, false, false)
+        }
+    }
+#undef ETC_WIDE_STEP
+#undef ETC_WIDE_CHUNK
+    trace_mark(P, task_id, 3);
+
+    // ---- KH == 2: the two wavefronts of a row group hold sums over half of K each; each finishes half of the tiles ----
+    constexpr int TF = TW / KH;                    // tiles a wavefront finishes: rg * TW + kh * TF + t
+    f32x4 sum[TF][NB];
+    if constexpr (KH == 2) {
+        __syncthreads();                           // every wavefront is done with the operand buffers
+#pragma unroll
+        for (int t = 0; t < TF; ++t)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                *reinterpret_cast<ETC_AS_LDS f32x4 *>(tb + ((size_t)((wave * TF + t) * NB + nb) * 64 + lane) * 4) = kh ? acc[t][nb] : acc[TF + t][nb];
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < TF; ++t)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                sum[t][nb] = (kh ? acc[TF + t][nb] : acc[t][nb]) +
+                             *reinterpret_cast<ETC_AS_LDS const f32x4 *>(tb + ((size_t)(((wave ^ 1) * TF + t) * NB + nb) * 64 + lane) * 4);
+    } else {
+#pragma unroll
+        for (int t = 0; t < TF; ++t)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) sum[t][nb] = acc[t][nb];
+    }
+    if (epilogue_is_direct(e.kind)) {
+#pragma unroll
+        for (int t = 0; t < TF; ++t) {
+            const int ti = rg * TW + kh * TF + t;
+            if (ti < n_tiles) epilogue_direct<NB>(e, e.row0 + ti * g.tile_rows, g.n_cols, sum[t], rs, g.ssq_parts != nullptr);
+        }
+        __syncthreads();                           // the next pass parks its operand over these buffers
+        return;
+    }
+    // ---- sums through LDS into the layout of the epilogue threads, then the epilogue tile by tile ----
+    __syncthreads();                               // the buffers (KH == 2: the exchanged halves) have been read
+#pragma unroll
+    for (int t = 0; t < TF; ++t) {
+        const int ti = rg * TW + kh * TF + t;
+        if (ti < n_tiles) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                *reinterpret_cast<ETC_AS_LDS f32x4 *>(tb + ((size_t)(ti * NB + nb) * 64 + lane) * 4) = sum[t][nb];
+        }
+    }
+    tiles_epilogue<NB>(P, a, tb, rs, rs_part, n_tiles);
+}
+
+// The wide path for up to 32 columns (NG groups of 8), with whole lines of weights per load (see unit_row): the same split
+// of the output over the wavefronts and the same operand buffers, but a ring entry is 8 rows x one unit of K, streamed
+// non-temporally, and the products run on 8 columns each.  Twice the matrix instructions (12 us of a 35 us gate/up stage
+// at 32 columns), which is why 64 columns stay with the fragments above.
+template <int TW, int NG>
+__device__ __noinline__ void gemm_tiles_lines(const Params &P, const ChunkedArgs *args, float *sm, int *frame_anchor)
+{
+    const ChunkedArgs a = lds_get_uniform(args);
+    if (a.task_id == -0x7FFFFFFF) *frame_anchor = 1;      // never true; see gemm_tiles_chunked
+    const GemmTile &g = a.g;
+    const Epilogue &e = a.e;
+    constexpr int COLS = 8 * NG, NB = NG / 2, KC = 256, STRIDE = KC + 16;      // 32 bytes more per column: a fragment read hits every bank once
+    constexpr int PPC = KC / 8, U = COLS * PPC / kWgThreads, BUF = 2 * COLS * STRIDE;
+    constexpr int PASS = kWaves * TW;
+    constexpr int KSW = KC / kUnitK;               // units of a chunk
+    constexpr int RD = KSW * TW >= 8 ? 1 : 8 / (KSW * TW);      // chunks of weights in flight
+    constexpr int RING = KSW * TW * RD * 2;        // loads in flight per lane: rows A and rows B of every unit
+    constexpr int FD = NG == 2 ? 2 : 1;            // chunks of the operand in flight, as the registers allow
+    static_assert((NG == 2 || NG == 4) && RD <= 2 && U >= 1 && COLS * PPC == U * kWgThreads, "shapes");
+    static_assert((size_t)2 * BUF * 2 + (64 + kWgThreads) * 4 <= (size_t)kLdsBytes, "two operand buffers and the norm scratch fit");
+    static_assert((size_t)PASS * NB * 256 * 4 <= (size_t)2 * BUF * 2, "the tiles' sums alias the operand buffers");
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id()), lane = lane_id();
+    const int n16 = lane & 15, kg = lane >> 4;
+    const int K = __builtin_amdgcn_readfirstlane(g.K), n_chunks = K / KC;
+    const int n_tiles = __builtin_amdgcn_readfirstlane(g.n_tiles);
+    const size_t tile_step = (size_t)g.tile_rows * (size_t)g.ldw;
+    const uint16_t *wA = unit_row(g.rowsA, g.ldw), *wB = unit_row(g.rowsB, g.ldw);
+    uint32_t toff[TW];                             // a tile beyond n_tiles streams the last live one again and is never stored
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+        const int ti = wave * TW + t;
+        toff[t] = __builtin_amdgcn_readfirstlane((uint32_t)((size_t)(ti < n_tiles ? ti : n_tiles - 1) * tile_step));
+    }
+    ETC_AS_LDS uint16_t *buf0 = reinterpret_cast<ETC_AS_LDS uint16_t *>(as_lds(sm));
+    ETC_AS_LDS float *tb = as_lds(sm);             // after the last chunk
+    ETC_AS_LDS float *rs = reinterpret_cast<ETC_AS_LDS float *>(buf0 + 2 * BUF), *rs_part = rs + 64;
+
+    u32x4 wr[RING];
+#pragma unroll
+    for (int j = 0; j < RING / 2; ++j) {           // ring entry (chunk, unit, tile)
+        const int k = (j / TW / KSW) * KC + (j / TW % KSW) * kUnitK;
+        const uint32_t o = toff[j % TW] + (uint32_t)(RD == 1 || k < K ? k : 0);      // beyond K (one chunk, two in the ring): never used
+        wr[2 * j] = load16_nt(wA + o);
+        wr[2 * j + 1] = load16_nt(wB + o);
+    }
+    gemm_wait(P, a.w);
+    trace_mark(P, a.task_id, 1);
+
+    const __amdgpu_buffer_rsrc_t hi_b = buf_of(g.b_hi), lo_b = buf_of(g.b_lo);
+    uint32_t off[U];
+    const int pc = (int)threadIdx.x % PPC;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int col = ((int)threadIdx.x + kWgThreads * u) / PPC;
+        int row = 0;
+        if (col < g.n_cols) row = g.col_rows ? ld_i32(g.col_rows + col) : col;
+        if (row < 0) row = 0;
+        off[u] = col < g.n_cols ? ((uint32_t)row * (uint32_t)g.ldb + (uint32_t)pc * 8u) * 2u : kBufNone;
+    }
+    u32x4 vh[FD][U], vl[FD][U];
+    auto fetch_chunk = [&](int c, u32x4 (&h)[U], u32x4 (&l)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            h[u] = buf_ld_16B(hi_b, off[u], (uint32_t)c * (KC * 2));
+            l[u] = buf_ld_16B(lo_b, off[u], (uint32_t)c * (KC * 2));
+        }
+    };
+    auto park_chunk = [&](int b, const u32x4 (&h)[U], const u32x4 (&l)[U]) {
+        ETC_AS_LDS uint16_t *hi = buf0 + b * BUF, *lo = hi + COLS * STRIDE;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int col = ((int)threadIdx.x + kWgThreads * u) / PPC;
+            *reinterpret_cast<ETC_AS_LDS u32x4 *>(hi + col * STRIDE + pc * 8) = h[u];
+            *reinterpret_cast<ETC_AS_LDS u32x4 *>(lo + col * STRIDE + pc * 8) = l[u];
+        }
+    };
+    fetch_chunk(0, vh[0], vl[0]);
+    if (FD == 2 && n_chunks > 1) fetch_chunk(1, vh[FD - 1], vl[FD - 1]);
+    if (g.ssq_parts) norm_shares<64>(g, rs_part);
+    park_chunk(0, vh[0], vl[0]);
+    __syncthreads();
+    if (g.ssq_parts) norm_factors<64>(g, rs, rs_part);        // read behind the barrier after the last chunk
+    trace_mark(P, a.task_id, 2);
+
+    f32x4 acc[TW][2][NG];
+#pragma unroll
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+        for (int ng = 0; ng < NG; ++ng) acc[t][0][ng] = acc[t][1][ng] = f32x4{0, 0, 0, 0};
+    // chunk c out of ring part r, in the order as written (see ETC_WIDE_CHUNK)
+#define ETC_LINES_CHUNK(c, r, RELOAD)                                                                             \
+    {                                                                                                             \
+        ETC_AS_LDS const uint16_t *hi = buf0 + ((c) & 1) * BUF + (n16 >> 1) * STRIDE + (kg * 2 + (n16 & 1)) * 8; \
+        ETC_AS_LDS const uint16_t *lo = hi + COLS * STRIDE;                                                       \
+        u32x4 fh[NG], fl[NG];                                                                                     \
+        _Pragma("unroll") for (int ng = 0; ng < NG; ++ng)                                                         \
+            fh[ng] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(hi + ng * 8 * STRIDE);                           \
+        __builtin_amdgcn_sched_barrier(0);                                                                        \
+        _Pragma("unroll") for (int kk = 0; kk < KSW; ++kk) {                                                      \
+            _Pragma("unroll") for (int ng = 0; ng < NG; ++ng)                                                     \
+                fl[ng] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(lo + ng * 8 * STRIDE + kk * kUnitK);          \
+            _Pragma("unroll") for (int t = 0; t < TW; ++t)                                                        \
+                _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                   \
+                    const bf16x8 av = __builtin_bit_cast(bf16x8, wr[(((r) * KSW + kk) * TW + t) * 2 + h]);        \
+                    _Pragma("unroll") for (int ng = 0; ng < NG; ++ng) acc[t][h][ng] =                             \
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, fh[ng]), acc[t][h][ng], 0, 0, 0); \
+                }                                                                                                 \
+            __builtin_amdgcn_sched_barrier(0);                                                                    \
+            if (kk + 1 < KSW) {                                                                                   \
+                _Pragma("unroll") for (int ng = 0; ng < NG; ++ng)                                                 \
+                    fh[ng] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(hi + ng * 8 * STRIDE + (kk + 1) * kUnitK); \
+            }                                                                                                     \
+            _Pragma("unroll") for (int t = 0; t < TW; ++t)                                                        \
+                _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                   \
+                    const bf16x8 av = __builtin_bit_cast(bf16x8, wr[(((r) * KSW + kk) * TW + t) * 2 + h]);        \
+                    _Pragma("unroll") for (int ng = 0; ng < NG; ++ng) acc[t][h][ng] =                             \
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, fl[ng]), acc[t][h][ng], 0, 0, 0); \
+                }                                                                                                 \
+            __builtin_amdgcn_sched_barrier(0);                                                                    \
+            if (RELOAD) {                                                                                         \
+                _Pragma("unroll") for (int t = 0; t < TW; ++t) {                                                  \
+                    const int j = (((r) * KSW + kk) * TW + t) * 2;                                                \
+                    const size_t o = toff[t] + (size_t)((c) + RD) * KC + kk * kUnitK;                             \
+                    wr[j] = load16_nt(wA + o);                                                                    \
+                    wr[j + 1] = load16_nt(wB + o);                                                                \
+                }                                                                                                 \
+            }                                                                                                     \
+        }                                                                                                         \
+        __builtin_amdgcn_sched_barrier(0);                                                                        \
+    }
+    // one chunk of parity p: request the operand FD chunks ahead, compute, park the next chunk's operand
+#define ETC_LINES_STEP(c, p, FETCH, RELOAD, PARK)                                                                 \
+    {                                                                                                             \
+        if (FETCH) fetch_chunk((c) + FD, vh[(p) % FD], vl[(p) % FD]);                                             \
+        ETC_LINES_CHUNK(c, (p) % RD, RELOAD)                                                                      \
+        if (PARK) {                                                                                               \
+            park_chunk((p) ^ 1, vh[((p) + 1) % FD], vl[((p) + 1) % FD]);                                          \
+            __syncthreads();                                                                                      \
+        }                                                                                                         \
+    }
+    int c = 0;
+    if constexpr (RD == 1 && FD == 1) {
+        for (; c + 1 < n_chunks; ++c) {            // steady state: the next chunk exists
+            fetch_chunk(c + 1, vh[0], vl[0]);
+            ETC_LINES_CHUNK(c, 0, true)
+            park_chunk((c + 1) & 1, vh[0], vl[0]);
+            __syncthreads();
+        }
+        ETC_LINES_CHUNK(c, 0, false)
+    } else {
+        for (; c + 4 <= n_chunks; c += 2) {        // steady state: everything ahead exists; c is even
+            ETC_LINES_STEP(c, 0, true, true, true)
+            ETC_LINES_STEP(c + 1, 1, true, true, true)
+        }
+        if (n_chunks - c == 3) {
+            ETC_LINES_STEP(c, 0, true, true, true)
+            ETC_LINES_STEP(c + 1, 1, FD == 1, RD == 1, true)
+            ETC_LINES_STEP(c + 2, 0, false, false, false)
+        } else if (n_chunks - c == 2) {
+            ETC_LINES_STEP(c, 0, FD == 1, RD == 1, true)
+            ETC_LINES_STEP(c + 1, 1, false, false, false)
+        } else {
+            ETC_LINES_STEP(c, 0, false, false, false)
+        }
+    }
+#undef ETC_LINES_STEP
+#undef ETC_LINES_CHUNK
+    trace_mark(P, a.task_id, 3);
+
+    // ---- sums: lane (n16, kg) has rows 2 kg, 2 kg + 1 of group n16 % 2 for column ng * 8 + n16 / 2 ----
+    float v[TW][NG][2];
+#pragma unroll
+    for (int t = 0; t < TW; ++t)
+#pragma unroll
+        for (int ng = 0; ng < NG; ++ng) unit_sums(acc[t][0][ng], acc[t][1][ng], v[t][ng]);
+    __syncthreads();                               // every wavefront is done with the operand buffers
+    if (epilogue_is_direct(e.kind)) {
+#pragma unroll
+        for (int t = 0; t < TW; ++t) {
+            const int ti = wave * TW + t;
+            if (ti < n_tiles) epilogue_direct_units<NG>(e, e.row0 + ti * g.tile_rows, g.n_cols, v[t], rs, g.ssq_parts != nullptr);
+        }
+        __syncthreads();                           // the next pass parks its operand over these buffers
+        return;
+    }
+    // ---- the other epilogues, tile by tile from LDS: [tile][column block][row / 4][column][row % 4] ----
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+        const int ti = wave * TW + t, r = (n16 & 1) * 8 + 2 * kg;
+        if (ti < n_tiles) {
+#pragma unroll
+            for (int ng = 0; ng < NG; ++ng) {
+                const int n = (ng & 1) * 8 + (n16 >> 1);
+                ETC_AS_LDS float *dst = tb + (size_t)(ti * NB + (ng >> 1)) * 256 + ((r >> 2) * 16 + n) * 4 + (r & 3);
+                dst[0] = v[t][ng][0];
+                dst[1] = v[t][ng][1];
+            }
+        }
+    }
+    tiles_epilogue<NB>(P, a, tb, rs, rs_part, n_tiles);
+}
+
+// ---- GroupGEMM paths (row blocks of the MoE block: EPI_MOE_ACT, EPI_MOE_Y) -----------------------------------------
+// Up to 16 columns, 8 or more row tiles: the whole operand sits in LDS (64 KB for 8 columns of K = 2048) and every
+// wavefront streams row tiles of its own (wave, wave + 8, ...) through all of K: one linear stream of weights with 16
+// loads in flight that never drains between tiles, no barrier and no reduction behind the staging, the epilogue straight
+// from the accumulators.  Bound by HBM.  The staged path splits K over the wavefronts instead and meets in one reduction
+// per task, whose buffer limits a task to 16 tiles at 6 columns: a token block of 100 runs three rounds of 1 MB tasks
+// there (wait, staging and reduction three times) and one round of 3 MB tasks here.
+template <int NG>
+__device__ __noinline__ void gemm_tiles_stream(const Params &P, const ChunkedArgs *args, float *sm, int *frame_anchor)
+{
+    const ChunkedArgs a = lds_get_uniform(args);
+    if (a.task_id == -0x7FFFFFFF) *frame_anchor = 1;      // never true; see gemm_tiles_chunked
+    const GemmTile &g = a.g;
+    const Epilogue &e = a.e;
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id()), lane = lane_id();
+    const int n16 = lane & 15, kg = lane >> 4;
+    const int K = __builtin_amdgcn_readfirstlane(g.K), n_tiles = __builtin_amdgcn_readfirstlane(g.n_tiles);
+    const int upt = K >> 8;                        // steps of 4 units (256 elements of K) per tile
+    const int total = n_tiles > wave ? (n_tiles - wave + kWaves - 1) / kWaves * upt : 0;      // steps of this wavefront
+    const size_t tile_step = (size_t)g.tile_rows * (size_t)g.ldw;
+    const uint16_t *ipA = unit_row(g.rowsA, g.ldw) + (size_t)wave * tile_step;      // next step to request
+    const uint16_t *ipB = unit_row(g.rowsB, g.ldw) + (size_t)wave * tile_step;
+    const long long tile_jump = (long long)(kWaves * tile_step) - (long long)K;
+    int iu = 0;                                    // its place in its tile
+    auto next_step = [&]() {
+        const bool wrap = ++iu == upt;
+        const long long by = 256 + (wrap ? tile_jump : 0);
+        ipA += by;
+        ipB += by;
+        iu = wrap ? 0 : iu;
+    };
+    u32x4 wr[16];                                  // two steps of 4 units, rows A and rows B of each
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (h < total) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                wr[h * 8 + 2 * j] = gld_16B_nt(ipA + j * kUnitK);
+                wr[h * 8 + 2 * j + 1] = gld_16B_nt(ipB + j * kUnitK);
+            }
+            next_step();
+        }
+    }
+    gemm_wait(P, a.w);
+    trace_mark(P, a.task_id, 1);
+
+    // ---- the operand, hi and lo, whole; its columns K + kOpPad elements apart ----------------------------------
+    const int Kp = K + kOpPad, ppc = K >> 3, pieces = g.n_cols * ppc;       // 16-byte pieces
+    ETC_AS_LDS float *rs = as_lds(sm), *rs_part = rs + 64;
+    ETC_AS_LDS uint16_t *op_hi = reinterpret_cast<ETC_AS_LDS uint16_t *>(rs_part + kWgThreads), *op_lo = op_hi + (size_t)g.n_cols * Kp;
+    const __amdgpu_buffer_rsrc_t hi_b = buf_of(g.b_hi), lo_b = buf_of(g.b_lo);
+    constexpr int U = 4;
+    for (int i0 = threadIdx.x; i0 < pieces; i0 += U * kWgThreads) {
+        u32x4 vh[U], vl[U];
+        uint32_t at[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * kWgThreads;
+            const int col = i < pieces ? i / ppc : 0, pc = i - col * ppc;
+            int row = col;
+            if (g.col_rows) row = ld_i32(g.col_rows + col);
+            if (row < 0) row = 0;
+            at[u] = (uint32_t)(col * Kp + pc * 8);
+            const uint32_t off = i < pieces ? ((uint32_t)row * (uint32_t)g.ldb + (uint32_t)pc * 8u) * 2u : kBufNone;
+            vh[u] = buf_ld_16B(hi_b, off, 0);
+            vl[u] = buf_ld_16B(lo_b, off, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i0 + u * kWgThreads < pieces) {
+                *reinterpret_cast<ETC_AS_LDS u32x4 *>(op_hi + at[u]) = vh[u];
+                *reinterpret_cast<ETC_AS_LDS u32x4 *>(op_lo + at[u]) = vl[u];
+            }
+        }
+    }
+    if (g.ssq_parts) norm_shares<64>(g, rs_part);
+    __syncthreads();
+    if (g.ssq_parts) {
+        norm_factors<64>(g, rs, rs_part);
+        __syncthreads();
+    }
+    trace_mark(P, a.task_id, 2);
+
+    ETC_AS_LDS const uint16_t *sh[NG], *sl[NG];    // columns beyond n_cols read column 0's operand and are never stored
+#pragma unroll
+    for (int ng = 0; ng < NG; ++ng) {
+        const int col = ng * 8 + (n16 >> 1), c = col < g.n_cols ? col : 0;
+        sh[ng] = op_hi + (size_t)c * Kp + (kg * 2 + (n16 & 1)) * 8;
+        sl[ng] = op_lo + (size_t)c * Kp + (kg * 2 + (n16 & 1)) * 8;
+    }
+    f32x4 accA[NG], accB[NG];
+#pragma unroll
+    for (int ng = 0; ng < NG; ++ng) accA[ng] = accB[ng] = f32x4{0, 0, 0, 0};
+    int cu = 0, ti = wave;                         // step inside its tile, tile
+    auto finish_tile = [&]() {                     // straight from the accumulators
+        float v[NG][2];
+#pragma unroll
+        for (int ng = 0; ng < NG; ++ng) {
+            unit_sums(accA[ng], accB[ng], v[ng]);
+            accA[ng] = accB[ng] = f32x4{0, 0, 0, 0};
+        }
+        epilogue_direct_units<NG>(e, e.row0 + ti * g.tile_rows, g.n_cols, v, rs, g.ssq_parts != nullptr);
+    };
+    // one step out of ring half h; RELOAD: its slots are refilled for the step after the next, behind their use
+#define ETC_STREAM_STEP(h, RELOAD)                                                                                \
+    {                                                                                                             \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                           \
+            const bf16x8 a0 = __builtin_bit_cast(bf16x8, wr[(h) * 8 + 2 * j]), a1 = __builtin_bit_cast(bf16x8, wr[(h) * 8 + 2 * j + 1]); \
+            _Pragma("unroll") for (int ng = 0; ng < NG; ++ng) {                                                   \
+                const bf16x8 bh = __builtin_bit_cast(bf16x8, *reinterpret_cast<ETC_AS_LDS const u32x4 *>(sh[ng] + cu * 256 + j * kUnitK)); \
+                const bf16x8 bl = __builtin_bit_cast(bf16x8, *reinterpret_cast<ETC_AS_LDS const u32x4 *>(sl[ng] + cu * 256 + j * kUnitK)); \
+                accA[ng] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bh, accA[ng], 0, 0, 0);                    \
+                accB[ng] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bh, accB[ng], 0, 0, 0);                    \
+                accA[ng] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bl, accA[ng], 0, 0, 0);                    \
+                accB[ng] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bl, accB[ng], 0, 0, 0);                    \
+            }                                                                                                     \
+            if (RELOAD) {                                                                                         \
+                wr[(h) * 8 + 2 * j] = gld_16B_nt(ipA + j * kUnitK);                                               \
+                wr[(h) * 8 + 2 * j + 1] = gld_16B_nt(ipB + j * kUnitK);                                           \
+                __builtin_amdgcn_sched_barrier(0);                                                                \
+            }                                                                                                     \
+        }                                                                                                         \
+        if (RELOAD) next_step();                                                                                  \
+        if (++cu == upt) {                                                                                        \
+            finish_tile();                                                                                        \
+            cu = 0;                                                                                               \
+            ti += kWaves;                                                                                         \
+        }                                                                                                         \
+    }
+    int u = 0;
+    for (; u + 4 <= total; u += 2) {
+        ETC_STREAM_STEP(0, true)
+        ETC_STREAM_STEP(1, true)
+    }
+    if (total - u == 3) {
+        ETC_STREAM_STEP(0, true)
+        ETC_STREAM_STEP(1, false)
+        ETC_STREAM_STEP(0, false)
+    } else if (total - u >= 1) {
+        ETC_STREAM_STEP(0, false)
+        if (total - u == 2) ETC_STREAM_STEP(1, false)
+    }
+#undef ETC_STREAM_STEP
+    trace_mark(P, a.task_id, 3);
+    __syncthreads();                               // the operand in LDS is free again
+}
+__device__ __forceinline__ bool stream_fits(int n_tiles, int n_cols, int K, int ldb)
+{
+    return n_cols <= 16 && ldb <= kMaxBufLd && n_tiles >= kWaves && K % 256 == 0 &&
+           (long long)(64 + kWgThreads) * 4 + (long long)n_cols * (K + kOpPad) * 4 <= (long long)kLdsBytes;
+}
+
+// Row blocks of up to 16 * NB columns (128 at most) against any number of row tiles, 16 per pass (two per wavefront).
+// The operand is walked in chunks through two LDS buffers as in the wide path, but the passes are one stream: the weights
+// of the next pass and its first operand chunk are requested while this one ends, and the epilogue needs no LDS, so
+// nothing drains between them.  Weight loads may allocate in the caches: the row blocks of one expert stream the same
+// rows.  A block of 64 columns moves 768 bytes per element of K and pass for 65 kflop, one of 128 columns 1 KB for 131:
+// what bounds the large token blocks is bytes through the fabric, 40 - 48 GB/s per compute unit.
+template <int NB>
+__device__ __noinline__ void gemm_tiles_blocks(const Params &P, const ChunkedArgs *args, float *sm, int *frame_anchor)
+{
+    const ChunkedArgs a = lds_get_uniform(args);
+    if (a.task_id == -0x7FFFFFFF) *frame_anchor = 1;      // never true; see gemm_tiles_chunked
+    const GemmTile &g = a.g;
+    const Epilogue &e = a.e;
+    constexpr int TW = 2, PASS = kWaves * TW;
+    constexpr int COLS = 16 * NB, KC = NB == 8 ? 128 : 256, KS = KC / 32, STRIDE = KC + 8;
+    constexpr int PPC = KC / 8, U = COLS * PPC / kWgThreads, BUF = 2 * COLS * STRIDE;
+    constexpr int RING = KS * TW;                  // weight fragments in flight per lane: one chunk
+    constexpr int NCOL = COLS < 64 ? 64 : COLS;
+    static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "column blocks");
+    static_assert(U >= 1 && COLS * PPC == U * kWgThreads, "every thread moves U pieces of each half");
+    static_assert((size_t)2 * BUF * 2 + (NCOL + kWgThreads) * 4 <= (size_t)kLdsBytes, "two operand buffers and the norm scratch fit");
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id()), lane = lane_id();
+    const int m = lane & 15, kg = lane >> 4;
+    const int n_tiles = __builtin_amdgcn_readfirstlane(g.n_tiles);
+    const int n_chunks = __builtin_amdgcn_readfirstlane(g.K) / KC;
+    const int total = (n_tiles + PASS - 1) / PASS * n_chunks;
+    const uint32_t tile_step = (uint32_t)g.tile_rows * (uint32_t)g.ldw;
+    const uint16_t *wbase = (m < 8 ? g.rowsA + (size_t)m * (size_t)g.ldw : g.rowsB + (size_t)(m - 8) * (size_t)g.ldw) + kg * 8;
+    // request cursor of the weights: chunk rc of the pass whose first tile of this wavefront is rt (tiles beyond the task
+    // stream its last one again and are never stored: no branch in the loop)
+    int rc = 0, rt = wave * TW;
+    size_t ro[TW];
+    auto set_offsets = [&]() {
+#pragma unroll
+        for (int t = 0; t < TW; ++t) ro[t] = (size_t)(rt + t < n_tiles ? rt + t : n_tiles - 1) * tile_step + (size_t)rc * KC;
+    };
+    auto next_request = [&]() {
+        if (++rc == n_chunks) { rc = 0; rt += PASS; }
+        set_offsets();
+    };
+    set_offsets();
+    u32x4 wr[RING];
+#pragma unroll
+    for (int j = 0; j < RING; ++j) wr[j] = gld_16B(wbase + ro[j % TW] + (j / TW) * 32);
+    next_request();
+    gemm_wait(P, a.w);
+    trace_mark(P, a.task_id, 1);
+
+    ETC_AS_LDS uint16_t *buf0 = reinterpret_cast<ETC_AS_LDS uint16_t *>(as_lds(sm));
+    ETC_AS_LDS float *rs = reinterpret_cast<ETC_AS_LDS float *>(buf0 + 2 * BUF), *rs_part = rs + NCOL;
+    const __amdgpu_buffer_rsrc_t hi_b = buf_of(g.b_hi), lo_b = buf_of(g.b_lo);
+    uint32_t off[U];
+    const int pc = (int)threadIdx.x % PPC;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int col = ((int)threadIdx.x + kWgThreads * u) / PPC;
+        int row = 0;
+        if (col < g.n_cols) row = g.col_rows ? ld_i32(g.col_rows + col) : col;
+        if (row < 0) row = 0;
+        off[u] = col < g.n_cols ? ((uint32_t)row * (uint32_t)g.ldb + (uint32_t)pc * 8u) * 2u : kBufNone;
+    }
+    u32x4 vh[U], vl[U];
+    auto fetch_chunk = [&](int c) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            vh[u] = buf_ld_16B(hi_b, off[u], (uint32_t)c * (KC * 2));
+            vl[u] = buf_ld_16B(lo_b, off[u], (uint32_t)c * (KC * 2));
+        }
+    };
+    auto park_chunk = [&](int b) {
+        ETC_AS_LDS uint16_t *hi = buf0 + b * BUF, *lo = hi + COLS * STRIDE;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int col = ((int)threadIdx.x + kWgThreads * u) / PPC;
+            *reinterpret_cast<ETC_AS_LDS u32x4 *>(hi + col * STRIDE + pc * 8) = vh[u];
+            *reinterpret_cast<ETC_AS_LDS u32x4 *>(lo + col * STRIDE + pc * 8) = vl[u];
+        }
+    };
+    fetch_chunk(0);
+    if (g.ssq_parts) norm_shares<NCOL>(g, rs_part);
+    park_chunk(0);
+    __syncthreads();
+    if (g.ssq_parts) norm_factors<NCOL>(g, rs, rs_part);      // read behind at least one more barrier (n_chunks > 1) ...
+    if (g.ssq_parts && total == 1) __syncthreads();           // ... or this one
+    trace_mark(P, a.task_id, 2);
+
+    f32x4 acc[TW][NB];
+    auto clear = [&]() {
+#pragma unroll
+        for (int t = 0; t < TW; ++t)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[t][nb] = f32x4{0, 0, 0, 0};
+    };
+    clear();
+    int ti0 = wave * TW;                           // this wavefront's first tile of the pass being computed
+    auto finish_pass = [&]() {
+#pragma unroll
+        for (int t = 0; t < TW; ++t)
+            if (ti0 + t < n_tiles)
+                epilogue_direct<NB>(e, e.row0 + (ti0 + t) * g.tile_rows, g.n_cols, acc[t], rs, g.ssq_parts != nullptr);
+    };
+    // One chunk out of LDS buffer b, in the order as written (see ETC_WIDE_CHUNK).
+#define ETC_BLOCK_CHUNK(b, RELOAD)                                                                             \
+    {                                                                                                             \
+        ETC_AS_LDS const uint16_t *hi = buf0 + (b) * BUF + m * STRIDE + kg * 8;                                   \
+        ETC_AS_LDS const uint16_t *lo = hi + COLS * STRIDE;                                                       \
+        u32x4 fh[NB], fl[NB];                                                                                     \
+        _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                         \
+            fh[nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(hi + nb * 16 * STRIDE);                          \
+        __builtin_amdgcn_sched_barrier(0);                                                                        \
+        _Pragma("unroll") for (int kk = 0; kk < KS; ++kk) {                                                       \
+            _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                     \
+                fl[nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(lo + nb * 16 * STRIDE + kk * 32);             \
+            _Pragma("unroll") for (int t = 0; t < TW; ++t) {                                                      \
+                const bf16x8 av = __builtin_bit_cast(bf16x8, wr[kk * TW + t]);                       \
+                _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) acc[t][nb] =                                    \
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, fh[nb]), acc[t][nb], 0, 0, 0); \
+            }                                                                                                     \
+            __builtin_amdgcn_sched_barrier(0);                                                                    \
+            if (kk + 1 < KS) {                                                                                    \
+                _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                 \
+                    fh[nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(hi + nb * 16 * STRIDE + (kk + 1) * 32);   \
+            }                                                                                                     \
+            _Pragma("unroll") for (int t = 0; t < TW; ++t) {                                                      \
+                const bf16x8 av = __builtin_bit_cast(bf16x8, wr[kk * TW + t]);                       \
+                _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) acc[t][nb] =                                    \
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, fl[nb]), acc[t][nb], 0, 0, 0); \
+            }                                                                                                     \
+            __builtin_amdgcn_sched_barrier(0);                                                                    \
+            if (RELOAD) {                                                                                         \
+                _Pragma("unroll") for (int t = 0; t < TW; ++t) wr[kk * TW + t] = gld_16B(wbase + ro[t] + kk * 32); \
+            }                                                                                                     \
+        }                                                                                                         \
+        if (RELOAD) next_request();                                                                               \
+        __builtin_amdgcn_sched_barrier(0);                                                                        \
+    }
+    int c = 0, gc = 0;                             // chunk inside the pass, chunk of the task
+    auto next_chunk = [&]() { return c + 1 == n_chunks ? 0 : c + 1; };
+    auto advance = [&]() {
+        ++gc;
+        if (++c == n_chunks) {
+            finish_pass();
+            clear();
+            c = 0;
+            ti0 += PASS;
+        }
+    };
+    for (; gc + 1 < total;) {
+        fetch_chunk(next_chunk());
+        ETC_BLOCK_CHUNK(gc & 1, true)
+        park_chunk((gc + 1) & 1);
+        __syncthreads();
+        advance();
+    }
+    ETC_BLOCK_CHUNK(gc & 1, false)
+    finish_pass();
+#undef ETC_BLOCK_CHUNK
+    trace_mark(P, a.task_id, 3);
+    __syncthreads();                               // the operand buffers are free again
+}
+
+// Passes of the wide path: 8 / KH x TW row tiles each.
+template <int TW, int NB, int KH>
+__device__ __forceinline__ void gemm_tiles_wide_pass(const Params &PL, ChunkedArgs *slot, float *sm, int *frame_anchor)
+{
+    if constexpr (NB == 4) gemm_tiles_wide<TW, NB, KH>(PL, slot, sm, frame_anchor);
+    else gemm_tiles_lines<TW, 2 * NB>(PL, slot, sm, frame_anchor);
+}
+template <int TW, int NB, int KH>
 __device__ __forceinline__ void gemm_tiles_wide_passes(const Params &PL, ChunkedArgs a, ChunkedArgs *slot, float *sm, int *frame_anchor)
 {
-    constexpr int PASS = kWaves * TW;
+    constexpr int PASS = kWaves / KH * TW;
     const int total = a.g.n_tiles;
     for (int t0 = 0; t0 < total; t0 += PASS) {
         a.g.n_tiles = total - t0 < PASS ? total - t0 : PASS;
@@ -908,7 +1729,7 @@ __device__ __forceinline__ void gemm_tiles_wide_passes(const Params &PL, Chunked
             if (threadIdx.x == 0) lds_put(slot, a);
             __syncthreads();
         }
-        gemm_tiles_wide<TW, NB>(PL, slot, sm, frame_anchor);
+        gemm_tiles_wide_pass<TW, NB, KH>(PL, slot, sm, frame_anchor);
         a.g.rowsA += (size_t)PASS * a.g.tile_rows * a.g.ldw;
         a.g.rowsB += (size_t)PASS * a.g.tile_rows * a.g.ldw;
         a.e.row0 += PASS * a.g.tile_rows;
@@ -918,7 +1739,7 @@ __device__ __forceinline__ void gemm_tiles_wide_passes(const Params &PL, Chunked
 }
 
 // One call per pass over the operand: T row tiles each (the events have been seen after the first pass).
-template <int NB, int T>
+template <int NB, int T, bool BUF16 = true>
 __device__ __forceinline__ void gemm_tiles_chunked_passes(const Params &PL, ChunkedArgs a, ChunkedArgs *slot, float *sm, int *frame_anchor)
 {
     const int total = a.g.n_tiles;
@@ -931,7 +1752,7 @@ __device__ __forceinline__ void gemm_tiles_chunked_passes(const Params &PL, Chun
             if (threadIdx.x == 0) lds_put(slot, a);
             __syncthreads();
         }
-        gemm_tiles_chunked<NB, T>(PL, slot, sm, frame_anchor);
+        gemm_tiles_chunked<NB, T, BUF16>(PL, slot, sm, frame_anchor);
         a.g.rowsA += (size_t)T * a.g.tile_rows * a.g.ldw;
         a.g.rowsB += (size_t)T * a.g.tile_rows * a.g.ldw;
         a.e.row0 += T * a.g.tile_rows;
@@ -951,18 +1772,32 @@ __device__ __noinline__ void gemm_chunked_entry(const Params &PL, ChunkedArgs *s
     int anchor = 0;
 #define ETC_CHUNKED(NB_)                                                                         \
     {                                                                                            \
-        if (a.g.n_tiles == 1) gemm_tiles_chunked_passes<NB_, 1>(PL, a, slot, sm, &anchor);      \
+        if (!buf_ok) gemm_tiles_chunked_passes<NB_, 1, false>(PL, a, slot, sm, &anchor);         \
+        else if (a.g.n_tiles == 1) gemm_tiles_chunked_passes<NB_, 1>(PL, a, slot, sm, &anchor); \
         else if (a.g.n_tiles == 2) gemm_tiles_chunked_passes<NB_, 2>(PL, a, slot, sm, &anchor); \
         else if (a.g.n_tiles <= 4 || NB_ == 4) gemm_tiles_chunked_passes<NB_, 4>(PL, a, slot, sm, &anchor);  \
         else gemm_tiles_chunked_passes<NB_, NB_ == 4 ? 4 : 8>(PL, a, slot, sm, &anchor);   /* several passes: crowded expert */ \
     }
-    if (a.g.n_cols > 32 && a.g.n_tiles >= 16 && a.g.K % 256 == 0) gemm_tiles_wide_passes<2, 4>(PL, a, slot, sm, &anchor);
-    else if (a.g.n_cols > 32 && a.g.n_tiles >= 5 && a.g.K % 256 == 0) gemm_tiles_wide_passes<1, 4>(PL, a, slot, sm, &anchor);
+    const bool buf_ok = a.g.ldb <= kMaxBufLd;
+    if (buf_ok && (a.e.kind == EPI_MOE_ACT || a.e.kind == EPI_MOE_Y)) {      // row blocks of more than 64 columns exist here only
+        if (stream_fits(a.g.n_tiles, a.g.n_cols, a.g.K, a.g.ldb)) {
+            if (a.g.n_cols <= 8) gemm_tiles_stream<1>(PL, slot, sm, &anchor);
+            else gemm_tiles_stream<2>(PL, slot, sm, &anchor);
+            return;
+        }
+        if (a.g.n_cols > 64) { gemm_tiles_blocks<8>(PL, slot, sm, &anchor); return; }
+        if (a.g.n_tiles >= 5 && a.g.n_cols > 32) { gemm_tiles_blocks<4>(PL, slot, sm, &anchor); return; }
+        if (a.g.n_tiles >= 5 && a.g.n_cols > 16) { gemm_tiles_blocks<2>(PL, slot, sm, &anchor); return; }
+        if (a.g.n_tiles >= 5) { gemm_tiles_blocks<1>(PL, slot, sm, &anchor); return; }
+    }
+    const bool wide_ok = buf_ok && a.g.K % 256 == 0;
+    if (a.g.n_cols > 32 && a.g.n_tiles >= 16 && wide_ok) gemm_tiles_wide_passes<4, 4, 2>(PL, a, slot, sm, &anchor);
+    else if (a.g.n_cols > 32 && a.g.n_tiles >= 5 && wide_ok) gemm_tiles_wide_passes<2, 4, 2>(PL, a, slot, sm, &anchor);
     else if (a.g.n_cols > 32) ETC_CHUNKED(4)
-    else if (a.g.n_cols > 16 && a.g.n_tiles >= 9 && a.g.K % 256 == 0) gemm_tiles_wide_passes<2, 2>(PL, a, slot, sm, &anchor);   // 9 .. 16 tiles against ONE pass over the operand
-    else if (a.g.n_cols > 16 && a.g.n_tiles >= 5 && a.g.K % 256 == 0) gemm_tiles_wide_passes<1, 2>(PL, a, slot, sm, &anchor);
+    else if (a.g.n_cols > 16 && a.g.n_tiles >= 9 && wide_ok) gemm_tiles_wide_passes<2, 2, 1>(PL, a, slot, sm, &anchor);   // 9 .. 16 tiles against ONE pass over the operand
+    else if (a.g.n_cols > 16 && a.g.n_tiles >= 5 && wide_ok) gemm_tiles_wide_passes<1, 2, 1>(PL, a, slot, sm, &anchor);
     else if (a.g.n_cols > 16) ETC_CHUNKED(2)
-    else if (a.g.n_tiles >= 5 && a.g.K % 256 == 0) gemm_tiles_wide_passes<1, 1>(PL, a, slot, sm, &anchor);
+    else if (a.g.n_tiles >= 5 && wide_ok) gemm_tiles_wide_passes<1, 1, 1>(PL, a, slot, sm, &anchor);
     else ETC_CHUNKED(1)
 #undef ETC_CHUNKED
 }
@@ -1044,8 +1879,6 @@ __device__ __forceinline__ unsigned long long logit_key(float v, int id)
     const uint32_t ordered = u ^ ((u >> 31) ? 0xFFFFFFFFu : 0x80000000u);
     return ((unsigned long long)ordered << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)id);
 }
-
-__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 
 __device__ __forceinline__ void store_split(uint16_t *hi_p, uint16_t *lo_p, size_t idx, float v)
 {

@@ -16,7 +16,8 @@ struct RowTile {
     int expert, row0, n;     // rows [row0, row0 + n) of the grouped tensors
 };
 
-// Slot r of the static GroupGEMM grid -> its expert and rows; false for the surplus slots of this step.
+// Slot r of the static GroupGEMM grid -> its expert and rows; false for the surplus slots of this step, and for slots
+// whose rows another slot of their expert has taken over (moel_scan).
 __device__ __forceinline__ bool resolve_row_tile(const Params &P, int r, RowTile &rt)
 {
     const int total = __builtin_amdgcn_readfirstlane(ld_i32(P.exp_indptr + P.E));
@@ -24,7 +25,7 @@ __device__ __forceinline__ bool resolve_row_tile(const Params &P, int r, RowTile
     rt.expert = __builtin_amdgcn_readfirstlane(ld_i32(P.tile_expert + r));
     rt.row0 = __builtin_amdgcn_readfirstlane(ld_i32(P.tile_row0 + r));
     rt.n = __builtin_amdgcn_readfirstlane(ld_i32(P.tile_n + r));
-    return true;
+    return rt.n > 0;
 }
 
 // ---- wavefront arg-max of the router's top-k -------------------------------------------------------------
@@ -298,8 +299,8 @@ __device__ __noinline__ void moe_route_and_group(const Params &P, int layer, int
 constexpr int kMoelBlock = 64;
 
 
-// 16 tokens: x_in (bf16) -> residual stream fp32, (x * gain) split into hi + lo, per-16-element sums of squares.
-// A lane takes 8 consecutive elements (one 16-byte load), two neighbouring lanes one 16-element part.
+// 16 tokens: x_in (bf16) -> residual stream fp32, (x * gain) split into hi + lo, the row's sum of squares.
+// A wavefront takes a token, a lane 8 consecutive elements (one 16-byte load).
 __device__ __noinline__ void moel_load(const Params &P, int blk16)
 {
     blk16 = __builtin_amdgcn_readfirstlane(blk16);
@@ -308,6 +309,7 @@ __device__ __noinline__ void moel_load(const Params &P, int blk16)
     for (int i = wave_id(); i < 16; i += kWaves) {
         const int tok = blk16 * 16 + i;
         if (tok >= P.B) break;
+        float total = 0.f;
         for (int oct = lane_id(); oct < n_oct; oct += 64) {
             const size_t o = (size_t)tok * P.H + (size_t)oct * 8;
             const u32x4 xa = gld_16B(P.hidden_in + o), ga = gld_16B(g2 + oct * 8);
@@ -331,9 +333,12 @@ __device__ __noinline__ void moel_load(const Params &P, int blk16)
                 st_u64(P.xmg_hi + o + q, (uint64_t)hi[q] | ((uint64_t)hi[q + 1] << 16) | ((uint64_t)hi[q + 2] << 32) | ((uint64_t)hi[q + 3] << 48));
                 st_u64(P.xmg_lo + o + q, (uint64_t)lo[q] | ((uint64_t)lo[q + 1] << 16) | ((uint64_t)lo[q + 2] << 32) | ((uint64_t)lo[q + 3] << 48));
             }
-            s += dpp_f32<0xB1>(s);               // the neighbouring lane's half of the part (quad_perm [1,0,3,2])
-            if ((lane_id() & 1) == 0) st_f32(P.ssq_xmid + (size_t)(oct >> 1) * (size_t)P.col_stride + tok, s);
+            total += s;
         }
+        // the whole row's sum of squares: one part per token (a consumer that gathers its columns would otherwise fetch
+        // hidden / 16 scattered words for each of them)
+        total = wave_sum(total);
+        if (lane_id() == 0) st_f32(P.ssq_xmid + tok, total);
     }
 }
 
@@ -418,6 +423,11 @@ __device__ __noinline__ void moel_scan(const Params &P, float *sm)
     ETC_AS_LDS int32_t *til = cnt + kMaxExperts;                                       // [E]
     ETC_AS_LDS int32_t *tokp = til + kMaxExperts;                                      // [E+1]
     ETC_AS_LDS int32_t *expp = tokp + kMaxExperts + 1;                                 // [E+1]
+    ETC_AS_LDS int32_t *blkp = expp + kMaxExperts + 1;                                 // [E+1] row blocks
+    // A GroupGEMM task takes a row BLOCK of up to row_merge row tiles of one expert: the weights are streamed once for all
+    // its columns.  Static grids: the blocks fill the first slots, in order; the other slots are left without rows.
+    // Dynamic scheduler: an expert's tasks are released as the slots of its row tiles, so its blocks take the first of them.
+    const int MB = M * P.row_merge;
     const bool dbg = (P.debug_flags & 4u) != 0 && P.dbg_logits != nullptr;
     for (int e = threadIdx.x; e < E; e += kWgThreads) {
         int n = 0;
@@ -433,12 +443,15 @@ __device__ __noinline__ void moel_scan(const Params &P, float *sm)
     }
     __syncthreads();
     for (int e = threadIdx.x; e <= E; e += kWgThreads) {
-        int a = 0, c = 0;
-        for (int j = 0; j < e; ++j) { a += cnt[j]; c += til[j]; }
+        int a = 0, c = 0, d = 0;
+        for (int j = 0; j < e; ++j) { a += cnt[j]; c += til[j]; d += (cnt[j] + MB - 1) / MB; }
         tokp[e] = a;
         expp[e] = c;
+        blkp[e] = d;
     }
     __syncthreads();
+    if (!P.moe_dd)
+        for (int r = blkp[E] + (int)threadIdx.x; r < expp[E]; r += kWgThreads) st_i32(P.tile_n + r, 0);
     for (int e = threadIdx.x; e < E; e += kWgThreads) {
         int row = tokp[e];
         for (int b0 = 0; b0 < n_blk; b0 += 16) {
@@ -452,13 +465,15 @@ __device__ __noinline__ void moel_scan(const Params &P, float *sm)
             }
         }
         st_i32(P.moel_count + e, cnt[e]);
-        int n = cnt[e], r = expp[e];
+        int n = cnt[e], r = P.moe_dd ? expp[e] : blkp[e];
         row = tokp[e];
-        for (; n > 0; n -= M, ++r, row += M) {
+        for (; n > 0; n -= MB, ++r, row += MB) {
             st_i32(P.tile_expert + r, e);
             st_i32(P.tile_row0 + r, row);
-            st_i32(P.tile_n + r, n < M ? n : M);
+            st_i32(P.tile_n + r, n < MB ? n : MB);
         }
+        if (P.moe_dd)
+            for (; r < expp[e + 1]; ++r) st_i32(P.tile_n + r, 0);
     }
     for (int e = threadIdx.x; e <= E; e += kWgThreads) {
         st_i32(P.tok_indptr + e, tokp[e]);

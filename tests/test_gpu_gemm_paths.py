@@ -1,0 +1,74 @@
+"""The projection and GroupGEMM loop forms at the sizes where each can go wrong: column counts on and around their limits
+(8 and 16 columns per product group, 16 / 32 / 64 / 128 per block), K of fewer 64-element units than wavefronts and of a
+number of units they cannot share evenly, task shapes of one and of several passes (few queues make the tasks large).
+Against the CPU oracle, within the bar of the other parity tests (max|err| <= 2e-2 of the RMS: the outputs are bf16, half a
+unit is up to 4e-3 of a value); every scheduler gives the same bits."""
+import numpy as np
+import pytest
+
+import synth
+from harness import GpuModel, bf16_to_f32_np, fixed_step, oracle_step, rel_err
+from test_gpu_moe_layer import SPIN, TOL, _check_against_oracle, _routing, _run, _weights
+
+pytestmark = pytest.mark.gpu
+
+# K = 768 = 12 units over 8 wavefronts, 1280 = 20, 256 = 4
+ODD_K = synth.ModelShape("odd-k", 2, 768, 4, 2, 64, 1280)
+MOE_EDGES = synth.ModelShape("moe-edges", 1, 512, 4, 2, 64, 0, n_experts=16, top_k=2, moe_F=768)
+
+
+@pytest.mark.parametrize("batch", [1, 8, 9, 16, 17, 33, 64])
+@pytest.mark.parametrize("shape,n_queues", [(synth.TINY, 0), (ODD_K, 0), (ODD_K, 8)])
+def test_projection_paths(shape, n_queues, batch):
+    import torch
+
+    import paper_2604_13327_amd as etc
+    pages = batch * 3 + 4
+    model = GpuModel(shape, seed=71, n_pool_pages=pages)
+    step = fixed_step(shape, batch, [(7 * b + 3) % 40 for b in range(batch)], pages, seed=72)
+    x = model.hidden(0, batch)
+    ref = oracle_step(shape, model.seed, pages, step, 0)["final"]
+    outs = []
+    for kind in (etc.SCHED_STATIC, etc.SCHED_DYNAMIC):
+        model.reset_pools()
+        dec = etc.Decoder(shape, kv_chunk_tokens=32, sampled_batches=[batch], max_kv_len=41, kind=kind, spin_budget=SPIN,
+                          n_queues=n_queues)
+        model.bind(dec)
+        dec.bind_step(step)
+        out = torch.full_like(x, float("nan"))
+        dec.launch(x, out)
+        torch.cuda.synchronize()
+        assert (dec.error_word() == 0).all() and (dec.event_counters() == 0).all()
+        outs.append(bf16_to_f32_np(out))
+        dec.close()
+    assert rel_err(outs[0], ref) <= TOL
+    np.testing.assert_array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("tile_m,n_queues", [(64, 0), (64, 4), (48, 4), (16, 4), (64, 1)])
+def test_group_gemm_row_blocks(tile_m, n_queues):
+    """Experts with 0, 1, 7, 8, 9, ... 128, 130 and 175 rows in one block of tokens (forced routing)."""
+    import paper_2604_13327_amd as etc
+    from synth import gpu as sgpu
+    s, seed = MOE_EDGES, 73
+    first, second = [1, 8, 9, 16, 17, 33, 130, 175], [32, 64, 65, 0, 128, 15, 7, 78]
+    tokens = sum(first)
+    assert tokens == sum(second) == 389
+    ids = np.stack([np.repeat(np.arange(8), first), np.repeat(np.arange(8, 16), second)[::-1]], 1).astype(np.int32)
+    w = _weights(s, seed)
+    x = sgpu.hidden_gpu(s, seed, tokens, tokens)
+    outs = []
+    for kind, kbk in ((0, False), (0, True), (1, False), (2, False)):
+        layer = etc.MoeLayer(s, [tokens], kind=kind, moe_tile_m=tile_m, debug_flags=etc.DEBUG_ROUTING, spin_budget=SPIN,
+                             n_queues=n_queues)
+        layer.bind_weights(w)
+        layer.bind_tokens(tokens)
+        layer.force_routing(0, ids)
+        for rep in range(2):
+            y = _run(layer, x, kbk)
+            assert (layer.error_word() == 0).all(), layer.error_word()
+        outs.append((y, _routing(layer, s, tokens)))
+        layer.close()
+    _check_against_oracle(s, seed, x, outs[0][0], outs[0][1], tile_m, forced=ids)
+    for y, r in outs[1:]:
+        np.testing.assert_array_equal(y, outs[0][0])
