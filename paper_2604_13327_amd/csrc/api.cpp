@@ -742,7 +742,7 @@ etc_status etc_moe_layer_create(const etc_model_desc *m, const etc_tile_desc *t,
         if (e != hipSuccess) { c->err = std::string("device allocation failed: ") + hipGetErrorString(e); return false; }
         return true;
     };
-    bool okk = A(&P.x, T * H) && A(&P.x_mid, T * H) && A(&P.xmg_hi, Tp * H) && A(&P.xmg_lo, Tp * H) &&
+    bool okk = A(&P.x_copy, T * H) && A(&P.xmg_hi, Tp * H) && A(&P.xmg_lo, Tp * H) &&
                A(&P.ssq_xmid, Tp) && A(&c->d_weights, 1) &&
                A(&P.router_logits, Tp * E) && A(&P.topk_ids, rows) && A(&P.topk_w, rows) &&
                A(&P.tok_indptr, E + 1) && A(&P.exp_indptr, E + 1) && A(&P.exp_event, E) && A(&P.perm, rows) && A(&P.inv_perm, rows) &&

@@ -72,6 +72,18 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t k)
     return best;
 }
 
+// The same for 32-bit values.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
+{
+    v = max(v, (uint32_t)dpp_i32<0xB1>((int)v));
+    v = max(v, (uint32_t)dpp_i32<0x4E>((int)v));
+    v = max(v, (uint32_t)dpp_i32<0x141>((int)v));
+    v = max(v, (uint32_t)dpp_i32<0x140>((int)v));
+    const uint32_t a = max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
+    const uint32_t b = max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
+    return max(a, b);
+}
+
 // Data-dependent event update and task triggering (Sec. 2.4), dynamic scheduler only.  The expert event
 // tensor E_exp[e] is armed at run time with the number of tokens routed to e, plus one for tile 0, which
 // publishes the per-expert tables: every tile knows that count from its own copy of the routing, so nobody
@@ -299,46 +311,65 @@ __device__ __noinline__ void moe_route_and_group(const Params &P, int layer, int
 constexpr int kMoelBlock = 64;
 
 
-// 16 tokens: x_in (bf16) -> residual stream fp32, (x * gain) split into hi + lo, the row's sum of squares.
-// A wavefront takes a token, a lane 8 consecutive elements (one 16-byte load).
+// 16 tokens: (x_in * gain) split into hi + lo, the row's sum of squares.  A wavefront takes two tokens at a time, a lane 8
+// consecutive elements of each per step (16-byte loads and stores), four steps in flight: one round trip for a hidden size
+// of 2048.  The residual is kept as it came (bf16): y may overlap x_in, and the combine tasks read it when y is written.
 __device__ __noinline__ void moel_load(const Params &P, int blk16)
 {
     blk16 = __builtin_amdgcn_readfirstlane(blk16);
     const uint16_t *g2 = (const uint16_t *)as_global(P.weights)[0].g2;
-    const int n_oct = P.H / 8;
-    for (int i = wave_id(); i < 16; i += kWaves) {
-        const int tok = blk16 * 16 + i;
-        if (tok >= P.B) break;
-        float total = 0.f;
-        for (int oct = lane_id(); oct < n_oct; oct += 64) {
-            const size_t o = (size_t)tok * P.H + (size_t)oct * 8;
-            const u32x4 xa = gld_16B(P.hidden_in + o), ga = gld_16B(g2 + oct * 8);
-            const uint32_t xw[4] = {xa.x, xa.y, xa.z, xa.w}, gw[4] = {ga.x, ga.y, ga.z, ga.w};
-            float v[8];
-            uint16_t hi[8], lo[8];
-            float s = 0.f;
+    const int n_oct = P.H / 8, wave = __builtin_amdgcn_readfirstlane(wave_id()), lane = lane_id();
+    const int tok0 = blk16 * 16 + 2 * wave;
+    if (tok0 >= P.B) return;
+    const bool two = tok0 + 1 < P.B;
+    const size_t row[2] = {(size_t)tok0 * P.H, (size_t)(two ? tok0 + 1 : tok0) * P.H};
+    float total[2] = {0.f, 0.f};
+    constexpr int U = 4;
+    for (int o0 = lane; o0 - lane < n_oct; o0 += U * 64) {
+        u32x4 xa[2][U], ga[U];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const uint32_t xx = xw[q >> 1], gg = gw[q >> 1];
-                v[q] = bf16_bits_to_f32((uint16_t)((q & 1) ? (xx >> 16) : (xx & 0xFFFFu)));
-                const float gv = bf16_bits_to_f32((uint16_t)((q & 1) ? (gg >> 16) : (gg & 0xFFFFu)));
-                split_bf16(v[q] * gv, hi[q], lo[q]);
-                s += v[q] * v[q];
-            }
+        for (int u = 0; u < U; ++u) {
+            const int oct = o0 + u * 64 < n_oct ? o0 + u * 64 : 0;
+            ga[u] = gld_16B(g2 + oct * 8);
 #pragma unroll
-            for (int q = 0; q < 8; q += 2)
-                st_u64(P.x_mid + o + q, (uint64_t)__float_as_uint(v[q]) | ((uint64_t)__float_as_uint(v[q + 1]) << 32));
-#pragma unroll
-            for (int q = 0; q < 8; q += 4) {
-                st_u64(P.xmg_hi + o + q, (uint64_t)hi[q] | ((uint64_t)hi[q + 1] << 16) | ((uint64_t)hi[q + 2] << 32) | ((uint64_t)hi[q + 3] << 48));
-                st_u64(P.xmg_lo + o + q, (uint64_t)lo[q] | ((uint64_t)lo[q + 1] << 16) | ((uint64_t)lo[q + 2] << 32) | ((uint64_t)lo[q + 3] << 48));
-            }
-            total += s;
+            for (int t = 0; t < 2; ++t) xa[t][u] = gld_16B(P.hidden_in + row[t] + (size_t)oct * 8);
         }
-        // the whole row's sum of squares: one part per token (a consumer that gathers its columns would otherwise fetch
-        // hidden / 16 scattered words for each of them)
-        total = wave_sum(total);
-        if (lane_id() == 0) st_f32(P.ssq_xmid + tok, total);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool live = o0 + u * 64 < n_oct;
+            const uint32_t gw[4] = {ga[u].x, ga[u].y, ga[u].z, ga[u].w};
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const uint32_t xw[4] = {xa[t][u].x, xa[t][u].y, xa[t][u].z, xa[t][u].w};
+                uint32_t hw[4], lw[4];
+                float s = 0.f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float v0 = bf16_bits_to_f32(xw[q] & 0xFFFFu), v1 = bf16_bits_to_f32(xw[q] >> 16);
+                    uint16_t h0, l0, h1, l1;
+                    split_bf16(v0 * bf16_bits_to_f32(gw[q] & 0xFFFFu), h0, l0);
+                    split_bf16(v1 * bf16_bits_to_f32(gw[q] >> 16), h1, l1);
+                    hw[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+                    lw[q] = (uint32_t)l0 | ((uint32_t)l1 << 16);
+                    s += v0 * v0 + v1 * v1;
+                }
+                if (live) {
+                    total[t] += s;
+                    const uint32_t at = (uint32_t)(o0 + u * 64) * 16u;
+                    buf_st_16B(buf_of(P.x_copy + row[t]), at, xa[t][u]);
+                    buf_st_16B(buf_of(P.xmg_hi + row[t]), at, u32x4{hw[0], hw[1], hw[2], hw[3]});
+                    buf_st_16B(buf_of(P.xmg_lo + row[t]), at, u32x4{lw[0], lw[1], lw[2], lw[3]});
+                }
+            }
+        }
+    }
+    // the whole row's sum of squares: one part per token (a consumer that gathers its columns would otherwise fetch
+    // hidden / 16 scattered words for each of them)
+    total[0] = wave_sum(total[0]);
+    total[1] = wave_sum(total[1]);
+    if (lane == 0) {
+        st_f32(P.ssq_xmid + tok0, total[0]);
+        if (two) st_f32(P.ssq_xmid + tok0 + 1, total[1]);
     }
 }
 
@@ -355,57 +386,82 @@ __device__ __noinline__ void moel_topk(const Params &P, int blk, float *sm)
     const bool dbg = (P.debug_flags & 4u) != 0 && P.dbg_logits != nullptr;
     for (int e = threadIdx.x; e < E; e += kWgThreads) cnt[e] = 0;
     __syncthreads();
-    for (int i = wave; i < kMoelBlock; i += kWaves) {
-        const int b = blk * kMoelBlock + i;
-        if (b >= P.B) break;
-        const float *lg = P.router_logits + (size_t)b * E;
-        float v[kMaxExperts / 64];
-        bool taken[kMaxExperts / 64];
+    // A wavefront takes its 8 tokens four at a time: the logits of all four in one round trip, and four independent
+    // chains through the K rounds of arg-max (alone each chain waits for its own cross-lane moves: 25 us for 8 tokens).
+    // A round: the largest remaining ordered logit over lanes and registers, then the lowest expert that holds it.
+    constexpr int TG = 4, NJ = kMaxExperts / 64;
+    for (int i0 = wave; i0 < kMoelBlock; i0 += TG * kWaves) {
+        uint32_t key[TG][NJ];
+        int my_id[TG];
+        float my_v[TG];
 #pragma unroll
-        for (int j = 0; j < kMaxExperts / 64; ++j) {
-            const int e = lane + 64 * j;
-            taken[j] = false;
-            v[j] = e < E ? ld_f32(lg + e) : -INFINITY;
-            if (dbg && e < E) as_global(P.dbg_logits)[(size_t)b * E + e] = v[j];
+        for (int u = 0; u < TG; ++u) {
+            const int b = blk * kMoelBlock + i0 + u * kWaves;
+            my_id[u] = 0;
+            my_v[u] = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int e = lane + 64 * j;
+                const bool live = b < P.B && e < E;
+                const float v = live ? ld_f32(P.router_logits + (size_t)b * E + e) : 0.f;
+                if (dbg && live) as_global(P.dbg_logits)[(size_t)b * E + e] = v;
+                const uint32_t bits = __float_as_uint(v), ord = (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
+                key[u][j] = live ? max(ord, 1u) : 0u;      // 0: taken, or no expert
+            }
         }
-        int my_id = 0;
-        float my_v = -INFINITY;
         if (forced) {
-            if (lane < K) {
-                my_id = gld_i32(P.forced_topk + (size_t)b * K + lane);
-                my_v = ld_f32(lg + my_id);
+#pragma unroll
+            for (int u = 0; u < TG; ++u) {
+                const int b = blk * kMoelBlock + i0 + u * kWaves;
+                if (b < P.B && lane < K) {
+                    my_id[u] = gld_i32(P.forced_topk + (size_t)b * K + lane);
+                    my_v[u] = ld_f32(P.router_logits + (size_t)b * E + my_id[u]);
+                }
             }
         } else {
             for (int k = 0; k < K; ++k) {
-                uint64_t key = 0;
 #pragma unroll
-                for (int j = 0; j < kMaxExperts / 64; ++j) {
-                    const int e = lane + 64 * j;
-                    if (e < E && !taken[j]) key = max(key, topk_key(v[j], e));
+                for (int u = 0; u < TG; ++u) {
+                    uint32_t mx = key[u][0];
+#pragma unroll
+                    for (int j = 1; j < NJ; ++j) mx = max(mx, key[u][j]);
+                    mx = wave_max_u32(mx);
+                    int e = -1;
+#pragma unroll
+                    for (int j = NJ - 1; j >= 0; --j) {
+                        const uint64_t who = __ballot(key[u][j] == mx);
+                        if (who) e = 64 * j + __builtin_ctzll(who);
+                    }
+                    if (lane == k) {
+                        my_id[u] = e;
+                        my_v[u] = __uint_as_float((mx & 0x80000000u) ? (mx & 0x7FFFFFFFu) : ~mx);
+                    }
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j)
+                        if (lane + 64 * j == e) key[u][j] = 0u;
                 }
-                key = wave_max_u64(key);
-                const int bi = (int)(0xFFFFFFFFu - (uint32_t)key);
-                if (lane == k) { my_id = bi; my_v = topk_key_logit(key); }
-#pragma unroll
-                for (int j = 0; j < kMaxExperts / 64; ++j)
-                    if (lane + 64 * j == bi) taken[j] = true;
             }
         }
-        float mx = lane < K ? my_v : -INFINITY;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-        const float p = lane < K ? __expf(my_v - mx) : 0.f;
-        const float den = wave_sum(p);
-        if (lane < K) {
-            float wgt = p / den;
-            if (forced_w) wgt = *as_global(P.forced_w + (size_t)b * K + lane);
-            st_i32(P.topk_ids + (size_t)b * K + lane, my_id);
-            st_f32(P.topk_w + (size_t)b * K + lane, wgt);
-            if (dbg) {
-                as_global(P.dbg_topk_ids)[(size_t)b * K + lane] = my_id;
-                as_global(P.dbg_topk_w)[(size_t)b * K + lane] = wgt;
+        for (int u = 0; u < TG; ++u) {
+            const int b = blk * kMoelBlock + i0 + u * kWaves;
+            if (b >= P.B) continue;
+            float mx = lane < K ? my_v[u] : -INFINITY;
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 16));      // K <= 16: one row of lanes
+            const float p = lane < K ? __expf(my_v[u] - mx) : 0.f;
+            const float den = wave_sum(p);
+            if (lane < K) {
+                float wgt = p / den;
+                if (forced_w) wgt = *as_global(P.forced_w + (size_t)b * K + lane);
+                st_i32(P.topk_ids + (size_t)b * K + lane, my_id[u]);
+                st_f32(P.topk_w + (size_t)b * K + lane, wgt);
+                if (dbg) {
+                    as_global(P.dbg_topk_ids)[(size_t)b * K + lane] = my_id[u];
+                    as_global(P.dbg_topk_w)[(size_t)b * K + lane] = wgt;
+                }
+                __hip_atomic_fetch_add(cnt + my_id[u], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);      // integer count: order-free
             }
-            __hip_atomic_fetch_add(cnt + my_id, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);      // integer count: order-free
         }
     }
     __syncthreads();
@@ -424,6 +480,8 @@ __device__ __noinline__ void moel_scan(const Params &P, float *sm)
     ETC_AS_LDS int32_t *tokp = til + kMaxExperts;                                      // [E+1]
     ETC_AS_LDS int32_t *expp = tokp + kMaxExperts + 1;                                 // [E+1]
     ETC_AS_LDS int32_t *blkp = expp + kMaxExperts + 1;                                 // [E+1] row blocks
+    typedef __attribute__((ext_vector_type(4))) int i32x4;
+    ETC_AS_LDS i32x4 *all = reinterpret_cast<ETC_AS_LDS i32x4 *>(cnt + 8 * kMaxExperts);   // [E] the three counts of an expert: one read each in the sums
     // A GroupGEMM task takes a row BLOCK of up to row_merge row tiles of one expert: the weights are streamed once for all
     // its columns.  Static grids: the blocks fill the first slots, in order; the other slots are left without rows.
     // Dynamic scheduler: an expert's tasks are released as the slots of its row tiles, so its blocks take the first of them.
@@ -440,11 +498,13 @@ __device__ __noinline__ void moel_scan(const Params &P, float *sm)
         }
         cnt[e] = n;
         til[e] = (n + M - 1) / M;
+        all[e] = i32x4{n, (n + M - 1) / M, (n + MB - 1) / MB, 0};
     }
     __syncthreads();
     for (int e = threadIdx.x; e <= E; e += kWgThreads) {
         int a = 0, c = 0, d = 0;
-        for (int j = 0; j < e; ++j) { a += cnt[j]; c += til[j]; d += (cnt[j] + MB - 1) / MB; }
+#pragma unroll 8
+        for (int j = 0; j < e; ++j) { const i32x4 v = all[j]; a += v.x; c += v.y; d += v.z; }
         tokp[e] = a;
         expp[e] = c;
         blkp[e] = d;
@@ -558,7 +618,14 @@ __device__ __noinline__ void moel_place(const Params &P, int blk, int group_ev, 
         for (int p = threadIdx.x; p < n_pairs; p += kWgThreads) {
             const int e = ids_s[p];
             int rank = 0;
-            for (int q = 0; q < p; ++q) rank += ids_s[q] == e ? 1 : 0;
+            typedef __attribute__((ext_vector_type(4))) int i32x4;
+            ETC_AS_LDS const i32x4 *ids4 = reinterpret_cast<ETC_AS_LDS const i32x4 *>(ids_s);
+            const int whole = p >> 2;              // every lane of a wavefront reads the same four: one access for all
+            for (int q = 0; q < whole; ++q) {
+                const i32x4 v = ids4[q];
+                rank += (v.x == e ? 1 : 0) + (v.y == e ? 1 : 0) + (v.z == e ? 1 : 0) + (v.w == e ? 1 : 0);
+            }
+            for (int q = whole * 4; q < p; ++q) rank += ids_s[q] == e ? 1 : 0;
             const int pos = base_s[e] + rank, pair = pair0 + p;
             st_i32(P.perm + pos, pair);
             st_i32(P.inv_perm + pair, pos);
@@ -603,46 +670,51 @@ __device__ __forceinline__ void moe_combine(const Params &P, const Task &t)
 
 // Combine of the stand-alone layer: task (block of `n_tok` tokens starting at tok0, 2048 consecutive elements).  One
 // task per token and 512 elements would be 16 384 tasks of two dependent load rounds each at 4096 tokens (415 us for
-// 320 MB); here a thread takes 4 consecutive elements (8-byte accesses) of two tokens at a time, so the row look-ups
-// and expert rows of both are in flight together.  The layer's output is y; no residual copy is kept.
+// 320 MB); here a thread takes 4 consecutive elements (16-byte loads) of a token, with the rows of up to 8 slots in
+// flight together.  The layer's output is y; no fp32 residual is kept.
 __device__ __forceinline__ void moel_combine(const Params &P, int tok0, int n_tok, int chunk)
 {
     const int h = (chunk * kWgThreads + (int)threadIdx.x) * 4;
     if (h >= P.H) return;
     const int K = P.topk;
-    constexpr int TB = 2;                        // tokens in flight per thread
     const int end = tok0 + n_tok < P.B ? tok0 + n_tok : P.B;
-    for (int b0 = tok0; b0 < end; b0 += TB) {
-        float acc[TB][4];
+    constexpr int SL = 8;
+    for (int b = tok0; b < end; ++b) {
+        const uint64_t xw = ld_u64(P.x_copy + (size_t)b * P.H + h);
+        float sum[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int k0 = 0; k0 < K; k0 += SL) {             // slots in ascending order
+            int pos[SL];
+            float wk[SL];
+            u32x4 y[SL];
 #pragma unroll
-        for (int u = 0; u < TB; ++u) {
-            const int b = b0 + u < end ? b0 + u : end - 1;
-            ld_f32x2(P.x_mid + (size_t)b * P.H + h, acc[u][0], acc[u][1]);
-            ld_f32x2(P.x_mid + (size_t)b * P.H + h + 2, acc[u][2], acc[u][3]);
-        }
-#pragma unroll
-        for (int u = 0; u < TB; ++u) {
-            const int b = b0 + u < end ? b0 + u : end - 1;
-            float sum[4] = {0.f, 0.f, 0.f, 0.f};
-            for (int k = 0; k < K; ++k) {            // slots in ascending order
-                const int pos = ld_i32(P.inv_perm + (size_t)b * K + k);
-                const float wk = ld_f32(P.topk_w + (size_t)b * K + k);
-                float y0, y1, y2, y3;
-                ld_f32x2(P.ey + (size_t)pos * P.H + h, y0, y1);
-                ld_f32x2(P.ey + (size_t)pos * P.H + h + 2, y2, y3);
-                sum[0] += wk * y0; sum[1] += wk * y1; sum[2] += wk * y2; sum[3] += wk * y3;
+            for (int k = 0; k < SL; ++k) {               // slots beyond K read the last one, weight 0, and are not added
+                const size_t p = (size_t)b * K + (k0 + k < K ? k0 + k : K - 1);
+                pos[k] = ld_i32(P.inv_perm + p);
+                wk[k] = ld_f32(P.topk_w + p);
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[u][q] += sum[q];
-        }
-#pragma unroll
-        for (int u = 0; u < TB; ++u) {
-            const int b = b0 + u;
-            if (b < end && P.hidden_out) {
-                const uint64_t v = (uint64_t)f32_to_bf16_bits(acc[u][0]) | ((uint64_t)f32_to_bf16_bits(acc[u][1]) << 16) |
-                                   ((uint64_t)f32_to_bf16_bits(acc[u][2]) << 32) | ((uint64_t)f32_to_bf16_bits(acc[u][3]) << 48);
-                *as_global(reinterpret_cast<uint64_t *>(P.hidden_out + (size_t)b * P.H + h)) = v;
+            for (int k = 0; k < SL; ++k) {
+                const int row = __builtin_amdgcn_readfirstlane(pos[k]);
+                y[k] = buf_ld_16B(buf_of(P.ey + (size_t)row * P.H), (uint32_t)h * 4u, 0);
             }
+#pragma unroll
+            for (int k = 0; k < SL; ++k) {
+                if (k0 + k < K) {                        // uniform
+                    sum[0] += wk[k] * __uint_as_float(y[k].x);
+                    sum[1] += wk[k] * __uint_as_float(y[k].y);
+                    sum[2] += wk[k] * __uint_as_float(y[k].z);
+                    sum[3] += wk[k] * __uint_as_float(y[k].w);
+                }
+            }
+        }
+        if (P.hidden_out) {
+            uint64_t v = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float x = bf16_bits_to_f32((uint32_t)(xw >> (16 * q)) & 0xFFFFu);
+                v |= (uint64_t)f32_to_bf16_bits(x + sum[q]) << (16 * q);
+            }
+            *as_global(reinterpret_cast<uint64_t *>(P.hidden_out + (size_t)b * P.H + h)) = v;
         }
     }
 }

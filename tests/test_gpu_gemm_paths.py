@@ -72,3 +72,25 @@ def test_group_gemm_row_blocks(tile_m, n_queues):
     _check_against_oracle(s, seed, x, outs[0][0], outs[0][1], tile_m, forced=ids)
     for y, r in outs[1:]:
         np.testing.assert_array_equal(y, outs[0][0])
+
+
+@pytest.mark.parametrize("shift", [0, 64])
+def test_moe_layer_output_over_its_input(shift):
+    """y may lie over x, whole or shifted by some rows."""
+    import torch
+
+    import paper_2604_13327_amd as etc
+    from synth import gpu as sgpu
+    s, seed, tokens = MOE_EDGES, 74, 300
+    w = _weights(s, seed)
+    x = sgpu.hidden_gpu(s, seed, tokens, tokens)
+    layer = etc.MoeLayer(s, [tokens], moe_tile_m=64, spin_budget=SPIN)
+    layer.bind_weights(w)
+    layer.bind_tokens(tokens)
+    want = _run(layer, x)
+    both = torch.zeros(tokens + shift, s.H, dtype=x.dtype, device="cuda")
+    both[shift:] = x
+    layer.launch(both[shift:], both[:tokens])
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(bf16_to_f32_np(both[:tokens]), want)
+    layer.close()
