@@ -205,7 +205,7 @@ int moe_tiles_per_task(const ModelDims &m, int tokens, int row_block, int per_sl
     for (int r = 1; r <= per_slot; ++r) {
         if (per_slot % r) continue;
         const double rounds = std::ceil(std::floor(blocks + 0.5) * (per_slot / r) / n_queues);
-        const double passes = cols <= 16 ? 1 : (r + 15) / 16;
+        const double passes = cols <= 16 ? 1 : (cols <= 32 ? (r + 15) / 16 : (r + 31) / 32);
         const double cost = rounds * (384.0 * 1024 + r * tile_bytes + passes * operand_bytes);
         if (best < 0 || cost < best) { best = cost; best_r = r; }
     }

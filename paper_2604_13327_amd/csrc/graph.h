@@ -110,7 +110,7 @@ inline int moe_row_merge(int tile_m, int hidden) { return tile_m > 32 && hidden 
 // drain, hand-over: about 15 us) is worth 384 KB of streaming; rounds = live tasks per queue, rounded up.  The live row
 // blocks are those uniform routing would give: the grid has a slot for every block any routing can produce, but at 100
 // tokens over 128 experts (top-8) 128 blocks live in 138 slots, and two tasks each are one round of 256 queues.  Blocks
-// of more than 16 columns pass over their operand once per 16 tiles.
+// of more than 16 columns pass over their operand once per 16 tiles, of more than 32 once per 32.
 int moe_tiles_per_task(const ModelDims &m, int tokens, int row_block, int per_slot, int K, int n_queues);
 
 // Keys per split-KV attention task for one sampled batch size.  `min_chunk` is the caller's tile shape; it

@@ -256,6 +256,7 @@ __device__ __forceinline__ void setup_moe_gemm(const Params &P, const Task &t, c
     const ETC_AS_GLOBAL LayerWeights *W = as_global(P.weights) + t.layer;
     g.n_tiles = t.c2;
     g.n_cols = rt.n;
+    g.w_shared = rt.shared;
     e.layer = t.layer;
     e.col0 = rt.row0;
     if (t.fn == FN_MOE_GATEUP) {

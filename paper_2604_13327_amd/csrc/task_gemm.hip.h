@@ -40,6 +40,7 @@ struct GemmTile {
     float eps;
     int n_tiles;                     // consecutive 16-row tiles this task streams back to back
     int tile_rows;                   // rows between consecutive tiles inside each 8-row group (8 or 16)
+    int w_shared;                    // GroupGEMM: other row blocks stream the same weights (they may stay in the caches)
 };
 
 constexpr uint16_t EPF_DUMP_LAYER = 0x8000;   // epilogue also records the layer's hidden state
@@ -1549,34 +1550,45 @@ __device__ __forceinline__ bool stream_fits(int n_tiles, int n_cols, int K, int 
            (long long)(64 + kWgThreads) * 4 + (long long)n_cols * (K + kOpPad) * 4 <= (long long)kLdsBytes;
 }
 
-// Row blocks of up to 16 * NB columns (128 at most) against any number of row tiles, 16 per pass (two per wavefront).
+// Row blocks of 33 .. 16 * NB columns (128 at most) against any number of row tiles, 8 * TW per pass (TW per wavefront).
 // The operand is walked in chunks through two LDS buffers as in the wide path, but the passes are one stream: the weights
 // of the next pass and its first operand chunk are requested while this one ends, and the epilogue needs no LDS, so
-// nothing drains between them.  Weight loads may allocate in the caches: the row blocks of one expert stream the same
-// rows.  A block of 64 columns moves 768 bytes per element of K and pass for 65 kflop, one of 128 columns 1 KB for 131:
-// what bounds the large token blocks is bytes through the fabric, 40 - 48 GB/s per compute unit.
-template <int NB>
+// nothing drains between them.  What bounds a large block is bytes through the fabric (40 - 48 GB/s per compute unit) and LDS reads of the
+// operand, which every wavefront takes whole; both shrink with the tiles of a pass, so a wavefront takes as many as its
+// registers hold (4 x 128 columns: 128 accumulators) and the chunk shrinks instead.
+// LINES (not for two tiles per wavefront): weights arrive as whole lines (8 rows x 64 elements of K per load, see unit_row;
+// here lane / 8 is the row and lane % 8 the piece) and turn into the product's fragments through 2 KB of LDS per wavefront;
+// the ring entry is free for its next load once it is written there.  48 tiles x 64 columns of K = 2048: 185 us with
+// fragments loaded as they stand, 161 with whole lines, 126 with whole lines past the caches (NT); the row blocks of an
+// expert that has several stream the same rows and find them in the caches, where fragments as they stand do better (32
+// tiles x 128 columns: 130 us, through LDS 145).
+template <int NB, int TW, bool LINES, bool NT>
 __device__ __noinline__ void gemm_tiles_blocks(const Params &P, const ChunkedArgs *args, float *sm, int *frame_anchor)
 {
     const ChunkedArgs a = lds_get_uniform(args);
     if (a.task_id == -0x7FFFFFFF) *frame_anchor = 1;      // never true; see gemm_tiles_chunked
     const GemmTile &g = a.g;
     const Epilogue &e = a.e;
-    constexpr int TW = 2, PASS = kWaves * TW;
-    constexpr int COLS = 16 * NB, KC = NB == 8 ? 128 : 256, KS = KC / 32, STRIDE = KC + 8;
+    constexpr int PASS = kWaves * TW;
+    constexpr int COLS = 16 * NB, KC = (TW == 2 ? 1024 : 512) / NB, KS = KC / 32, STRIDE = KC + 8;
     constexpr int PPC = KC / 8, U = COLS * PPC / kWgThreads, BUF = 2 * COLS * STRIDE;
     constexpr int RING = KS * TW;                  // weight fragments in flight per lane: one chunk
-    constexpr int NCOL = COLS < 64 ? 64 : COLS;
-    static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "column blocks");
+    constexpr int NBH = 4;                         // column blocks of one operand read
+    constexpr int NCOL = NB == 4 ? 64 : 128;       // norm factors: threads (column, group)
+    constexpr int UNITS = KC / kUnitK;             // LINES: units of a chunk; a ring entry pair is rows A and rows B of one
+    static_assert((NB == 4 || NB == 8) && TW >= 2 && TW <= 4 && (!LINES || TW > 2), "column blocks, tiles per wavefront");
     static_assert(U >= 1 && COLS * PPC == U * kWgThreads, "every thread moves U pieces of each half");
-    static_assert((size_t)2 * BUF * 2 + (NCOL + kWgThreads) * 4 <= (size_t)kLdsBytes, "two operand buffers and the norm scratch fit");
+    static_assert((size_t)2 * BUF * 2 + (NCOL + kWgThreads) * 4 + (LINES ? kWaves * 2048 : 0) <= (size_t)kLdsBytes, "two operand buffers, the norm scratch and the fragments fit");
     const int wave = __builtin_amdgcn_readfirstlane(wave_id()), lane = lane_id();
     const int m = lane & 15, kg = lane >> 4;
     const int n_tiles = __builtin_amdgcn_readfirstlane(g.n_tiles);
     const int n_chunks = __builtin_amdgcn_readfirstlane(g.K) / KC;
     const int total = (n_tiles + PASS - 1) / PASS * n_chunks;
     const uint32_t tile_step = (uint32_t)g.tile_rows * (uint32_t)g.ldw;
-    const uint16_t *wbase = (m < 8 ? g.rowsA + (size_t)m * (size_t)g.ldw : g.rowsB + (size_t)(m - 8) * (size_t)g.ldw) + kg * 8;
+    const uint16_t *wbase = LINES ? g.rowsA + (size_t)(lane >> 3) * (size_t)g.ldw + (lane & 7) * 8
+                                  : (m < 8 ? g.rowsA + (size_t)m * (size_t)g.ldw : g.rowsB + (size_t)(m - 8) * (size_t)g.ldw) + kg * 8;
+    const uint16_t *wbaseB = LINES ? g.rowsB + (size_t)(lane >> 3) * (size_t)g.ldw + (lane & 7) * 8 : wbase;
+    auto load_w = [&](const uint16_t *p) { return NT ? gld_16B_nt(p) : gld_16B(p); };
     // request cursor of the weights: chunk rc of the pass whose first tile of this wavefront is rt (tiles beyond the task
     // stream its last one again and are never stored: no branch in the loop)
     int rc = 0, rt = wave * TW;
@@ -1592,13 +1604,17 @@ __device__ __noinline__ void gemm_tiles_blocks(const Params &P, const ChunkedArg
     set_offsets();
     u32x4 wr[RING];
 #pragma unroll
-    for (int j = 0; j < RING; ++j) wr[j] = gld_16B(wbase + ro[j % TW] + (j / TW) * 32);
+    for (int j = 0; j < RING; ++j) {
+        if constexpr (LINES) wr[j] = load_w((j & 1 ? wbaseB : wbase) + ro[j / 2 % TW] + (j / 2 / TW) * kUnitK);
+        else wr[j] = load_w(wbase + ro[j % TW] + (j / TW) * 32);
+    }
     next_request();
     gemm_wait(P, a.w);
     trace_mark(P, a.task_id, 1);
 
     ETC_AS_LDS uint16_t *buf0 = reinterpret_cast<ETC_AS_LDS uint16_t *>(as_lds(sm));
     ETC_AS_LDS float *rs = reinterpret_cast<ETC_AS_LDS float *>(buf0 + 2 * BUF), *rs_part = rs + NCOL;
+    ETC_AS_LDS char *turn = reinterpret_cast<ETC_AS_LDS char *>(rs_part + kWgThreads) + wave * 2048;      // LINES: [16 rows][8 pieces], piece p of row r at p ^ (r & 7)
     const __amdgpu_buffer_rsrc_t hi_b = buf_of(g.b_hi), lo_b = buf_of(g.b_lo);
     uint32_t off[U];
     const int pc = (int)threadIdx.x % PPC;
@@ -1650,41 +1666,62 @@ __device__ __noinline__ void gemm_tiles_blocks(const Params &P, const ChunkedArg
             if (ti0 + t < n_tiles)
                 epilogue_direct<NB>(e, e.row0 + (ti0 + t) * g.tile_rows, g.n_cols, acc[t], rs, g.ssq_parts != nullptr);
     };
-    // One chunk out of LDS buffer b, in the order as written (see ETC_WIDE_CHUNK).
-#define ETC_BLOCK_CHUNK(b, RELOAD)                                                                             \
+    // One chunk out of LDS buffer b, in the order as written (see ETC_WIDE_CHUNK): per step of 32 elements of K hi, then lo,
+    // of NBH column blocks at a time; the fragments of the next read are requested ahead of this one's products.
+    // frag(t, kk): the weight fragment of step kk of the chunk.
+#define ETC_BLOCK_READS(b, k0, nk, FRAG, BEHIND)      /* steps k0 .. k0 + nk */                                   \
     {                                                                                                             \
-        ETC_AS_LDS const uint16_t *hi = buf0 + (b) * BUF + m * STRIDE + kg * 8;                                   \
-        ETC_AS_LDS const uint16_t *lo = hi + COLS * STRIDE;                                                       \
-        u32x4 fh[NB], fl[NB];                                                                                     \
-        _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                         \
-            fh[nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(hi + nb * 16 * STRIDE);                          \
+        ETC_AS_LDS const uint16_t *op = buf0 + (b) * BUF + m * STRIDE + kg * 8 + (k0) * 32;                       \
+        constexpr int NP = NB / NBH, READS = (nk) * NP * 2;                                                       \
+        u32x4 f[2][NBH];                                                                                          \
+        _Pragma("unroll") for (int nb = 0; nb < NBH; ++nb)                                                        \
+            f[0][nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(op + nb * 16 * STRIDE);                        \
         __builtin_amdgcn_sched_barrier(0);                                                                        \
-        _Pragma("unroll") for (int kk = 0; kk < KS; ++kk) {                                                       \
-            _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                     \
-                fl[nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(lo + nb * 16 * STRIDE + kk * 32);             \
-            _Pragma("unroll") for (int t = 0; t < TW; ++t) {                                                      \
-                const bf16x8 av = __builtin_bit_cast(bf16x8, wr[kk * TW + t]);                       \
-                _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) acc[t][nb] =                                    \
-                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, fh[nb]), acc[t][nb], 0, 0, 0); \
-            }                                                                                                     \
-            __builtin_amdgcn_sched_barrier(0);                                                                    \
-            if (kk + 1 < KS) {                                                                                    \
-                _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                 \
-                    fh[nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(hi + nb * 16 * STRIDE + (kk + 1) * 32);   \
+        _Pragma("unroll") for (int q = 0; q < READS; ++q) {      /* q = (step, column part, hi / lo) */           \
+            const int kk = q / (2 * NP), part = q / 2 % NP, qn = q + 1;                                           \
+            if (qn < READS) {                                                                                     \
+                _Pragma("unroll") for (int nb = 0; nb < NBH; ++nb) f[qn & 1][nb] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>( \
+                    op + (qn & 1) * (COLS * STRIDE) + ((qn / 2 % NP) * NBH + nb) * 16 * STRIDE + (qn / (2 * NP)) * 32); \
             }                                                                                                     \
             _Pragma("unroll") for (int t = 0; t < TW; ++t) {                                                      \
-                const bf16x8 av = __builtin_bit_cast(bf16x8, wr[kk * TW + t]);                       \
-                _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) acc[t][nb] =                                    \
-                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, fl[nb]), acc[t][nb], 0, 0, 0); \
+                const bf16x8 av = __builtin_bit_cast(bf16x8, FRAG);                                               \
+                _Pragma("unroll") for (int nb = 0; nb < NBH; ++nb) acc[t][part * NBH + nb] =                      \
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, f[q & 1][nb]), acc[t][part * NBH + nb], 0, 0, 0); \
             }                                                                                                     \
             __builtin_amdgcn_sched_barrier(0);                                                                    \
-            if (RELOAD) {                                                                                         \
-                _Pragma("unroll") for (int t = 0; t < TW; ++t) wr[kk * TW + t] = gld_16B(wbase + ro[t] + kk * 32); \
+            if (q % (2 * NP) == 2 * NP - 1) BEHIND                                                                \
+        }                                                                                                         \
+    }
+#define ETC_BLOCK_CHUNK(b, RELOAD)                                                                                \
+    if constexpr (LINES) {                                                                                        \
+        _Pragma("unroll") for (int un = 0; un < UNITS; ++un) {                                                    \
+            u32x4 fr[TW][2];                                                                                      \
+            _Pragma("unroll") for (int t = 0; t < TW; ++t) {      /* lines in, fragments out: in order within the wavefront */ \
+                const int j = (un * TW + t) * 2;                                                                  \
+                *reinterpret_cast<ETC_AS_LDS u32x4 *>(turn + lane_line) = wr[j];                                  \
+                *reinterpret_cast<ETC_AS_LDS u32x4 *>(turn + 1024 + lane_line) = wr[j + 1];                       \
+                fr[t][0] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(turn + lane_frag0);                        \
+                fr[t][1] = *reinterpret_cast<ETC_AS_LDS const u32x4 *>(turn + lane_frag1);                        \
+                if (RELOAD) {                                                                                     \
+                    wr[j] = load_w(wbase + ro[t] + un * kUnitK);                                                  \
+                    wr[j + 1] = load_w(wbaseB + ro[t] + un * kUnitK);                                             \
+                }                                                                                                 \
             }                                                                                                     \
+            ETC_BLOCK_READS(b, un * 2, 2, fr[t][kk], {})                                                          \
         }                                                                                                         \
         if (RELOAD) next_request();                                                                               \
         __builtin_amdgcn_sched_barrier(0);                                                                        \
+    } else {                                                                                                      \
+        ETC_BLOCK_READS(b, 0, KS, wr[kk * TW + t], {                                                              \
+            if (RELOAD) {                                                                                         \
+                _Pragma("unroll") for (int t = 0; t < TW; ++t) wr[kk * TW + t] = load_w(wbase + ro[t] + kk * 32); \
+            }                                                                                                     \
+        })                                                                                                        \
+        if (RELOAD) next_request();                                                                               \
+        __builtin_amdgcn_sched_barrier(0);                                                                        \
     }
+    const int lane_line = (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 3)) * 16);
+    const int lane_frag0 = m * 128 + ((kg ^ (m & 7)) * 16), lane_frag1 = m * 128 + (((4 + kg) ^ (m & 7)) * 16);
     int c = 0, gc = 0;                             // chunk inside the pass, chunk of the task
     auto next_chunk = [&]() { return c + 1 == n_chunks ? 0 : c + 1; };
     auto advance = [&]() {
@@ -1706,6 +1743,7 @@ __device__ __noinline__ void gemm_tiles_blocks(const Params &P, const ChunkedArg
     ETC_BLOCK_CHUNK(gc & 1, false)
     finish_pass();
 #undef ETC_BLOCK_CHUNK
+#undef ETC_BLOCK_READS
     trace_mark(P, a.task_id, 3);
     __syncthreads();                               // the operand buffers are free again
 }
@@ -1785,10 +1823,22 @@ __device__ __noinline__ void gemm_chunked_entry(const Params &PL, ChunkedArgs *s
             else gemm_tiles_stream<2>(PL, slot, sm, &anchor);
             return;
         }
-        if (a.g.n_cols > 64) { gemm_tiles_blocks<8>(PL, slot, sm, &anchor); return; }
-        if (a.g.n_tiles >= 5 && a.g.n_cols > 32) { gemm_tiles_blocks<4>(PL, slot, sm, &anchor); return; }
-        if (a.g.n_tiles >= 5 && a.g.n_cols > 16) { gemm_tiles_blocks<2>(PL, slot, sm, &anchor); return; }
-        if (a.g.n_tiles >= 5) { gemm_tiles_blocks<1>(PL, slot, sm, &anchor); return; }
+        // as few passes as four tiles per wavefront give, with as few tiles per wavefront as give them
+        const int n = a.g.n_tiles, passes = (n + 4 * kWaves - 1) / (4 * kWaves);
+        const int tw = n <= passes * 2 * kWaves ? 2 : (n <= passes * 3 * kWaves ? 3 : 4);
+#define ETC_BLOCKS(NB_, TW_, L_, NT_) { gemm_tiles_blocks<NB_, TW_, L_, NT_>(PL, slot, sm, &anchor); return; }
+        if (a.g.n_cols > 64) {
+            if (tw == 2) ETC_BLOCKS(8, 2, false, false)
+            if (a.g.w_shared) { if (tw == 3) ETC_BLOCKS(8, 3, false, false) else ETC_BLOCKS(8, 4, false, false) }
+            if (tw == 3) ETC_BLOCKS(8, 3, true, true)
+            ETC_BLOCKS(8, 4, true, true)
+        }
+        if (n >= 5 && a.g.n_cols > 32) {       // an expert's only block, or what its full blocks left: streamed once more at most
+            if (tw == 2) ETC_BLOCKS(4, 2, false, false)
+            if (tw == 3) ETC_BLOCKS(4, 3, true, true)
+            ETC_BLOCKS(4, 4, true, true)
+        }
+#undef ETC_BLOCKS
     }
     const bool wide_ok = buf_ok && a.g.K % 256 == 0;
     if (a.g.n_cols > 32 && a.g.n_tiles >= 16 && wide_ok) gemm_tiles_wide_passes<4, 4, 2>(PL, a, slot, sm, &anchor);

@@ -14,7 +14,9 @@ namespace etc {
 
 struct RowTile {
     int expert, row0, n;     // rows [row0, row0 + n) of the grouped tensors
+    int shared;              // the expert has other row blocks
 };
+constexpr int kTileShared = 1 << 16;      // flag in tile_n
 
 // Slot r of the static GroupGEMM grid -> its expert and rows; false for the surplus slots of this step, and for slots
 // whose rows another slot of their expert has taken over (moel_scan).
@@ -24,7 +26,9 @@ __device__ __forceinline__ bool resolve_row_tile(const Params &P, int r, RowTile
     if (r >= total) return false;
     rt.expert = __builtin_amdgcn_readfirstlane(ld_i32(P.tile_expert + r));
     rt.row0 = __builtin_amdgcn_readfirstlane(ld_i32(P.tile_row0 + r));
-    rt.n = __builtin_amdgcn_readfirstlane(ld_i32(P.tile_n + r));
+    const int n = __builtin_amdgcn_readfirstlane(ld_i32(P.tile_n + r));
+    rt.n = n & (kTileShared - 1);
+    rt.shared = n >= kTileShared;
     return rt.n > 0;
 }
 
@@ -530,7 +534,7 @@ __device__ __noinline__ void moel_scan(const Params &P, float *sm)
         for (; n > 0; n -= MB, ++r, row += MB) {
             st_i32(P.tile_expert + r, e);
             st_i32(P.tile_row0 + r, row);
-            st_i32(P.tile_n + r, n < MB ? n : MB);
+            st_i32(P.tile_n + r, (n < MB ? n : MB) | (cnt[e] > MB ? kTileShared : 0));
         }
         if (P.moe_dd)
             for (; r < expp[e + 1]; ++r) st_i32(P.tile_n + r, 0);
