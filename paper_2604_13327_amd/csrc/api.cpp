@@ -38,7 +38,7 @@ const char *kDynamicOffMsg = "the dynamic scheduler is switched off in this buil
 
 struct DevPlan {          // one instantiated plan (one sampled batch size), host + device copies
     int sampled_batch = 0;
-    int kv_chunk = 0;     // keys per attention task of this plan
+    int attn_grid = 1;    // attention task slots of a KV head
     int k_slices_o = 0, k_slices_d = 0;   // slices of K of this plan's O / down projection tasks
     bool all_staged = false;              // every projection task of this plan fits the staged path
     Plan host;
@@ -283,7 +283,7 @@ void fill_launch_params(etc_ctx *c, Params &P)
     P.B = c->bound_batch;
     P.Bs = dp.sampled_batch;
     P.max_chunks = c->max_chunks;
-    if (dp.kv_chunk > 0) P.kv_chunk = dp.kv_chunk;
+    P.attn_grid = dp.attn_grid;
     P.k_slices_o = dp.k_slices_o;
     P.k_slices_d = dp.k_slices_d;
     P.all_staged = dp.all_staged ? 1 : 0;
@@ -489,8 +489,9 @@ etc_status etc_create(const etc_model_desc *m, const etc_tile_desc *t, const etc
         c->plans.emplace_back();
         DevPlan &dp = c->plans.back();
         dp.sampled_batch = s->sampled_batch[i];
-        dp.kv_chunk = effective_kv_chunk(t->kv_chunk_tokens, m->page_size, s->max_kv_len, dp.sampled_batch, m->n_kv_heads, c->n_queues);
-        int syms[4] = {dp.sampled_batch, (s->max_kv_len + dp.kv_chunk - 1) / dp.kv_chunk, 0, 0};
+        const int kv_chunk = effective_kv_chunk(t->kv_chunk_tokens, m->page_size, s->max_kv_len, dp.sampled_batch, m->n_kv_heads, c->n_queues);
+        int syms[4] = {dp.sampled_batch, (s->max_kv_len + kv_chunk - 1) / kv_chunk, 0, 0};
+        dp.attn_grid = syms[0] * syms[1];
         std::string err = build_decoder_graph(d, dp.sampled_batch, c->n_queues, s->kind != ETC_SCHED_DYNAMIC, &c->graph);
         if (!err.empty()) { c->err = err; return bail(ETC_EINVAL); }
         dp.k_slices_o = c->graph.k_slices_o;

@@ -47,8 +47,8 @@ enum Fn : uint8_t {
     FN_ROWSUM_FINAL_PERM = 17,   // generic graphs: final sum of row block perm[task], tasks beyond indptr[last] do nothing
     FN_LOAD_HIDDEN = 3,   // hidden_in bf16 -> residual stream fp32
     FN_QKV = 4,           // RMSNorm prologue, 16 rows of Wq|Wk|Wv (8 RoPE pairs), RoPE, KV append
-    FN_ATTN = 5,          // split-KV partial attention of (sequence, kv head, chunk)
-    FN_MERGE = 6,         // merge of the chunk partials of (sequence, kv head)
+    FN_ATTN = 5,          // split-KV attention of a (sequence, kv head, chunk): see attn_chunk_keys
+    // 6: free (the chunk that arrives last merges the partials of its sequence)
     FN_OPROJ = 7,         // 16 rows of Wo + residual
     FN_GATEUP = 8,        // RMSNorm prologue, 8 gate + 8 up rows, SiLU-mul epilogue
     FN_DOWN = 9,          // 16 rows of Wd + residual (waves split K; each waits for its own K slice)
@@ -109,7 +109,7 @@ struct Params {
     int32_t page_shift;                // log2(page): pages hold a power of two of tokens
     float eps, theta;
     const double *rope_inv_freq;       // [d/2] theta^(-2i/d), computed on the host in double
-    int32_t kv_chunk, tile_m;
+    int32_t kv_chunk, tile_m;          // least keys of an attention chunk, tokens per row tile
     int32_t qk_norm;                   // per-head RMSNorm of q and k before RoPE (Qwen3-style)
     int32_t vocab;                     // > 0: final norm + vocabulary projection + greedy token at the end of the step
     const uint16_t *embed, *gf, *wlm;  // bf16: embedding table [vocab, H] (null: steps start from hidden states), final norm gain [H],
@@ -125,7 +125,8 @@ struct Params {
     // step shape
     int32_t B;                         // bound batch
     int32_t Bs;                        // sampled batch the queues were built for
-    int32_t max_chunks;                // attention chunk slots per sequence in the queues
+    int32_t max_chunks;                // most chunks of a sequence: stride of the partial results
+    int32_t attn_grid;                 // attention slots of a KV head in the queues
     const int32_t *kv_len, *page_indptr, *page_ids;
     const uint16_t *hidden_in;
     uint16_t *hidden_out;

@@ -113,7 +113,7 @@ inline int moe_row_merge(int tile_m, int hidden) { return tile_m > 32 && hidden 
 // of more than 16 columns pass over their operand once per 16 tiles, of more than 32 once per 32.
 int moe_tiles_per_task(const ModelDims &m, int tokens, int row_block, int per_slot, int K, int n_queues);
 
-// Keys per split-KV attention task for one sampled batch size.  `min_chunk` is the caller's tile shape; it
+// Attention task slots for one sampled batch size, as keys of a slot of the longest sequence.  `min_chunk` is the caller's tile shape; it
 // is enlarged (in whole pages) until a layer has at most one attention task per queue: every chunk costs a
 // partial result the merge reads back, and a second task per queue only adds such chunks (half a task per
 // queue leaves queues idle and measured slower from batch 4 on).

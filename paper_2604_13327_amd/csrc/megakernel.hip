@@ -406,46 +406,29 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
         if (!STAGED_ONLY || STAGED_SLICES) k_slice_sum_task(PL, t, w0, w1);
         break;
     case FN_ATTN: {
-        const int b = t.c0, kvh = t.c1, ch = t.c2;
-        const bool active = b < P.B && ch * P.kv_chunk < gld_i32(P.kv_len + b) + 1;
-        if (active) {     // inactive slots of the sampled-shape queue neither wait nor compute; they still notify
+        const int slot = t.c2 * P.Bs + t.c0, kvh = t.c1, ch = slot / P.B, b = slot - ch * P.B;
+        const int n_keys = gld_i32(P.kv_len + b) + 1, chunk = __builtin_amdgcn_readfirstlane(attn_chunk_keys(P, n_keys));
+        if (ch * chunk < n_keys) {     // inactive slots of the sampled-shape queue neither wait nor compute; they still notify
             st.staged_key = -1;      // the attention scratch overlaps the staged operand (the task waits inside)
             const int grp = P.nq / P.nkv;
-            const bool lds_pages = P.kv_chunk > 128;      // more than one batch of keys per chunk
-            const bool mfma_fits = (P.kv_chunk >> P.page_shift) <= 8192;      // page ids of a chunk next to the wavefronts' V tiles in LDS
+            const bool lds_pages = chunk > 128;      // more than one batch of keys per chunk
+            const bool mfma_fits = (chunk >> P.page_shift) <= 8192;      // page ids of a chunk next to the wavefronts' V tiles in LDS
             bool ran = false;
 #define ETC_ATTN(DD, GG)                                                                   \
     if (!ran && P.d == DD && grp == GG) {                                                  \
         ran = true;                                                                        \
         if constexpr (DD == 128 && GG == 8) {                                              \
-            if (lds_pages && mfma_fits) attn_chunk_mfma<GG>(PL, t.layer, b, kvh, ch, sm, w0, w1, t.id);   \
-            else if (lds_pages) attn_chunk<DD, GG, true>(PL, t.layer, b, kvh, ch, sm, w0, w1, t.id);       \
-            else attn_chunk<DD, GG, false>(PL, t.layer, b, kvh, ch, sm, w0, w1, t.id);     \
+            if (lds_pages && mfma_fits) attn_chunk_mfma<GG>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);   \
+            else if (lds_pages) attn_chunk<DD, GG, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);       \
+            else attn_chunk<DD, GG, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);     \
         } else {                                                                           \
-            if (lds_pages) attn_chunk<DD, GG, true>(PL, t.layer, b, kvh, ch, sm, w0, w1, t.id);  \
-            else attn_chunk<DD, GG, false>(PL, t.layer, b, kvh, ch, sm, w0, w1, t.id);     \
+            if (lds_pages) attn_chunk<DD, GG, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);  \
+            else attn_chunk<DD, GG, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);     \
         }                                                                                  \
     }
             ETC_ATTN_SHAPES(ETC_ATTN)
 #undef ETC_ATTN
             if (!ran && threadIdx.x == 0) raise_error(P, ERR_NO_BODY, FN_ATTN, P.d * 256 + grp);   // refused at create; never silently skipped
-        }
-        break;
-    }
-    case FN_MERGE: {
-        const int b = t.c0, kvh = t.c1;
-        if (b < P.B) {
-            wg_wait_cached(P, st, w0, w1, t.fn);
-            const int grp = P.nq / P.nkv;
-            bool ran = false;
-#define ETC_MERGE(DD, GG)                                                                  \
-    if (!ran && P.d == DD && grp == GG) {                                                  \
-        ran = true;                                                                        \
-        attn_merge<DD, GG>(PL, b, kvh);                                                    \
-    }
-            ETC_ATTN_SHAPES(ETC_MERGE)
-#undef ETC_MERGE
-            if (!ran && threadIdx.x == 0) raise_error(P, ERR_NO_BODY, FN_MERGE, P.d * 256 + grp);
         }
         break;
     }

@@ -1,7 +1,7 @@
-// Paged decode attention as two task kinds (split-KV):
+// Paged decode attention (split-KV):
 //   attn_chunk  (sequence b, kv head, chunk): online-softmax partial (m, l, o) of the group's query
 //               heads over the chunk's keys, K/V rows gathered through the page table;
-//   attn_merge  (sequence b, kv head): combines the chunk partials in ascending chunk order.
+//               the chunk that arrives last at its (sequence, kv head) combines the partials in ascending order.
 // Head dim D is split 8 elements per lane (16-byte loads of a bf16 K or V row slice), so D/8 lanes
 // cover one key and a wavefront covers 64/(D/8) keys per load instruction; the 8 wavefronts of the
 // workgroup stride over the chunk.  Reductions are wavefront shuffles, then LDS across waves.
@@ -21,17 +21,30 @@ template <int GRP> constexpr int kAttnOff = (2 * kAttnEnt * GRP + 3) & ~3;      
 
 template <int D, int GRP> __device__ __forceinline__ void attn_merge_chunks(const Params &P, int b, int kvh, int nc);
 
+// Keys per chunk of sequence b, and the chunk a slot of the attention grid stands for.  The grid has max_slots slots per
+// KV head; a step of P.B sequences gives each max_slots / P.B of them and splits it evenly, in whole pages and not finer than
+// the caller's chunk: the slots of one sequence are equally long, and a batch below the sampled one uses all of them.  With
+// chunks of a fixed number of keys (the longest sequence cut into the sampled batch's slots) a sequence of 1.5 chunks left
+// half of its second slot idle, and a batch of 5 in the plan of 8 three eighths of the queues.
+__device__ __forceinline__ int attn_chunk_keys(const Params &P, int n_keys)
+{
+    const int slots = P.attn_grid / P.B;
+    const int pages = (n_keys + P.page - 1) >> P.page_shift;
+    const int even = ((pages + slots - 1) / slots) << P.page_shift;
+    return even > P.kv_chunk ? even : P.kv_chunk;
+}
+
 // The end of a chunk task: the first n_ent LDS entries (complete, behind a barrier) are reduced to the chunk's result,
 // which is the attention output itself or one of the sequence's partial results.
 template <int D, int GRP>
-__device__ __forceinline__ void attn_finish(const Params &P, int b, int kvh, int ch, int n_keys, int n_ent, float *sm, int task_id)
+__device__ __forceinline__ void attn_finish(const Params &P, int b, int kvh, int ch, int chunk, int n_keys, int n_ent, float *sm, int task_id)
 {
     ETC_AS_LDS float *s_m = as_lds(sm);
     ETC_AS_LDS float *s_l = s_m + kAttnEnt * GRP;
     ETC_AS_LDS float *s_o = s_m + kAttnOff<GRP>;
     // A sequence that is one chunk long needs no partial results, no arrival count and no merge: what a merge of one
     // chunk would compute is exactly num / den below (three memory round trips less at the end of the task).
-    const int nc = (n_keys + P.kv_chunk - 1) / P.kv_chunk;
+    const int nc = (n_keys + chunk - 1) / chunk;
     const bool whole = nc == 1 && P.attn_arrive != nullptr;
     for (int idx = threadIdx.x; idx < GRP * D / 4; idx += kWgThreads) {      // four consecutive elements per thread: 8-byte stores
         const int g = idx / (D / 4), i = (idx % (D / 4)) * 4;
@@ -85,13 +98,14 @@ __device__ __forceinline__ void attn_finish(const Params &P, int b, int kvh, int
 // rows do not depend on them: a chunk of one batch requests its rows BEFORE it waits, like a projection task its
 // weights, so that after the wait only the queries are a round trip away (3.72 -> 3.62 ms per 8B step).
 template <int D, int GRP, bool PAGES_IN_LDS>
-__device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int kvh, int ch, float *sm, int ev0, int ev1, int task_id)
+__device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int kvh, int ch, int chunk, float *sm, int ev0, int ev1, int task_id)
 {
     task_id = __builtin_amdgcn_readfirstlane(task_id);
     layer = __builtin_amdgcn_readfirstlane(layer);      // uniform arguments back into scalar registers
     b = __builtin_amdgcn_readfirstlane(b);
     kvh = __builtin_amdgcn_readfirstlane(kvh);
     ch = __builtin_amdgcn_readfirstlane(ch);
+    chunk = __builtin_amdgcn_readfirstlane(chunk);
     ev0 = __builtin_amdgcn_readfirstlane(ev0);
     ev1 = __builtin_amdgcn_readfirstlane(ev1);
     constexpr int LPT = D / 8;        // lanes per key
@@ -99,8 +113,8 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
     const int wave = wave_id(), lane = lane_id();
     const int tq = lane / LPT, dl = lane % LPT;
     const int n_keys = gld_i32(P.kv_len + b) + 1;
-    const int j0 = ch * P.kv_chunk;
-    const int j1 = min(n_keys, j0 + P.kv_chunk);
+    const int j0 = ch * chunk;
+    const int j1 = min(n_keys, j0 + chunk);
     const int32_t *pages = P.page_ids + gld_i32(P.page_indptr + b);
     const size_t lbase = (size_t)layer * (size_t)P.pool_layer_stride;
     const float qscale = 1.0f / sqrtf((float)D);
@@ -335,7 +349,7 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
         }
     }
     __syncthreads();
-    attn_finish<D, GRP>(P, b, kvh, ch, n_keys, kWaves, sm, task_id);
+    attn_finish<D, GRP>(P, b, kvh, ch, chunk, n_keys, kWaves, sm, task_id);
 }
 
 // Long chunks on the matrix cores (head dim 128, 8 query heads per KV head).  With 8 query heads per key the VALU
@@ -353,7 +367,7 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
 // K and V rows of the next step are in flight while a step computes (V from the step's start, K from the end of its
 // score products); the step's own token goes into an LDS entry of its own, next to the wavefronts' partial results.
 template <int GRP>
-__device__ __noinline__ void attn_chunk_mfma(const Params &P, int layer, int b, int kvh, int ch, float *sm, int ev0, int ev1, int task_id)
+__device__ __noinline__ void attn_chunk_mfma(const Params &P, int layer, int b, int kvh, int ch, int chunk, float *sm, int ev0, int ev1, int task_id)
 {
     static_assert(GRP == 4 || GRP == 8, "query heads per KV head");
     constexpr int D = 128, RS = 264;                     // RS: bytes between two rows of the V tile (264 = 66 words: 2-byte reads of 4 rows x 16 columns hit 32 different banks)
@@ -362,13 +376,14 @@ __device__ __noinline__ void attn_chunk_mfma(const Params &P, int layer, int b, 
     b = __builtin_amdgcn_readfirstlane(b);
     kvh = __builtin_amdgcn_readfirstlane(kvh);
     ch = __builtin_amdgcn_readfirstlane(ch);
+    chunk = __builtin_amdgcn_readfirstlane(chunk);
     ev0 = __builtin_amdgcn_readfirstlane(ev0);
     ev1 = __builtin_amdgcn_readfirstlane(ev1);
     const int wave = wave_id(), lane = lane_id();
     const int n16 = lane & 15, kg = lane >> 4;
     const int n_keys = gld_i32(P.kv_len + b) + 1;
-    const int j0 = ch * P.kv_chunk;
-    const int j1 = min(n_keys, j0 + P.kv_chunk);
+    const int j0 = ch * chunk;
+    const int j1 = min(n_keys, j0 + chunk);
     const int32_t *pages = P.page_ids + gld_i32(P.page_indptr + b);
     const size_t lbase = (size_t)layer * (size_t)P.pool_layer_stride;
     const float qscale = 1.0f / sqrtf((float)D);
@@ -590,7 +605,7 @@ __device__ __noinline__ void attn_chunk_mfma(const Params &P, int layer, int b, 
         }
     }
     __syncthreads();
-    attn_finish<D, GRP>(P, b, kvh, ch, n_keys, has_new ? kWaves + 1 : kWaves, sm, task_id);
+    attn_finish<D, GRP>(P, b, kvh, ch, chunk, n_keys, has_new ? kWaves + 1 : kWaves, sm, task_id);
 }
 
 // Merge of the chunk partials of (sequence b, KV head kvh): ascending chunk order, whoever runs it.
@@ -629,16 +644,6 @@ __device__ __forceinline__ void attn_merge_chunks(const Params &P, int b, int kv
         st_u16(P.attn_hi + o, hi);
         st_u16(P.attn_lo + o, lo);
     }
-}
-
-// The merge as a task of its own (graphs that keep a merge stage).
-template <int D, int GRP>
-__device__ __noinline__ void attn_merge(const Params &P, int b, int kvh)
-{
-    b = __builtin_amdgcn_readfirstlane(b);
-    kvh = __builtin_amdgcn_readfirstlane(kvh);
-    const int n_keys = gld_i32(P.kv_len + b) + 1;
-    attn_merge_chunks<D, GRP>(P, b, kvh, (n_keys + P.kv_chunk - 1) / P.kv_chunk);
 }
 
 }  // namespace etc

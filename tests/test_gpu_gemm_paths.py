@@ -94,3 +94,34 @@ def test_moe_layer_output_over_its_input(shift):
     torch.cuda.synchronize()
     np.testing.assert_array_equal(bf16_to_f32_np(both[:tokens]), want)
     layer.close()
+
+
+@pytest.mark.parametrize("batch", [1, 3, 5, 8])
+def test_attention_slots_of_a_batch_below_the_sampled_one(batch):
+    """The slots of the sampled batch (8) are shared out to the bound one: chunk counts from 1 to all slots, lengths on and
+    around the chunk and page boundaries those give."""
+    import torch
+
+    import paper_2604_13327_amd as etc
+    s, lens = synth.TINY, [300, 0, 31, 32, 255, 127, 128, 511][:batch]
+    pages = sum(n // 16 + 1 for n in lens) + 4
+    model = GpuModel(s, seed=75, n_pool_pages=pages)
+    step = fixed_step(s, batch, lens, pages, seed=76)
+    x = model.hidden(0, batch)
+    ref = oracle_step(s, model.seed, pages, step, 0)["final"]
+    outs = []
+    for kind in (etc.SCHED_STATIC, etc.SCHED_DYNAMIC, etc.SCHED_UNFUSED):
+        model.reset_pools()
+        dec = etc.Decoder(s, kv_chunk_tokens=32, sampled_batches=[8], max_kv_len=512, kind=kind, spin_budget=SPIN)
+        model.bind(dec)
+        dec.bind_step(step)
+        out = torch.full_like(x, float("nan"))
+        for _ in range(2):
+            dec.launch(x, out)
+        torch.cuda.synchronize()
+        assert (dec.error_word() == 0).all() and (dec.event_counters() == 0).all()
+        outs.append(bf16_to_f32_np(out))
+        dec.close()
+    assert rel_err(outs[0], ref) <= TOL
+    for o in outs[1:]:
+        np.testing.assert_array_equal(o, outs[0])
