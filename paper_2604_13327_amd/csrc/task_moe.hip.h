@@ -8,6 +8,8 @@
 // counting and ranking, never by grabbing slots with atomics, so the permutation is the same in
 // every run and under every schedule.
 #pragma once
+#include <type_traits>
+
 #include "device_rt.hip.h"
 
 namespace etc {
@@ -33,50 +35,8 @@ __device__ __forceinline__ bool resolve_row_tile(const Params &P, int r, RowTile
 }
 
 // ---- wavefront arg-max of the router's top-k -------------------------------------------------------------
-// (logit, expert) as one unsigned key: floats map to integers of the same order (sign bit flipped for
-// non-negative values, all bits for negative ones), the index is complemented so that a lower index wins a tie.
-__device__ __forceinline__ uint64_t topk_key(float logit, int expert)
-{
-    const uint32_t u = __float_as_uint(logit);
-    const uint32_t ord = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-    return ((uint64_t)ord << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)expert);
-}
-
-__device__ __forceinline__ float topk_key_logit(uint64_t key)
-{
-    const uint32_t ord = (uint32_t)(key >> 32);
-    return __uint_as_float((ord & 0x80000000u) ? (ord & 0x7FFFFFFFu) : ~ord);
-}
-
-template <int CTRL>
-__device__ __forceinline__ uint64_t dpp_max_u64(uint64_t k)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)k, CTRL, 0xF, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(k >> 32), CTRL, 0xF, 0xF, false);
-    const uint64_t o = ((uint64_t)hi << 32) | lo;
-    return o > k ? o : k;
-}
-
-// Maximum over the 64 lanes, the same value in every lane: quad exchanges, half-row mirror and row mirror leave
-// each row of 16 lanes with its maximum; the four row maxima are read as scalars.
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t k)
-{
-    k = dpp_max_u64<0xB1>(k);      // quad_perm [1,0,3,2]
-    k = dpp_max_u64<0x4E>(k);      // quad_perm [2,3,0,1]
-    k = dpp_max_u64<0x141>(k);     // row_half_mirror
-    k = dpp_max_u64<0x140>(k);     // row_mirror
-    uint64_t best = 0;
-#pragma unroll
-    for (int row = 0; row < 4; ++row) {
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)k, row * 16);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(k >> 32), row * 16);
-        const uint64_t r = ((uint64_t)hi << 32) | lo;
-        best = r > best ? r : best;
-    }
-    return best;
-}
-
-// The same for 32-bit values.
+// Maximum over the 64 lanes, the same value in every lane: quad exchanges, half-row mirror and row mirror leave each row of 16
+// lanes with its maximum; the four row maxima are read as scalars.
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 {
     v = max(v, (uint32_t)dpp_i32<0xB1>((int)v));
@@ -86,6 +46,57 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
     const uint32_t a = max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
     const uint32_t b = max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
     return max(a, b);
+}
+
+// Top-k of TG tokens by one wavefront (token u's logits at row row0 + u * step, valid below n_rows): lane k < K gets the k-th
+// expert and its logit; larger logit first, equal logits: lower expert first.  The logits of all tokens arrive in one round
+// trip, and the tokens are independent chains through the K rounds of arg-max (alone each waits for its own cross-lane
+// moves: 3 us a token).  A round: the largest remaining ordered logit over lanes and registers, then the lowest expert that
+// holds it.  seen(u, e, v): called with every logit.
+template <int TG, class SEEN>
+__device__ __forceinline__ void wave_topk(const float *logits, int E, int K, int row0, int step, int n_rows, int (&id)[TG], float (&val)[TG],
+                                          const SEEN &seen)
+{
+    constexpr int NJ = kMaxExperts / 64;
+    const int lane = lane_id();
+    uint32_t key[TG][NJ];
+#pragma unroll
+    for (int u = 0; u < TG; ++u) {
+        const int b = row0 + u * step;
+        id[u] = 0;
+        val[u] = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int e = lane + 64 * j;
+            const bool live = b < n_rows && e < E;
+            const float v = live ? ld_f32(logits + (size_t)b * E + e) : 0.f;
+            if (live) seen(u, e, v);
+            const uint32_t bits = __float_as_uint(v), ord = (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
+            key[u][j] = live ? max(ord, 1u) : 0u;          // 0: taken, or no expert
+        }
+    }
+    for (int k = 0; k < K; ++k) {
+#pragma unroll
+        for (int u = 0; u < TG; ++u) {
+            uint32_t mx = key[u][0];
+#pragma unroll
+            for (int j = 1; j < NJ; ++j) mx = max(mx, key[u][j]);
+            mx = wave_max_u32(mx);
+            int e = -1;
+#pragma unroll
+            for (int j = NJ - 1; j >= 0; --j) {
+                const uint64_t who = __ballot(key[u][j] == mx);
+                if (who) e = 64 * j + __builtin_ctzll(who);
+            }
+            if (lane == k) {
+                id[u] = e;
+                val[u] = __uint_as_float((mx & 0x80000000u) ? (mx & 0x7FFFFFFFu) : ~mx);
+            }
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                if (lane + 64 * j == e) key[u][j] = 0u;
+        }
+    }
 }
 
 // Data-dependent event update and task triggering (Sec. 2.4), dynamic scheduler only.  The expert event
@@ -186,8 +197,7 @@ __device__ __noinline__ void moe_route_and_group(const Params &P, int layer, int
     const int E = P.E, K = P.topk, B = P.B, N = B * K, M = P.tile_m;
     ETC_AS_LDS int32_t *ids_s = reinterpret_cast<ETC_AS_LDS int32_t *>(as_lds(sm));   // [B*K] expert of every pair
     ETC_AS_LDS int32_t *cnt = ids_s + kMaxBatch * kMaxTopK;                            // [E]
-    ETC_AS_LDS int32_t *til = cnt + kMaxExperts;                                       // [E] row tiles per expert
-    ETC_AS_LDS int32_t *tokp = til + kMaxExperts;                                      // [E+1]
+    ETC_AS_LDS int32_t *tokp = cnt + kMaxExperts;                                      // [E+1]
     ETC_AS_LDS int32_t *expp = tokp + kMaxExperts + 1;                                 // [E+1]
     const int forced_bits = P.forced_mask != nullptr ? (int)*as_global(P.forced_mask + layer) : 0;
     const bool forced = (forced_bits & 1) != 0, forced_w = forced && (forced_bits & 2) != 0 && P.forced_w != nullptr;
@@ -195,73 +205,60 @@ __device__ __noinline__ void moe_route_and_group(const Params &P, int layer, int
     const size_t dbg_row = (size_t)layer * P.max_batch + t;
 
     for (int e = threadIdx.x; e < E; e += kWgThreads) cnt[e] = 0;
-    for (int b = wave; b < B; b += kWaves) {
-        const float *lg = P.router_logits + (size_t)b * E;
-        float v[kMaxExperts / 64];
-        bool taken[kMaxExperts / 64];
+    auto route = [&](auto tokens) {      // tokens in flight per wavefront
+        constexpr int TG = decltype(tokens)::value;
+        for (int b0 = wave; b0 < B; b0 += TG * kWaves) {
+            int id[TG];
+            float val[TG];
+            wave_topk<TG>(P.router_logits, E, forced ? 0 : K, b0, kWaves, B, id, val, [&](int u, int e, float v) {
+                if (dbg && b0 + u * kWaves == t) as_global(P.dbg_logits)[dbg_row * E + e] = v;
+            });
 #pragma unroll
-        for (int j = 0; j < kMaxExperts / 64; ++j) {
-            const int e = lane + 64 * j;
-            taken[j] = false;
-            v[j] = e < E ? ld_f32(lg + e) : -INFINITY;
-            if (dbg && b == t && e < E) as_global(P.dbg_logits)[dbg_row * E + e] = v[j];
-        }
-        int my_id = 0;
-        float my_v = -INFINITY;
-        if (forced) {
-            if (lane < K) {
-                my_id = gld_i32(P.forced_topk + ((size_t)layer * P.max_batch + b) * K + lane);
-                my_v = ld_f32(lg + my_id);
-            }
-        } else {
-            for (int k = 0; k < K; ++k) {
-                // One 64-bit key per candidate: the logit in an order-preserving integer form above, the
-                // complement of the expert index below, so the largest key is the largest logit and, among equal
-                // logits, the lowest index.  The wavefront maximum takes four DPP steps inside each row of 16
-                // lanes and a scalar maximum over the four rows (a shuffle-based arg-max, six dependent LDS
-                // round trips of two words each, made a router tile of a large batch the longest task of the layer).
-                uint64_t key = 0;
-#pragma unroll
-                for (int j = 0; j < kMaxExperts / 64; ++j) {
-                    const int e = lane + 64 * j;
-                    if (e < E && !taken[j]) key = max(key, topk_key(v[j], e));
+            for (int u = 0; u < TG; ++u) {
+                const int b = b0 + u * kWaves;
+                if (b >= B) continue;
+                int my_id = id[u];
+                float my_v = val[u];
+                if (forced && lane < K) {
+                    my_id = gld_i32(P.forced_topk + ((size_t)layer * P.max_batch + b) * K + lane);
+                    my_v = ld_f32(P.router_logits + (size_t)b * E + my_id);
                 }
-                key = wave_max_u64(key);
-                const int bi = (int)(0xFFFFFFFFu - (uint32_t)key);
-                if (lane == k) { my_id = bi; my_v = topk_key_logit(key); }
+                if (lane < K) ids_s[b * K + lane] = my_id;
+                if (b == t) {
+                    float mx = lane < K ? my_v : -INFINITY;
 #pragma unroll
-                for (int j = 0; j < kMaxExperts / 64; ++j)
-                    if (lane + 64 * j == bi) taken[j] = true;
-            }
-        }
-        if (lane < K) ids_s[b * K + lane] = my_id;
-        if (b == t) {
-            float mx = lane < K ? my_v : -INFINITY;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-            const float p = lane < K ? __expf(my_v - mx) : 0.f;
-            const float den = wave_sum(p);
-            if (lane < K) {
-                float wgt = p / den;
-                if (forced_w) wgt = *as_global(P.forced_w + ((size_t)layer * P.max_batch + b) * K + lane);
-                st_i32(P.topk_ids + (size_t)t * K + lane, my_id);
-                st_f32(P.topk_w + (size_t)t * K + lane, wgt);
-                if (dbg) {
-                    as_global(P.dbg_topk_ids)[dbg_row * K + lane] = my_id;
-                    as_global(P.dbg_topk_w)[dbg_row * K + lane] = wgt;
+                    for (int off = 8; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 16));      // K <= 16: one row of lanes
+                    const float p = lane < K ? __expf(my_v - mx) : 0.f;
+                    const float den = wave_sum(p);
+                    if (lane < K) {
+                        float wgt = p / den;
+                        if (forced_w) wgt = *as_global(P.forced_w + ((size_t)layer * P.max_batch + b) * K + lane);
+                        st_i32(P.topk_ids + (size_t)t * K + lane, my_id);
+                        st_f32(P.topk_w + (size_t)t * K + lane, wgt);
+                        if (dbg) {
+                            as_global(P.dbg_topk_ids)[dbg_row * K + lane] = my_id;
+                            as_global(P.dbg_topk_w)[dbg_row * K + lane] = wgt;
+                        }
+                    }
                 }
             }
         }
-    }
+    };
+    // up to 8 tokens a wavefront has one at most, and dead chains would cost it 4 us
+    if (B <= kWaves) route(std::integral_constant<int, 1>());
+    else route(std::integral_constant<int, 4>());
     __syncthreads();
     for (int i = threadIdx.x; i < N; i += kWgThreads)
         __hip_atomic_fetch_add(cnt + ids_s[i], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __syncthreads();
-    for (int e = threadIdx.x; e < E; e += kWgThreads) til[e] = (cnt[e] + M - 1) / M;
+    typedef __attribute__((ext_vector_type(2))) int i32x2;
+    ETC_AS_LDS i32x2 *both = reinterpret_cast<ETC_AS_LDS i32x2 *>(expp + kMaxExperts + 2);      // [E] pairs and row tiles of an expert: one read in the sums
+    for (int e = threadIdx.x; e < E; e += kWgThreads) both[e] = i32x2{cnt[e], (cnt[e] + M - 1) / M};
     __syncthreads();
     for (int e = threadIdx.x; e <= E; e += kWgThreads) {
         int a = 0, c = 0;
-        for (int j = 0; j < e; ++j) { a += cnt[j]; c += til[j]; }
+#pragma unroll 8
+        for (int j = 0; j < e; ++j) { const i32x2 v = both[j]; a += v.x; c += v.y; }
         tokp[e] = a;
         expp[e] = c;
     }
@@ -390,29 +387,13 @@ __device__ __noinline__ void moel_topk(const Params &P, int blk, float *sm)
     const bool dbg = (P.debug_flags & 4u) != 0 && P.dbg_logits != nullptr;
     for (int e = threadIdx.x; e < E; e += kWgThreads) cnt[e] = 0;
     __syncthreads();
-    // A wavefront takes its 8 tokens four at a time: the logits of all four in one round trip, and four independent
-    // chains through the K rounds of arg-max (alone each chain waits for its own cross-lane moves: 25 us for 8 tokens).
-    // A round: the largest remaining ordered logit over lanes and registers, then the lowest expert that holds it.
-    constexpr int TG = 4, NJ = kMaxExperts / 64;
+    constexpr int TG = 4;      // a wavefront takes its 8 tokens four at a time
     for (int i0 = wave; i0 < kMoelBlock; i0 += TG * kWaves) {
-        uint32_t key[TG][NJ];
         int my_id[TG];
         float my_v[TG];
-#pragma unroll
-        for (int u = 0; u < TG; ++u) {
-            const int b = blk * kMoelBlock + i0 + u * kWaves;
-            my_id[u] = 0;
-            my_v[u] = -INFINITY;
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const int e = lane + 64 * j;
-                const bool live = b < P.B && e < E;
-                const float v = live ? ld_f32(P.router_logits + (size_t)b * E + e) : 0.f;
-                if (dbg && live) as_global(P.dbg_logits)[(size_t)b * E + e] = v;
-                const uint32_t bits = __float_as_uint(v), ord = (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
-                key[u][j] = live ? max(ord, 1u) : 0u;      // 0: taken, or no expert
-            }
-        }
+        wave_topk<TG>(P.router_logits, E, forced ? 0 : K, blk * kMoelBlock + i0, kWaves, P.B, my_id, my_v, [&](int u, int e, float v) {
+            if (dbg) as_global(P.dbg_logits)[(size_t)(blk * kMoelBlock + i0 + u * kWaves) * E + e] = v;
+        });
         if (forced) {
 #pragma unroll
             for (int u = 0; u < TG; ++u) {
@@ -420,29 +401,6 @@ __device__ __noinline__ void moel_topk(const Params &P, int blk, float *sm)
                 if (b < P.B && lane < K) {
                     my_id[u] = gld_i32(P.forced_topk + (size_t)b * K + lane);
                     my_v[u] = ld_f32(P.router_logits + (size_t)b * E + my_id[u]);
-                }
-            }
-        } else {
-            for (int k = 0; k < K; ++k) {
-#pragma unroll
-                for (int u = 0; u < TG; ++u) {
-                    uint32_t mx = key[u][0];
-#pragma unroll
-                    for (int j = 1; j < NJ; ++j) mx = max(mx, key[u][j]);
-                    mx = wave_max_u32(mx);
-                    int e = -1;
-#pragma unroll
-                    for (int j = NJ - 1; j >= 0; --j) {
-                        const uint64_t who = __ballot(key[u][j] == mx);
-                        if (who) e = 64 * j + __builtin_ctzll(who);
-                    }
-                    if (lane == k) {
-                        my_id[u] = e;
-                        my_v[u] = __uint_as_float((mx & 0x80000000u) ? (mx & 0x7FFFFFFFu) : ~mx);
-                    }
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j)
-                        if (lane + 64 * j == e) key[u][j] = 0u;
                 }
             }
         }
@@ -650,12 +608,25 @@ __device__ __forceinline__ void moe_combine(const Params &P, const Task &t)
     if (h >= P.H) return;
     const int K = P.topk;
     float acc = 0.f;
-    for (int k = 0; k < K; ++k) {
-        const int pos = ld_i32(P.inv_perm + (size_t)b * K + k);
-        acc += ld_f32(P.topk_w + (size_t)b * K + k) * ld_f32(P.ey + (size_t)pos * P.H + h);
-    }
     const size_t o = (size_t)b * P.H + h;
-    const float v = ld_f32(P.x_mid + o) + acc;
+    const float x0 = ld_f32(P.x_mid + o);
+    constexpr int SL = 8;
+    for (int k0 = 0; k0 < K; k0 += SL) {               // the look-ups of 8 slots in one round trip, their rows in the next
+        int pos[SL];
+        float wk[SL], y[SL];
+#pragma unroll
+        for (int k = 0; k < SL; ++k) {
+            const size_t p = (size_t)b * K + (k0 + k < K ? k0 + k : K - 1);
+            pos[k] = ld_i32(P.inv_perm + p);
+            wk[k] = ld_f32(P.topk_w + p);
+        }
+#pragma unroll
+        for (int k = 0; k < SL; ++k) y[k] = ld_f32(P.ey + (size_t)pos[k] * P.H + h);
+#pragma unroll
+        for (int k = 0; k < SL; ++k)
+            if (k0 + k < K) acc += wk[k] * y[k];
+    }
+    const float v = x0 + acc;
     st_f32(P.x + o, v);
     const bool last = (t.flags & TF_LAST_LAYER) != 0;
     if (last && P.hidden_out) gst_u16(P.hidden_out + o, f32_to_bf16_bits(v));
