@@ -212,6 +212,22 @@ int moe_tiles_per_task(const ModelDims &m, int tokens, int row_block, int per_sl
     return best_r;
 }
 
+// Row tiles per task of a projection on the staged path: what a queue takes longest over, in bytes: rounds x (fixed cost of a
+// task, about 15 us = 384 KB of streaming, + the weights of its tiles).  `tiles` in all, a task's count divides `per_group` and
+// is at most `most`.  One round with three quarters of the queues beats two whose second is a quarter full: Qwen3-32B shape
+// (3200 gate/up tiles), batch 3: 200 tasks of 16 tiles against 320 of 10, and 160 QKV tasks of 4 against 320 of 2.
+static int staged_tiles(int tiles, int per_group, int most, int cols, int K, int n_queues)
+{
+    long long best = -1;
+    int best_r = 1;
+    for (int r = 1; r <= per_group && r <= most; ++r) {
+        if (per_group % r || (r > 1 && !staged_fits(r, cols, K))) continue;
+        const long long rounds = (tiles / r + n_queues - 1) / n_queues, cost = rounds * (384LL * 1024 + (long long)r * 32 * K);
+        if (best < 0 || cost < best) { best = cost; best_r = r; }
+    }
+    return best_r;
+}
+
 std::string build_decoder_graph(const ModelDims &m, int Bs, int n_queues, bool moe_static_coarse, GraphDecl *out)
 {
     (void)moe_static_coarse;
@@ -244,12 +260,10 @@ std::string build_decoder_graph(const ModelDims &m, int Bs, int n_queues, bool m
     };
     int r_qkv = 1, r_gu = 1;
     if (staged_ok(m.H)) {
-        if ((m.nq + 2 * m.nkv) * sub > n_queues && sub % 2 == 0 && staged_fits(2, Bs, m.H)) r_qkv = 2;
+        r_qkv = staged_tiles((m.nq + 2 * m.nkv) * sub, sub, sub, Bs, m.H, n_queues);
         if (m.E == 0) {
             const int tiles = m.F / 8, per_slice = tiles / kWaves;
-            int cand = tiles / std::max(1, n_queues);
-            while (cand > 1 && (tiles % cand || per_slice % cand || !staged_fits(cand, Bs, m.H))) --cand;
-            r_gu = std::max(1, cand);
+            r_gu = staged_tiles(tiles, per_slice, per_slice, Bs, m.H, n_queues);
             // The down projection's operand (K = ffn) leaves LDS first, at batch 3 on the 8B shape.  One slice of K
             // still fits, so it is cut along K like the large-batch projections and stays on the staged path.
             const int s_d = k_slices_for(m.F);
@@ -288,7 +302,10 @@ std::string build_decoder_graph(const ModelDims &m, int Bs, int n_queues, bool m
         }
     }
     const int n_ht = m.H / 16, pass_tiles = pass_tiles_for(Bs);
-    const int pass_o = sliced_pass_tiles(Bs, n_ht, g.k_slices_o, n_queues), pass_d = sliced_pass_tiles(Bs, n_ht, g.k_slices_d, n_queues);
+    const int pass_o = sliced_pass_tiles(Bs, n_ht, g.k_slices_o, n_queues);
+    // a slice on the staged path: the tiles per task that fill the queues (Qwen3-32B shape: 256 tasks of 5 instead of 160 of 8)
+    const int pass_d = g.k_slices_d > 0 && staged_ok(m.H) ? staged_tiles(n_ht * g.k_slices_d, n_ht, pass_tiles, Bs, m.F / g.k_slices_d, n_queues)
+                                                          : sliced_pass_tiles(Bs, n_ht, g.k_slices_d, n_queues);
     const bool slice_o = g.k_slices_o > 0 && n_ht % pass_o == 0;
     const bool slice_d = g.k_slices_d > 0 && n_ht % pass_d == 0;
     if (!slice_o) g.k_slices_o = 0;
@@ -296,7 +313,7 @@ std::string build_decoder_graph(const ModelDims &m, int Bs, int n_queues, bool m
     // (the staged-only kernel instances carry one group of 8 columns)
     g.all_staged = m.E == 0 && Bs <= 8 && staged_fits(r_qkv, Bs, m.H) && staged_fits(r_gu, Bs, m.H) &&
                    (slice_o ? staged_fits(pass_tiles, Bs, m.nq * m.d / g.k_slices_o) : staged_fits(1, Bs, m.nq * m.d)) &&
-                   (slice_d ? staged_fits(pass_tiles, Bs, m.F / g.k_slices_d) : staged_fits(1, Bs, m.F));
+                   (slice_d ? staged_fits(pass_d, Bs, m.F / g.k_slices_d) : staged_fits(1, Bs, m.F));
 
     int stage = 0;
     int e_x = g.add_event({one});
