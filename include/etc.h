@@ -82,7 +82,8 @@ typedef struct {
 typedef struct {
     int32_t kv_chunk_tokens; /* smallest number of keys per split-KV attention task; multiple of page_size.
                                 Per sampled batch size the library enlarges it (in whole pages) until a layer
-                                has about one attention task per queue. */
+                                has about one attention task per queue; a sequence is cut into chunks of equal
+                                length (in whole pages). */
     int32_t moe_tile_m;      /* tokens per GroupGEMM row tile (exp_indptr unit, Sec. 2.4); 1..16 */
 } etc_tile_desc;
 

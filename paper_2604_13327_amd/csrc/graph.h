@@ -114,7 +114,8 @@ inline int moe_row_merge(int tile_m, int hidden) { return tile_m > 32 && hidden 
 int moe_tiles_per_task(const ModelDims &m, int tokens, int row_block, int per_slot, int K, int n_queues);
 
 // Attention task slots for one sampled batch size, as keys of a slot of the longest sequence.  `min_chunk` is the caller's tile shape; it
-// is enlarged (in whole pages) until a layer has at most one attention task per queue: every chunk costs a
+// is enlarged (in whole pages) until a layer has at most one attention task per queue (the device deals the slots to the
+// sequences of the bound batch, in chunks of equal length per sequence): every chunk costs a
 // partial result the merge reads back, and a second task per queue only adds such chunks (half a task per
 // queue leaves queues idle and measured slower from batch 4 on).
 inline int effective_kv_chunk(int min_chunk, int page, int max_kv_len, int batch, int n_kv_heads, int n_queues)
@@ -130,10 +131,10 @@ inline int effective_kv_chunk(int min_chunk, int page, int max_kv_len, int batch
     return chunk < min_chunk ? min_chunk : chunk;
 }
 
-// Row tiles a large-batch projection task streams against one pass over its operand: 8.  (Above 32 columns the
-// K-split chunked path holds accumulators for 4 tiles at most; such tasks take the wide path, one tile per wavefront.)
+// Row tiles a large-batch projection task streams against one pass over its operand: 8, a pass of the paths whose
+// wavefronts split the output.
 inline int pass_tiles_for(int batch) { (void)batch; return 8; }
-// Above 16 columns the wide path takes two row tiles per wavefront: 16 tiles against one pass over the operand.  A
+// Above 16 columns those paths take two row tiles per wavefront: 16 tiles against one pass over the operand.  A
 // projection uses that where it still leaves every queue a task: gate/up by its cost per queue (fewer rounds, each
 // with one more operand pass), a projection cut along K when (row tiles / 16) x slices fill the queues.
 inline int wide_pass_tiles_for(int batch) { return batch > 16 ? 16 : 8; }

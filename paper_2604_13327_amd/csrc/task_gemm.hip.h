@@ -1,9 +1,9 @@
 // Projection tile task: 16 weight rows x K against up to 64 activation columns, bf16 MFMA with
 // fp32 accumulation (v_mfma_f32_16x16x32_bf16), weights streamed from HBM exactly once.
 //
-// Work split.  The 8 wavefronts of the workgroup split K; each streams its slice of all 16 rows with
-// 16-byte non-temporal loads, keeping PF loads (PF KB per wave, 128 KB per CU) in flight.  The first
-// PF loads are issued BEFORE the task waits on its events (weight prefetch, paper Sec. 3.4 / 4.3), so
+// Work split (small batches; the out-of-line paths have their own).  The 8 wavefronts of the workgroup split K; each
+// streams its slice of all 16 rows with 16-byte non-temporal loads of whole lines (unit_row), keeping PF loads (PF KB per
+// wave, 128 KB per CU) in flight.  The first of them are issued BEFORE the task waits on its events (weight prefetch, paper Sec. 3.4 / 4.3), so
 // HBM keeps streaming while the dependency resolves.
 //
 // Activation operand.  Activations reach the MFMA as bf16, which alone would cost ~2^-9 relative error
@@ -166,10 +166,10 @@ __device__ __forceinline__ void wg_wait_cached(const Params &P, WgState &st, int
 // stream (+10 %: the compute unit's read rate follows the bytes it keeps in flight, and the gap between
 // two stages is longer than what its registers can buffer either way).
 //
-// Shape of the streaming loop.  The task's weights are ONE linear stream of (tile, step) pairs; an issue cursor
-// runs PF steps ahead of the consume cursor.  The compiler places wait counts per basic block, and what it
+// Shape of the streaming loop.  The task's weights are ONE linear stream of (tile, unit) pairs; an issue cursor
+// runs PF / 2 units ahead of the consume cursor.  The compiler places wait counts per basic block, and what it
 // cannot follow it answers with a full drain of the loads in flight, so the loop is written for it:
-//   - the steady state (whole revolutions of the ring whose look-ahead steps all exist) has no branch around
+//   - the steady state (whole revolutions of the ring whose look-ahead units all exist) has no branch around
 //     a load, and so have the common endings (one revolution left; one and a half);
 //   - a ring slot is refilled BEHIND the MFMAs that read it, so the new fragment can land in the same
 //     registers: refilled in front of them it needs other registers, and the copy back at the loop's end
@@ -476,16 +476,16 @@ __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTil
     }
 }
 
-// Out-of-line path for batches above 16 columns, or operands too large for a whole copy in LDS.
-// The operand is walked in chunks of KC elements of K: a chunk of ALL columns (hi and lo) sits in LDS,
-// double buffered; while the wavefronts run the MFMAs of chunk c out of one buffer, every thread already
-// has its 8-byte pieces of chunk c+1 in flight into registers and drops them into the other buffer at the
-// end of the chunk: one barrier per chunk.  Within a chunk a wavefront owns 32 of every 256 elements of K
-// (S = KC / 256 MFMA steps); a task streams T (4 or 8) row tiles against one pass over the operand, which
-// every task has to read in full, with a ring of PFC weight fragments in flight per lane running over
+// Out-of-line path of tasks of at most 4 row tiles whose operand does not fit a whole copy in LDS (batches above 16
+// columns, QKV above all).  The operand is walked in chunks of KC elements of K: a chunk of ALL columns (hi and lo) sits
+// in LDS, double buffered; while the wavefronts run the MFMAs of chunk c out of one buffer, every thread already
+// has its 16-byte pieces of chunk c+1 in flight into registers (8-byte ones ran at 41 GB/s per compute unit, these at 67)
+// and drops them into the other buffer at the end of the chunk: one barrier per chunk.  Within a chunk a wavefront owns 32
+// of every 256 elements of K (S = KC / 256 MFMA steps); a task streams T row tiles against one pass over the operand,
+// which every task has to read in full, with a ring of PFC weight fragments in flight per lane running over
 // (chunk, step, tile) triples.  Register budget decides the shape: accumulators take T x NB x 4 registers,
 // the ring 4 PFC, the operand pieces in flight COLS x KC / 512 - so 16 columns keep the full ring of 16, 32
-// columns a ring of 8, 64 columns 4 row tiles and a ring of 4.  Nothing may spill inside the loop: a
+// columns a ring of 8, 64 columns a ring of 4.  Nothing may spill inside the loop: a
 // register reload is a memory load that queues behind the whole ring.
 //
 // The steady state of the loop is free of branches.  The compiler places its wait counts per basic block;
@@ -522,7 +522,7 @@ __device__ __noinline__ void gemm_tiles_chunked(const Params &P, const ChunkedAr
     const Epilogue &e = a.e;
     const TaskWaits &w = a.w;
     const int task_id = a.task_id;
-    static_assert(T == 1 || T == 2 || T == 4 || T == 8, "row tiles per pass");
+    static_assert(T == 1 || T == 2 || T == 4, "row tiles per pass");
     constexpr int PFC = NB == 1 ? (T >= 4 ? PF : 8) : (NB == 2 ? 8 : 4);   // weight loads in flight per lane, as the registers allow
     constexpr int COLS = NB * 16;
     constexpr int S = (4 / NB) < (PFC / T) ? (4 / NB) : (PFC / T);   // MFMA steps per wavefront, chunk and tile
@@ -941,16 +941,16 @@ __device__ __forceinline__ void tiles_epilogue(const Params &P, const ChunkedArg
         __hip_atomic_fetch_max(as_global(P.best + threadIdx.x), lbest[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Wide path: tasks of 5 or more row tiles at any column count (16 * NB columns, up to 128).  The chunked path splits K
-// over the 8 wavefronts, so every wavefront holds accumulators for all tiles of the pass (at 64 columns a pass is 4
-// tiles: the operand, hi and lo, is read again for every 256 KB of weights) and the tiles meet in a reduction across
-// wavefronts.  Here the wavefronts split the OUTPUT instead: each owns TW row tiles of the pass and runs over all of K,
-// the operand chunk in LDS (double buffered) is shared by all of them, and a pass is 8 x TW tiles.  No reduction across
-// wavefronts, and the epilogues that allow it run straight from the accumulators.
-// What bounds it is bytes in flight per compute unit: the ring holds RD chunks of weights per wavefront (128 KB per unit)
-// next to one chunk of the operand in registers.  128 columns (a GroupGEMM row block) halve the chunk, so that two
-// buffers still fit: a block of 128 columns x 256 rows moves 1 KB per element of K for 131 kflop.
-template <int TW, int NB, int KH>
+// Wide path: decoder tasks of 5 or more row tiles at 33 .. 64 columns.  The chunked path splits K over the 8 wavefronts, so
+// every wavefront holds accumulators for all tiles of the pass (at 64 columns a pass is 4 tiles: the operand, hi and lo, is
+// read again for every 256 KB of weights) and the tiles meet in a reduction across wavefronts.  Here the wavefronts split
+// the OUTPUT: a pair of them owns TW row tiles of the pass, each half of every chunk of K (which halves the operand reads
+// from LDS, 27 us of a 56 us gate/up stage of the 8B shape when every wavefront took the whole operand); the operand chunk
+// in LDS (double buffered) is shared by all of them, a pass is 4 x TW tiles, and the pair exchanges half of its sums.
+// What bounds it is bytes through the fabric: at 64 columns the operand is as large as the weights of a task (43 us for 1 MB
+// of each at 24 + 24 GB/s per compute unit; this loop takes 50 - 54, before 56).  Loaded past the caches the half lines of
+// its fragments cost 5 %, so these loads may allocate.  Up to 32 columns: gemm_tiles_lines.
+template <int TW>
 __device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs *args, float *sm, int *frame_anchor)
 {
     const ChunkedArgs a = lds_get_uniform(args);
@@ -959,17 +959,17 @@ __device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs 
     const Epilogue &e = a.e;
     const TaskWaits &w = a.w;
     const int task_id = a.task_id;
-    constexpr int COLS = 16 * NB, KC = NB == 8 ? 128 : 256, KS = KC / 32, STRIDE = KC + 8;
+    constexpr int NB = 4, KH = 2;                  // column blocks of 16; wavefronts per row group
+    constexpr int COLS = 16 * NB, KC = 256, KS = KC / 32, STRIDE = KC + 8;
     constexpr int PPC = KC / 8;                    // 16-byte pieces per column and half
     constexpr int U = COLS * PPC / kWgThreads;     // pieces per thread, chunk and half
     constexpr int BUF = 2 * COLS * STRIDE;         // elements of one operand buffer: hi columns, then lo columns
     constexpr int PASS = kWaves / KH * TW;         // row tiles per pass
     constexpr int KSW = KS / KH;                   // k steps of a chunk that one wavefront takes: kh * KSW on (whole 128-byte lines)
-    constexpr int RD = KSW * TW >= 16 || NB == 8 ? 1 : 16 / (KSW * TW);      // chunks of weights in flight
+    constexpr int RD = KSW * TW >= 16 ? 1 : 16 / (KSW * TW);      // chunks of weights in flight
     constexpr int RING = KSW * TW * RD;            // weight fragments in flight per lane
-    constexpr int FD = KH == 2 && NB < 4 ? 2 : 1;   // chunks of the operand in flight, as the registers allow
     constexpr int NCOL = COLS < 64 ? 64 : COLS, GRPS = kWgThreads / NCOL;      // norm factors: threads (column, group)
-    static_assert((KH == 1 || (KH == 2 && TW % 2 == 0)) && (NB == 1 || NB == 2 || NB == 4 || NB == 8), "wavefronts per row group, column blocks");
+    static_assert(TW == 2 || TW == 4, "tiles per pair of wavefronts");
     static_assert(U >= 1 && COLS * PPC == U * kWgThreads && RD <= 2, "every thread moves U pieces of each half");
     static_assert((size_t)2 * BUF * 2 + (NCOL + kWgThreads) * 4 <= (size_t)kLdsBytes, "two operand buffers and the norm scratch fit");
     static_assert((size_t)PASS * NB * 256 * 4 <= (size_t)2 * BUF * 2, "the tiles' accumulators alias the operand buffers");
@@ -1021,25 +1021,24 @@ __device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs 
         if (row < 0) row = 0;
         off[u] = col < g.n_cols ? ((uint32_t)row * (uint32_t)g.ldb + (uint32_t)pc * 8u) * 2u : kBufNone;
     }
-    u32x4 vh[FD][U], vl[FD][U];                    // pieces in flight: set c % FD holds chunk c
-    auto fetch_chunk = [&](int c, u32x4 (&h)[U], u32x4 (&l)[U]) {
+    u32x4 vh[U], vl[U];                            // pieces of the next chunk in flight
+    auto fetch_chunk = [&](int c) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            h[u] = buf_ld_16B(hi_b, off[u], (uint32_t)c * (KC * 2));
-            l[u] = buf_ld_16B(lo_b, off[u], (uint32_t)c * (KC * 2));
+            vh[u] = buf_ld_16B(hi_b, off[u], (uint32_t)c * (KC * 2));
+            vl[u] = buf_ld_16B(lo_b, off[u], (uint32_t)c * (KC * 2));
         }
     };
-    auto park_chunk = [&](int b, const u32x4 (&h)[U], const u32x4 (&l)[U]) {
+    auto park_chunk = [&](int b) {
         ETC_AS_LDS uint16_t *hi = buf0 + b * BUF, *lo = hi + COLS * STRIDE;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int col = ((int)threadIdx.x + kWgThreads * u) / PPC;
-            *reinterpret_cast<ETC_AS_LDS u32x4 *>(hi + col * STRIDE + pc * 8) = h[u];
-            *reinterpret_cast<ETC_AS_LDS u32x4 *>(lo + col * STRIDE + pc * 8) = l[u];
+            *reinterpret_cast<ETC_AS_LDS u32x4 *>(hi + col * STRIDE + pc * 8) = vh[u];
+            *reinterpret_cast<ETC_AS_LDS u32x4 *>(lo + col * STRIDE + pc * 8) = vl[u];
         }
     };
-    fetch_chunk(0, vh[0], vl[0]);
-    if (FD == 2 && n_chunks > 1) fetch_chunk(1, vh[FD - 1], vl[FD - 1]);
+    fetch_chunk(0);
     if (g.ssq_parts) {       // RMSNorm factors, as in the chunked path
         const int col = (int)threadIdx.x % NCOL, grp = (int)threadIdx.x / NCOL;
         int row = -1;
@@ -1057,7 +1056,7 @@ __device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs 
         }
         rs_part[grp * NCOL + col] = s;
     }
-    park_chunk(0, vh[0], vl[0]);
+    park_chunk(0);
     __syncthreads();
     if (g.ssq_parts && threadIdx.x < NCOL) {
         float s = 0.f;
@@ -1111,22 +1110,22 @@ __device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs 
         }                                                                                                         \
         __builtin_amdgcn_sched_barrier(0);                                                                        \
     }
-    // one chunk of parity p: request the operand FD chunks ahead, compute, park the next chunk's operand
+    // one chunk of parity p: request the next chunk's operand, compute, park it
 #define ETC_WIDE_STEP(c, p, FETCH, RELOAD, PARK)                                                                  \
     {                                                                                                             \
-        if (FETCH) fetch_chunk((c) + FD, vh[(p) % FD], vl[(p) % FD]);                                             \
+        if (FETCH) fetch_chunk((c) + 1);                                                                          \
         ETC_WIDE_CHUNK(c, (p) % RD, RELOAD)                                                                       \
         if (PARK) {                                                                                               \
-            park_chunk(((p) + 1) & 1, vh[((p) + 1) % FD], vl[((p) + 1) % FD]);                                    \
+            park_chunk(((p) + 1) & 1);                                                                            \
             __syncthreads();                                                                                      \
         }                                                                                                         \
     }
     int c = 0;
-    if constexpr (RD == 1 && FD == 1) {
+    if constexpr (RD == 1) {
         for (; c + 1 < n_chunks; ++c) {            // steady state: the next chunk exists
-            fetch_chunk(c + 1, vh[0], vl[0]);
+            fetch_chunk(c + 1);
             ETC_WIDE_CHUNK(c, 0, true)
-            park_chunk((c + 1) & 1, vh[0], vl[0]);
+            park_chunk((c + 1) & 1);
             __syncthreads();
         }
         ETC_WIDE_CHUNK(c, 0, false)
@@ -1137,10 +1136,10 @@ __device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs 
         }
         if (n_chunks - c == 3) {
             ETC_WIDE_STEP(c, 0, true, true, true)
-            ETC_WIDE_STEP(c + 1, 1, FD == 1, RD == 1, true)
+            ETC_WIDE_STEP(c + 1, 1, true, false, true)
             ETC_WIDE_STEP(c + 2, 0, false, false, false)
         } else if (n_chunks - c == 2) {
-            ETC_WIDE_STEP(c, 0, FD == 1, RD == 1, true)
+            ETC_WIDE_STEP(c, 0, true, false, true)
             ETC_WIDE_STEP(c + 1, 1, false, false, false)
         } else {
             ETC_WIDE_STEP(c, 0, false, false, false)
@@ -1150,29 +1149,22 @@ __device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs 
 #undef ETC_WIDE_CHUNK
     trace_mark(P, task_id, 3);
 
-    // ---- KH == 2: the two wavefronts of a row group hold sums over half of K each; each finishes half of the tiles ----
+    // ---- the two wavefronts of a row group hold sums over half of K each; each finishes half of the tiles ----
     constexpr int TF = TW / KH;                    // tiles a wavefront finishes: rg * TW + kh * TF + t
     f32x4 sum[TF][NB];
-    if constexpr (KH == 2) {
-        __syncthreads();                           // every wavefront is done with the operand buffers
+    __syncthreads();                           // every wavefront is done with the operand buffers
 #pragma unroll
-        for (int t = 0; t < TF; ++t)
+    for (int t = 0; t < TF; ++t)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                *reinterpret_cast<ETC_AS_LDS f32x4 *>(tb + ((size_t)((wave * TF + t) * NB + nb) * 64 + lane) * 4) = kh ? acc[t][nb] : acc[TF + t][nb];
-        __syncthreads();
+        for (int nb = 0; nb < NB; ++nb)
+            *reinterpret_cast<ETC_AS_LDS f32x4 *>(tb + ((size_t)((wave * TF + t) * NB + nb) * 64 + lane) * 4) = kh ? acc[t][nb] : acc[TF + t][nb];
+    __syncthreads();
 #pragma unroll
-        for (int t = 0; t < TF; ++t)
+    for (int t = 0; t < TF; ++t)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                sum[t][nb] = (kh ? acc[TF + t][nb] : acc[t][nb]) +
-                             *reinterpret_cast<ETC_AS_LDS const f32x4 *>(tb + ((size_t)(((wave ^ 1) * TF + t) * NB + nb) * 64 + lane) * 4);
-    } else {
-#pragma unroll
-        for (int t = 0; t < TF; ++t)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) sum[t][nb] = acc[t][nb];
-    }
+        for (int nb = 0; nb < NB; ++nb)
+            sum[t][nb] = (kh ? acc[TF + t][nb] : acc[t][nb]) +
+                         *reinterpret_cast<ETC_AS_LDS const f32x4 *>(tb + ((size_t)(((wave ^ 1) * TF + t) * NB + nb) * 64 + lane) * 4);
     if (epilogue_is_direct(e.kind)) {
 #pragma unroll
         for (int t = 0; t < TF; ++t) {
@@ -1183,7 +1175,7 @@ __device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs 
         return;
     }
     // ---- sums through LDS into the layout of the epilogue threads, then the epilogue tile by tile ----
-    __syncthreads();                               // the buffers (KH == 2: the exchanged halves) have been read
+    __syncthreads();                               // the exchanged halves have been read
 #pragma unroll
     for (int t = 0; t < TF; ++t) {
         const int ti = rg * TW + kh * TF + t;
@@ -1748,17 +1740,11 @@ __device__ __noinline__ void gemm_tiles_blocks(const Params &P, const ChunkedArg
     __syncthreads();                               // the operand buffers are free again
 }
 
-// Passes of the wide path: 8 / KH x TW row tiles each.
-template <int TW, int NB, int KH>
-__device__ __forceinline__ void gemm_tiles_wide_pass(const Params &PL, ChunkedArgs *slot, float *sm, int *frame_anchor)
-{
-    if constexpr (NB == 4) gemm_tiles_wide<TW, NB, KH>(PL, slot, sm, frame_anchor);
-    else gemm_tiles_lines<TW, 2 * NB>(PL, slot, sm, frame_anchor);
-}
-template <int TW, int NB, int KH>
+// Passes of the wide (33 .. 64 columns) and the lines path (NG groups of 8 columns).
+template <int TW, int NG>
 __device__ __forceinline__ void gemm_tiles_wide_passes(const Params &PL, ChunkedArgs a, ChunkedArgs *slot, float *sm, int *frame_anchor)
 {
-    constexpr int PASS = kWaves / KH * TW;
+    constexpr int PASS = NG == 8 ? kWaves / 2 * TW : kWaves * TW;
     const int total = a.g.n_tiles;
     for (int t0 = 0; t0 < total; t0 += PASS) {
         a.g.n_tiles = total - t0 < PASS ? total - t0 : PASS;
@@ -1767,7 +1753,8 @@ __device__ __forceinline__ void gemm_tiles_wide_passes(const Params &PL, Chunked
             if (threadIdx.x == 0) lds_put(slot, a);
             __syncthreads();
         }
-        gemm_tiles_wide_pass<TW, NB, KH>(PL, slot, sm, frame_anchor);
+        if constexpr (NG == 8) gemm_tiles_wide<TW>(PL, slot, sm, frame_anchor);
+        else gemm_tiles_lines<TW, NG>(PL, slot, sm, frame_anchor);
         a.g.rowsA += (size_t)PASS * a.g.tile_rows * a.g.ldw;
         a.g.rowsB += (size_t)PASS * a.g.tile_rows * a.g.ldw;
         a.e.row0 += PASS * a.g.tile_rows;
@@ -1799,10 +1786,12 @@ __device__ __forceinline__ void gemm_tiles_chunked_passes(const Params &PL, Chun
     }
 }
 
-// Entry of the out-of-line path: one call site in the task loop.  The streaming loop always moves T row tiles, so T
-// follows the task: 1, 2, 4 or 8.  Up to 32 columns a pass takes up to 8 tiles; with 64 columns the accumulators of
-// 8 tiles no longer fit the register file next to the weight ring (spills inside the streaming loop queue behind the
-// weight loads), so a pass takes at most 4.
+// Entry of the out-of-line path: one call site in the task loop.  Tasks of 5 or more row tiles have a loop whose wavefronts
+// split the output (wide, lines; row blocks of experts: stream, blocks); the fewer tiles of the others (QKV, narrow plans)
+// would leave wavefronts idle there, so they split K (chunked, 1, 2 or 4 tiles: the loop always moves T, so T follows the
+// task).  Operand rows longer than kMaxBufLd lie outside one buffer descriptor: split K, a tile at a time, 8-byte loads.
+// Measured at the change (16 x 64-byte fragments and 8-byte operand loads before): 8B batch 5 / 16 / 64 680 / 950 / 1327 ->
+// 573 / 864 / 1293 us per four layers, the MoE layer at 1024 tokens 810 -> 424.
 __device__ __noinline__ void gemm_chunked_entry(const Params &PL, ChunkedArgs *slot, float *sm, int *frame_anchor)
 {
     const ChunkedArgs a = lds_get_uniform(slot);
@@ -1813,8 +1802,7 @@ __device__ __noinline__ void gemm_chunked_entry(const Params &PL, ChunkedArgs *s
         if (!buf_ok) gemm_tiles_chunked_passes<NB_, 1, false>(PL, a, slot, sm, &anchor);         \
         else if (a.g.n_tiles == 1) gemm_tiles_chunked_passes<NB_, 1>(PL, a, slot, sm, &anchor); \
         else if (a.g.n_tiles == 2) gemm_tiles_chunked_passes<NB_, 2>(PL, a, slot, sm, &anchor); \
-        else if (a.g.n_tiles <= 4 || NB_ == 4) gemm_tiles_chunked_passes<NB_, 4>(PL, a, slot, sm, &anchor);  \
-        else gemm_tiles_chunked_passes<NB_, NB_ == 4 ? 4 : 8>(PL, a, slot, sm, &anchor);   /* several passes: crowded expert */ \
+        else gemm_tiles_chunked_passes<NB_, 4>(PL, a, slot, sm, &anchor);                        \
     }
     const bool buf_ok = a.g.ldb <= kMaxBufLd;
     if (buf_ok && (a.e.kind == EPI_MOE_ACT || a.e.kind == EPI_MOE_Y)) {      // row blocks of more than 64 columns exist here only
@@ -1840,14 +1828,13 @@ __device__ __noinline__ void gemm_chunked_entry(const Params &PL, ChunkedArgs *s
         }
 #undef ETC_BLOCKS
     }
-    const bool wide_ok = buf_ok && a.g.K % 256 == 0;
-    if (a.g.n_cols > 32 && a.g.n_tiles >= 16 && wide_ok) gemm_tiles_wide_passes<4, 4, 2>(PL, a, slot, sm, &anchor);
-    else if (a.g.n_cols > 32 && a.g.n_tiles >= 5 && wide_ok) gemm_tiles_wide_passes<2, 4, 2>(PL, a, slot, sm, &anchor);
+    if (a.g.n_cols > 32 && a.g.n_tiles >= 16 && buf_ok) gemm_tiles_wide_passes<4, 8>(PL, a, slot, sm, &anchor);
+    else if (a.g.n_cols > 32 && a.g.n_tiles >= 5 && buf_ok) gemm_tiles_wide_passes<2, 8>(PL, a, slot, sm, &anchor);
     else if (a.g.n_cols > 32) ETC_CHUNKED(4)
-    else if (a.g.n_cols > 16 && a.g.n_tiles >= 9 && wide_ok) gemm_tiles_wide_passes<2, 2, 1>(PL, a, slot, sm, &anchor);   // 9 .. 16 tiles against ONE pass over the operand
-    else if (a.g.n_cols > 16 && a.g.n_tiles >= 5 && wide_ok) gemm_tiles_wide_passes<1, 2, 1>(PL, a, slot, sm, &anchor);
+    else if (a.g.n_cols > 16 && a.g.n_tiles >= 9 && buf_ok) gemm_tiles_wide_passes<2, 4>(PL, a, slot, sm, &anchor);   // 9 .. 16 tiles against ONE pass over the operand
+    else if (a.g.n_cols > 16 && a.g.n_tiles >= 5 && buf_ok) gemm_tiles_wide_passes<1, 4>(PL, a, slot, sm, &anchor);
     else if (a.g.n_cols > 16) ETC_CHUNKED(2)
-    else if (a.g.n_tiles >= 5 && wide_ok) gemm_tiles_wide_passes<1, 1, 1>(PL, a, slot, sm, &anchor);
+    else if (a.g.n_tiles >= 5 && buf_ok) gemm_tiles_wide_passes<1, 2>(PL, a, slot, sm, &anchor);
     else ETC_CHUNKED(1)
 #undef ETC_CHUNKED
 }
