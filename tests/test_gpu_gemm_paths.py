@@ -125,3 +125,23 @@ def test_attention_slots_of_a_batch_below_the_sampled_one(batch):
     assert rel_err(outs[0], ref) <= TOL
     for o in outs[1:]:
         np.testing.assert_array_equal(o, outs[0])
+
+
+@pytest.mark.parametrize("n_experts,top_k,batch,tile_m", [(256, 16, 64, 3), (256, 1, 9, 16), (240, 16, 8, 7), (16, 16, 1, 1)])
+def test_router_sums_over_experts(n_experts, top_k, batch, tile_m):
+    """Ids, permutation and both index arrays bit for bit where the sums over experts end: a full last lane, one in the middle of
+    the wavefront, one and four tokens in flight, row tiles that divide nothing, the most pairs a step can have."""
+    import paper_2604_13327_amd as etc
+    from test_gpu_moe import check_moe_step
+    s = synth.ModelShape("moe-sums", 1, 256, 4, 2, 64, 0, n_experts=n_experts, top_k=top_k, moe_F=256)
+    pages = batch * 2 + 4
+    model = GpuModel(s, seed=77, n_pool_pages=pages)
+    step = fixed_step(s, batch, [(5 * b + 1) % 30 for b in range(batch)], pages, seed=78)
+    for kind in (etc.SCHED_STATIC, etc.SCHED_DYNAMIC):
+        model.reset_pools()
+        dec = etc.Decoder(s, kv_chunk_tokens=32, sampled_batches=[batch], max_kv_len=129, moe_tile_m=tile_m, kind=kind,
+                          spin_budget=SPIN, debug_flags=etc.DEBUG_ROUTING | etc.DEBUG_LAYER_HIDDEN | etc.DEBUG_EXEC_COUNT)
+        model.bind(dec)
+        dec.bind_step(step)
+        check_moe_step(dec, model, s, step, tile_m)
+        dec.close()
