@@ -15,8 +15,8 @@ constexpr int kLdsBytes = 148 * 1024;    // of the 160 KB LDS per CU: exactly on
 constexpr int kRsFloats = 64;                     // LDS: RMSNorm factors of the columns
 constexpr int kStagedMaxCols = 16;                // widest batch the staged (latency-critical) projection path takes
 
-// LDS layout of the staged projection path: reduction buffer [tiles][waves][cols][16], norm factors, then
-// the whole operand (all columns, hi and lo).  A task takes that path when this fits.
+// LDS layout of the staged projection path: norm factors, the whole operand (all columns, hi and lo), then the
+// reduction buffer [tiles][waves][cols][16].  A task takes that path when this fits.
 // A column of the operand is K + kOpPad elements apart from the next: with a stride of K (a multiple of the bank
 // span) the 16 columns a wavefront reads in one instruction would all sit in the same banks.
 constexpr int kOpPad = 8;

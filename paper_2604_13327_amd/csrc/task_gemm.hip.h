@@ -188,11 +188,13 @@ __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTil
     wave_units(g.K, wave, unit0, n_it);
     const size_t tile_step = (size_t)g.tile_rows * (size_t)g.ldw;
 
-    ETC_AS_LDS float *red = as_lds(sm);               // [tile][wave][col][16 rows]
-    ETC_AS_LDS float *rs = red + staged_red_floats(g.n_tiles, g.n_cols);
+    // What a later task may find again (norm factors, operand) lies in front of what depends on this task's tile count: the
+    // tasks of a stage share the operand, and the last one of the vocabulary projection has fewer tiles than the others.
+    ETC_AS_LDS float *rs = as_lds(sm);
     ETC_AS_LDS uint16_t *op_hi = reinterpret_cast<ETC_AS_LDS uint16_t *>(rs + kRsFloats);
     const int Kp = g.K + kOpPad;                        // column stride of the operand in LDS
     ETC_AS_LDS uint16_t *op_lo = op_hi + (size_t)g.n_cols * Kp;
+    ETC_AS_LDS float *red = reinterpret_cast<ETC_AS_LDS float *>(op_lo + (size_t)g.n_cols * Kp);      // [tile][wave][col][16 rows]
 
     const int key = w.op_key;
     const bool restage = key < 0 || key != st.staged_key;

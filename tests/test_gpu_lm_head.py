@@ -317,3 +317,45 @@ def test_llama3_vocabulary_at_full_width(batch):
     ref_logits, ref_tok = oracle.lm_head(oracle.shape_of(s), ref["final"], w["gf"], w["wlm"])
     _check_tokens(tok.cpu().numpy(), logits.cpu().numpy(), ref_logits, ref_tok)
     dec.close()
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("batch,n_queues", [(4, 1), (4, 2), (12, 1)])
+def test_ragged_vocabulary_task_behind_a_full_one_on_the_same_workgroup(batch, n_queues, kind):
+    """All vocabulary tasks read one operand, and a workgroup keeps its copy in LDS from task to task: the last task, which
+    has fewer row tiles than the others, finds it where the full one left it.  The kernel-by-kernel run never reuses a copy."""
+    import dataclasses
+    import torch
+    import oracle
+    etc = _etc()
+    s = dataclasses.replace(synth.TINY_LM, name="tiny-lm-ragged", vocab=16 * 150)
+    t = etc.plan_build(s, 32, batch, n_queues, 129)
+    tiles = [[min(int(c1), 150 - int(c0)) for fn, c0, c1 in t["queue_tasks"][["fn", "c0", "c1"]][b:e] if fn == 18]
+             for b, e in zip(t["queue_begin"][:-1], t["queue_begin"][1:])]
+    assert any(len(q) > 1 and q[-1] < q[-2] for q in tiles), tiles
+    model = GpuModel(s, seed=44, n_pool_pages=64)
+    lm = _lm(s, 44)
+    step = fixed_step(s, batch, [(11 * b + 5) % 40 for b in range(batch)], model.n_pool_pages, seed=10)
+    x = model.hidden(0, batch)
+    got = []
+    for kbk in (False, True):
+        model.reset_pools()
+        dec = etc.Decoder(s, kv_chunk_tokens=32, sampled_batches=[batch], max_kv_len=129, kind=kind, spin_budget=SPIN,
+                          n_queues=n_queues)
+        model.bind(dec)
+        dec.bind_lm_head(None, lm["gf"], lm["wlm"])
+        tok = torch.full((batch,), -1, dtype=torch.int32, device="cuda")
+        logits = torch.full((batch, s.vocab), float("nan"), device="cuda")
+        dec.bind_step(step)
+        dec.launch_tokens(tok, hidden_in=x, logits_out=logits, kernel_by_kernel=kbk)
+        torch.cuda.synchronize()
+        assert (dec.error_word() == 0).all()
+        got.append((tok.cpu().numpy(), logits.cpu().numpy()))
+        dec.close()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+    model.reset_pools()
+    ref = oracle_step(s, model.seed, model.n_pool_pages, step, 0)
+    w = synth.lm_weights_f32(s, model.seed)
+    ref_logits, ref_tok = oracle.lm_head(oracle.shape_of(s), ref["final"], w["gf"], w["wlm"])
+    _check_tokens(got[0][0], got[0][1], ref_logits, ref_tok)
