@@ -736,7 +736,7 @@ etc_status etc_moe_layer_create(const etc_model_desc *m, const etc_tile_desc *t,
     const size_t r_max = (size_t)moe_max_row_tiles(m->n_experts, m->top_k, s->max_batch, d.tile_m);
     P.n_layers = 1; P.H = m->hidden; P.E = m->n_experts; P.topk = m->top_k; P.moeF = m->moe_ffn; P.page = 1;
     P.eps = m->rms_eps; P.tile_m = d.tile_m; P.moel = 1; P.max_batch = s->max_batch;
-    P.row_merge = moe_row_merge(d.tile_m, d.H);
+    P.row_merge = moe_row_merge(d.tile_m, d.H, d.moeF);
     P.col_stride = (int32_t)Tp;
     auto A = [&](auto **p, size_t n) -> bool {
         hipError_t e = dev_alloc(p, n, c->owned);

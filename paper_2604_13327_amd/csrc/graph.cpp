@@ -537,7 +537,7 @@ std::string build_moe_layer_graph(const ModelDims &m, int Ts, int n_queues, Grap
     const DimExpr one = dim_const(1);
     const int n_blk = (Ts + 63) / 64, n_ht = m.H / 16, n_ft = m.moeF / 8;
     const int r_max = moe_max_row_tiles(m.E, m.topk, Ts, m.tile_m);
-    const int row_block = m.tile_m * moe_row_merge(m.tile_m, m.H);
+    const int row_block = m.tile_m * moe_row_merge(m.tile_m, m.H, m.moeF);
     const int r_g = moe_tiles_per_task(m, Ts, row_block, n_ft, m.H, n_queues);
     const int r_d = moe_tiles_per_task(m, Ts, row_block, n_ht, m.moeF, n_queues);
     const int e_x = g.add_event({one});

@@ -101,9 +101,13 @@ inline int moe_max_row_tiles(int n_experts, int top_k, int batch, int tile_m)
 }
 
 // Row tiles of one expert that a GroupGEMM task of the stand-alone MoE layer takes as one row block: row tiles of more
-// than 32 tokens in pairs, up to the 128 columns of the widest task body.  (Smaller row tiles are the caller's choice for
-// small blocks, where an expert rarely has a second one.)
-inline int moe_row_merge(int tile_m, int hidden) { return tile_m > 32 && hidden <= kMaxBufLd ? 128 / tile_m : 1; }
+// than 32 tokens, as many as fit the 128 columns of the widest task body (two or three).  Smaller row tiles are the caller's
+// choice for small blocks, where an expert rarely has a second one.  Both operand rows (hidden in the gate/up GroupGEMM,
+// moe_ffn in the down one) have to lie inside one buffer descriptor: the path of longer ones holds 64 columns.
+inline int moe_row_merge(int tile_m, int hidden, int moe_ffn)
+{
+    return tile_m > 32 && hidden <= kMaxBufLd && moe_ffn <= kMaxBufLd ? 128 / tile_m : 1;
+}
 
 // Row tiles of the weights a GroupGEMM task streams, of `per_slot` in all (K elements each): what a queue takes longest
 // over, in bytes: rounds x (fixed cost of a task + weights + operand).  The fixed cost (slot look-up, operand, epilogue,

@@ -160,3 +160,48 @@ def test_qwen3_moe_layer_matches_oracle(tokens):
     np.testing.assert_array_equal(outs[0][0], outs[1][0])
     e = _check_against_oracle(s, seed, x, outs[0][0], outs[0][1], tile_m)
     print(f"qwen3 MoE layer, {tokens} tokens: max|err|/rms = {e:.3e}, row tiles {int(outs[0][1]['exp_indptr'][-1])}")
+
+
+@pytest.mark.parametrize("H,moe_F", [(256, 131328), (131328, 256)])
+def test_operand_rows_longer_than_one_buffer_descriptor(H, moe_F):
+    """Operand rows of more than 131072 elements (the expert FFN size in the down GroupGEMM, the hidden size elsewhere) are
+    read 64 columns at a time: an expert's 100 rows must not become one block.  Against plain torch in fp32."""
+    import torch
+    etc = _etc()
+    s = synth.ModelShape("moe-long-rows", 1, H, 4, 2, 64, 0, n_experts=16, top_k=1, moe_F=moe_F)
+    g = torch.Generator(device="cuda").manual_seed(57)
+
+    def normal(sigma, *shape):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, sigma, generator=g)
+    rows = {3: 100, 5: 7}
+    T = sum(rows.values())
+    ids = np.repeat(np.array(list(rows), np.int32), list(rows.values()))[:, None]
+    w = {"g2": 1 + normal(0.1, H), "wr": normal(H ** -0.5, 16, H)}
+    for name, shape, sigma in (("eg", (moe_F, H), H ** -0.5), ("eu", (moe_F, H), H ** -0.5), ("ed", (H, moe_F), 4 * moe_F ** -0.5)):
+        w[name] = torch.zeros((16,) + shape, dtype=torch.bfloat16, device="cuda")
+        for e in rows:
+            w[name][e] = normal(sigma, *shape)
+    x = normal(1.0, T, H)
+    outs = []
+    for kind, kbk in ((0, False), (0, True), (1, False), (2, False)):
+        layer = etc.MoeLayer(s, [T], kind=kind, moe_tile_m=64, spin_budget=SPIN)
+        layer.bind_weights(w)
+        layer.bind_tokens(T)
+        layer.force_routing(0, ids)
+        outs.append(_run(layer, x, kbk))
+        assert (layer.error_word() == 0).all(), layer.error_word()
+        layer.close()
+    xf = x.float()
+    h = xf * torch.rsqrt((xf * xf).mean(-1, keepdim=True) + s.eps) * w["g2"].float()
+    ref, t0 = xf.clone(), 0
+    for e, n in rows.items():
+        he = h[t0:t0 + n]
+        act = torch.nn.functional.silu(he @ w["eg"][e].float().t()) * (he @ w["eu"][e].float().t())
+        ref[t0:t0 + n] += act @ w["ed"][e].float().t()
+        t0 += n
+    # 14 million elements at hidden 131328, up to 8 RMS: y is rounded to bf16 once, half a unit is at most 2^-8 of a value;
+    # operands carry 16 bits (hi + lo), sums 24: far below 1e-3 of the RMS
+    ref = ref.cpu().numpy()
+    assert (np.abs(outs[0] - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-3 * np.sqrt(np.mean(ref ** 2))).all()
+    for y in outs[1:]:
+        np.testing.assert_array_equal(y, outs[0])
