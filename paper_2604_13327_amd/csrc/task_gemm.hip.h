@@ -1794,6 +1794,11 @@ __device__ __forceinline__ void gemm_tiles_chunked_passes(const Params &PL, Chun
 // task).  Operand rows longer than kMaxBufLd lie outside one buffer descriptor: split K, a tile at a time, 8-byte loads.
 // Measured at the change (16 x 64-byte fragments and 8-byte operand loads before): 8B batch 5 / 16 / 64 680 / 950 / 1327 ->
 // 573 / 864 / 1293 us per four layers, the MoE layer at 1024 tokens 810 -> 424.
+//
+// MOE: a dense instance carries no row blocks of experts.  The task loop saves what a callee may clobber, also the ones it never
+// calls: with the bodies of three and four tiles per wavefront behind the one entry the dense instance's loop had 106 accesses to
+// scratch memory, without them 40 (8B batch 16 / 64, 70B batch 32: 886 / 1256 / 1306 us with them, 837 / 1213 / 1266 without).
+template <bool MOE>
 __device__ __noinline__ void gemm_chunked_entry(const Params &PL, ChunkedArgs *slot, float *sm, int *frame_anchor)
 {
     const ChunkedArgs a = lds_get_uniform(slot);
@@ -1807,7 +1812,7 @@ __device__ __noinline__ void gemm_chunked_entry(const Params &PL, ChunkedArgs *s
         else gemm_tiles_chunked_passes<NB_, 4>(PL, a, slot, sm, &anchor);                        \
     }
     const bool buf_ok = a.g.ldb <= kMaxBufLd;
-    if (buf_ok && (a.e.kind == EPI_MOE_ACT || a.e.kind == EPI_MOE_Y)) {      // row blocks of more than 64 columns exist here only
+    if (MOE && buf_ok && (a.e.kind == EPI_MOE_ACT || a.e.kind == EPI_MOE_Y)) {      // row blocks of more than 64 columns exist here only
         if (stream_fits(a.g.n_tiles, a.g.n_cols, a.g.K, a.g.ldb)) {
             if (a.g.n_cols <= 8) gemm_tiles_stream<1>(PL, slot, sm, &anchor);
             else gemm_tiles_stream<2>(PL, slot, sm, &anchor);
@@ -1852,16 +1857,16 @@ __device__ __noinline__ void gemm_chunked_entry_by_value(const Params &PL, GemmT
     if (threadIdx.x == 0) lds_put(slot, a);
     __syncthreads();
     int frame_anchor = 0;
-    gemm_chunked_entry(PL, slot, sm, &frame_anchor);
+    gemm_chunked_entry<true>(PL, slot, sm, &frame_anchor);
 }
 
-// The chunked path from the task loop.  ARGS_BY_VALUE: see gemm_chunked_entry_by_value.
-template <bool ARGS_BY_VALUE>
+// The chunked path from the task loop.  The MoE instances hand the arguments over by value: see gemm_chunked_entry_by_value.
+template <bool MOE>
 __device__ __forceinline__ void gemm_chunked_dispatch(const Params &PL, const GemmTile &g, const Epilogue &e, const TaskWaits &w,
                                                       float *sm, WgState &st, int task_id)
 {
     st.staged_key = -1;
-    if (ARGS_BY_VALUE) {
+    if (MOE) {
         gemm_chunked_entry_by_value(PL, g, e, w, sm, task_id);
         return;
     }
@@ -1869,7 +1874,7 @@ __device__ __forceinline__ void gemm_chunked_dispatch(const Params &PL, const Ge
     if (threadIdx.x == 0) lds_put(slot, ChunkedArgs{g, e, w, task_id});
     __syncthreads();
     int frame_anchor = 0;
-    gemm_chunked_entry(PL, slot, sm, &frame_anchor);
+    gemm_chunked_entry<false>(PL, slot, sm, &frame_anchor);
 }
 
 // Second stage of a K-sliced projection: adds the partial sums of the slices in slice order (fixed, so the
