@@ -162,6 +162,25 @@ def test_qwen3_moe_layer_matches_oracle(tokens):
     print(f"qwen3 MoE layer, {tokens} tokens: max|err|/rms = {e:.3e}, row tiles {int(outs[0][1]['exp_indptr'][-1])}")
 
 
+@pytest.mark.parametrize("tokens", [8, 9, 72, 73, 95, 97])
+def test_topk_where_the_tokens_in_flight_change(tokens):
+    """The last block of 64 tokens holds 8, 9, 31 or 33: one token a wavefront, one and a second, four and none or one more;
+    and fewer tokens than the plan, whose last block then has none."""
+    from synth import gpu as sgpu
+    etc = _etc()
+    s, seed, tile_m = synth.TINY_MOE, 58, 16
+    w = _weights(s, seed)
+    layer = etc.MoeLayer(s, [tokens + 64], moe_tile_m=tile_m, debug_flags=etc.DEBUG_ROUTING, spin_budget=SPIN)
+    layer.bind_weights(w)
+    for T in (tokens, tokens + 64):
+        x = sgpu.hidden_gpu(s, seed, T, T)
+        layer.bind_tokens(T)
+        y = _run(layer, x)
+        assert (layer.error_word() == 0).all() and (layer.event_counters() == 0).all()
+        _check_against_oracle(s, seed, x, y, _routing(layer, s, T), tile_m)
+    layer.close()
+
+
 @pytest.mark.parametrize("H,moe_F", [(256, 131328), (131328, 256)])
 def test_operand_rows_longer_than_one_buffer_descriptor(H, moe_F):
     """Operand rows of more than 131072 elements (the expert FFN size in the down GroupGEMM, the hidden size elsewhere) are
