@@ -310,8 +310,7 @@ std::string build_decoder_graph(const ModelDims &m, int Bs, int n_queues, bool m
     const bool slice_d = g.k_slices_d > 0 && n_ht % pass_d == 0;
     if (!slice_o) g.k_slices_o = 0;
     if (!slice_d) g.k_slices_d = 0;
-    // (the staged-only kernel instances carry one group of 8 columns)
-    g.all_staged = m.E == 0 && Bs <= 8 && staged_fits(r_qkv, Bs, m.H) && staged_fits(r_gu, Bs, m.H) &&
+    g.all_staged = m.E == 0 && staged_fits(r_qkv, Bs, m.H) && staged_fits(r_gu, Bs, m.H) &&
                    (slice_o ? staged_fits(pass_tiles, Bs, m.nq * m.d / g.k_slices_o) : staged_fits(1, Bs, m.nq * m.d)) &&
                    (slice_d ? staged_fits(pass_d, Bs, m.F / g.k_slices_d) : staged_fits(1, Bs, m.F));
 

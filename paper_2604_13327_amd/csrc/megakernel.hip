@@ -329,8 +329,12 @@ __device__ __forceinline__ void dispatch_projection(const Params &PL, const Task
 // decoder, 2 MoE decoder, 3 dense decoder whose projection tasks all fit the staged path (small batches), 4 the
 // same with K-slice tasks (the batches at which only a slice of the down projection's operand fits).  The
 // one large kernel is short of registers, and code that cannot run still costs some: the dense instance alone
-// is 5 % faster than an instance that carries everything, the staged-only instance another 2 %.
+// is 5 % faster than an instance that carries everything, the staged-only instance another 2 %.  5 and 6: 3 and 4 for 9 to
+// 16 bound sequences (two groups of 8 columns; only shapes of small hidden size fit there).  Four layers of hidden 512 / 1024 /
+// 2048 at batch 9 in the plan of 16, up to 1024 keys: 244 / 328 / 454 us on instance 1, 211 / 281 / 408 on these.  Instances of
+// their own, because both groups in one cost the whole 8B iteration 1.4 % (3222 against 3268 us).
 constexpr int KIND_GENERIC = 0, KIND_DENSE = 1, KIND_MOE = 2, KIND_DENSE_STAGED = 3, KIND_DENSE_STAGED_K = 4;
+constexpr int KIND_DENSE_STAGED_16 = 5, KIND_DENSE_STAGED_K_16 = 6;
 // Added to a decoder kind: the instance also carries the end of the iteration (embedding look-up, vocabulary projection,
 // sampling).  A flag of the instance for the same reason as the kinds: on the 8B step the code costs 1.5 % where it never runs.
 constexpr int KIND_LM = 8;
@@ -362,8 +366,8 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
         dispatch_projection<MOE, LM>(PL, t, tw, rt, 1, g, e, sm, st);
         return;
     }
-    constexpr bool STAGED_ONLY = BASE == KIND_DENSE_STAGED || BASE == KIND_DENSE_STAGED_K;
-    constexpr bool STAGED_SLICES = BASE == KIND_DENSE_STAGED_K;
+    constexpr bool STAGED_ONLY = BASE >= KIND_DENSE_STAGED;
+    constexpr bool STAGED_SLICES = BASE == KIND_DENSE_STAGED_K || BASE == KIND_DENSE_STAGED_K_16;
     if (BASE != KIND_GENERIC && !STAGED_ONLY && (t.flags & TF_K_SLICE)) {      // first stage of a K-sliced projection
         setup_gemm<false, false>(P, t, g, e);
         slice_of_k(P, t, t.fn == FN_OPROJ ? P.k_slices_o : P.k_slices_d, g, e);
@@ -378,7 +382,7 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
                 slice_of_k(P, t, t.fn == FN_OPROJ ? P.k_slices_o : P.k_slices_d, g, e);
                 if (w0 >= 0) tw.op_key = w0 + ((t.c1 + 1) << 20);
             }
-            gemm_tiles_staged<5, 1, LM>(P, g, e, tw, sm, st, t.id);
+            gemm_tiles_staged<5, BASE >= KIND_DENSE_STAGED_16 ? 2 : 1, LM>(P, g, e, tw, sm, st, t.id);
         } else {
             dispatch_projection<MOE, LM>(PL, t, tw, RowTile{}, 0, g, e, sm, st);
         }
@@ -868,6 +872,8 @@ hipError_t launch_rowsum_noalloc(const float *A, float *C, int n, hipStream_t s)
 // ---------------------------------------------------------------------------------------------
 namespace etc {
 
+// Asks for the whole LDS.  The runtime gives it at the launch all the same (the LM instances and kinds 5 and 6 are not asked
+// for: 16 us of a create each).
 hipError_t configure_kernels()
 {
 #ifdef ETC_GENERIC_ONLY
@@ -903,7 +909,9 @@ static int kind_of(const Params &P)
     const int lm = P.vocab > 0 ? KIND_LM : 0;
     if (P.E > 0) return KIND_MOE | lm;
     if (!P.all_staged) return KIND_DENSE | lm;
-    return ((P.k_slices_o > 0 || P.k_slices_d > 0) ? KIND_DENSE_STAGED_K : KIND_DENSE_STAGED) | lm;
+    const bool sliced = P.k_slices_o > 0 || P.k_slices_d > 0;
+    if (P.B > 8) return (sliced ? KIND_DENSE_STAGED_K_16 : KIND_DENSE_STAGED_16) | lm;
+    return (sliced ? KIND_DENSE_STAGED_K : KIND_DENSE_STAGED) | lm;
 }
 
 #ifdef ETC_GENERIC_ONLY      // a library generated for one graph: no decoder instances (they are most of the compile time)
@@ -917,10 +925,14 @@ static int kind_of(const Params &P)
     case KIND_DENSE: hipLaunchKernelGGL(KERNEL<KIND_DENSE>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break;     \
     case KIND_DENSE_STAGED: hipLaunchKernelGGL(KERNEL<KIND_DENSE_STAGED>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break; \
     case KIND_DENSE_STAGED_K: hipLaunchKernelGGL(KERNEL<KIND_DENSE_STAGED_K>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break; \
+    case KIND_DENSE_STAGED_16: hipLaunchKernelGGL(KERNEL<KIND_DENSE_STAGED_16>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break; \
+    case KIND_DENSE_STAGED_K_16: hipLaunchKernelGGL(KERNEL<KIND_DENSE_STAGED_K_16>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break; \
     case KIND_MOE: hipLaunchKernelGGL(KERNEL<KIND_MOE>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break;         \
     case KIND_DENSE | KIND_LM: hipLaunchKernelGGL(KERNEL<KIND_DENSE | KIND_LM>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break; \
     case KIND_DENSE_STAGED | KIND_LM: hipLaunchKernelGGL(KERNEL<KIND_DENSE_STAGED | KIND_LM>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break; \
     case KIND_DENSE_STAGED_K | KIND_LM: hipLaunchKernelGGL(KERNEL<KIND_DENSE_STAGED_K | KIND_LM>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break; \
+    case KIND_DENSE_STAGED_16 | KIND_LM: hipLaunchKernelGGL(KERNEL<KIND_DENSE_STAGED_16 | KIND_LM>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break; \
+    case KIND_DENSE_STAGED_K_16 | KIND_LM: hipLaunchKernelGGL(KERNEL<KIND_DENSE_STAGED_K_16 | KIND_LM>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break; \
     default: hipLaunchKernelGGL(KERNEL<KIND_MOE | KIND_LM>, GRID, dim3(kWgThreads), kLdsBytes, s, __VA_ARGS__); break;     \
     }
 #endif

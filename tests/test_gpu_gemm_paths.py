@@ -145,3 +145,36 @@ def test_router_sums_over_experts(n_experts, top_k, batch, tile_m):
         dec.bind_step(step)
         check_moe_step(dec, model, s, step, tile_m)
         dec.close()
+
+
+@pytest.mark.parametrize("bound", [5, 8, 9, 12, 16])
+@pytest.mark.parametrize("shape,sliced", [(synth.TINY, False), (synth.ModelShape("small-sliced", 2, 1024, 8, 2, 64, 3072), True)])
+def test_staged_only_plan_of_up_to_16_sequences(shape, sliced, bound):
+    """A plan of 16 whose projections all fit the staged path, with and without slices of K: bound batches on both sides of
+    the 8 columns of one product group, on the instances for one and for two groups, against the oracle."""
+    import torch
+
+    import paper_2604_13327_amd as etc
+    fns = etc.plan_build(shape, 32, 16, 256, 41)["tasks"]["fn"]
+    assert (fns == 16).any() == sliced                    # the sums of a down projection cut along K
+    pages = bound * 3 + 4
+    model = GpuModel(shape, seed=79, n_pool_pages=pages)
+    step = fixed_step(shape, bound, [(7 * b + 3) % 40 for b in range(bound)], pages, seed=80)
+    x = model.hidden(0, bound)
+    ref = oracle_step(shape, model.seed, pages, step, 0)["final"]
+    outs = []
+    for kind in (etc.SCHED_STATIC, etc.SCHED_DYNAMIC, etc.SCHED_UNFUSED):
+        model.reset_pools()
+        dec = etc.Decoder(shape, kv_chunk_tokens=32, sampled_batches=[16], max_kv_len=41, kind=kind, spin_budget=SPIN)
+        model.bind(dec)
+        dec.bind_step(step)
+        out = torch.full_like(x, float("nan"))
+        for _ in range(2):
+            dec.launch(x, out)
+        torch.cuda.synchronize()
+        assert (dec.error_word() == 0).all() and (dec.event_counters() == 0).all()
+        outs.append(bf16_to_f32_np(out))
+        dec.close()
+    assert rel_err(outs[0], ref) <= TOL
+    for o in outs[1:]:
+        np.testing.assert_array_equal(o, outs[0])
