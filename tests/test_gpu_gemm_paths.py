@@ -178,3 +178,34 @@ def test_staged_only_plan_of_up_to_16_sequences(shape, sliced, bound):
     assert rel_err(outs[0], ref) <= TOL
     for o in outs[1:]:
         np.testing.assert_array_equal(o, outs[0])
+
+
+@pytest.mark.parametrize("tile_m,n_queues,gate_up,down", [(64, 32, 48, 24), (40, 64, 24, 12), (40, 32, 48, 24), (64, 48, 32, 16)])
+def test_group_gemm_three_tiles_per_wavefront(tile_m, n_queues, gate_up, down):
+    """Task shapes of 24 and 48 row tiles (three per wavefront, one pass and two), at 33 .. 64 columns, at more on an expert's
+    only block and on one of several; three row tiles of 40 to a block of 120 columns."""
+    import paper_2604_13327_amd as etc
+    from synth import gpu as sgpu
+    s, seed = synth.ModelShape("moe-edges-3", 1, 768, 4, 2, 64, 0, n_experts=16, top_k=2, moe_F=768), 81
+    first, second = [1, 8, 9, 16, 17, 33, 130, 175], [32, 64, 65, 0, 128, 15, 7, 78]
+    tokens = sum(first)
+    t = etc.moe_layer_plan_build(s, tokens, n_queues, moe_tile_m=tile_m)["tasks"]
+    assert set(t["c2"][t["fn"] == 12]) == {gate_up} and set(t["c2"][t["fn"] == 13]) == {down}
+    ids = np.stack([np.repeat(np.arange(8), first), np.repeat(np.arange(8, 16), second)[::-1]], 1).astype(np.int32)
+    w = _weights(s, seed)
+    x = sgpu.hidden_gpu(s, seed, tokens, tokens)
+    outs = []
+    for kind in (etc.SCHED_STATIC, etc.SCHED_DYNAMIC, etc.SCHED_UNFUSED):
+        layer = etc.MoeLayer(s, [tokens], kind=kind, moe_tile_m=tile_m, debug_flags=etc.DEBUG_ROUTING, spin_budget=SPIN,
+                             n_queues=n_queues)
+        layer.bind_weights(w)
+        layer.bind_tokens(tokens)
+        layer.force_routing(0, ids)
+        for rep in range(2):
+            y = _run(layer, x)
+            assert (layer.error_word() == 0).all(), layer.error_word()
+        outs.append((y, _routing(layer, s, tokens)))
+        layer.close()
+    _check_against_oracle(s, seed, x, outs[0][0], outs[0][1], tile_m, forced=ids)
+    for y, r in outs[1:]:
+        np.testing.assert_array_equal(y, outs[0][0])
