@@ -314,14 +314,14 @@ __device__ __noinline__ WgState staged_task_out_of_line(const Params &PL, Task t
 }
 
 // Staged path (out of line, from the task record) or chunked path (out of line, from the descriptors).  A GroupGEMM task that
-// fits both the staged and the stream path takes the latter from three tiles per wavefront on: fewer leave the wavefronts that
-// share a tile's K ahead of those that own tiles (Qwen3-30B-A3B shape, three layers, 12 and 16 tiles per task at batch 3: 423
-// us staged, 437 stream; 24 and 32 at batch 5 / 8: 591 / 671 staged, 538 / 595 stream).
+// fits both the staged path and the stream path of the latter is faster on the staged one (Qwen3-30B-A3B shape, three layers, on
+// the staged / on the stream path: 12 and 16 tiles per task at batch 3 404 / 461 us, 24 and 32 at batch 5 535 / 585 and at batch 8
+// 602 / 652; MoE layer of 9 tokens 154 / 169; from 48 tokens on few tasks fit and the two are level).
 template <bool MOE, bool LM>
 __device__ __forceinline__ void dispatch_projection(const Params &PL, const Task &t, const TaskWaits &tw, const RowTile &rt, int mode,
                                                     const GemmTile &g, const Epilogue &e, float *sm, WgState &st)
 {
-    if (staged_fits(g.n_tiles, g.n_cols, g.K) && !(MOE && mode == 1 && g.n_tiles > 2 * kWaves && stream_fits(g.n_tiles, g.n_cols, g.K, g.ldb))) st = staged_task_out_of_line<MOE, LM>(PL, t, tw, rt, mode, sm, st);
+    if (staged_fits(g.n_tiles, g.n_cols, g.K)) st = staged_task_out_of_line<MOE, LM>(PL, t, tw, rt, mode, sm, st);
     else gemm_chunked_dispatch<MOE>(PL, g, e, tw, sm, st, t.id);
 }
 

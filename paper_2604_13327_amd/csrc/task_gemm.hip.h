@@ -1393,7 +1393,7 @@ __device__ __noinline__ void gemm_tiles_lines(const Params &P, const ChunkedArgs
 }
 
 // ---- GroupGEMM paths (row blocks of the MoE block: EPI_MOE_ACT, EPI_MOE_Y) -----------------------------------------
-// Up to 16 columns, 8 or more row tiles: the whole operand sits in LDS (64 KB for 8 columns of K = 2048) and every
+// Up to 16 columns, 8 or more row tiles that do not fit the staged path: the whole operand sits in LDS (64 KB for 8 columns of K = 2048) and every
 // wavefront streams row tiles of its own (wave, wave + 8, ...) through all of K: one linear stream of weights with 16
 // loads in flight that never drains between tiles, no barrier and no reduction behind the staging, the epilogue straight
 // from the accumulators.  Bound by HBM.  The staged path splits K over the wavefronts instead and meets in one reduction
