@@ -82,8 +82,12 @@ typedef struct {
 typedef struct {
     int32_t kv_chunk_tokens; /* smallest number of keys per split-KV attention task; multiple of page_size.
                                 Per sampled batch size the library enlarges it (in whole pages) until a layer
-                                has about one attention task per queue; a sequence is cut into chunks of equal
-                                length (in whole pages). */
+                                has about one attention task per queue; the task slots are shared out to the
+                                sequences of the bound batch, and a sequence is cut into chunks of equal length
+                                (in whole pages).  The order of a sequence's fp32 sums follows the sampled batch
+                                and the bound one (here, and in the choice of a projection's loop by its columns):
+                                the same call gives the same bits under every scheduler, but the last bits of a
+                                sequence may differ from a step in which more or fewer are bound beside it. */
     int32_t moe_tile_m;      /* tokens per GroupGEMM row tile (exp_indptr unit, Sec. 2.4); 1..16 */
 } etc_tile_desc;
 

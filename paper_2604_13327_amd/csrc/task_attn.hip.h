@@ -25,7 +25,8 @@ template <int D, int GRP> __device__ __forceinline__ void attn_merge_chunks(cons
 // KV head; a step of P.B sequences gives each max_slots / P.B of them and splits it evenly, in whole pages and not finer than
 // the caller's chunk: the slots of one sequence are equally long, and a batch below the sampled one uses all of them.  With
 // chunks of a fixed number of keys (the longest sequence cut into the sampled batch's slots) a sequence of 1.5 chunks left
-// half of its second slot idle, and a batch of 5 in the plan of 8 three eighths of the queues.
+// half of its second slot idle, and a batch of 5 in the plan of 8 three eighths of the queues.  The chunk bounds, and so the
+// order of a sequence's sums, follow P.B.
 __device__ __forceinline__ int attn_chunk_keys(const Params &P, int n_keys)
 {
     const int slots = P.attn_grid / P.B;

@@ -1792,8 +1792,8 @@ __device__ __forceinline__ void gemm_tiles_chunked_passes(const Params &PL, Chun
 // split the output (wide, lines; row blocks of experts: stream, blocks); the fewer tiles of the others (QKV, narrow plans)
 // would leave wavefronts idle there, so they split K (chunked, 1, 2 or 4 tiles: the loop always moves T, so T follows the
 // task).  Operand rows longer than kMaxBufLd lie outside one buffer descriptor: split K, a tile at a time, 8-byte loads.
-// Measured at the change (16 x 64-byte fragments and 8-byte operand loads before): 8B batch 5 / 16 / 64 680 / 950 / 1327 ->
-// 573 / 864 / 1293 us per four layers, the MoE layer at 1024 tokens 810 -> 424.
+// Measured against 16 x 64-byte fragments and 8-byte operand loads: 8B batch 5 / 16 / 64 686 / 929 / 1314 -> 562 / 817 / 1210 us
+// per four layers, the MoE layer at 1024 tokens 808 -> 436.
 //
 // MOE: a dense instance carries no row blocks of experts.  The task loop saves what a callee may clobber, also the ones it never
 // calls: with the bodies of three and four tiles per wavefront behind the one entry the dense instance's loop had 106 accesses to
