@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <string>
 #include <vector>
@@ -34,6 +35,8 @@ std::string g_create_error;
 // Switch for the dynamic-scheduler kernel (off: launching it is refused; the static and unfused schedulers
 // are unaffected).
 constexpr bool kDynamicEnabled = true;
+// Plans of at most this many event counters give each a 128-byte line of its own (A | B and the dispatch counters: 32 MB then).
+constexpr size_t kLineCountersMax = 65536;
 const char *kDynamicOffMsg = "the dynamic scheduler is switched off in this build";
 
 struct DevPlan {          // one instantiated plan (one sampled batch size), host + device copies
@@ -42,6 +45,7 @@ struct DevPlan {          // one instantiated plan (one sampled batch size), hos
     int k_slices_o = 0, k_slices_d = 0;   // slices of K of this plan's O / down projection tasks
     bool all_staged = false;              // every projection task of this plan fits the staged path
     Plan host;
+    Counters ctr;         // its task records are dropped once they are on the device
     Task *d_queue_tasks = nullptr, *d_tasks = nullptr;
     int32_t *d_queue_begin = nullptr, *d_ev_init = nullptr, *d_ev_consumers = nullptr, *d_consumer_ids = nullptr,
             *d_seed = nullptr;
@@ -96,7 +100,7 @@ struct etc_ctx {
     int32_t *d_disp = nullptr;              // [2][n_events_max]: dispatch counters of the dynamic scheduler, A | B
     int32_t *d_pending = nullptr;           // [n_tasks_max]: dynamic scheduler, waited events passed per task
     size_t n_tasks_max = 0;
-    int n_events_max = 0;
+    int n_events_max = 0;                   // words
     int parity = 0;
     uint32_t epoch = 1;
     int32_t *d_qctrl = nullptr;             // [2][8]
@@ -146,10 +150,13 @@ etc_status fail(etc_ctx *c, etc_status s, const std::string &msg)
 
 etc_status upload_plan(etc_ctx *c, DevPlan &dp)
 {
-    HIP_TRY(c, dev_upload(&dp.d_queue_tasks, dp.host.queue_tasks, c->plan_owned));
-    HIP_TRY(c, dev_upload(&dp.d_tasks, dp.host.tasks, c->plan_owned));
+    dp.ctr = place_counters(dp.host, c->sched.kind != ETC_SCHED_DYNAMIC);
+    HIP_TRY(c, dev_upload(&dp.d_queue_tasks, dp.ctr.queue_tasks, c->plan_owned));
+    HIP_TRY(c, dev_upload(&dp.d_tasks, dp.ctr.tasks, c->plan_owned));
+    std::vector<Task>().swap(dp.ctr.queue_tasks);
+    std::vector<Task>().swap(dp.ctr.tasks);
     HIP_TRY(c, dev_upload(&dp.d_queue_begin, dp.host.queue_begin, c->plan_owned));
-    HIP_TRY(c, dev_upload(&dp.d_ev_init, dp.host.ev_init, c->plan_owned));
+    HIP_TRY(c, dev_upload(&dp.d_ev_init, dp.ctr.init, c->plan_owned));
     HIP_TRY(c, dev_upload(&dp.d_ev_consumers, dp.host.ev_consumers, c->plan_owned));
     HIP_TRY(c, dev_upload(&dp.d_consumer_ids, dp.host.consumer_ids, c->plan_owned));
     HIP_TRY(c, dev_upload(&dp.d_seed, dp.host.seed_tasks, c->plan_owned));
@@ -199,9 +206,11 @@ etc_status alloc_events_and_queue(etc_ctx *c)
 {
     size_t n_ev = 1, n_tasks = 1;
     for (const DevPlan &dp : c->plans) {
-        n_ev = std::max(n_ev, dp.host.ev_init.size());
+        n_ev = std::max(n_ev, dp.ctr.init.size());
         n_tasks = std::max(n_tasks, dp.host.tasks.size());
     }
+    c->base.ev_shift = n_ev <= kLineCountersMax ? 5 : 0;
+    n_ev <<= c->base.ev_shift;
     c->n_events_max = (int)n_ev;
     HIP_TRY(c, dev_alloc(&c->d_events, 2 * n_ev, c->plan_owned));
     HIP_TRY(c, dev_alloc(&c->d_disp, 2 * n_ev, c->plan_owned));
@@ -227,7 +236,8 @@ etc_status arm_on_stream(etc_ctx *c, hipStream_t s)
     if (c->need_arm) {
         a.ev_cur = c->d_events + (c->parity ? N : 0);
         a.ev_init = dp.d_ev_init;
-        a.n_events = (int)dp.host.ev_init.size();
+        a.n_events = (int)dp.ctr.init.size();
+        a.ev_shift = c->base.ev_shift;
         a.disp_cur = c->d_disp + (c->parity ? N : 0);
         a.pending = c->d_pending;
         a.n_pending = (int)c->n_tasks_max;
@@ -252,7 +262,7 @@ void fill_launch_params(etc_ctx *c, Params &P)
     P.ev_cur = c->d_events + (c->parity ? N : 0);
     P.ev_init = dp.d_ev_init;
     P.ev_next = c->d_events + (c->parity ? 0 : N);
-    P.n_events = (int)dp.host.ev_init.size();
+    P.n_events = (int)dp.ctr.init.size();
     P.tasks = dp.d_queue_tasks;
     P.queue_begin = dp.d_queue_begin;
     P.n_queues = c->n_queues;
@@ -297,10 +307,20 @@ void fill_launch_params(etc_ctx *c, Params &P)
     for (int i = 0; i < 4; ++i) P.gsym[i] = c->sym_values[i];
 }
 
+// The error word; of a wait that gave up the device names the counter, the caller gets the event.
+etc_status read_error_word(etc_ctx *c, int32_t (&w)[4])
+{
+    HIP_TRY(c, hipMemcpy(w, c->base.error_word, sizeof(w), hipMemcpyDeviceToHost));
+    if (w[0] == ERR_WAIT_TIMEOUT && c->cur_plan >= 0 && w[2] >= 0 && w[2] < (int)c->plans[c->cur_plan].ctr.event.size())
+        w[2] = c->plans[c->cur_plan].ctr.event[w[2]];
+    return ETC_OK;
+}
+
 etc_status check_error_word(etc_ctx *c)
 {
     int32_t w[4];
-    HIP_TRY(c, hipMemcpy(w, c->base.error_word, sizeof(w), hipMemcpyDeviceToHost));
+    const etc_status st = read_error_word(c, w);
+    if (st != ETC_OK) return st;
     if (w[0] != 0) {
         char buf[200];
         snprintf(buf, sizeof(buf), "device watchdog: code %d in task function %d, event/ticket %d, queue %d", w[0],
@@ -859,13 +879,28 @@ etc_status etc_read_debug(etc_ctx *c, int32_t kind, int32_t layer, void *dst, si
     size_t avail = 0;
     const size_t MB = (size_t)c->sched.max_batch;
     switch (kind) {
-    case ETC_DBG_ERROR_WORD: src = P.error_word; avail = 4 * sizeof(int32_t); break;
-    case ETC_DBG_EVENT_COUNTERS:
+    case ETC_DBG_ERROR_WORD: {
+        int32_t w[4];
+        if (bytes > sizeof(w)) return fail(c, ETC_EINVAL, "more bytes requested than the item holds");
+        const etc_status st = read_error_word(c, w);
+        if (st == ETC_OK) memcpy(dst, w, bytes);
+        return st;
+    }
+    case ETC_DBG_EVENT_COUNTERS: {
         if (c->cur_plan < 0) return fail(c, ETC_ESTATE, "nothing bound");
+        const DevPlan &dp = c->plans[c->cur_plan];
+        std::vector<int32_t> events(dp.host.ev_init.size(), 0), raw(dp.ctr.init.size() << P.ev_shift);
+        if (bytes > events.size() * sizeof(int32_t)) return fail(c, ETC_EINVAL, "more bytes requested than the item holds");
         // the buffer the last launch consumed is the one the next launch re-arms... it was `cur` before the flip
-        src = c->d_events + (c->parity ? 0 : N);
-        avail = c->plans[c->cur_plan].host.ev_init.size() * sizeof(int32_t);
-        break;
+        HIP_TRY(c, hipMemcpy(raw.data(), c->d_events + (c->parity ? 0 : N), raw.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+        for (size_t i = 0; i < dp.ctr.init.size(); ++i) {      // of a spread event: what its counters are off zero, in all
+            const int32_t v = raw[i << P.ev_shift];
+            int32_t &e = events[dp.ctr.event[i]];
+            e = (i > 0 && dp.ctr.event[i - 1] == dp.ctr.event[i]) || (i + 1 < dp.ctr.init.size() && dp.ctr.event[i + 1] == dp.ctr.event[i]) ? e + std::abs(v) : v;
+        }
+        memcpy(dst, events.data(), bytes);
+        return check_error_word(c);
+    }
     case ETC_DBG_TASK_EXEC_COUNT:
         if (!P.exec_count || c->cur_plan < 0) return fail(c, ETC_ESTATE, "exec counting is off");
         src = P.exec_count; avail = c->plans[c->cur_plan].host.tasks.size() * sizeof(int32_t); break;
@@ -897,7 +932,6 @@ etc_status etc_read_debug(etc_ctx *c, int32_t kind, int32_t layer, void *dst, si
     }
     if (bytes > avail) return fail(c, ETC_EINVAL, "more bytes requested than the item holds");
     HIP_TRY(c, hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost));
-    if (kind == ETC_DBG_ERROR_WORD) return ETC_OK;
     return check_error_word(c);
 }
 

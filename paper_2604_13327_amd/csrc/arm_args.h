@@ -9,7 +9,7 @@ struct ArmArgs {
     int32_t *ev_cur;            // [n_events] <- ev_init: the event tensor the next launch drains
     const int32_t *ev_init;
     int32_t *disp_cur;          // [n_events] <- ev_init: dispatch counters of the dynamic scheduler
-    int n_events;
+    int n_events, ev_shift;     // counter i at [i << ev_shift] of cur
     int32_t *pending;           // [n_pending] <- 0: per-task counters of the dynamic scheduler
     int n_pending;
     int32_t *exp_event;         // [n_exp] <- 0: run-time armed expert events

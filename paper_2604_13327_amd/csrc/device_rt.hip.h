@@ -169,10 +169,12 @@ __device__ __forceinline__ void raise_error(const Params &P, int code, int fn, i
     }
 }
 
-// Spin of one lane until E[ev] reaches zero: bounded backoff, bounded budget.
+__device__ __forceinline__ int32_t *ev_counter(const Params &P, int i) { return P.ev_cur + ((size_t)i << P.ev_shift); }
+
+// Spin of one lane until counter ev reaches zero: bounded backoff, bounded budget.
 __device__ __forceinline__ void spin_until_zero(const Params &P, int ev, int fn)
 {
-    const int32_t *p = P.ev_cur + ev;
+    const int32_t *p = ev_counter(P, ev);
     long long spins = 0;
     while (ev_peek(p) > 0) {
         if (spins < 16) __builtin_amdgcn_s_sleep(1); else __builtin_amdgcn_s_sleep(4);
@@ -182,23 +184,21 @@ __device__ __forceinline__ void spin_until_zero(const Params &P, int ev, int fn)
     }
 }
 
-// E[ev].wait() for one wavefront (lane 0 polls).  A wait that gives up records the error and the task
-// still runs (on stale data), so every wave keeps the same barrier sequence and the kernel drains.
-__device__ __forceinline__ void wave_wait(const Params &P, int ev, int fn)
+// E[ev].wait() by the lanes of wavefront 0, a lane for each counter of a spread event (ev < 0: none).  A wait that gives up
+// records the error and the task still runs (on stale data), so every wave keeps the same barrier sequence and the kernel drains.
+__device__ __forceinline__ void spin_event(const Params &P, int ev, int fn)
 {
     if (ev < 0) return;
-    if (lane_id() == 0) spin_until_zero(P, ev, fn);
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");    // orders later loads after the poll (no cache op)
+    if (lane_id() < ((ev & kEvSpread) ? kEvSpreadN : 1)) spin_until_zero(P, (ev & kEvIndex) + lane_id(), fn);
 }
 
-// E[ev0].wait(), E[ev1].wait() for the whole workgroup: one polling lane, then a barrier.
+// E[ev0].wait(), E[ev1].wait() for the whole workgroup: one polling wavefront, then a barrier.
 __device__ __forceinline__ void wg_wait(const Params &P, int ev0, int ev1, int fn)
 {
     if (ev0 < 0 && ev1 < 0) return;
-    if (threadIdx.x == 0) {
-        if (ev0 >= 0) spin_until_zero(P, ev0, fn);
-        if (ev1 >= 0) spin_until_zero(P, ev1, fn);
+    if (wave_id() == 0) {
+        spin_event(P, ev0, fn);
+        spin_event(P, ev1, fn);
     }
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -216,10 +216,10 @@ __device__ __forceinline__ void wg_release()
     __syncthreads();
 }
 
-// E[ev].notify(): returns the value before the decrement (1 means this call fired the event).
+// E[ev].notify(): returns the value of the counter before the decrement.
 __device__ __forceinline__ int ev_notify(const Params &P, int ev)
 {
-    return __hip_atomic_fetch_sub(as_global(P.ev_cur + ev), 1, __ATOMIC_RELAXED, ETC_SCOPE);
+    return __hip_atomic_fetch_sub(as_global(ev_counter(P, ev)), 1, __ATOMIC_RELAXED, ETC_SCOPE);
 }
 
 // Per-task trace mark (debug): thread 0 stamps the device wall clock.

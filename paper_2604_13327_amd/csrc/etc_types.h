@@ -71,6 +71,10 @@ enum Fn : uint8_t {
     FN_COUNT
 };
 
+// An event index of a device task record names counters: `index` alone, or, with kEvSpread set, the kEvSpreadN counters from
+// `index` on, among which the event's producers are divided; the event has fired when all of them are zero.
+constexpr int kEvSpread = 1 << 30, kEvIndex = kEvSpread - 1, kEvSpreadN = 16;
+
 // Task flags
 enum : uint16_t {
     TF_WAIT0_PER_WAVE = 1,   // wave w waits on event wait0 + w instead of the whole workgroup on wait0
@@ -174,11 +178,12 @@ struct Params {
     int32_t *dbg_topk_ids, *dbg_perm;  // [n_layers, maxB, topk], [n_layers, maxB*topk]
     int32_t *dbg_tok_indptr, *dbg_exp_indptr; // [n_layers, E+1]
     int32_t max_batch;                 // row stride of the per-layer debug copies
-    // event tensors: three equal arrays [cur | init | next]; the kernel re-arms `next` from `init`
+    // event counters: counter i sits at [i << ev_shift] of cur and next, and at [i] of init; the kernel re-arms `next` from `init`
     int32_t *ev_cur;
     const int32_t *ev_init;
     int32_t *ev_next;
-    int32_t n_events;
+    int32_t n_events;                  // counters
+    int32_t ev_shift;                  // 5: a 128-byte line each
     // static queues
     const Task *tasks;                 // all queues back to back
     const int32_t *queue_begin;        // [n_queues + 1]

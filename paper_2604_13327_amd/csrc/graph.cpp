@@ -192,6 +192,41 @@ std::string instantiate(const GraphDecl &g, const int *sym, int n_queues, bool u
     return "";
 }
 
+Counters place_counters(const Plan &p, bool spread)
+{
+    Counters c;
+    const int n = (int)p.ev_init.size();
+    std::vector<uint8_t> wide((size_t)n, 0);
+    if (spread) {
+        for (int e = 0; e < n; ++e) wide[e] = p.ev_init[e] >= kSpreadMinProducers;
+        for (const Task &t : p.tasks)
+            if ((t.flags & TF_WAIT0_PER_WAVE) && t.wait0 >= 0)
+                for (int w = 0; w < kWaves && t.wait0 + w < n; ++w) wide[t.wait0 + w] = 0;
+    }
+    std::vector<int32_t> first((size_t)n, 0), seen((size_t)n, 0), notify(p.tasks.size(), -1);
+    for (int e = 0; e < n; ++e) {
+        first[e] = (int32_t)c.init.size();
+        c.init.insert(c.init.end(), wide[e] ? kEvSpreadN : 1, 0);
+        c.event.insert(c.event.end(), wide[e] ? kEvSpreadN : 1, e);
+        if (!wide[e]) c.init.back() = p.ev_init[e];      // also of notifies that are counted at run time only
+    }
+    for (const Task &t : p.tasks)
+        if (t.notify0 >= 0) {
+            const int e = t.notify0;
+            notify[t.id] = first[e] + (wide[e] ? seen[e]++ % kEvSpreadN : 0);
+            if (wide[e]) c.init[notify[t.id]]++;
+        }
+    auto place = [&](Task t) {
+        if (t.wait0 >= 0) t.wait0 = first[t.wait0] | (wide[t.wait0] ? kEvSpread : 0);
+        if (t.wait1 >= 0) t.wait1 = first[t.wait1] | (wide[t.wait1] ? kEvSpread : 0);
+        t.notify0 = notify[t.id];
+        return t;
+    };
+    for (const Task &t : p.tasks) c.tasks.push_back(place(t));
+    for (const Task &t : p.queue_tasks) c.queue_tasks.push_back(place(t));
+    return c;
+}
+
 int moe_tiles_per_task(const ModelDims &m, int tokens, int row_block, int per_slot, int K, int n_queues)
 {
     const double pairs = (double)tokens * m.topk, per_expert = pairs / m.E;

@@ -79,6 +79,23 @@ struct Plan {
     int dd_table_len = 0;              // extent of the first grid dimension of the indirectly notifying call
 };
 
+// Where the events of a plan count on the device.  An event's decrements are serialised where its counter lives (16 ns each), and
+// so are the looks of those who wait for it, also those at other counters of the same 128-byte line.  An all-to-all hand-over
+// among 256 workgroups on an idle chip takes 5.8 us with one counter, 4.6 / 3.6 / 3.3 / 3.0 / 3.0 with its producers dealt to
+// 2 / 4 / 8 / 16 / 32 counters in lines of their own, and 5.8 again with 16 counters in one line.  So an event of
+// kSpreadMinProducers or more counts in kEvSpreadN places (they follow one another; kEvSpread marks its index in the task
+// records).  Whole 8B iteration 3250 -> 2980 us, 8B batch 5 / 16 / 64 561 / 822 / 1207 -> 479 / 722 / 1108 per four layers, MoE
+// decoder batch 1 374 -> 324; fewest producers 32 instead of 16: the two-layer decoder of hidden 256 takes 71 us instead of 67.
+// Not spread: events a task waits for eight at a time (its wavefront's lanes poll those), and everything under the dynamic
+// scheduler, whose workgroups find an event by its index and learn from one decrement that they were the last.
+struct Counters {
+    std::vector<int32_t> init;         // initial count of every counter
+    std::vector<int32_t> event;        // counter -> event
+    std::vector<Task> tasks, queue_tasks;   // the plan's records with counters in place of events
+};
+constexpr int kSpreadMinProducers = 16;
+Counters place_counters(const Plan &p, bool spread);
+
 // Binds the symbols and materialises the plan.  unfused: ignore the declared edges and put one
 // coarse event between consecutive stages (Sec. 4.5 baseline).  Returns "" or an error text.
 // data_dependent: keep MAP_INDIRECT / MAP_INDPTR edges as run-time edges (dynamic scheduler); otherwise they are

@@ -343,7 +343,7 @@ template <bool SYNC_EVENTS, int KIND>
 __device__ __forceinline__ void run_task(const Params &P, const Params &PL, const Task &t, float *sm, WgState &st)
 {
     const int w0 = SYNC_EVENTS ? t.wait0 : -1, w1 = SYNC_EVENTS ? t.wait1 : -1;
-    TaskWaits tw{w0, w1, (int)t.fn, (t.flags & TF_WAIT0_PER_WAVE) != 0 && SYNC_EVENTS, w0};
+    TaskWaits tw{w0, w1, (int)t.fn, (t.flags & TF_WAIT0_PER_WAVE) != 0 && SYNC_EVENTS, w0 < 0 ? -1 : (w0 & kEvIndex)};
     GemmTile g{};
     Epilogue e{};
     constexpr int BASE = kind_base(KIND);
@@ -361,7 +361,7 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
         RowTile rt;
         if (!resolve_row_tile(P, t.c0, rt)) return;        // surplus slot of the static grid: nothing to do but notify
         setup_moe_gemm(P, t, rt, g, e);
-        const int key = w0 < 0 ? -1 : w0 + ((t.c0 + 1) << 20);
+        const int key = w0 < 0 ? -1 : (w0 & kEvIndex) + ((t.c0 + 1) << 20);
         tw = routed ? TaskWaits{w0, w1, (int)t.fn, false, key} : TaskWaits{-1, -1, (int)t.fn, false, key};
         dispatch_projection<MOE, LM>(PL, t, tw, rt, 1, g, e, sm, st);
         return;
@@ -371,7 +371,7 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
     if (BASE != KIND_GENERIC && !STAGED_ONLY && (t.flags & TF_K_SLICE)) {      // first stage of a K-sliced projection
         setup_gemm<false, false>(P, t, g, e);
         slice_of_k(P, t, t.fn == FN_OPROJ ? P.k_slices_o : P.k_slices_d, g, e);
-        if (tw.ev0 >= 0) tw.op_key = tw.ev0 + ((t.c1 + 1) << 20);      // a staged copy holds one slice
+        if (tw.ev0 >= 0) tw.op_key += (t.c1 + 1) << 20;      // a staged copy holds one slice
         dispatch_projection<MOE, LM>(PL, t, tw, RowTile{}, 2, g, e, sm, st);
         return;
     }
@@ -380,7 +380,7 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
         if (STAGED_ONLY) {
             if (STAGED_SLICES && (t.flags & TF_K_SLICE)) {      // here a slice of K fits the staged path as well
                 slice_of_k(P, t, t.fn == FN_OPROJ ? P.k_slices_o : P.k_slices_d, g, e);
-                if (w0 >= 0) tw.op_key = w0 + ((t.c1 + 1) << 20);
+                if (w0 >= 0) tw.op_key += (t.c1 + 1) << 20;
             }
             gemm_tiles_staged<5, BASE >= KIND_DENSE_STAGED_16 ? 2 : 1, LM>(P, g, e, tw, sm, st, t.id);
         } else {
@@ -505,7 +505,7 @@ __device__ __forceinline__ void stage_params(const Params &P, Params *dst)
 __device__ __forceinline__ void rearm_next(const Params &P)
 {
     for (int i = blockIdx.x * kWgThreads + threadIdx.x; i < P.n_events; i += gridDim.x * kWgThreads)
-        as_global(P.ev_next)[i] = as_global(P.ev_init)[i];
+        as_global(P.ev_next)[(size_t)i << P.ev_shift] = as_global(P.ev_init)[i];
 }
 
 template <int KIND>
@@ -624,7 +624,7 @@ __global__ void __launch_bounds__(kWgThreads) megakernel_dynamic(const Params P)
     stage_params(P, &sP);
     rearm_next(P);
     for (int i = blockIdx.x * kWgThreads + threadIdx.x; i < P.n_events; i += gridDim.x * kWgThreads)
-        as_global(P.ev_disp_next)[i] = as_global(P.ev_init)[i];
+        as_global(P.ev_disp_next)[(size_t)i << P.ev_shift] = as_global(P.ev_init)[i];
     if (blockIdx.x == 0 && threadIdx.x == 0) {            // reset the control words of the next launch
         for (int i = 0; i < 8; ++i) P.q_ctrl_next[i] = 0;
     }
@@ -671,7 +671,7 @@ __global__ void __launch_bounds__(kWgThreads) megakernel_dynamic(const Params P)
             // This task is dispatched: the last producer of its event to get here pushes the consumers.
             int last = 0;
             if (lane_id() == 0 && t.notify0 >= 0 && !dd_producer)
-                last = __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + t.notify0), 1, __ATOMIC_RELAXED, ETC_SCOPE) == 1;
+                last = __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + ((size_t)t.notify0 << P.ev_shift)), 1, __ATOMIC_RELAXED, ETC_SCOPE) == 1;
             if (__builtin_amdgcn_readfirstlane(last)) q_push_consumers_wave(P, t.notify0);
         }
         WgState st;
@@ -692,9 +692,9 @@ __global__ void __launch_bounds__(kWgThreads) megakernel_dynamic(const Params P)
                 if (!ev_ok) {
                     if (lane_id() == 0) raise_error(P, ERR_BAD_TABLE, t.fn, t.c0);
                 } else if (lane_id() == 0) {
-                    const int before = __hip_atomic_fetch_sub(as_global(P.ev_cur + P.dd_event_base + ev), 1, __ATOMIC_RELAXED, ETC_SCOPE);
+                    const int before = __hip_atomic_fetch_sub(as_global(ev_counter(P, P.dd_event_base + ev)), 1, __ATOMIC_RELAXED, ETC_SCOPE);
                     fired = before - 1 == -gld_i32(count + ev);
-                    if (fired) st_i32(P.ev_cur + P.dd_event_base + ev, 0);
+                    if (fired) st_i32(ev_counter(P, P.dd_event_base + ev), 0);
                 }
                 drain_vmem();        // the counter is back at zero before anything this event releases is published
                 if (__builtin_amdgcn_readfirstlane(fired)) {
@@ -956,8 +956,8 @@ __global__ void arm_step_kernel(const ArmArgs a)
     if (a.ev_cur != nullptr)
         for (int i = gid; i < a.n_events; i += stride) {
             const int32_t v = a.ev_init[i];
-            a.ev_cur[i] = v;
-            if (a.disp_cur != nullptr) a.disp_cur[i] = v;
+            a.ev_cur[(size_t)i << a.ev_shift] = v;
+            if (a.disp_cur != nullptr) a.disp_cur[(size_t)i << a.ev_shift] = v;
         }
     if (a.pending != nullptr)
         for (int i = gid; i < a.n_pending; i += stride) a.pending[i] = 0;

@@ -266,7 +266,7 @@ __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTil
             if (!event_known_zero(st, w.ev1)) { st.zero1 = st.zero0; st.zero0 = w.ev1; }
         } else if (w.per_wave) {    // the staged copy needs every K slice: lanes 0..7 of wave 0 poll one slice each
             if (wave == 0 && lane < kWaves) spin_until_zero(P, w.ev0 + lane, w.fn);
-            if (threadIdx.x == 0 && w.ev1 >= 0) spin_until_zero(P, w.ev1, w.fn);
+            if (wave_id() == 0) spin_event(P, w.ev1, w.fn);
             __syncthreads();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         } else {
@@ -574,7 +574,7 @@ __device__ __noinline__ void gemm_tiles_chunked(const Params &P, const ChunkedAr
     // ---- E.wait(): the operand is needed in full, so every K slice event is waited for ---------------
     if (w.per_wave) {
         if (wave == 0 && lane < kWaves) spin_until_zero(P, w.ev0 + lane, w.fn);
-        if (threadIdx.x == 0 && w.ev1 >= 0) spin_until_zero(P, w.ev1, w.fn);
+        if (wave_id() == 0) spin_event(P, w.ev1, w.fn);
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     } else {
@@ -769,7 +769,7 @@ __device__ __forceinline__ void gemm_wait(const Params &P, const TaskWaits &w)
 {
     if (w.per_wave) {
         if (wave_id() == 0 && lane_id() < kWaves) spin_until_zero(P, w.ev0 + lane_id(), w.fn);
-        if (threadIdx.x == 0 && w.ev1 >= 0) spin_until_zero(P, w.ev1, w.fn);
+        if (wave_id() == 0) spin_event(P, w.ev1, w.fn);
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     } else {
@@ -1004,7 +1004,7 @@ __device__ __noinline__ void gemm_tiles_wide(const Params &P, const ChunkedArgs 
     }
     if (w.per_wave) {
         if (wave == 0 && lane < kWaves) spin_until_zero(P, w.ev0 + lane, w.fn);
-        if (threadIdx.x == 0 && w.ev1 >= 0) spin_until_zero(P, w.ev1, w.fn);
+        if (wave_id() == 0) spin_event(P, w.ev1, w.fn);
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     } else {

@@ -128,10 +128,10 @@ __device__ __forceinline__ void moe_update_and_trigger(const Params &P, int laye
     if (t == 0) {
         const int live = expp[E], dead = P.moe_rmax - live;
         const int ev_slot0 = gld_i32(P.moe_layer_events + 2 * layer), ev_y = gld_i32(P.moe_layer_events + 2 * layer + 1);
-        for (int r = live + lane; r < P.moe_rmax; r += 64) st_i32(P.ev_cur + ev_slot0 + r, 0);
+        for (int r = live + lane; r < P.moe_rmax; r += 64) st_i32(ev_counter(P, ev_slot0 + r), 0);
         if (lane == 0 && dead > 0) {
-            __hip_atomic_fetch_sub(as_global(P.ev_cur + ev_y), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
-            __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + ev_y), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
+            __hip_atomic_fetch_sub(as_global(ev_counter(P, ev_y)), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
+            __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + ((size_t)ev_y << P.ev_shift)), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
             __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + 3), dead * (G + Gd), __ATOMIC_RELAXED, ETC_SCOPE);
         }
         drain_vmem();        // the counts are in place before this tile's notifies can release anything
@@ -539,10 +539,10 @@ __device__ __noinline__ void moel_scan(const Params &P, float *sm)
         const int lane = lane_id(), G = P.moe_groups_gu, Gd = P.moe_groups_down;
         const int live = expp[E], dead = P.moe_rmax - live;
         const int ev_slot0 = gld_i32(P.moe_layer_events), ev_y = gld_i32(P.moe_layer_events + 1);
-        for (int r = live + lane; r < P.moe_rmax; r += 64) st_i32(P.ev_cur + ev_slot0 + r, 0);
+        for (int r = live + lane; r < P.moe_rmax; r += 64) st_i32(ev_counter(P, ev_slot0 + r), 0);
         if (lane == 0 && dead > 0) {
-            __hip_atomic_fetch_sub(as_global(P.ev_cur + ev_y), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
-            __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + ev_y), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
+            __hip_atomic_fetch_sub(as_global(ev_counter(P, ev_y)), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
+            __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + ((size_t)ev_y << P.ev_shift)), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
             __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + 3), dead * (G + Gd), __ATOMIC_RELAXED, ETC_SCOPE);
         }
     }

@@ -1,0 +1,88 @@
+"""Where events count on the device: an event of 16 or more producers has 16 counters among which they are divided, and a plan of at
+most 65536 counters keeps each in a line of its own.  Row sums of small whole numbers are exact, whatever the layout."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+SPIN = 400000
+
+
+def _coarse_graph(etc, kind, consumers_first=False, **kw):
+    """partial_sum (n, 4) -> one event -> final_sum (n) -> another event; an event nobody notifies lies in front of them."""
+    from paper_2604_13327_amd import binding as b
+    g = etc.EventGraph(kind=kind, **kw)
+    n, one = g.dim(sym=0, mul=1, add=0), g.dim(add=1)
+    g.add_event([g.dim(add=3)])
+    e1, e2 = g.add_event([one]), g.add_event([one])
+    whole = lambda e: g.edge(e, [(b.MAP_CONST, 0, 0)])
+    calls = [lambda: g.add_call(b.FN_ROWSUM_PARTIAL, [n, g.dim(add=4)], out_edges=[whole(e1)]),
+             lambda: g.add_call(b.FN_ROWSUM_FINAL, [n], in_edges=[whole(e1)], out_edges=[whole(e2)])]
+    for add in reversed(calls) if consumers_first else calls:
+        add()
+    return g
+
+
+def _buffers(g, n, seed):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    A = torch.randint(-8, 9, (n * 32, 128), device="cuda", generator=gen).float()
+    B = torch.full((n * 32, 4), float("nan"), device="cuda")
+    C = torch.full((n * 32,), float("nan"), device="cuda")
+    for slot, t in enumerate((A, B, C)):
+        g.bind_buffer(slot, t)
+    g.bind_shape([n])
+    return A, C
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2])
+def test_events_around_the_number_of_producers_that_spreads_them(kind):
+    import torch
+    import paper_2604_13327_amd as etc
+    g = _coarse_graph(etc, kind, debug_flags=etc.DEBUG_EXEC_COUNT, spin_budget=SPIN)
+    for n in (3, 4, 5, 15, 16, 17, 67):          # 4 n producers of the first event, n of the second
+        A, C = _buffers(g, n, n)
+        for rep in range(3):                     # the later launches run on re-armed counters
+            C.fill_(float("nan"))
+            g.launch()
+            torch.cuda.synchronize()
+            assert torch.equal(C, A.sum(1)), (n, rep)
+            assert (g.event_counters() == 0).all() and (g.exec_counts() == rep + 1).all(), (n, rep)
+        assert g.step_info().n_events == (2 if kind == 2 else 5)
+    g.close()
+
+
+def test_more_counters_than_lines():
+    """65600 row blocks with an event each: more counters than get a line of their own."""
+    import torch
+    import paper_2604_13327_amd as etc
+    from paper_2604_13327_amd import binding as b
+    g = etc.EventGraph(kind=0, spin_budget=SPIN)
+    n = g.dim(sym=0, mul=1, add=0)
+    ev = g.add_event([n])
+    g.add_call(b.FN_ROWSUM_PARTIAL, [n, g.dim(add=4)], out_edges=[g.edge(ev, [(b.MAP_DIM, 0, 1)])])
+    g.add_call(b.FN_ROWSUM_FINAL, [n], in_edges=[g.edge(ev, [(b.MAP_DIM, 0, 1)])])
+    for blocks in (65600, 7):
+        A, C = _buffers(g, blocks, 1)
+        for _ in range(2):
+            C.fill_(float("nan"))
+            g.launch()
+            torch.cuda.synchronize()
+            assert torch.equal(C, A.sum(1))
+            assert (g.event_counters() == 0).all()
+    g.close()
+
+
+def test_a_wait_that_gives_up_names_the_event():
+    """One queue, consumers listed ahead of their 20 producers, a tiny budget: the kernel drains, and the error word names the
+    event (3: behind the three nobody notifies), not one of its counters."""
+    import torch
+    import paper_2604_13327_amd as etc
+    g = _coarse_graph(etc, 0, consumers_first=True, spin_budget=2000, n_queues=1)
+    _buffers(g, 5, 1)
+    g.launch()
+    torch.cuda.synchronize()
+    word = g.error_word()
+    assert word[0] == 1 and word[2] == 3, np.asarray(word)
+    with pytest.raises(etc.EtcError):
+        g.event_counters()
+    g.close()
