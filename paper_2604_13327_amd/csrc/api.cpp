@@ -47,7 +47,7 @@ struct DevPlan {          // one instantiated plan (one sampled batch size), hos
     Plan host;
     Counters ctr;         // its task records are dropped once they are on the device
     Task *d_queue_tasks = nullptr, *d_tasks = nullptr;
-    int32_t *d_queue_begin = nullptr, *d_ev_init = nullptr, *d_ev_consumers = nullptr, *d_consumer_ids = nullptr,
+    int32_t *d_queue_begin = nullptr, *d_ev_init = nullptr, *d_disp_init = nullptr, *d_ev_consumers = nullptr, *d_consumer_ids = nullptr,
             *d_seed = nullptr;
     // MoE plans: per layer the flat ids of the event of row-tile slot 0 and of the combine event; static grid sizes
     std::vector<int32_t> moe_layer_events;
@@ -103,7 +103,7 @@ struct etc_ctx {
     int n_events_max = 0;                   // words
     int parity = 0;
     uint32_t epoch = 1;
-    int32_t *d_qctrl = nullptr;             // [2][8]
+    int32_t *d_qctrl = nullptr;             // [2][kQWords]
     int32_t *d_kv_len = nullptr, *d_page_indptr = nullptr, *d_page_ids = nullptr;   // parts of d_step
     // Step shapes travel host -> pinned staging slot (during etc_bind_step) -> device block (one asynchronous copy on
     // the stream of the next launch): binding a step neither synchronises nor touches the device.
@@ -150,14 +150,16 @@ etc_status fail(etc_ctx *c, etc_status s, const std::string &msg)
 
 etc_status upload_plan(etc_ctx *c, DevPlan &dp)
 {
-    dp.ctr = place_counters(dp.host, c->sched.kind != ETC_SCHED_DYNAMIC);
+    dp.ctr = place_counters(dp.host, c->sched.kind == ETC_SCHED_DYNAMIC);
+    if (dp.ctr.init.size() >= (1u << kEvNthShift)) return fail(c, ETC_EINVAL, "more than 2^24 event counters in one plan");
     HIP_TRY(c, dev_upload(&dp.d_queue_tasks, dp.ctr.queue_tasks, c->plan_owned));
     HIP_TRY(c, dev_upload(&dp.d_tasks, dp.ctr.tasks, c->plan_owned));
     std::vector<Task>().swap(dp.ctr.queue_tasks);
     std::vector<Task>().swap(dp.ctr.tasks);
     HIP_TRY(c, dev_upload(&dp.d_queue_begin, dp.host.queue_begin, c->plan_owned));
     HIP_TRY(c, dev_upload(&dp.d_ev_init, dp.ctr.init, c->plan_owned));
-    HIP_TRY(c, dev_upload(&dp.d_ev_consumers, dp.host.ev_consumers, c->plan_owned));
+    HIP_TRY(c, dev_upload(&dp.d_ev_consumers, dp.ctr.consumers, c->plan_owned));
+    HIP_TRY(c, dev_upload(&dp.d_disp_init, dp.ctr.disp_init, c->plan_owned));
     HIP_TRY(c, dev_upload(&dp.d_consumer_ids, dp.host.consumer_ids, c->plan_owned));
     HIP_TRY(c, dev_upload(&dp.d_seed, dp.host.seed_tasks, c->plan_owned));
     // what the data-dependent MoE events need to know of the static grids (dynamic scheduler, Sec. 2.4)
@@ -167,8 +169,8 @@ etc_status upload_plan(etc_ctx *c, DevPlan &dp)
     dp.moe_rmax = dp.moe_groups_gu = dp.moe_groups_down = 0;
     for (const Task &t : dp.host.tasks) {
         if (t.fn == FN_MOE_DOWN && t.c0 == 0) {
-            dp.moe_layer_events[2 * t.layer] = t.wait0;
-            dp.moe_layer_events[2 * t.layer + 1] = t.notify0;
+            dp.moe_layer_events[2 * t.layer] = dp.ctr.wait[t.wait0];
+            dp.moe_layer_events[2 * t.layer + 1] = dp.ctr.wait[t.notify0];
             if (t.layer == 0) dp.moe_groups_down++;
         }
         if (t.fn == FN_MOE_GATEUP && t.layer == 0) {
@@ -198,7 +200,7 @@ etc_status common_device_setup(etc_ctx *c, const etc_sched_desc *s)
     HIP_TRY(c, hipHostMalloc((void **)&c->h_error, 4 * sizeof(int32_t), hipHostMallocMapped));
     memset(c->h_error, 0, 4 * sizeof(int32_t));
     HIP_TRY(c, hipHostGetDevicePointer((void **)&c->base.error_host, c->h_error, 0));
-    HIP_TRY(c, dev_alloc(&c->d_qctrl, 16, c->owned));
+    HIP_TRY(c, dev_alloc(&c->d_qctrl, 2 * kQWords, c->owned));
     return ETC_OK;
 }
 
@@ -238,12 +240,13 @@ etc_status arm_on_stream(etc_ctx *c, hipStream_t s)
         a.ev_init = dp.d_ev_init;
         a.n_events = (int)dp.ctr.init.size();
         a.ev_shift = c->base.ev_shift;
+        a.disp_init = dp.d_disp_init;
         a.disp_cur = c->d_disp + (c->parity ? N : 0);
         a.pending = c->d_pending;
         a.n_pending = (int)c->n_tasks_max;
         a.exp_event = c->base.exp_event;
         a.n_exp = c->base.exp_event ? c->base.E : 0;
-        a.qctrl = c->d_qctrl + (c->parity ? 8 : 0);
+        a.qctrl = c->d_qctrl + (c->parity ? kQWords : 0);
     }
     if (c->base.exec_count) {
         a.exec_count = c->base.exec_count;
@@ -271,13 +274,14 @@ void fill_launch_params(etc_ctx *c, Params &P)
     P.consumer_ids = dp.d_consumer_ids;
     P.ev_disp_cur = c->d_disp + (c->parity ? N : 0);
     P.ev_disp_next = c->d_disp + (c->parity ? 0 : N);
+    P.ev_disp_init = dp.d_disp_init;
     P.task_pending = c->d_pending;
     P.moe_dd = (c->sched.kind == ETC_SCHED_DYNAMIC && dp.moe_rmax > 0) ? 1 : 0;
     P.moe_layer_events = dp.d_moe_layer_events;
     P.moe_rmax = dp.moe_rmax;
     P.moe_groups_gu = dp.moe_groups_gu;
     P.moe_groups_down = dp.moe_groups_down;
-    P.dd_event_base = dp.host.dd_event_base;
+    P.dd_event_base = dp.host.dd_n_events > 0 ? dp.ctr.wait[dp.host.dd_event_base] : 0;
     P.dd_n_events = dp.host.dd_n_events;
     P.dd_consumer_first = dp.host.dd_consumer_first;
     P.dd_consumer_n = dp.host.dd_consumer_n;
@@ -285,8 +289,8 @@ void fill_launch_params(etc_ctx *c, Params &P)
     P.seed_tasks = dp.d_seed;
     P.n_seed = (int)dp.host.seed_tasks.size();
     P.n_static_tasks = (int)dp.host.tasks.size();
-    P.q_ctrl_cur = c->d_qctrl + (c->parity ? 8 : 0);
-    P.q_ctrl_next = c->d_qctrl + (c->parity ? 0 : 8);
+    P.q_ctrl_cur = c->d_qctrl + (c->parity ? kQWords : 0);
+    P.q_ctrl_next = c->d_qctrl + (c->parity ? 0 : kQWords);
     P.epoch = c->epoch;
     P.spin_budget = c->sched.spin_budget;
     P.debug_flags = c->sched.debug_flags;

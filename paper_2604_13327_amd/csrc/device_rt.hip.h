@@ -219,7 +219,7 @@ __device__ __forceinline__ void wg_release()
 // E[ev].notify(): returns the value of the counter before the decrement.
 __device__ __forceinline__ int ev_notify(const Params &P, int ev)
 {
-    return __hip_atomic_fetch_sub(as_global(ev_counter(P, ev)), 1, __ATOMIC_RELAXED, ETC_SCOPE);
+    return __hip_atomic_fetch_sub(as_global(ev_counter(P, notify_counter(ev))), 1, __ATOMIC_RELAXED, ETC_SCOPE);
 }
 
 // Per-task trace mark (debug): thread 0 stamps the device wall clock.
@@ -227,6 +227,16 @@ __device__ __forceinline__ void trace_mark(const Params &P, int task_id, int slo
 {
     if (P.trace != nullptr && threadIdx.x == 0 && task_id >= 0)
         as_global(P.trace)[(size_t)task_id * 8 + slot] = slot == 7 ? (uint64_t)blockIdx.x : (uint64_t)wall_clock64();
+}
+
+// Takes the notifies of the last producers [done, all) of an event, which will never run, off its counters (its `w`-th producer
+// decrements counter w modulo their number), by one wavefront.
+__device__ __forceinline__ void ev_drop_producers(const Params &P, int wait, int done, int all)
+{
+    const int n = (wait & kEvSpread) ? kEvSpreadN : 1, l = lane_id();
+    if (l >= n || all <= done) return;
+    const int left = (all - l + n - 1) / n - (done - l + n - 1) / n;
+    if (left > 0) __hip_atomic_fetch_sub(as_global(ev_counter(P, (wait & kEvIndex) + l)), left, __ATOMIC_RELAXED, ETC_SCOPE);
 }
 
 // ---- ready queue of the dynamic scheduler: what the kernel's loop and a triggering task share ----
@@ -239,7 +249,7 @@ __device__ __forceinline__ uint64_t q_slot_word(const Params &P, int task_id)
 __device__ __forceinline__ int q_reserve_wave(const Params &P, int cnt)
 {
     int base = 0;
-    if (lane_id() == 0) base = __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + 1), cnt, __ATOMIC_RELAXED, ETC_SCOPE);
+    if (lane_id() == 0) base = __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + kQTail), cnt, __ATOMIC_RELAXED, ETC_SCOPE);
     base = __builtin_amdgcn_readfirstlane(base);
     if (base + cnt > P.q_capacity) {
         if (lane_id() == 0) raise_error(P, ERR_QUEUE_OVERFLOW, 0, base);

@@ -71,9 +71,16 @@ enum Fn : uint8_t {
     FN_COUNT
 };
 
-// An event index of a device task record names counters: `index` alone, or, with kEvSpread set, the kEvSpreadN counters from
-// `index` on, among which the event's producers are divided; the event has fired when all of them are zero.
-constexpr int kEvSpread = 1 << 30, kEvIndex = kEvSpread - 1, kEvSpreadN = 16;
+// The event indices of a device task record name counters.  A wait: `index` alone, or, with kEvSpread set, the kEvSpreadN counters
+// from `index` on, among which the event's producers are divided; the event has fired when all of them are zero.  A notify: the
+// event's first counter, and above kEvNthShift which one from there the producer decrements.
+constexpr int kEvSpread = 1 << 30, kEvIndex = kEvSpread - 1, kEvSpreadN = 16, kEvNthShift = 24;
+constexpr int notify_event(int notify) { return notify & ((1 << kEvNthShift) - 1); }
+constexpr int notify_counter(int notify) { return notify_event(notify) + (notify >> kEvNthShift); }
+
+// Control words of the ready queue (int32 each, in lines of their own: every workgroup takes a ticket and counts a task done
+// around every task, and one line takes an atomic every 16 ns).
+constexpr int kQHead = 0, kQTail = 32, kQDone = 64, kQWords = 96;
 
 // Task flags
 enum : uint16_t {
@@ -193,19 +200,20 @@ struct Params {
     const int32_t *ev_consumers;       // [n_events + 1] CSR: tasks that wait on the event
     const int32_t *consumer_ids;       // task id | (number of events the task waits on << 24 when that is > 1)
     int32_t *ev_disp_cur;              // per event: producers not yet dispatched (early push, App. E)
-    int32_t *ev_disp_next;             //   re-armed from ev_init like the event tensors
+    int32_t *ev_disp_next;             //   re-armed like the event counters, from:
+    const int32_t *ev_disp_init;       //   all producers of the event at its first counter, 0 at the others
     int32_t *task_pending;             // per task: waited events whose producers are all dispatched (counts up)
     // MoE under the dynamic scheduler: data-dependent event update and task triggering (Sec. 2.4)
     int32_t moe_dd;                    // 1: expert events armed at run time trigger the GroupGEMM-1 tiles
     int32_t *exp_event;                // [E] expert event tensor E_exp of the layer in flight
-    const int32_t *moe_layer_events;   // [n_layers][2] flat ids: event of row-tile slot 0 (GroupGEMM-1 -> 2), combine event
+    const int32_t *moe_layer_events;   // [n_layers][2] waits (counters): event of row-tile slot 0 (GroupGEMM-1 -> 2), combine event
     int32_t moe_rmax, moe_groups_gu, moe_groups_down;   // row-tile slots of the static grids, tasks per slot
     const int32_t *seed_tasks;         // tasks with no trigger edge, pushed at start
     int32_t n_seed;
     int32_t n_static_tasks;
     uint64_t *q_slots;                 // (epoch << 32 | task id + 1)
     int32_t q_capacity;
-    int32_t *q_ctrl_cur;               // [head, tail, -, tasks completed, ...]
+    int32_t *q_ctrl_cur;               // head, tail and tasks completed at kQHead, kQTail, kQDone
     int32_t *q_ctrl_next;
     uint32_t epoch;
     // debug / safety

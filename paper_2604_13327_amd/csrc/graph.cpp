@@ -192,33 +192,40 @@ std::string instantiate(const GraphDecl &g, const int *sym, int n_queues, bool u
     return "";
 }
 
-Counters place_counters(const Plan &p, bool spread)
+Counters place_counters(const Plan &p, bool dynamic)
 {
     Counters c;
     const int n = (int)p.ev_init.size();
     std::vector<uint8_t> wide((size_t)n, 0);
-    if (spread) {
-        for (int e = 0; e < n; ++e) wide[e] = p.ev_init[e] >= kSpreadMinProducers;
-        for (const Task &t : p.tasks)
-            if ((t.flags & TF_WAIT0_PER_WAVE) && t.wait0 >= 0)
-                for (int w = 0; w < kWaves && t.wait0 + w < n; ++w) wide[t.wait0 + w] = 0;
+    for (int e = 0; e < n; ++e) wide[e] = p.ev_init[e] >= kSpreadMinProducers;
+    for (const Task &t : p.tasks) {
+        if (t.wait0 < 0) continue;
+        if (t.flags & TF_WAIT0_PER_WAVE)
+            for (int w = 0; w < kWaves && t.wait0 + w < n; ++w) wide[t.wait0 + w] = 0;
+        if (dynamic && t.fn == FN_MOE_DOWN) wide[t.wait0] = 0;
     }
+    for (int e = 0; e < p.dd_n_events; ++e) wide[p.dd_event_base + e] = 0;
     std::vector<int32_t> first((size_t)n, 0), seen((size_t)n, 0), notify(p.tasks.size(), -1);
     for (int e = 0; e < n; ++e) {
         first[e] = (int32_t)c.init.size();
-        c.init.insert(c.init.end(), wide[e] ? kEvSpreadN : 1, 0);
-        c.event.insert(c.event.end(), wide[e] ? kEvSpreadN : 1, e);
-        if (!wide[e]) c.init.back() = p.ev_init[e];      // also of notifies that are counted at run time only
+        const int k = wide[e] ? kEvSpreadN : 1;
+        for (int i = 0; i < k; ++i) {       // producer j decrements counter j % k
+            c.init.push_back((p.ev_init[e] + k - 1 - i) / k);
+            c.event.push_back(e);
+            c.disp_init.push_back(i == 0 ? p.ev_init[e] : 0);
+            c.consumers.push_back(p.ev_consumers[i == 0 ? e : e + 1]);
+        }
+        c.wait.push_back(first[e] | (wide[e] ? kEvSpread : 0));
     }
+    c.consumers.push_back(p.ev_consumers.back());
     for (const Task &t : p.tasks)
         if (t.notify0 >= 0) {
             const int e = t.notify0;
-            notify[t.id] = first[e] + (wide[e] ? seen[e]++ % kEvSpreadN : 0);
-            if (wide[e]) c.init[notify[t.id]]++;
+            notify[t.id] = first[e] | (wide[e] ? (seen[e]++ % kEvSpreadN) << kEvNthShift : 0);
         }
     auto place = [&](Task t) {
-        if (t.wait0 >= 0) t.wait0 = first[t.wait0] | (wide[t.wait0] ? kEvSpread : 0);
-        if (t.wait1 >= 0) t.wait1 = first[t.wait1] | (wide[t.wait1] ? kEvSpread : 0);
+        if (t.wait0 >= 0) t.wait0 = c.wait[t.wait0];
+        if (t.wait1 >= 0) t.wait1 = c.wait[t.wait1];
         t.notify0 = notify[t.id];
         return t;
     };

@@ -86,15 +86,18 @@ struct Plan {
 // kSpreadMinProducers or more counts in kEvSpreadN places (they follow one another; kEvSpread marks its index in the task
 // records).  Whole 8B iteration 3250 -> 2980 us, 8B batch 5 / 16 / 64 561 / 822 / 1207 -> 479 / 722 / 1108 per four layers, MoE
 // decoder batch 1 374 -> 324; fewest producers 32 instead of 16: the two-layer decoder of hidden 256 takes 71 us instead of 67.
-// Not spread: events a task waits for eight at a time (its wavefront's lanes poll those), and everything under the dynamic
-// scheduler, whose workgroups find an event by its index and learn from one decrement that they were the last.
+// Not spread: events a task waits for eight at a time (its wavefront's lanes poll those), events whose count is known at run time
+// only, and under the dynamic scheduler those of row-tile slots, which the routing may cancel one by one.
 struct Counters {
     std::vector<int32_t> init;         // initial count of every counter
     std::vector<int32_t> event;        // counter -> event
+    std::vector<int32_t> wait;         // event -> what a wait for it names: its first counter, kEvSpread
     std::vector<Task> tasks, queue_tasks;   // the plan's records with counters in place of events
+    // dynamic scheduler, by first counter: producers not dispatched, consumers (CSR)
+    std::vector<int32_t> disp_init, consumers;
 };
 constexpr int kSpreadMinProducers = 16;
-Counters place_counters(const Plan &p, bool spread);
+Counters place_counters(const Plan &p, bool dynamic);
 
 // Binds the symbols and materialises the plan.  unfused: ignore the declared edges and put one
 // coarse event between consecutive stages (Sec. 4.5 baseline).  Returns "" or an error text.

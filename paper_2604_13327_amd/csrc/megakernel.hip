@@ -590,7 +590,7 @@ __device__ __forceinline__ void q_push_consumers_wave(const Params &P, int ev)
 // queue is exhausted or an error was raised.
 __device__ __forceinline__ int q_take_ticket(const Params &P)
 {
-    return __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + 0), 1, __ATOMIC_RELAXED, ETC_SCOPE);
+    return __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + kQHead), 1, __ATOMIC_RELAXED, ETC_SCOPE);
 }
 
 __device__ __forceinline__ int q_wait_slot(const Params &P, int ticket)
@@ -600,7 +600,7 @@ __device__ __forceinline__ int q_wait_slot(const Params &P, int ticket)
     for (;;) {
         const uint64_t v = ld_u64(P.q_slots + ticket);
         if ((uint32_t)(v >> 32) == P.epoch) return (int)(uint32_t)v - 1;
-        if (ev_peek(P.q_ctrl_cur + 3) >= P.n_static_tasks) return -1;
+        if (ev_peek(P.q_ctrl_cur + kQDone) >= P.n_static_tasks) return -1;
         if (spins < 32) __builtin_amdgcn_s_sleep(2); else __builtin_amdgcn_s_sleep(32);
         ++spins;
         if ((spins & 63) == 0 && ev_peek(P.error_word) != 0) return -1;
@@ -624,14 +624,14 @@ __global__ void __launch_bounds__(kWgThreads) megakernel_dynamic(const Params P)
     stage_params(P, &sP);
     rearm_next(P);
     for (int i = blockIdx.x * kWgThreads + threadIdx.x; i < P.n_events; i += gridDim.x * kWgThreads)
-        as_global(P.ev_disp_next)[(size_t)i << P.ev_shift] = as_global(P.ev_init)[i];
+        as_global(P.ev_disp_next)[(size_t)i << P.ev_shift] = as_global(P.ev_disp_init)[i];
     if (blockIdx.x == 0 && threadIdx.x == 0) {            // reset the control words of the next launch
-        for (int i = 0; i < 8; ++i) P.q_ctrl_next[i] = 0;
+        for (int i = 0; i < kQWords; i += 32) P.q_ctrl_next[i] = 0;
     }
     if (kind_base(KIND) == KIND_GENERIC && P.dd_consumer_n > 0 && blockIdx.x == 0 && threadIdx.x == 0) {
         // tasks of the triggered grid beyond the last indptr range are never released: count them completed
         const int surplus = P.dd_consumer_n - gld_i32(reinterpret_cast<const int32_t *>(P.gbuf[4]) + P.dd_n_events);
-        if (surplus > 0) __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + 3), surplus, __ATOMIC_RELAXED, ETC_SCOPE);
+        if (surplus > 0) __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + kQDone), surplus, __ATOMIC_RELAXED, ETC_SCOPE);
     }
     // Wavefront 0 is the scheduler of its workgroup: its lane 0 notifies and pops, all its lanes push.
     const bool sched_wave = wave_id() == 0;
@@ -671,8 +671,8 @@ __global__ void __launch_bounds__(kWgThreads) megakernel_dynamic(const Params P)
             // This task is dispatched: the last producer of its event to get here pushes the consumers.
             int last = 0;
             if (lane_id() == 0 && t.notify0 >= 0 && !dd_producer)
-                last = __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + ((size_t)t.notify0 << P.ev_shift)), 1, __ATOMIC_RELAXED, ETC_SCOPE) == 1;
-            if (__builtin_amdgcn_readfirstlane(last)) q_push_consumers_wave(P, t.notify0);
+                last = __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + ((size_t)notify_event(t.notify0) << P.ev_shift)), 1, __ATOMIC_RELAXED, ETC_SCOPE) == 1;
+            if (__builtin_amdgcn_readfirstlane(last)) q_push_consumers_wave(P, notify_event(t.notify0));
         }
         WgState st;
         wg_state_init(st);
@@ -714,7 +714,7 @@ __global__ void __launch_bounds__(kWgThreads) megakernel_dynamic(const Params P)
                 // queue compares the count with the number of tasks of the step
                 if (P.debug_flags & 1u) atomicAdd(P.exec_count + t.id, 1);
                 if (t.notify0 >= 0 && !dd_notify) ev_notify(P, t.notify0);
-                __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + 3), 1, __ATOMIC_RELAXED, ETC_SCOPE);
+                __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + kQDone), 1, __ATOMIC_RELAXED, ETC_SCOPE);
                 // The next ticket is taken only now.  Taken a task ahead (in the round trip of the dispatch
                 // decrement) it cost more than it saved: a workgroup that sits in a long wait, such as the
                 // projection behind the attention chunks, then holds a task that an idle workgroup could run
@@ -957,13 +957,13 @@ __global__ void arm_step_kernel(const ArmArgs a)
         for (int i = gid; i < a.n_events; i += stride) {
             const int32_t v = a.ev_init[i];
             a.ev_cur[(size_t)i << a.ev_shift] = v;
-            if (a.disp_cur != nullptr) a.disp_cur[(size_t)i << a.ev_shift] = v;
+            if (a.disp_cur != nullptr) a.disp_cur[(size_t)i << a.ev_shift] = a.disp_init[i];
         }
     if (a.pending != nullptr)
         for (int i = gid; i < a.n_pending; i += stride) a.pending[i] = 0;
     if (a.exp_event != nullptr)
         for (int i = gid; i < a.n_exp; i += stride) a.exp_event[i] = 0;
-    if (a.qctrl != nullptr && gid < 8) a.qctrl[gid] = 0;
+    if (a.qctrl != nullptr && gid < kQWords) a.qctrl[gid] = 0;
     if (a.exec_count != nullptr)
         for (int i = gid; i < a.n_exec; i += stride) a.exec_count[i] = 0;
 }

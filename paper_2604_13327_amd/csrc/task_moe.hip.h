@@ -129,10 +129,10 @@ __device__ __forceinline__ void moe_update_and_trigger(const Params &P, int laye
         const int live = expp[E], dead = P.moe_rmax - live;
         const int ev_slot0 = gld_i32(P.moe_layer_events + 2 * layer), ev_y = gld_i32(P.moe_layer_events + 2 * layer + 1);
         for (int r = live + lane; r < P.moe_rmax; r += 64) st_i32(ev_counter(P, ev_slot0 + r), 0);
+        ev_drop_producers(P, ev_y, live * Gd, P.moe_rmax * Gd);
         if (lane == 0 && dead > 0) {
-            __hip_atomic_fetch_sub(as_global(ev_counter(P, ev_y)), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
-            __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + ((size_t)ev_y << P.ev_shift)), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
-            __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + 3), dead * (G + Gd), __ATOMIC_RELAXED, ETC_SCOPE);
+            __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + ((size_t)(ev_y & kEvIndex) << P.ev_shift)), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
+            __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + kQDone), dead * (G + Gd), __ATOMIC_RELAXED, ETC_SCOPE);
         }
         drain_vmem();        // the counts are in place before this tile's notifies can release anything
     }
@@ -199,7 +199,7 @@ __device__ __noinline__ void moe_route_and_group(const Params &P, int layer, int
 {
     layer = __builtin_amdgcn_readfirstlane(layer);
     t = __builtin_amdgcn_readfirstlane(t);
-    group_ev = __builtin_amdgcn_readfirstlane(group_ev);
+    group_ev = notify_event(__builtin_amdgcn_readfirstlane(group_ev));
     const int wave = wave_id(), lane = lane_id();
     const int E = P.E, K = P.topk, B = P.B, N = B * K, M = P.tile_m;
     ETC_AS_LDS int32_t *ids_s = reinterpret_cast<ETC_AS_LDS int32_t *>(as_lds(sm));   // [B*K] expert of every pair
@@ -540,10 +540,10 @@ __device__ __noinline__ void moel_scan(const Params &P, float *sm)
         const int live = expp[E], dead = P.moe_rmax - live;
         const int ev_slot0 = gld_i32(P.moe_layer_events), ev_y = gld_i32(P.moe_layer_events + 1);
         for (int r = live + lane; r < P.moe_rmax; r += 64) st_i32(ev_counter(P, ev_slot0 + r), 0);
+        ev_drop_producers(P, ev_y, live * Gd, P.moe_rmax * Gd);
         if (lane == 0 && dead > 0) {
-            __hip_atomic_fetch_sub(as_global(ev_counter(P, ev_y)), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
-            __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + ((size_t)ev_y << P.ev_shift)), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
-            __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + 3), dead * (G + Gd), __ATOMIC_RELAXED, ETC_SCOPE);
+            __hip_atomic_fetch_sub(as_global(P.ev_disp_cur + ((size_t)(ev_y & kEvIndex) << P.ev_shift)), dead * Gd, __ATOMIC_RELAXED, ETC_SCOPE);
+            __hip_atomic_fetch_add(as_global(P.q_ctrl_cur + kQDone), dead * (G + Gd), __ATOMIC_RELAXED, ETC_SCOPE);
         }
     }
     __syncthreads();
@@ -596,7 +596,7 @@ __device__ __forceinline__ void moel_update_and_trigger(const Params &P, int blk
 __device__ __noinline__ void moel_place(const Params &P, int blk, int group_ev, float *sm)
 {
     blk = __builtin_amdgcn_readfirstlane(blk);
-    group_ev = __builtin_amdgcn_readfirstlane(group_ev);
+    group_ev = notify_event(__builtin_amdgcn_readfirstlane(group_ev));
     const int E = P.E, K = P.topk;
     const int n_tok = P.B - blk * kMoelBlock < kMoelBlock ? P.B - blk * kMoelBlock : kMoelBlock;
     ETC_AS_LDS int32_t *ids_s = reinterpret_cast<ETC_AS_LDS int32_t *>(as_lds(sm));    // [64 * K]
