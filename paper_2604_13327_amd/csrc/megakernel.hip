@@ -72,20 +72,13 @@ __device__ __forceinline__ void rowsum_final_perm(const Params &P, int t)
 // operand (x * g1, split) and the partial sums of squares per 16 elements, as every later producer does.
 // Also what every layer's QKV epilogue needs of the step's shape, resolved once: the (cos, sin) of the RoPE
 // angles at the sequence's position and the KV slot the new row goes to (page table look-up).
+// One workgroup, nothing else of the step runs: bound by the round trips of its loads, so all of them are requested in front of
+// the first store (a load behind a store that might alias it waits), 16 bytes of two places of the row at a time.
 template <bool LM>
 __device__ __forceinline__ void load_hidden(const Params &P, int b)
 {
-    const int pos = gld_i32(P.kv_len + b);
-    for (int i = threadIdx.x; i < P.d / 2; i += kWgThreads) {
-        float cs, sn;
-        rope_cos_sin(P, pos, i, &cs, &sn);
-        st_f32(P.rope_cs + ((size_t)b * (P.d / 2) + i) * 2, cs);
-        st_f32(P.rope_cs + ((size_t)b * (P.d / 2) + i) * 2 + 1, sn);
-    }
-    if (threadIdx.x == 0) {
-        const int page = gld_i32(P.page_ids + gld_i32(P.page_indptr + b) + pos / P.page);
-        st_i32(P.kv_slot + b, page * P.page + pos % P.page);
-    }
+    constexpr int U = 2;
+    const int n_oct = P.H / 8, tid = (int)threadIdx.x;      // a multiple of 32
     // The step starts from the sequence's hidden state, or from the embedding row of its token (the token the
     // previous iteration sampled).  An id outside the table raises an error and reads row 0.
     const uint16_t *src = P.hidden_in + (size_t)b * P.H;
@@ -97,22 +90,70 @@ __device__ __forceinline__ void load_hidden(const Params &P, int b)
         }
         src = P.embed + (size_t)tok * P.H;
     }
-    if (LM && threadIdx.x == 0 && P.best)       // below the key of every logit
-        __hip_atomic_store(as_global(P.best + b), 0ull, __ATOMIC_RELAXED, ETC_SCOPE);
     const uint16_t *g1 = (const uint16_t *)as_global(P.weights)[0].g1;
-    for (int part = threadIdx.x; part < P.H / 16; part += kWgThreads) {
-        float s = 0.f;
-        for (int i = 0; i < 16; ++i) {
-            const size_t o = (size_t)b * P.H + part * 16 + i;
-            const float v = bf16_bits_to_f32(gld_u16(src + part * 16 + i));
-            st_f32(P.x + o, v);
-            uint16_t hi, lo;
-            split_bf16(v * bf16_bits_to_f32(gld_u16(g1 + part * 16 + i)), hi, lo);
-            st_u16(P.xg_hi + o, hi);
-            st_u16(P.xg_lo + o, lo);
-            s += v * v;
+    const bool aligned = ((uintptr_t)src & 15) == 0;        // a caller's hidden state may start anywhere
+    u32x4 xv[U], gv[U];
+    auto request = [&](int o0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int o = o0 + u * kWgThreads < n_oct ? o0 + u * kWgThreads : 0;
+            if (aligned) {
+                xv[u] = gld_16B(src + (size_t)o * 8);
+            } else {
+                uint32_t w[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    w[q] = (uint32_t)gld_u16(src + (size_t)o * 8 + 2 * q) | ((uint32_t)gld_u16(src + (size_t)o * 8 + 2 * q + 1) << 16);
+                xv[u] = u32x4{w[0], w[1], w[2], w[3]};
+            }
+            gv[u] = gld_16B(g1 + (size_t)o * 8);
         }
-        st_f32(P.ssq_x + (size_t)part * kMaxBatch + b, s);
+    };
+    request(tid);
+    const int pos = gld_i32(P.kv_len + b);
+    const int page = gld_i32(P.page_ids + gld_i32(P.page_indptr + b) + (pos >> P.page_shift));
+    float cs = 0.f, sn = 0.f;
+    const int half = P.d / 2;                               // 32 or 64
+    rope_cos_sin(P, pos, tid < half ? tid : 0, &cs, &sn);
+    if (tid < half) {
+        float *dst = P.rope_cs + ((size_t)b * half + tid) * 2;
+        st_u64(dst, (uint64_t)__float_as_uint(cs) | ((uint64_t)__float_as_uint(sn) << 32));
+    }
+    if (tid == 0) {
+        st_i32(P.kv_slot + b, page * P.page + (pos & (P.page - 1)));
+        if (LM && P.best)                                   // below the key of every logit
+            __hip_atomic_store(as_global(P.best + b), 0ull, __ATOMIC_RELAXED, ETC_SCOPE);
+    }
+    const __amdgpu_buffer_rsrc_t x_b = buf_of(P.x + (size_t)b * P.H), hi_b = buf_of(P.xg_hi + (size_t)b * P.H), lo_b = buf_of(P.xg_lo + (size_t)b * P.H);
+    for (int o0 = tid; o0 - tid < n_oct; o0 += U * kWgThreads) {
+        if (o0 != tid) request(o0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int o = o0 + u * kWgThreads;
+            const uint32_t xw[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w}, gw[4] = {gv[u].x, gv[u].y, gv[u].z, gv[u].w};
+            uint32_t vw[8], hw[4], lw[4];
+            float s = 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float v0 = bf16_bits_to_f32(xw[q] & 0xFFFFu), v1 = bf16_bits_to_f32(xw[q] >> 16);
+                uint16_t h0, l0, h1, l1;
+                split_bf16(v0 * bf16_bits_to_f32(gw[q] & 0xFFFFu), h0, l0);
+                split_bf16(v1 * bf16_bits_to_f32(gw[q] >> 16), h1, l1);
+                vw[2 * q] = __float_as_uint(v0);
+                vw[2 * q + 1] = __float_as_uint(v1);
+                hw[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+                lw[q] = (uint32_t)l0 | ((uint32_t)l1 << 16);
+                s += v0 * v0 + v1 * v1;
+            }
+            s += dpp_f32<0xB1>(s);                          // two neighbouring lanes hold 16 elements
+            if (o < n_oct) {
+                buf_st_16B(x_b, (uint32_t)o * 32u, u32x4{vw[0], vw[1], vw[2], vw[3]});
+                buf_st_16B(x_b, (uint32_t)o * 32u + 16u, u32x4{vw[4], vw[5], vw[6], vw[7]});
+                buf_st_16B(hi_b, (uint32_t)o * 16u, u32x4{hw[0], hw[1], hw[2], hw[3]});
+                buf_st_16B(lo_b, (uint32_t)o * 16u, u32x4{lw[0], lw[1], lw[2], lw[3]});
+                if ((o & 1) == 0) st_f32(P.ssq_x + (size_t)(o >> 1) * kMaxBatch + b, s);
+            }
+        }
     }
 }
 
