@@ -459,20 +459,14 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
         if (ch * chunk < n_keys) {     // inactive slots of the sampled-shape queue neither wait nor compute; they still notify
             st.staged_key = -1;      // the attention scratch overlaps the staged operand (the task waits inside)
             const int grp = P.nq / P.nkv;
-            const bool lds_pages = chunk > 128;      // more than one batch of keys per chunk
-            const bool mfma_fits = (chunk >> P.page_shift) <= 8192;      // page ids of a chunk next to the wavefronts' V tiles in LDS
             bool ran = false;
+            int anchor = 0;
 #define ETC_ATTN(DD, GG)                                                                   \
     if (!ran && P.d == DD && grp == GG) {                                                  \
         ran = true;                                                                        \
-        if constexpr (DD == 128 && GG == 8) {                                              \
-            if (lds_pages && mfma_fits) attn_chunk_mfma<GG>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);   \
-            else if (lds_pages) attn_chunk<DD, GG, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);       \
-            else attn_chunk<DD, GG, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);     \
-        } else {                                                                           \
-            if (lds_pages) attn_chunk<DD, GG, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);  \
-            else attn_chunk<DD, GG, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);     \
-        }                                                                                  \
+        if (chunk <= 16 * kWaves) attn_chunk<DD, GG, 1, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, nullptr);       \
+        else if constexpr (STAGED_ONLY) attn_chunk<DD, GG, 1, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, nullptr); \
+        else attn_chunk<DD, GG, 2, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, &anchor);                            \
     }
             ETC_ATTN_SHAPES(ETC_ATTN)
 #undef ETC_ATTN

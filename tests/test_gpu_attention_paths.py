@@ -1,0 +1,74 @@
+"""Attention chunks at the edges of their steps: 16 keys a wavefront step (128 a chunk at most: one step; longer chunks of staged-only
+plans: several) and 32 (the other plans), chunks of the step's own token alone, more pages than the window of page ids in LDS holds,
+every (head dim, heads per KV head) there is a body for.  The place of the step's own token in the cache holds NaN beforehand: its
+row must come from the projection, not from the cache."""
+import numpy as np
+import pytest
+
+import synth
+from harness import GpuModel, bf16_to_f32_np, fixed_step, oracle_step, rel_err
+
+pytestmark = pytest.mark.gpu
+SPIN = 400000
+# Hidden states of a layer are fp32: what is rounded on the way are operands to 16 mantissa bits (2^-17 of a value, both
+# projections and attention) under sums of up to 512 terms; 1.2e-4 of RMS was measured after 32 layers of the 8B shape.
+TOL_LAYER, TOL_BF16 = 2e-3, 2e-2
+
+
+def _check(shape, lens, kv_chunk, max_len, kind=0):
+    import torch
+    import paper_2604_13327_amd as etc
+    n_pool = int(sum(synth.pages_needed(int(n), shape.page) for n in lens)) + 8
+    model = GpuModel(shape, seed=31, n_pool_pages=n_pool)
+    step = fixed_step(shape, len(lens), lens, n_pool, seed=5)
+    for b, n in enumerate(lens):
+        page = int(step.page_ids[step.page_indptr[b] + n // shape.page])
+        model.kpool[:, page, n % shape.page] = float("nan")
+        model.vpool[:, page, n % shape.page] = float("nan")
+    dec = etc.Decoder(shape, kv_chunk_tokens=kv_chunk, sampled_batches=[len(lens)], max_kv_len=max_len, kind=kind,
+                      debug_flags=etc.DEBUG_EXEC_COUNT | etc.DEBUG_LAYER_HIDDEN, spin_budget=SPIN)
+    model.bind(dec)
+    x = model.hidden(0, len(lens))
+    out = torch.empty_like(x)
+    dec.bind_step(step)
+    dec.launch(x, out)
+    torch.cuda.synchronize()
+    assert (dec.error_word() == 0).all() and (dec.event_counters() == 0).all() and (dec.exec_counts() == 1).all()
+    ref = oracle_step(shape, model.seed, n_pool, step, 0)
+    for l in range(shape.n_layers):
+        got, want = dec.layer_hidden(l), ref["layers"][l]
+        for b, n in enumerate(lens):
+            assert rel_err(got[b], want[b]) <= TOL_LAYER, f"layer {l}, sequence {b} (kv_len {n})"
+    assert rel_err(bf16_to_f32_np(out), ref["final"]) <= TOL_BF16
+    for b, n in enumerate(lens):                       # the appended rows replaced the NaN
+        page = int(step.page_ids[step.page_indptr[b] + n // shape.page])
+        assert torch.isfinite(model.kpool[:, page, n % shape.page].float()).all()
+        assert torch.isfinite(model.vpool[:, page, n % shape.page].float()).all()
+    dec.close()
+
+
+SHAPES = [(128, 1, False), (128, 4, False), (128, 8, True), (64, 2, True), (64, 4, False)]
+
+
+def _shape(d, grp, norm, page=16):
+    return synth.ModelShape(f"d{d}-g{grp}", 2, 256, 2 * grp, 2, d, 512, qk_norm=norm, page=page)
+
+
+@pytest.mark.parametrize("d,grp,norm", SHAPES)
+@pytest.mark.parametrize("lens,kv_chunk", [
+    ([0, 15, 16, 17, 127], 128),                                  # one step of 16 keys each
+    ([128, 129, 255, 300, 127], 128),                             # chunks of 128 keys, one of the new token alone
+    ([256, 257, 271, 512, 700], 512),                             # several steps of 16 keys
+    ([600, 767, 768, 831, 40], 768),                              # the same, six rounds
+    ([0, 1, 31, 32, 33, 128, 129, 255, 256, 257, 287, 288, 289, 511, 512, 513, 700], 512),      # steps of 32 keys
+])
+def test_steps_and_chunks(d, grp, norm, lens, kv_chunk):
+    _check(_shape(d, grp, norm), lens, kv_chunk, max(lens) + 1)
+
+
+@pytest.mark.parametrize("batch", [2, 17])
+@pytest.mark.parametrize("d,grp", [(128, 8), (64, 4)])
+def test_more_pages_than_the_window_holds(d, grp, batch):
+    """Pages of one token, chunks of 8192 keys: two windows of page ids, the second one key, 200 keys and 904 keys long."""
+    lens = ([4097, 5000] if batch == 2 else [4097, 4296, 5000, 4096, 4095] + [7] * (batch - 5))
+    _check(_shape(d, grp, False, page=1), lens, 8192, 8192)
