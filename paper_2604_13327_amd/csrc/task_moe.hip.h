@@ -34,48 +34,51 @@ __device__ __forceinline__ bool resolve_row_tile(const Params &P, int r, RowTile
     return rt.n > 0;
 }
 
-// ---- wavefront arg-max of the router's top-k -------------------------------------------------------------
-// Maximum over the 64 lanes, the same value in every lane: quad exchanges, half-row mirror and row mirror leave each row of 16
-// lanes with its maximum; the four row maxima are read as scalars.
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
+// ---- top-k of the router ---------------------------------------------------------------------------------
+// Maximum / minimum over 16 consecutive lanes, the same value in all of them.
+__device__ __forceinline__ uint32_t row_max_u32(uint32_t v)
 {
     v = max(v, (uint32_t)dpp_i32<0xB1>((int)v));
     v = max(v, (uint32_t)dpp_i32<0x4E>((int)v));
     v = max(v, (uint32_t)dpp_i32<0x141>((int)v));
-    v = max(v, (uint32_t)dpp_i32<0x140>((int)v));
-    const uint32_t a = max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
-    const uint32_t b = max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
-    return max(a, b);
+    return max(v, (uint32_t)dpp_i32<0x140>((int)v));
+}
+__device__ __forceinline__ int row_min_i32(int v)
+{
+    v = min(v, dpp_i32<0xB1>(v));
+    v = min(v, dpp_i32<0x4E>(v));
+    v = min(v, dpp_i32<0x141>(v));
+    return min(v, dpp_i32<0x140>(v));
 }
 
-// Top-k of TG tokens by one wavefront (token u's logits at row row0 + u * step, valid below n_rows): lane k < K gets the k-th
-// expert and its logit; larger logit first, equal logits: lower expert first.  The logits of all tokens arrive in one round
-// trip, and the tokens are independent chains through the K rounds of arg-max (alone each waits for its own cross-lane
-// moves: 3 us a token).  A round: the largest remaining ordered logit over lanes and registers, then the lowest expert that
-// holds it.  seen(u, e, v): called with every logit.
-template <int TG, class SEEN>
-__device__ __forceinline__ void wave_topk(const float *logits, int E, int K, int row0, int step, int n_rows, int (&id)[TG], float (&val)[TG],
+// Top-k of 4 TG tokens by one wavefront, a token per row of 16 lanes, which share its experts out (lane l: l, l + 16, ..: NJ at
+// most): token 4 u + row of the wavefront is row0 + u * step + row, valid below n_rows.  Lane k < K of the row gets the k-th expert
+// and its logit; larger logit first, equal logits: lower expert first.  A round: the largest remaining ordered logit over
+// registers and the row's lanes, then the lowest expert that holds it; four tokens to an instruction and no trip through scalar
+// registers (a token per wavefront, 45 instructions and six scalar reads a round: 17 us for the 64 tokens of a block, 128 experts,
+// now 6 with loads and stores).  seen(u, e, v): called with every logit.
+template <int NJ, int TG, class SEEN>
+__device__ __forceinline__ void rows_topk(const float *logits, int E, int K, int row0, int step, int n_rows, int (&id)[TG], float (&val)[TG],
                                           const SEEN &seen)
 {
-    constexpr int NJ = kMaxExperts / 64;
-    const int lane = lane_id();
+    const int l = lane_id() & 15, row = lane_id() >> 4;
     uint32_t key[TG][NJ];
     float v[TG][NJ];
 #pragma unroll
     for (int u = 0; u < TG; ++u)           // no branch around a load: it would wait for the one before
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const int b = row0 + u * step, e = lane + 64 * j;
-            v[u][j] = ld_f32(logits + (size_t)(b < n_rows ? b : n_rows - 1) * E + (e < E ? e : E - 1));
+            const int b = row0 + u * step + row, e = l + 16 * j;
+            v[u][j] = ld_f32(logits + (size_t)(b < n_rows ? b : n_rows - 1) * E + (e < E ? e : l));
         }
 #pragma unroll
     for (int u = 0; u < TG; ++u) {
-        const int b = row0 + u * step;
+        const int b = row0 + u * step + row;
         id[u] = 0;
         val[u] = -INFINITY;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const int e = lane + 64 * j;
+            const int e = l + 16 * j;
             const bool live = b < n_rows && e < E;
             if (live) seen(u, e, v[u][j]);
             const uint32_t bits = __float_as_uint(v[u][j]), ord = (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
@@ -88,22 +91,31 @@ __device__ __forceinline__ void wave_topk(const float *logits, int E, int K, int
             uint32_t mx = key[u][0];
 #pragma unroll
             for (int j = 1; j < NJ; ++j) mx = max(mx, key[u][j]);
-            mx = wave_max_u32(mx);
-            int e = -1;
+            mx = row_max_u32(mx);
+            int e = 0x7FFFFFFF;
 #pragma unroll
-            for (int j = NJ - 1; j >= 0; --j) {
-                const uint64_t who = __ballot(key[u][j] == mx);
-                if (who) e = 64 * j + __builtin_ctzll(who);
-            }
-            if (lane == k) {
+            for (int j = NJ - 1; j >= 0; --j) e = key[u][j] == mx ? l + 16 * j : e;
+            e = row_min_i32(e);
+            if (l == k) {
                 id[u] = e;
                 val[u] = __uint_as_float((mx & 0x80000000u) ? (mx & 0x7FFFFFFFu) : ~mx);
             }
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                if (lane + 64 * j == e) key[u][j] = 0u;
+            for (int j = 0; j < NJ; ++j) key[u][j] = l + 16 * j == e ? 0u : key[u][j];
         }
     }
+}
+// Softmax over the first K lanes of each row of 16 (K <= 16).
+__device__ __forceinline__ float row_softmax(float v, int K)
+{
+    const int l = lane_id() & 15;
+    float mx = l < K ? v : -INFINITY;
+    mx = fmaxf(mx, dpp_f32<0xB1>(mx));
+    mx = fmaxf(mx, dpp_f32<0x4E>(mx));
+    mx = fmaxf(mx, dpp_f32<0x141>(mx));
+    mx = fmaxf(mx, dpp_f32<0x140>(mx));
+    const float p = l < K ? __expf(v - mx) : 0.f;
+    return p / lanes_sum<16>(p);
 }
 
 // Data-dependent event update and task triggering (Sec. 2.4), dynamic scheduler only.  The expert event
@@ -212,48 +224,44 @@ __device__ __noinline__ void moe_route_and_group(const Params &P, int layer, int
     const size_t dbg_row = (size_t)layer * P.max_batch + t;
 
     for (int e = threadIdx.x; e < E; e += kWgThreads) cnt[e] = 0;
-    auto route = [&](auto tokens) {      // tokens in flight per wavefront
-        constexpr int TG = decltype(tokens)::value;
-        for (int b0 = wave; b0 < B; b0 += TG * kWaves) {
+    auto route = [&](auto per_lane, auto groups) {
+        constexpr int NJ = decltype(per_lane)::value, TG = decltype(groups)::value;
+        const int l = lane & 15;
+        for (int b0 = wave * 4; b0 < B; b0 += TG * 4 * kWaves) {
             int id[TG];
             float val[TG];
-            wave_topk<TG>(P.router_logits, E, forced ? 0 : K, b0, kWaves, B, id, val, [&](int u, int e, float v) {
-                if (dbg && b0 + u * kWaves == t) as_global(P.dbg_logits)[dbg_row * E + e] = v;
+            rows_topk<NJ, TG>(P.router_logits, E, forced ? 0 : K, b0, 4 * kWaves, B, id, val, [&](int u, int e, float v) {
+                if (dbg && b0 + u * 4 * kWaves + (lane >> 4) == t) as_global(P.dbg_logits)[dbg_row * E + e] = v;
             });
 #pragma unroll
             for (int u = 0; u < TG; ++u) {
-                const int b = b0 + u * kWaves;
-                if (b >= B) continue;
+                const int b = b0 + u * 4 * kWaves + (lane >> 4);
                 int my_id = id[u];
                 float my_v = val[u];
-                if (forced && lane < K) {
-                    my_id = gld_i32(P.forced_topk + ((size_t)layer * P.max_batch + b) * K + lane);
+                if (forced && b < B && l < K) {
+                    my_id = gld_i32(P.forced_topk + ((size_t)layer * P.max_batch + b) * K + l);
                     my_v = ld_f32(P.router_logits + (size_t)b * E + my_id);
                 }
-                if (lane < K) ids_s[b * K + lane] = my_id;
-                if (b == t) {
-                    float mx = lane < K ? my_v : -INFINITY;
-#pragma unroll
-                    for (int off = 8; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 16));      // K <= 16: one row of lanes
-                    const float p = lane < K ? __expf(my_v - mx) : 0.f;
-                    const float den = wave_sum(p);
-                    if (lane < K) {
-                        float wgt = p / den;
-                        if (forced_w) wgt = *as_global(P.forced_w + ((size_t)layer * P.max_batch + b) * K + lane);
-                        st_i32(P.topk_ids + (size_t)t * K + lane, my_id);
-                        st_f32(P.topk_w + (size_t)t * K + lane, wgt);
+                float wgt = row_softmax(my_v, K);
+                if (b < B && l < K) {
+                    ids_s[b * K + l] = my_id;
+                    if (b == t) {
+                        if (forced_w) wgt = *as_global(P.forced_w + ((size_t)layer * P.max_batch + b) * K + l);
+                        st_i32(P.topk_ids + (size_t)t * K + l, my_id);
+                        st_f32(P.topk_w + (size_t)t * K + l, wgt);
                         if (dbg) {
-                            as_global(P.dbg_topk_ids)[dbg_row * K + lane] = my_id;
-                            as_global(P.dbg_topk_w)[dbg_row * K + lane] = wgt;
+                            as_global(P.dbg_topk_ids)[dbg_row * K + l] = my_id;
+                            as_global(P.dbg_topk_w)[dbg_row * K + l] = wgt;
                         }
                     }
                 }
             }
         }
     };
-    // up to 8 tokens a wavefront has one at most, and dead chains would cost it 4 us
-    if (B <= kWaves) route(std::integral_constant<int, 1>());
-    else route(std::integral_constant<int, 4>());
+    if (E <= 128) {
+        if (B <= 4 * kWaves) route(std::integral_constant<int, 8>(), std::integral_constant<int, 1>());
+        else route(std::integral_constant<int, 8>(), std::integral_constant<int, 2>());
+    } else route(std::integral_constant<int, 16>(), std::integral_constant<int, 1>());
     __syncthreads();
     for (int i = threadIdx.x; i < N; i += kWgThreads)
         __hip_atomic_fetch_add(cnt + ids_s[i], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -411,51 +419,43 @@ __device__ __noinline__ void moel_topk(const Params &P, int blk, float *sm)
     for (int e = threadIdx.x; e < E; e += kWgThreads) cnt[e] = 0;
     __syncthreads();
     const int n_here = min(kMoelBlock, P.B - blk * kMoelBlock);      // <= 0: a block beyond the bound tokens
-    auto route = [&](auto tokens) {      // tokens in flight per wavefront
-        constexpr int TG = decltype(tokens)::value;
-        for (int i0 = wave; i0 < n_here; i0 += TG * kWaves) {
-            int my_id[TG];
-            float my_v[TG];
-            wave_topk<TG>(P.router_logits, E, forced ? 0 : K, blk * kMoelBlock + i0, kWaves, P.B, my_id, my_v, [&](int u, int e, float v) {
-                if (dbg) as_global(P.dbg_logits)[(size_t)(blk * kMoelBlock + i0 + u * kWaves) * E + e] = v;
+    auto route = [&](auto per_lane, auto groups) {
+        constexpr int NJ = decltype(per_lane)::value, TG = decltype(groups)::value;
+        const int l = lane & 15, t0 = blk * kMoelBlock;
+        for (int i0 = wave * 4; i0 < n_here; i0 += TG * 4 * kWaves) {
+            int id[TG];
+            float val[TG];
+            rows_topk<NJ, TG>(P.router_logits, E, forced ? 0 : K, t0 + i0, 4 * kWaves, P.B, id, val, [&](int u, int e, float v) {
+                if (dbg) as_global(P.dbg_logits)[(size_t)(t0 + i0 + u * 4 * kWaves + (lane >> 4)) * E + e] = v;
             });
-            if (forced) {
-#pragma unroll
-                for (int u = 0; u < TG; ++u) {
-                    const int b = blk * kMoelBlock + i0 + u * kWaves;
-                    if (b < P.B && lane < K) {
-                        my_id[u] = gld_i32(P.forced_topk + (size_t)b * K + lane);
-                        my_v[u] = ld_f32(P.router_logits + (size_t)b * E + my_id[u]);
-                    }
-                }
-            }
 #pragma unroll
             for (int u = 0; u < TG; ++u) {
-                const int b = blk * kMoelBlock + i0 + u * kWaves;
-                if (b >= P.B) continue;
-                float mx = lane < K ? my_v[u] : -INFINITY;
-#pragma unroll
-                for (int off = 8; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 16));      // K <= 16: one row of lanes
-                const float p = lane < K ? __expf(my_v[u] - mx) : 0.f;
-                const float den = wave_sum(p);
-                if (lane < K) {
-                    float wgt = p / den;
-                    if (forced_w) wgt = *as_global(P.forced_w + (size_t)b * K + lane);
-                    st_i32(P.topk_ids + (size_t)b * K + lane, my_id[u]);
-                    st_f32(P.topk_w + (size_t)b * K + lane, wgt);
+                const int i = i0 + u * 4 * kWaves + (lane >> 4), b = t0 + i;
+                const bool live = i < n_here && l < K;
+                int my_id = id[u];
+                float my_v = val[u];
+                if (forced && live) {
+                    my_id = gld_i32(P.forced_topk + (size_t)b * K + l);
+                    my_v = ld_f32(P.router_logits + (size_t)b * E + my_id);
+                }
+                float wgt = row_softmax(my_v, K);
+                if (live) {
+                    if (forced_w) wgt = *as_global(P.forced_w + (size_t)b * K + l);
+                    st_i32(P.topk_ids + (size_t)b * K + l, my_id);
+                    st_f32(P.topk_w + (size_t)b * K + l, wgt);
                     if (dbg) {
-                        as_global(P.dbg_topk_ids)[(size_t)b * K + lane] = my_id[u];
-                        as_global(P.dbg_topk_w)[(size_t)b * K + lane] = wgt;
+                        as_global(P.dbg_topk_ids)[(size_t)b * K + l] = my_id;
+                        as_global(P.dbg_topk_w)[(size_t)b * K + l] = wgt;
                     }
-                    __hip_atomic_fetch_add(cnt + my_id[u], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);      // integer count: order-free
+                    __hip_atomic_fetch_add(cnt + my_id, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);      // integer count: order-free
                 }
             }
         }
     };
-    // as in the decoder's router: up to 8 tokens a wavefront has one at most, and dead chains would cost it 4 us (one token,
-    // Qwen3-30B-A3B layer: 71 us with two rounds of four, 61 with one of one)
-    if (n_here <= kWaves) route(std::integral_constant<int, 1>());
-    else route(std::integral_constant<int, 4>());
+    if (E <= 128) {
+        if (n_here <= 4 * kWaves) route(std::integral_constant<int, 8>(), std::integral_constant<int, 1>());
+        else route(std::integral_constant<int, 8>(), std::integral_constant<int, 2>());
+    } else route(std::integral_constant<int, 16>(), std::integral_constant<int, 1>());
     __syncthreads();
     for (int e = threadIdx.x; e < E; e += kWgThreads) st_i32(P.moel_hist + (size_t)blk * E + e, cnt[e]);
     __syncthreads();
