@@ -354,16 +354,102 @@ __device__ __noinline__ WgState staged_task_out_of_line(const Params &PL, Task t
     return st;
 }
 
-// Staged path (out of line, from the task record) or chunked path (out of line, from the descriptors).  A GroupGEMM task that
-// fits both the staged path and the stream path of the latter is faster on the staged one (Qwen3-30B-A3B shape, three layers, on
+// The same for a task of a MoE instance on one of the other paths, whose arguments travel through LDS.
+template <bool LM>
+__device__ __noinline__ void moe_chunked_task(const Params &PL, Task t_in, TaskWaits tw_in, RowTile rt_in, int mode, float *sm,
+                                                      int *frame_anchor)
+{
+    const Task t = wave_uniform(t_in);
+    if (t.id == -0x7FFFFFFF) *frame_anchor = 1;      // never true; see gemm_tiles_chunked
+    const RowTile rt = wave_uniform(rt_in);
+    mode = __builtin_amdgcn_readfirstlane(mode);
+    ChunkedArgs a{GemmTile{}, Epilogue{}, wave_uniform(tw_in), t.id};
+    if (mode == 1) setup_moe_gemm(PL, t, rt, a.g, a.e);
+    else setup_gemm<true, LM>(PL, t, a.g, a.e);
+    if (mode == 2) slice_of_k(PL, t, t.fn == FN_OPROJ ? PL.k_slices_o : PL.k_slices_d, a.g, a.e);
+    ChunkedArgs *slot = chunked_args_slot();
+    if (threadIdx.x == 0) lds_put(slot, a);
+    __syncthreads();
+    int anchor = 0;
+    gemm_chunked_entry<true>(PL, slot, sm, &anchor);
+}
+
+// Row tiles, columns and reduction length of a projection task of a MoE instance; false for every other task kind.  Modes as above.
+template <bool LM>
+__device__ __forceinline__ bool moe_projection_shape(const Params &P, const Task &t, const RowTile &rt, int mode, int &n_tiles, int &n_cols, int &K)
+{
+    n_cols = P.B;
+    K = P.H;
+    if (mode == 1) {
+        n_tiles = t.c2;
+        n_cols = rt.n;
+        if (t.fn == FN_MOE_DOWN) K = P.moeF;
+        return true;
+    }
+    switch (t.fn) {
+    case FN_QKV: n_tiles = t.c2; return true;
+    case FN_OPROJ:
+        K = P.nq * P.d;
+        n_tiles = 1;
+        if (mode == 2) { n_tiles = t.c2; K /= P.k_slices_o; }
+        return true;
+    case FN_LMHEAD: {
+        const int left = (P.vocab >> 4) - t.c0;
+        n_tiles = left < t.c1 ? left : t.c1;
+        return LM;
+    }
+    case FN_ROUTER_LOGITS: {
+        const int left = P.B - t.c1 * 64;              // <= 0: a block beyond the bound tokens
+        n_tiles = 1;
+        n_cols = left < 64 ? left : 64;
+        return true;
+    }
+    default: return false;
+    }
+}
+
+// A projection task: staged path or another one; false: not a projection task.  In the MoE instances both are out of line and from
+// the task record: built in the task loop, the descriptors (50 words) take its scalar registers, and what they push out travels
+// through scratch memory around every task (122 stores and 84 loads in the loop, now 58 and 65; Qwen3-30B-A3B shape, two layers at
+// batch 1 / 8 / 33: 151 / 327 / 657 us with the descriptors handed over by value, 141 / 312 / 637 now; handed over in LDS, but
+// built in the loop: 183 / 370 / 640).  The dense instance is 2 - 4 % faster with the descriptors built in its loop (70B shape batch 8,
+// a layer: 375 us against 388).  A GroupGEMM task that
+// fits both the staged path and the stream path is faster on the staged one (Qwen3-30B-A3B shape, three layers, on
 // the staged / on the stream path: 12 and 16 tiles per task at batch 3 404 / 461 us, 24 and 32 at batch 5 535 / 585 and at batch 8
 // 602 / 652; MoE layer of 9 tokens 154 / 169; from 48 tokens on few tasks fit and the two are level).
 template <bool MOE, bool LM>
-__device__ __forceinline__ void dispatch_projection(const Params &PL, const Task &t, const TaskWaits &tw, const RowTile &rt, int mode,
-                                                    const GemmTile &g, const Epilogue &e, float *sm, WgState &st)
+__device__ __forceinline__ bool dispatch_projection(const Params &P, const Params &PL, const Task &t, const TaskWaits &tw, const RowTile &rt, int mode,
+                                                    float *sm, WgState &st)
 {
-    if (staged_fits(g.n_tiles, g.n_cols, g.K)) st = staged_task_out_of_line<MOE, LM>(PL, t, tw, rt, mode, sm, st);
-    else gemm_chunked_dispatch<MOE>(PL, g, e, tw, sm, st, t.id);
+    int anchor = 0;
+    if constexpr (MOE) {
+        int n_tiles = 0, n_cols = 0, K = 0;
+        if (!moe_projection_shape<LM>(P, t, rt, mode, n_tiles, n_cols, K)) return false;
+        if (n_cols <= 0) return true;                  // token block beyond the bound tokens: nothing to do but notify
+        if (staged_fits(n_tiles, n_cols, K)) {
+            st = staged_task_out_of_line<MOE, LM>(PL, t, tw, rt, mode, sm, st);
+        } else {
+            st.staged_key = -1;
+            moe_chunked_task<LM>(PL, t, tw, rt, mode, sm, &anchor);
+        }
+    } else {
+        GemmTile g{};
+        Epilogue e{};
+        if (mode == 2) {
+            setup_gemm<false, false>(P, t, g, e);
+            slice_of_k(P, t, t.fn == FN_OPROJ ? P.k_slices_o : P.k_slices_d, g, e);
+        } else if (!setup_gemm<false, LM>(P, t, g, e)) return false;
+        if (staged_fits(g.n_tiles, g.n_cols, g.K)) {
+            st = staged_task_out_of_line<MOE, LM>(PL, t, tw, rt, mode, sm, st);
+        } else {
+            st.staged_key = -1;
+            ChunkedArgs *slot = chunked_args_slot();
+            if (threadIdx.x == 0) lds_put(slot, ChunkedArgs{g, e, tw, t.id});
+            __syncthreads();
+            gemm_chunked_entry<false>(PL, slot, sm, &anchor);
+        }
+    }
+    return true;
 }
 
 // KIND: which task kinds the kernel instance carries: 0 generic graphs (the row-sum device functions), 1 dense
@@ -385,8 +471,6 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
 {
     const int w0 = SYNC_EVENTS ? t.wait0 : -1, w1 = SYNC_EVENTS ? t.wait1 : -1;
     TaskWaits tw{w0, w1, (int)t.fn, (t.flags & TF_WAIT0_PER_WAVE) != 0 && SYNC_EVENTS, w0 < 0 ? -1 : (w0 & kEvIndex)};
-    GemmTile g{};
-    Epilogue e{};
     constexpr int BASE = kind_base(KIND);
     constexpr bool LM = (KIND & KIND_LM) != 0;
     constexpr bool MOE = BASE == KIND_MOE;
@@ -401,33 +485,32 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
         }
         RowTile rt;
         if (!resolve_row_tile(P, t.c0, rt)) return;        // surplus slot of the static grid: nothing to do but notify
-        setup_moe_gemm(P, t, rt, g, e);
         const int key = w0 < 0 ? -1 : (w0 & kEvIndex) + ((t.c0 + 1) << 20);
         tw = routed ? TaskWaits{w0, w1, (int)t.fn, false, key} : TaskWaits{-1, -1, (int)t.fn, false, key};
-        dispatch_projection<MOE, LM>(PL, t, tw, rt, 1, g, e, sm, st);
+        dispatch_projection<MOE, LM>(P, PL, t, tw, rt, 1, sm, st);
         return;
     }
     constexpr bool STAGED_ONLY = BASE >= KIND_DENSE_STAGED;
     constexpr bool STAGED_SLICES = BASE == KIND_DENSE_STAGED_K || BASE == KIND_DENSE_STAGED_K_16;
-    if (BASE != KIND_GENERIC && !STAGED_ONLY && (t.flags & TF_K_SLICE)) {      // first stage of a K-sliced projection
-        setup_gemm<false, false>(P, t, g, e);
-        slice_of_k(P, t, t.fn == FN_OPROJ ? P.k_slices_o : P.k_slices_d, g, e);
-        if (tw.ev0 >= 0) tw.op_key += (t.c1 + 1) << 20;      // a staged copy holds one slice
-        dispatch_projection<MOE, LM>(PL, t, tw, RowTile{}, 2, g, e, sm, st);
-        return;
+    if (BASE != KIND_GENERIC && !STAGED_ONLY) {
+        if (t.flags & TF_K_SLICE) {                                    // first stage of a K-sliced projection
+            if (tw.ev0 >= 0) tw.op_key += (t.c1 + 1) << 20;            // a staged copy holds one slice
+            dispatch_projection<MOE, LM>(P, PL, t, tw, RowTile{}, 2, sm, st);
+            return;
+        }
+        if (dispatch_projection<MOE, LM>(P, PL, t, tw, RowTile{}, 0, sm, st)) return;
     }
-    if (BASE != KIND_GENERIC && setup_gemm<MOE, LM>(P, t, g, e)) {
-        if (MOE && g.n_cols <= 0) return;         // token block beyond the bound tokens: nothing to do but notify
-        if (STAGED_ONLY) {
+    if (STAGED_ONLY) {
+        GemmTile g{};
+        Epilogue e{};
+        if (setup_gemm<MOE, LM>(P, t, g, e)) {
             if (STAGED_SLICES && (t.flags & TF_K_SLICE)) {      // here a slice of K fits the staged path as well
                 slice_of_k(P, t, t.fn == FN_OPROJ ? P.k_slices_o : P.k_slices_d, g, e);
                 if (w0 >= 0) tw.op_key += (t.c1 + 1) << 20;
             }
             gemm_tiles_staged<5, BASE >= KIND_DENSE_STAGED_16 ? 2 : 1, LM>(P, g, e, tw, sm, st, t.id);
-        } else {
-            dispatch_projection<MOE, LM>(PL, t, tw, RowTile{}, 0, g, e, sm, st);
+            return;
         }
-        return;
     }
     if (BASE == KIND_GENERIC) {
         wg_wait_cached(P, st, w0, w1, t.fn);

@@ -198,6 +198,11 @@ __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTil
 
     const int key = w.op_key;
     const bool restage = key < 0 || key != st.staged_key;
+    // Gathered columns: lane n has the operand row of column n (16 at most).  Known since the routing, requested ahead of the weights:
+    // behind them every look-up is a round trip under load.
+    const bool gathered = g.col_rows != nullptr;
+    int lane_row = lane & 15;
+    if (gathered) lane_row = max(ld_i32(g.col_rows + ((lane & 15) < g.n_cols ? lane & 15 : g.n_cols - 1)), 0);
     // The task's weights are one linear stream of (tile, unit) pairs: unit s of tile t sits t * tile_step + 64 s behind the
     // first one.  The issue cursor runs PU units ahead of the consume cursor through that stream.
     const int total = g.n_tiles * n_it;
@@ -282,11 +287,11 @@ __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTil
         const bool one_col_per_wave = g.ssq_parts != nullptr && g.n_cols <= kWaves && g.n_parts <= 512;
         auto request_norm = [&]() {
             if (one_col_per_wave && wave < g.n_cols) {
-                const int row = g.col_rows ? ld_i32(g.col_rows + wave) : wave;
+                const int row = gathered ? __builtin_amdgcn_readlane(lane_row, wave) : wave;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const int pt = lane + 64 * j;
-                    sq[j] = (pt < g.n_parts && row >= 0) ? ld_f32(g.ssq_parts + (size_t)pt * (size_t)g.ssq_stride + row) : 0.f;
+                    sq[j] = pt < g.n_parts ? ld_f32(g.ssq_parts + (size_t)pt * (size_t)g.ssq_stride + row) : 0.f;
                 }
             }
         };
@@ -298,9 +303,7 @@ __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTil
             for (int u = 0; u < U; ++u) {
                 const int idx = i0 + u * kWgThreads;
                 const int col = idx < total_p ? idx / ppc : 0, q = idx - col * ppc;
-                int row = col;
-                if (g.col_rows) row = ld_i32(g.col_rows + col);
-                if (row < 0) row = 0;
+                const int row = gathered ? __shfl(lane_row, col, 64) : col;
                 at[u] = (uint32_t)(col * Kp + q * 8);
                 const uint32_t off = idx < total_p ? ((uint32_t)row * (uint32_t)g.ldb + (uint32_t)q * 8u) * 2u : kBufNone;
                 vh[u] = buf_ld_16B(hi_b, off, 0);
@@ -335,10 +338,9 @@ __device__ __forceinline__ void gemm_tiles_staged(const Params &P, const GemmTil
                 }
             } else {
                 for (int col = wave; col < g.n_cols; col += kWaves) {
-                    const int row = g.col_rows ? ld_i32(g.col_rows + col) : col;
+                    const int row = gathered ? __builtin_amdgcn_readlane(lane_row, col) : col;
                     float s = 0.f;
-                    if (row >= 0)
-                        for (int pt = lane; pt < g.n_parts; pt += 64) s += ld_f32(g.ssq_parts + (size_t)pt * (size_t)g.ssq_stride + row);
+                    for (int pt = lane; pt < g.n_parts; pt += 64) s += ld_f32(g.ssq_parts + (size_t)pt * (size_t)g.ssq_stride + row);
                     s = wave_sum(s);
                     if (lane == 0) rs[col] = 1.0f / sqrtf(s / (float)g.K + g.eps);
                 }
@@ -778,17 +780,36 @@ __device__ __forceinline__ void gemm_wait(const Params &P, const TaskWaits &w)
 }
 
 // RMSNorm factors of the columns, first half: thread (column, group) leaves its share of the column's sum of squares in
-// rs_part [512 / NCOL][NCOL].  Behind a barrier norm_factors() adds the shares.
+// rs_part [512 / NCOL][NCOL].  Behind a barrier norm_factors() adds the shares.  norm_request: the loads of its first 16 parts.
 template <int NCOL>
-__device__ __forceinline__ void norm_shares(const GemmTile &g, ETC_AS_LDS float *rs_part)
+__device__ __forceinline__ int norm_row(const GemmTile &g)      // operand row of this thread's column, -1: none
+{
+    const int col = (int)threadIdx.x % NCOL;
+    if (g.col_rows) {
+        const int row = ld_i32(g.col_rows + (col < g.n_cols ? col : g.n_cols - 1));
+        return col < g.n_cols ? row : -1;
+    }
+    return col < g.n_cols ? col : -1;
+}
+template <int NCOL>
+__device__ __forceinline__ void norm_request(const GemmTile &g, int row, float (&t)[16])
+{
+    constexpr int GRPS = kWgThreads / NCOL;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const int pt = (int)threadIdx.x / NCOL + GRPS * j;
+        t[j] = (pt < g.n_parts && row >= 0) ? ld_f32(g.ssq_parts + (size_t)pt * (size_t)g.ssq_stride + row) : 0.f;
+    }
+}
+template <int NCOL>
+__device__ __forceinline__ void norm_shares(const GemmTile &g, int row, float (&t)[16], ETC_AS_LDS float *rs_part)
 {
     constexpr int GRPS = kWgThreads / NCOL;
     const int col = (int)threadIdx.x % NCOL, grp = (int)threadIdx.x / NCOL;
-    int row = -1;
-    if (col < g.n_cols) row = g.col_rows ? ld_i32(g.col_rows + col) : col;
     float s = 0.f;
-    for (int p0 = grp; p0 < g.n_parts; p0 += GRPS * 16) {
-        float t[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s += t[j];
+    for (int p0 = grp + GRPS * 16; p0 < g.n_parts; p0 += GRPS * 16) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int pt = p0 + GRPS * j;
@@ -798,6 +819,14 @@ __device__ __forceinline__ void norm_shares(const GemmTile &g, ETC_AS_LDS float 
         for (int j = 0; j < 16; ++j) s += t[j];
     }
     rs_part[grp * NCOL + col] = s;
+}
+template <int NCOL>
+__device__ __forceinline__ void norm_shares(const GemmTile &g, ETC_AS_LDS float *rs_part)
+{
+    float t[16];
+    const int row = norm_row<NCOL>(g);
+    norm_request<NCOL>(g, row, t);
+    norm_shares<NCOL>(g, row, t, rs_part);
 }
 template <int NCOL>
 __device__ __forceinline__ void norm_factors(const GemmTile &g, ETC_AS_LDS float *rs, const ETC_AS_LDS float *rs_part)
@@ -1424,41 +1453,40 @@ __device__ __noinline__ void gemm_tiles_stream(const Params &P, const ChunkedArg
         iu = wrap ? 0 : iu;
     };
     u32x4 wr[16];                                  // two steps of 4 units, rows A and rows B of each
+    auto request_weights = [&]() {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        if (h < total) {
+        for (int h = 0; h < 2; ++h) {
+            if (h < total) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                wr[h * 8 + 2 * j] = gld_16B_nt(ipA + j * kUnitK);
-                wr[h * 8 + 2 * j + 1] = gld_16B_nt(ipB + j * kUnitK);
+                for (int j = 0; j < 4; ++j) {
+                    wr[h * 8 + 2 * j] = gld_16B_nt(ipA + j * kUnitK);
+                    wr[h * 8 + 2 * j + 1] = gld_16B_nt(ipB + j * kUnitK);
+                }
+                next_step();
             }
-            next_step();
         }
-    }
-    gemm_wait(P, a.w);
-    trace_mark(P, a.task_id, 1);
-
+    };
     // ---- the operand, hi and lo, whole; its columns K + kOpPad elements apart ----------------------------------
     const int Kp = K + kOpPad, ppc = K >> 3, pieces = g.n_cols * ppc;       // 16-byte pieces
     ETC_AS_LDS float *rs = as_lds(sm), *rs_part = rs + 64;
     ETC_AS_LDS uint16_t *op_hi = reinterpret_cast<ETC_AS_LDS uint16_t *>(rs_part + kWgThreads), *op_lo = op_hi + (size_t)g.n_cols * Kp;
     const __amdgpu_buffer_rsrc_t hi_b = buf_of(g.b_hi), lo_b = buf_of(g.b_lo);
     constexpr int U = 4;
-    for (int i0 = threadIdx.x; i0 < pieces; i0 += U * kWgThreads) {
-        u32x4 vh[U], vl[U];
-        uint32_t at[U];
+    u32x4 vh[U], vl[U];
+    uint32_t at[U];
+    int i0 = threadIdx.x;
+    auto load_pieces = [&](auto row_of) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = i0 + u * kWgThreads;
             const int col = i < pieces ? i / ppc : 0, pc = i - col * ppc;
-            int row = col;
-            if (g.col_rows) row = ld_i32(g.col_rows + col);
-            if (row < 0) row = 0;
             at[u] = (uint32_t)(col * Kp + pc * 8);
-            const uint32_t off = i < pieces ? ((uint32_t)row * (uint32_t)g.ldb + (uint32_t)pc * 8u) * 2u : kBufNone;
+            const uint32_t off = i < pieces ? ((uint32_t)row_of(col) * (uint32_t)g.ldb + (uint32_t)pc * 8u) * 2u : kBufNone;
             vh[u] = buf_ld_16B(hi_b, off, 0);
             vl[u] = buf_ld_16B(lo_b, off, 0);
         }
+    };
+    auto store_pieces = [&]() {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (i0 + u * kWgThreads < pieces) {
@@ -1466,8 +1494,32 @@ __device__ __noinline__ void gemm_tiles_stream(const Params &P, const ChunkedArg
                 *reinterpret_cast<ETC_AS_LDS u32x4 *>(op_lo + at[u]) = vl[u];
             }
         }
+    };
+    auto whole_operand = [&](auto row_of, auto behind) {
+        for (int left = pieces; left > U * kWgThreads; left -= U * kWgThreads) {
+            load_pieces(row_of);
+            store_pieces();
+            i0 += U * kWgThreads;
+        }
+        load_pieces(row_of);
+        behind();
+        store_pieces();
+    };
+    if (e.kind == EPI_MOE_ACT) {                   // its events have been seen (the rows depend on the routing): operand ahead of the weights
+        const int col_row = norm_row<64>(g);       // of column `lane`
+        float t[16];
+        whole_operand([&](int col) { return max(__shfl(col_row, col, 64), 0); }, [&]() {
+            norm_request<64>(g, col_row, t);
+            request_weights();
+        });
+        norm_shares<64>(g, col_row, t, rs_part);
+        trace_mark(P, a.task_id, 1);
+    } else {                                       // the activations of its own row block: rows as they stand
+        request_weights();
+        gemm_wait(P, a.w);
+        trace_mark(P, a.task_id, 1);
+        whole_operand([](int col) { return col; }, []() {});
     }
-    if (g.ssq_parts) norm_shares<64>(g, rs_part);
     __syncthreads();
     if (g.ssq_parts) {
         norm_factors<64>(g, rs, rs_part);
@@ -1597,29 +1649,27 @@ __device__ __noinline__ void gemm_tiles_blocks(const Params &P, const ChunkedArg
     };
     set_offsets();
     u32x4 wr[RING];
+    auto request_weights = [&]() {
 #pragma unroll
-    for (int j = 0; j < RING; ++j) {
-        if constexpr (LINES) wr[j] = load_w((j & 1 ? wbaseB : wbase) + ro[j / 2 % TW] + (j / 2 / TW) * kUnitK);
-        else wr[j] = load_w(wbase + ro[j % TW] + (j / TW) * 32);
-    }
-    next_request();
-    gemm_wait(P, a.w);
-    trace_mark(P, a.task_id, 1);
-
+        for (int j = 0; j < RING; ++j) {
+            if constexpr (LINES) wr[j] = load_w((j & 1 ? wbaseB : wbase) + ro[j / 2 % TW] + (j / 2 / TW) * kUnitK);
+            else wr[j] = load_w(wbase + ro[j % TW] + (j / TW) * 32);
+        }
+        next_request();
+    };
     ETC_AS_LDS uint16_t *buf0 = reinterpret_cast<ETC_AS_LDS uint16_t *>(as_lds(sm));
     ETC_AS_LDS float *rs = reinterpret_cast<ETC_AS_LDS float *>(buf0 + 2 * BUF), *rs_part = rs + NCOL;
     ETC_AS_LDS char *turn = reinterpret_cast<ETC_AS_LDS char *>(rs_part + kWgThreads) + wave * 2048;      // LINES: [16 rows][8 pieces], piece p of row r at p ^ (r & 7)
     const __amdgpu_buffer_rsrc_t hi_b = buf_of(g.b_hi), lo_b = buf_of(g.b_lo);
     uint32_t off[U];
     const int pc = (int)threadIdx.x % PPC;
+    auto operand_rows = [&](const int (&row)[U]) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int col = ((int)threadIdx.x + kWgThreads * u) / PPC;
-        int row = 0;
-        if (col < g.n_cols) row = g.col_rows ? ld_i32(g.col_rows + col) : col;
-        if (row < 0) row = 0;
-        off[u] = col < g.n_cols ? ((uint32_t)row * (uint32_t)g.ldb + (uint32_t)pc * 8u) * 2u : kBufNone;
-    }
+        for (int u = 0; u < U; ++u) {
+            const int col = ((int)threadIdx.x + kWgThreads * u) / PPC;
+            off[u] = col < g.n_cols ? ((uint32_t)row[u] * (uint32_t)g.ldb + (uint32_t)pc * 8u) * 2u : kBufNone;
+        }
+    };
     u32x4 vh[U], vl[U];
     auto fetch_chunk = [&](int c) {
 #pragma unroll
@@ -1637,9 +1687,32 @@ __device__ __noinline__ void gemm_tiles_blocks(const Params &P, const ChunkedArg
             *reinterpret_cast<ETC_AS_LDS u32x4 *>(lo + col * STRIDE + pc * 8) = vl[u];
         }
     };
-    fetch_chunk(0);
-    if (g.ssq_parts) norm_shares<NCOL>(g, rs_part);
-    park_chunk(0);
+    int row[U];
+    if (e.kind == EPI_MOE_ACT) {                   // its events have been seen (the rows depend on the routing): operand ahead of the weights
+        const int n_row = norm_row<NCOL>(g);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int col = ((int)threadIdx.x + kWgThreads * u) / PPC;
+            row[u] = max(ld_i32(g.col_rows + (col < g.n_cols ? col : g.n_cols - 1)), 0);
+        }
+        float t[16];
+        operand_rows(row);
+        fetch_chunk(0);
+        norm_request<NCOL>(g, n_row, t);
+        request_weights();
+        park_chunk(0);
+        norm_shares<NCOL>(g, n_row, t, rs_part);
+        trace_mark(P, a.task_id, 1);
+    } else {                                       // the activations of its own row block: rows as they stand
+        request_weights();
+        gemm_wait(P, a.w);
+        trace_mark(P, a.task_id, 1);
+#pragma unroll
+        for (int u = 0; u < U; ++u) row[u] = ((int)threadIdx.x + kWgThreads * u) / PPC;
+        operand_rows(row);
+        fetch_chunk(0);
+        park_chunk(0);
+    }
     __syncthreads();
     if (g.ssq_parts) norm_factors<NCOL>(g, rs, rs_part);      // read behind at least one more barrier (n_chunks > 1) ...
     if (g.ssq_parts && total == 1) __syncthreads();           // ... or this one
@@ -1788,7 +1861,7 @@ __device__ __forceinline__ void gemm_tiles_chunked_passes(const Params &PL, Chun
     }
 }
 
-// Entry of the out-of-line path: one call site in the task loop.  Tasks of 5 or more row tiles have a loop whose wavefronts
+// Entry of the out-of-line paths; the slot holds their arguments.  Tasks of 5 or more row tiles have a loop whose wavefronts
 // split the output (wide, lines; row blocks of experts: stream, blocks); the fewer tiles of the others (QKV, narrow plans)
 // would leave wavefronts idle there, so they split K (chunked, 1, 2 or 4 tiles: the loop always moves T, so T follows the
 // task).  Operand rows longer than kMaxBufLd lie outside one buffer descriptor: split K, a tile at a time, 8-byte loads.
@@ -1844,37 +1917,6 @@ __device__ __noinline__ void gemm_chunked_entry(const Params &PL, ChunkedArgs *s
     else if (a.g.n_tiles >= 5 && buf_ok) gemm_tiles_wide_passes<1, 2>(PL, a, slot, sm, &anchor);
     else ETC_CHUNKED(1)
 #undef ETC_CHUNKED
-}
-
-// The same entry with its arguments by value (some travel over the stack, which also keeps the call from being a tail
-// call).  Which hand-over is cheaper is a property of the calling instance, measured: the dense large-batch steps are
-// 6-7 % faster with the LDS slot (less scratch traffic per task), the MoE steps 13-18 % faster with the by-value call
-// (8B batch 64: 14.4 against 15.4 ms; Qwen3 shape batch 1: 6.1 against 5.0 ms).
-__device__ __noinline__ void gemm_chunked_entry_by_value(const Params &PL, GemmTile g, Epilogue e, TaskWaits w, float *sm, int task_id)
-{
-    const ChunkedArgs a{wave_uniform(g), wave_uniform(e), wave_uniform(w), __builtin_amdgcn_readfirstlane(task_id)};
-    ChunkedArgs *slot = chunked_args_slot();
-    if (threadIdx.x == 0) lds_put(slot, a);
-    __syncthreads();
-    int frame_anchor = 0;
-    gemm_chunked_entry<true>(PL, slot, sm, &frame_anchor);
-}
-
-// The chunked path from the task loop.  The MoE instances hand the arguments over by value: see gemm_chunked_entry_by_value.
-template <bool MOE>
-__device__ __forceinline__ void gemm_chunked_dispatch(const Params &PL, const GemmTile &g, const Epilogue &e, const TaskWaits &w,
-                                                      float *sm, WgState &st, int task_id)
-{
-    st.staged_key = -1;
-    if (MOE) {
-        gemm_chunked_entry_by_value(PL, g, e, w, sm, task_id);
-        return;
-    }
-    ChunkedArgs *slot = chunked_args_slot();
-    if (threadIdx.x == 0) lds_put(slot, ChunkedArgs{g, e, w, task_id});
-    __syncthreads();
-    int frame_anchor = 0;
-    gemm_chunked_entry<false>(PL, slot, sm, &frame_anchor);
 }
 
 // Second stage of a K-sliced projection: adds the partial sums of the slices in slice order (fixed, so the

@@ -24,14 +24,15 @@ constexpr int kTileShared = 1 << 16;      // flag in tile_n
 // whose rows another slot of their expert has taken over (moel_scan).
 __device__ __forceinline__ bool resolve_row_tile(const Params &P, int r, RowTile &rt)
 {
-    const int total = __builtin_amdgcn_readfirstlane(ld_i32(P.exp_indptr + P.E));
-    if (r >= total) return false;
-    rt.expert = __builtin_amdgcn_readfirstlane(ld_i32(P.tile_expert + r));
-    rt.row0 = __builtin_amdgcn_readfirstlane(ld_i32(P.tile_row0 + r));
-    const int n = __builtin_amdgcn_readfirstlane(ld_i32(P.tile_n + r));
+    // One round trip: the entries of a slot beyond exp_indptr[E] are of an earlier step and not used.
+    const int total_v = ld_i32(P.exp_indptr + P.E), expert_v = ld_i32(P.tile_expert + r), row0_v = ld_i32(P.tile_row0 + r),
+              n_v = ld_i32(P.tile_n + r);
+    const int total = __builtin_amdgcn_readfirstlane(total_v), n = __builtin_amdgcn_readfirstlane(n_v);
+    rt.expert = __builtin_amdgcn_readfirstlane(expert_v);
+    rt.row0 = __builtin_amdgcn_readfirstlane(row0_v);
     rt.n = n & (kTileShared - 1);
     rt.shared = n >= kTileShared;
-    return rt.n > 0;
+    return r < total && rt.n > 0;
 }
 
 // ---- top-k of the router ---------------------------------------------------------------------------------
