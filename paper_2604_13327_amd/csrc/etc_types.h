@@ -6,6 +6,7 @@ namespace etc {
 
 constexpr int kWgThreads = 512;          // one task = one workgroup of 8 wavefronts on one CU
 constexpr int kWaves = kWgThreads / 64;
+constexpr int kXcds = 8;                 // dies with an L2 each; workgroup i of a launch runs on die i % 8 (placement only: nothing depends on it)
 constexpr int kMaxBatch = 64;
 constexpr int kMaxLayers = 128;
 constexpr int kMaxExperts = 256;

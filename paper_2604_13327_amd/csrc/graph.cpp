@@ -89,7 +89,12 @@ std::string instantiate(const GraphDecl &g, const int *sym, int n_queues, bool u
         const int total = dims[0] * dims[1] * dims[2];
         for (int i = 0; i < total; ++i) {
             int coord[3];
-            if (c.last_dim_slowest && c.rank == 3) {      // (c2 slowest, then c0, c1)
+            if (c.first_dim_by_xcd && c.rank == 2) {
+                const int first = i / (kXcds * dims[1]) * kXcds, width = std::min(kXcds, dims[0] - first), r = i - first * dims[1];
+                coord[0] = first + r % width;
+                coord[1] = r / width;
+                coord[2] = 0;
+            } else if (c.last_dim_slowest && c.rank == 3) {      // (c2 slowest, then c0, c1)
                 coord[2] = i / (dims[0] * dims[1]);
                 coord[0] = (i / dims[1]) % dims[0];
                 coord[1] = i % dims[1];
@@ -186,6 +191,12 @@ std::string instantiate(const GraphDecl &g, const int *sym, int n_queues, bool u
     }
     p.ev_consumers.assign(1, 0);
     for (int e = 0; e < n_events; ++e) {
+        // GroupGEMM-1 tasks in the order of their row-tile slots, whatever the order of their ids: an expert releases a range of slots
+        if (!cons[e].empty() && p.tasks[cons[e][0] & 0xFFFFFF].fn == FN_MOE_GATEUP)
+            std::sort(cons[e].begin(), cons[e].end(), [&](int32_t a, int32_t b) {
+                const Task &x = p.tasks[a & 0xFFFFFF], &y = p.tasks[b & 0xFFFFFF];
+                return x.c0 != y.c0 ? x.c0 < y.c0 : x.c1 < y.c1;
+            });
         p.consumer_ids.insert(p.consumer_ids.end(), cons[e].begin(), cons[e].end());
         p.ev_consumers.push_back((int32_t)p.consumer_ids.size());
     }
@@ -218,10 +229,15 @@ Counters place_counters(const Plan &p, bool dynamic)
         c.wait.push_back(first[e] | (wide[e] ? kEvSpread : 0));
     }
     c.consumers.push_back(p.ev_consumers.back());
+    std::vector<int> per_slot(kMaxLayers, 0);        // GroupGEMM-2 tasks of a row-tile slot
+    for (const Task &t : p.tasks)
+        if (t.fn == FN_MOE_DOWN && t.c0 == 0) ++per_slot[t.layer];
     for (const Task &t : p.tasks)
         if (t.notify0 >= 0) {
             const int e = t.notify0;
-            notify[t.id] = first[e] | (wide[e] ? (seen[e]++ % kEvSpreadN) << kEvNthShift : 0);
+            // counted by slot, not by id: the slots a routing cancels are the last ones (ev_drop_producers)
+            const int nth = t.fn == FN_MOE_DOWN ? t.c0 * per_slot[t.layer] + t.c1 / std::max(1, t.c2) : seen[e]++;
+            notify[t.id] = first[e] | (wide[e] ? (nth % kEvSpreadN) << kEvNthShift : 0);
         }
     auto place = [&](Task t) {
         if (t.wait0 >= 0) t.wait0 = c.wait[t.wait0];
@@ -634,6 +650,7 @@ std::string build_moe_layer_graph(const ModelDims &m, int Ts, int n_queues, Grap
         c.fn = FN_MOE_GATEUP; c.stage = stage++;     // task record: (row-tile slot, first tile, tiles)
         c.rank = 2; c.shape[0] = dim_const(r_max); c.shape[1] = dim_const(n_ft / r_g);
         c.c_mul[1] = r_g; c.c_fill[2] = r_g;
+        c.first_dim_by_xcd = true;
         c.flags = TF_DYN_ROWTILE;
         c.in = {edge_const0(e_group)};
         c.out = {edge_dim(e_eact, 0)};
@@ -644,6 +661,7 @@ std::string build_moe_layer_graph(const ModelDims &m, int Ts, int n_queues, Grap
         c.fn = FN_MOE_DOWN; c.stage = stage++;
         c.rank = 2; c.shape[0] = dim_const(r_max); c.shape[1] = dim_const(n_ht / r_d);
         c.c_mul[1] = r_d; c.c_fill[2] = r_d;
+        c.first_dim_by_xcd = true;
         c.flags = TF_DYN_ROWTILE;
         c.in = {edge_dim(e_eact, 0)};
         c.out = {edge_const0(e_y)};

@@ -51,6 +51,8 @@ struct CallDecl {
     int c_off[3] = {0, 0, 0};
     int c_fill[3] = {0, 0, 0};         // ... and c_fill for the coordinates beyond the grid's rank
     bool last_dim_slowest = false;     // enumeration order (balances ragged grids across queues)
+    bool first_dim_by_xcd = false;     // rank 2: eight first coordinates at a time, the second one slower, so that the tasks of a first
+                                       //   coordinate go to every eighth queue: workgroups of one XCD, which share an L2
     uint16_t flags = 0;
     std::vector<EdgeMap> in, out;      // at most 2 in-edges, 1 out-edge
 };
