@@ -497,7 +497,7 @@ std::string build_decoder_graph(const ModelDims &m, int Bs, int n_queues, bool m
             {
                 CallDecl c;
                 c.fn = FN_ROUTER_LOGITS; c.layer = l; c.stage = stage++;
-                c.rank = 1; c.shape[0] = dim_const(m.E / 16);
+                c.rank = 1; c.shape[0] = dim_const(m.E / 16); c.c_fill[2] = 1;
                 c.in = {edge_const0(e_xmid)};
                 c.out = {edge_const0(e_logits)};
                 g.calls.push_back(c);
@@ -597,6 +597,12 @@ std::string build_moe_layer_graph(const ModelDims &m, int Ts, int n_queues, Grap
     const int row_block = m.tile_m * moe_row_merge(m.tile_m, m.H, m.moeF);
     const int r_g = moe_tiles_per_task(m, Ts, row_block, n_ft, m.H, n_queues);
     const int r_d = moe_tiles_per_task(m, Ts, row_block, n_ht, m.moeF, n_queues);
+    // Router tiles per task: 1, or the smallest power of two with which one round of tasks covers all token blocks.  A task's time is its
+    // operand (64 tokens x hidden, 512 KB at 2048, against 64 KB of router rows a tile), so a second tile costs next to nothing and a
+    // second round all of it again: layer of 3000 / 4001 tokens 876 / 1111 us with one tile a task, 848 / 1079 with two (dynamic 4001:
+    // 1074 and 1037).
+    int r_lg = 1;
+    while (r_lg < 4 && m.E / 16 % (2 * r_lg) == 0 && m.E / 16 / r_lg * n_blk > n_queues) r_lg *= 2;
     const int e_x = g.add_event({one});
     const int e_logits = g.add_event({dim_const(n_blk)});
     const int e_hist = g.add_event({one});
@@ -615,8 +621,9 @@ std::string build_moe_layer_graph(const ModelDims &m, int Ts, int n_queues, Grap
     }
     {
         CallDecl c;
-        c.fn = FN_ROUTER_LOGITS; c.stage = stage++;      // task record: (16 router rows, block of 64 tokens)
-        c.rank = 2; c.shape[0] = dim_const(m.E / 16); c.shape[1] = dim_const(n_blk);
+        c.fn = FN_ROUTER_LOGITS; c.stage = stage++;      // task record: (first tile of 16 router rows, block of 64 tokens, tiles)
+        c.rank = 2; c.shape[0] = dim_const(m.E / 16 / r_lg); c.shape[1] = dim_const(n_blk);
+        c.c_mul[0] = r_lg; c.c_fill[2] = r_lg;
         c.in = {edge_const0(e_x)};
         c.out = {edge_dim(e_logits, 1)};
         g.calls.push_back(c);

@@ -260,7 +260,7 @@ __device__ __forceinline__ bool setup_gemm(const Params &P, const Task &t, GemmT
         if (!MOE) return false;
         const int r0 = t.c0 * 16;
         const int cb = t.c1 * 64;      // stand-alone MoE layer: one task per block of 64 tokens (c1 = 0 in a decoder)
-        g.n_tiles = 1; g.tile_rows = 16;
+        g.n_tiles = t.c2; g.tile_rows = 16;
         g.rowsA = (const uint16_t *)W->wr + (size_t)r0 * P.H;
         g.rowsB = g.rowsA + (size_t)8 * P.H;
         g.ldw = P.H; g.K = P.H;
@@ -400,7 +400,7 @@ __device__ __forceinline__ bool moe_projection_shape(const Params &P, const Task
     }
     case FN_ROUTER_LOGITS: {
         const int left = P.B - t.c1 * 64;              // <= 0: a block beyond the bound tokens
-        n_tiles = 1;
+        n_tiles = t.c2;
         n_cols = left < 64 ? left : 64;
         return true;
     }
