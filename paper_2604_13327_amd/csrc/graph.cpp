@@ -250,6 +250,26 @@ Counters place_counters(const Plan &p, bool dynamic)
     return c;
 }
 
+// A task of the router projection: its tiles of 16 router rows and its block of columns (tokens).  Its time is its operand (columns x
+// hidden, 512 KB for 64 at 2048, against 64 KB of router rows a tile).  So the columns are cut to 16, which fit the staged path (the
+// whole operand in one round trip instead of eight chunks), where one round of tasks still covers them all, and a task takes two
+// or four tiles where 64 columns take more than one round.  Below a hidden size of 1024 a block is a round trip or two
+// whole, and stays.  Qwen3-30B-A3B shape, 64 columns and one tile against this: two layers at batch 33 / 64 620 / 690 -> 604 / 678 us,
+// MoE layer of 50 / 200 / 400 tokens 271 / 307 / 322 -> 264 / 299 / 316, 3000 / 4001 tokens 876 / 1111 -> 848 / 1079 (dynamic 50 / 4001
+// tokens 347 / 1074 -> 332 / 1036).  32 columns (1024 tokens in one round of 256 tasks): 374 -> 376, not taken.
+struct RouterTask {
+    int tiles = 1, cols = 64;
+    int record() const { return tiles | cols << 8; }
+};
+static RouterTask router_task(const ModelDims &m, int tokens, int n_queues)
+{
+    RouterTask r;
+    const int all = m.E / 16;
+    while (r.tiles < 4 && all % (2 * r.tiles) == 0 && all / r.tiles * ((tokens + 63) / 64) > n_queues) r.tiles *= 2;
+    if (m.H >= 1024 && staged_fits(1, 16, m.H) && tokens > 16 && all * ((tokens + 15) / 16) <= n_queues) r.cols = 16;
+    return r;
+}
+
 int moe_tiles_per_task(const ModelDims &m, int tokens, int row_block, int per_slot, int K, int n_queues)
 {
     const double pairs = (double)tokens * m.topk, per_expert = pairs / m.E;
@@ -497,7 +517,9 @@ std::string build_decoder_graph(const ModelDims &m, int Bs, int n_queues, bool m
             {
                 CallDecl c;
                 c.fn = FN_ROUTER_LOGITS; c.layer = l; c.stage = stage++;
-                c.rank = 1; c.shape[0] = dim_const(m.E / 16); c.c_fill[2] = 1;
+                const RouterTask rl = router_task(m, Bs, n_queues);
+                c.rank = 2; c.shape[0] = dim_const(m.E / 16 / rl.tiles); c.shape[1] = dim_const((Bs + rl.cols - 1) / rl.cols);
+                c.c_mul[0] = rl.tiles; c.c_fill[2] = rl.record();
                 c.in = {edge_const0(e_xmid)};
                 c.out = {edge_const0(e_logits)};
                 g.calls.push_back(c);
@@ -597,12 +619,7 @@ std::string build_moe_layer_graph(const ModelDims &m, int Ts, int n_queues, Grap
     const int row_block = m.tile_m * moe_row_merge(m.tile_m, m.H, m.moeF);
     const int r_g = moe_tiles_per_task(m, Ts, row_block, n_ft, m.H, n_queues);
     const int r_d = moe_tiles_per_task(m, Ts, row_block, n_ht, m.moeF, n_queues);
-    // Router tiles per task: 1, or the smallest power of two with which one round of tasks covers all token blocks.  A task's time is its
-    // operand (64 tokens x hidden, 512 KB at 2048, against 64 KB of router rows a tile), so a second tile costs next to nothing and a
-    // second round all of it again: layer of 3000 / 4001 tokens 876 / 1111 us with one tile a task, 848 / 1079 with two (dynamic 4001:
-    // 1074 and 1037).
-    int r_lg = 1;
-    while (r_lg < 4 && m.E / 16 % (2 * r_lg) == 0 && m.E / 16 / r_lg * n_blk > n_queues) r_lg *= 2;
+    const RouterTask rl = router_task(m, Ts, n_queues);
     const int e_x = g.add_event({one});
     const int e_logits = g.add_event({dim_const(n_blk)});
     const int e_hist = g.add_event({one});
@@ -621,11 +638,11 @@ std::string build_moe_layer_graph(const ModelDims &m, int Ts, int n_queues, Grap
     }
     {
         CallDecl c;
-        c.fn = FN_ROUTER_LOGITS; c.stage = stage++;      // task record: (first tile of 16 router rows, block of 64 tokens, tiles)
-        c.rank = 2; c.shape[0] = dim_const(m.E / 16 / r_lg); c.shape[1] = dim_const(n_blk);
-        c.c_mul[0] = r_lg; c.c_fill[2] = r_lg;
+        c.fn = FN_ROUTER_LOGITS; c.stage = stage++;      // task record: (first tile of 16 router rows, block of tokens, RouterTask)
+        c.rank = 2; c.shape[0] = dim_const(m.E / 16 / rl.tiles); c.shape[1] = dim_const((Ts + rl.cols - 1) / rl.cols);
+        c.c_mul[0] = rl.tiles; c.c_fill[2] = rl.record();
         c.in = {edge_const0(e_x)};
-        c.out = {edge_dim(e_logits, 1)};
+        c.out = {edge_dim(e_logits, 1, 64 / rl.cols)};
         g.calls.push_back(c);
     }
     {

@@ -259,15 +259,15 @@ __device__ __forceinline__ bool setup_gemm(const Params &P, const Task &t, GemmT
     case FN_ROUTER_LOGITS: {
         if (!MOE) return false;
         const int r0 = t.c0 * 16;
-        const int cb = t.c1 * 64;      // stand-alone MoE layer: one task per block of 64 tokens (c1 = 0 in a decoder)
-        g.n_tiles = t.c2; g.tile_rows = 16;
+        const int cols = t.c2 >> 8, cb = t.c1 * cols;      // this task's block of columns
+        g.n_tiles = t.c2 & 255; g.tile_rows = 16;
         g.rowsA = (const uint16_t *)W->wr + (size_t)r0 * P.H;
         g.rowsB = g.rowsA + (size_t)8 * P.H;
         g.ldw = P.H; g.K = P.H;
         g.b_hi = P.xmg_hi + (size_t)cb * P.H; g.b_lo = P.xmg_lo + (size_t)cb * P.H; g.ldb = P.H;
         g.ssq_parts = P.ssq_xmid; g.n_parts = P.moel ? 1 : P.H / 16; g.eps = P.eps; g.ssq_stride = MOE ? P.col_stride : kMaxBatch;
         g.ssq_parts += cb;
-        g.n_cols = P.B - cb < 64 ? P.B - cb : 64;      // <= 0: a block beyond the bound tokens (the caller skips the tile)
+        g.n_cols = P.B - cb < cols ? P.B - cb : cols;      // <= 0: a block beyond the bound tokens (the caller skips the tile)
         e.kind = EPI_STORE_F32; e.layer = t.layer; e.row0 = r0; e.outf = P.router_logits + (size_t)cb * P.E; e.ld = P.E;
         return true;
     }
@@ -399,9 +399,9 @@ __device__ __forceinline__ bool moe_projection_shape(const Params &P, const Task
         return LM;
     }
     case FN_ROUTER_LOGITS: {
-        const int left = P.B - t.c1 * 64;              // <= 0: a block beyond the bound tokens
-        n_tiles = t.c2;
-        n_cols = left < 64 ? left : 64;
+        const int cols = t.c2 >> 8, left = P.B - t.c1 * cols;   // <= 0: a block beyond the bound tokens
+        n_tiles = t.c2 & 255;
+        n_cols = left < cols ? left : cols;
         return true;
     }
     default: return false;
@@ -493,6 +493,7 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
     constexpr bool STAGED_ONLY = BASE >= KIND_DENSE_STAGED;
     constexpr bool STAGED_SLICES = BASE == KIND_DENSE_STAGED_K || BASE == KIND_DENSE_STAGED_K_16;
     if (BASE != KIND_GENERIC && !STAGED_ONLY) {
+        if (MOE && t.fn == FN_ROUTER_LOGITS && tw.ev0 >= 0) tw.op_key += t.c1 << 20;      // a staged copy holds one block of columns
         if (t.flags & TF_K_SLICE) {                                    // first stage of a K-sliced projection
             if (tw.ev0 >= 0) tw.op_key += (t.c1 + 1) << 20;            // a staged copy holds one slice
             dispatch_projection<MOE, LM>(P, PL, t, tw, RowTile{}, 2, sm, st);

@@ -21,7 +21,7 @@ def test_router_tiles_per_task(sampled, tokens, tiles):
     w, x = _weights(s, seed), sgpu.hidden_gpu(s, seed, tokens, tokens)
     plan = etc.moe_layer_plan_build(s, sampled, 256, kind=0, moe_tile_m=tile_m)
     t = plan["tasks"][plan["tasks"]["fn"] == FN_ROUTER_LOGITS]
-    assert (t["c2"] == tiles).all() and len(t) == 16 // tiles * -(-sampled // 64)
+    assert (t["c2"] & 255 == tiles).all() and len(t) == 16 // tiles * -(-sampled // 64)
     outs = []
     for kind in (0, 1):
         layer = etc.MoeLayer(s, [sampled], kind=kind, moe_tile_m=tile_m, debug_flags=etc.DEBUG_ROUTING, spin_budget=SPIN)
@@ -34,5 +34,31 @@ def test_router_tiles_per_task(sampled, tokens, tiles):
         outs.append(y)
         if kind == 0:
             _check_against_oracle(s, seed, x, y, r, tile_m)
+        layer.close()
+    np.testing.assert_array_equal(outs[1], outs[0])
+
+
+@pytest.mark.parametrize("sampled,tokens,cols", [(16, 16, 64), (17, 17, 16), (64, 64, 16), (64, 33, 16), (64, 3, 16), (512, 512, 16), (512, 90, 16), (513, 513, 64)])
+def test_router_columns_per_task(sampled, tokens, cols):
+    """Hidden 1024, 128 experts (8 tiles): 16 columns a task while one round of 256 covers all, else 64; column blocks that the bound
+    tokens leave part or all of empty."""
+    from synth import gpu as sgpu
+    etc = _etc()
+    s, seed, tile_m = dataclasses.replace(synth.TINY_MOE, H=1024, n_experts=128), 67, 32
+    w, x = _weights(s, seed), sgpu.hidden_gpu(s, seed, tokens, tokens)
+    t = etc.moe_layer_plan_build(s, sampled, 256, kind=0, moe_tile_m=tile_m)["tasks"]
+    t = t[t["fn"] == FN_ROUTER_LOGITS]
+    assert (t["c2"] >> 8 == cols).all() and len(t) == 8 * -(-sampled // cols)
+    outs = []
+    for kind in (0, 1):
+        layer = etc.MoeLayer(s, [sampled], kind=kind, moe_tile_m=tile_m, debug_flags=etc.DEBUG_ROUTING, spin_budget=SPIN)
+        layer.bind_weights(w)
+        layer.bind_tokens(tokens)
+        for _ in range(2):
+            y = _run(layer, x)
+            assert (layer.error_word() == 0).all() and (layer.event_counters() == 0).all()
+        outs.append(y)
+        if kind == 0:
+            _check_against_oracle(s, seed, x, y, _routing(layer, s, tokens), tile_m)
         layer.close()
     np.testing.assert_array_equal(outs[1], outs[0])
