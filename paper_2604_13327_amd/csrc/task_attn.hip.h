@@ -138,9 +138,9 @@ __device__ __forceinline__ float groups_sum(float v)
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// A chunk on the matrix cores.  A wavefront takes 32 keys per step:
-//   scores   S^T[key][column] = K[key][:] . Q[column][:]   A = K rows straight from the cache (lane (key % 16, kg) loads 16 bytes
-//            of its key's row: the A fragment), B = the queries as sums of bf16 parts.  The 16 columns hold the parts side by
+// A chunk on the matrix cores.  A wavefront takes 32 (NBLK = 1: 16) keys per step:
+//   scores   S^T[key][column] = K[key][:] . Q[column][:]   A = K rows, read as fragments (lane (key % 16, kg): 16 bytes of its
+//            key's row) from a wavefront-private LDS tile, B = the queries as sums of bf16 parts.  The 16 columns hold the parts side by
 //            side: column n is part n / GRP of head n % GRP (8 heads: two parts, 16 bits of a query; fewer heads: three, all 24),
 //            so one product per fragment does for all parts and the columns of a head are added across lanes.  The result
 //            lands as lane (column, kg) <- keys blk * 16 + kg * 4 + r: eight keys of one head per lane, and in exactly the order
