@@ -39,6 +39,16 @@ inline bool attn_shape_supported(int head_dim, int group)
     return false;
 }
 
+// An attention task has the page ids of its keys in LDS, a window of them at a time: the keys [w0, end) of one, of a chunk whose
+// cached keys end at k1 (w0 <= k1).  Pages hold any power of two of tokens: kAttnPages of 2^19 and more are over 2^31 tokens, which no
+// chunk has.  No sum in here is above k1.
+constexpr int kAttnPages = 4096;
+constexpr int attn_window_end(int w0, int k1, int page_shift)
+{
+    return page_shift < 19 && k1 - w0 > (kAttnPages << page_shift) ? w0 + (kAttnPages << page_shift) : k1;
+}
+constexpr int attn_window_pages(int w0, int w1, int page_shift) { return ((w1 - w0 - 1) >> page_shift) + 1; }      // w0: first key of a page
+
 // Device functions (task bodies).  One entry of the dispatch switch each (Alg. 1 "dispatch logic").
 enum Fn : uint8_t {
     FN_NOP = 0,

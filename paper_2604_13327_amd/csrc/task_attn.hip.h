@@ -18,8 +18,7 @@ namespace etc {
 // [entry][g] m, l, then [entry][g][D] o.
 constexpr int kAttnEnt = kWaves + 1;
 template <int GRP> constexpr int kAttnOff = (2 * kAttnEnt * GRP + 3) & ~3;      // floats in front of the o rows (which are read 16 bytes at a time)
-constexpr int kAttnScratch = 40 * 1024;             // bytes in front of the wavefronts' V tiles
-constexpr int kAttnPages = 4096;                    // page ids in LDS at a time (behind the tiles)
+constexpr int kAttnScratch = 40 * 1024;             // bytes in front of the wavefronts' V tiles (behind those: kAttnPages page ids)
 
 __device__ __forceinline__ float exp2_f(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -190,7 +189,7 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
     const int n16 = lane & 15, kg = lane >> 4;
     const int n_keys = __builtin_amdgcn_readfirstlane(gld_i32(P.kv_len + b)) + 1;
     const int j0 = ch * chunk;
-    const int j1 = min(n_keys, j0 + chunk);
+    const int j1 = j0 + min(n_keys - j0, chunk);
     const int jc1 = min(j1, n_keys - 1);                 // cached keys of the chunk: [j0, jc1), the step's own token is not read back
     const int32_t *pages = P.page_ids + __builtin_amdgcn_readfirstlane(gld_i32(P.page_indptr + b));
     const size_t lbase = (size_t)layer * (size_t)P.pool_layer_stride + (size_t)kvh * D;
@@ -208,10 +207,9 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
     ETC_AS_LDS int *s_pg = reinterpret_cast<ETC_AS_LDS int *>(tiles + kWaves * 32 * VS);
 
     // Page ids of the keys [w0, w1) sit in LDS: all of the chunk's, unless it is longer than kAttnPages pages.
-    const int win = kAttnPages << psh;                   // keys of a window (j0 is a whole number of pages)
-    int w0 = j0, w1 = LOOP ? min(jc1, j0 + win) : jc1;
+    int w0 = j0, w1 = LOOP ? attn_window_end(j0, jc1, psh) : jc1;      // (j0 is a whole number of pages)
     auto load_pages = [&](int first) {
-        for (int i = first + (int)threadIdx.x; i < (w1 - w0 + pmask) >> psh; i += kWgThreads) s_pg[i] = gld_i32(pages + (w0 >> psh) + i);
+        for (int i = first + (int)threadIdx.x; i < attn_window_pages(w0, w1, psh); i += kWgThreads) s_pg[i] = gld_i32(pages + (w0 >> psh) + i);
     };
     // K and V rows of a step, whole rows per load: this lane has piece lane % LPR of the rows of the keys base + i * RPI +
     // lane / LPR; beyond the window: its last key again, weight 0
@@ -427,7 +425,7 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
         }
         if (!LOOP || w1 >= jc1) break;               // uniform
         w0 = w1;
-        w1 = min(jc1, w0 + win);
+        w1 = attn_window_end(w0, jc1, psh);
         __syncthreads();                                 // every wavefront is done with the page ids
         load_pages(0);
         __syncthreads();

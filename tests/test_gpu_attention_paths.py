@@ -72,3 +72,39 @@ def test_more_pages_than_the_window_holds(d, grp, batch):
     """Pages of one token, chunks of 8192 keys: two windows of page ids, the second one key, 200 keys and 904 keys long."""
     lens = ([4097, 5000] if batch == 2 else [4097, 4296, 5000, 4096, 4095] + [7] * (batch - 5))
     _check(_shape(d, grp, False, page=1), lens, 8192, 8192)
+
+
+@pytest.mark.parametrize("page", [1 << 18, 1 << 19, 1 << 20])
+def test_pages_of_many_tokens(page):
+    """A contiguous cache as one page a sequence: the same bits as with the same keys in pages of 16 (one chunk either way), where
+    4096 pages are 2^30 tokens and where they are more than 32 bits count."""
+    import torch
+    import paper_2604_13327_amd as etc
+    lens, outs = [1000, 0, 4095], []
+    small = synth.ModelShape("pages", 1, 256, 4, 1, 64, 512)
+    n_pool = sum(synth.pages_needed(n, 16) for n in lens)
+    model = GpuModel(small, seed=37, n_pool_pages=n_pool)
+    x = model.hidden(0, len(lens))
+    rows = [torch.arange(n, device="cuda") for n in lens]                    # pages in order: position i of sequence b
+    first = np.cumsum([0] + [synth.pages_needed(n, 16) for n in lens])
+    for size in (16, page):
+        s = synth.ModelShape("pages", 1, 256, 4, 1, 64, 512, page=size)
+        if size == 16:
+            indptr, ids, k, v = first, np.arange(n_pool), model.kpool.clone(), model.vpool.clone()
+        else:
+            indptr, ids = np.arange(len(lens) + 1), np.arange(len(lens))
+            k, v = (torch.zeros((1,) + synth.kv_pool_shape(s, len(lens)), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+            for b, r in enumerate(rows):
+                for pool, to in ((model.kpool, k), (model.vpool, v)):
+                    to[0, b, :len(r)] = pool[0, first[b]:].flatten(0, 1)[:len(r)]
+        dec = etc.Decoder(s, kv_chunk_tokens=page, sampled_batches=[len(lens)], max_kv_len=max(lens) + 1, spin_budget=SPIN)
+        dec.bind_layer_weights(0, model.weights[0])
+        dec.bind_kv_pool(k, v)
+        dec.bind_step(synth.Step(len(lens), np.asarray(lens, np.int32), indptr.astype(np.int32), ids.astype(np.int32)))
+        out = torch.empty_like(x)
+        dec.launch(x, out)
+        torch.cuda.synchronize()
+        assert (dec.error_word() == 0).all() and torch.isfinite(out.float()).all()
+        outs.append(out)
+        dec.close()
+    assert torch.equal(outs[0], outs[1])
