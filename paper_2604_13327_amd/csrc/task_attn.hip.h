@@ -108,16 +108,16 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b)
 __device__ __forceinline__ float bf16_low(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_high(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// Part `part` of (a, b) as bf16: part 0 the rounded value, part 1 what that leaves, part 2 what both leave, then nothing; the
-// first PARTS parts of a value add up to its leading 8 PARTS bits.
-template <int PARTS>
-__device__ __forceinline__ uint32_t bf16_part(float a, float b, int part)
+// Part `part` of (a, b) as bf16: part 0 the rounded value, part 1 what that leaves, part 2 what both leave, then nothing: the
+// three add up to all 24 bits of a value.  What part 1 of 8 heads leaves has no column of its own and goes to `rest`.
+template <int GRP>
+__device__ __forceinline__ uint32_t bf16_part(float a, float b, int part, uint32_t &rest)
 {
     const uint32_t h = pack_bf16(a, b);
     const float a1 = a - bf16_low(h), b1 = b - bf16_high(h);
-    if constexpr (PARTS == 2) return pack_bf16(part ? a1 : a, part ? b1 : b);
     const uint32_t l = pack_bf16(a1, b1);
     const uint32_t l2 = pack_bf16(a1 - bf16_low(l), b1 - bf16_high(l));
+    rest = GRP == 8 && part == 1 ? l2 : 0u;
     return part == 0 ? h : (part == 1 ? l : (part == 2 ? l2 : 0u));
 }
 
@@ -140,9 +140,10 @@ __device__ __forceinline__ float groups_sum(float v)
 // A chunk on the matrix cores.  A wavefront takes 32 (NBLK = 1: 16) keys per step:
 //   scores   S^T[key][column] = K[key][:] . Q[column][:]   A = K rows, read as fragments (lane (key % 16, kg): 16 bytes of its
 //            key's row) from a wavefront-private LDS tile, B = the queries as sums of bf16 parts.  The 16 columns hold the parts side by
-//            side: column n is part n / GRP of head n % GRP (8 heads: two parts, 16 bits of a query; fewer heads: three, all 24),
-//            so one product per fragment does for all parts and the columns of a head are added across lanes.  The result
-//            lands as lane (column, kg) <- keys blk * 16 + kg * 4 + r: eight keys of one head per lane, and in exactly the order
+//            side: column n is part n / GRP of head n % GRP (three parts, all 24 bits of a query), so one product per
+//            fragment does for all parts and the columns of a head are added across lanes.  (8 heads fill the columns with two
+//            parts: a second product adds the third one to the columns of the second.  Without it their queries and probabilities had
+//            16 bits: 8.8e-6 instead of 2.1e-6 off where scores spread by tens, and 0.3 to 1 us a layer less.)  The result lands as lane (column, kg) <- keys blk * 16 + kg * 4 + r: eight keys of one head per lane, and in exactly the order
 //            the next product wants its A fragment in;
 //   softmax  per lane over its 8 keys, the maximum across the four lane groups by two row swaps, the running sum kept
 //            per lane until the end;
@@ -171,10 +172,10 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
                                         int *frame_anchor)
 {
     constexpr int KK = D / 32, DB = D / 16;              // steps of 32 elements of a head, blocks of 16
-    constexpr int PARTS = GRP == 8 ? 2 : 3;
+    constexpr bool REST = GRP == 8;                      // a second product for the third parts
     constexpr int VS = 2 * D + 32;                       // bytes between two rows of a tile: transposed reads of 8 rows hit every bank once
     constexpr int LPR = D / 8, RPI = 64 / LPR, STEP = 16 * NBLK, NI = STEP / RPI;      // lanes per row, rows per load, keys of a step, loads
-    static_assert((GRP & (GRP - 1)) == 0 && GRP * PARTS <= 16 && (D == 64 || D == 128), "heads and parts fill at most 16 columns");
+    static_assert((GRP & (GRP - 1)) == 0 && GRP <= 8 && (D == 64 || D == 128), "heads and parts fill at most 16 columns");
     static_assert((kAttnOff<GRP> + kAttnEnt * GRP * D) * 4 + 4 <= kAttnScratch && kAttnScratch + kWaves * 32 * VS + kAttnPages * 4 <= kLdsBytes, "LDS");
     task_id = __builtin_amdgcn_readfirstlane(task_id);
     if (NBLK > 1 && task_id == -0x7FFFFFFF) *frame_anchor = 1;       // never true: keeps the call from being a tail call (see gemm_tiles_chunked)
@@ -289,17 +290,18 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
         }
     }
     const float qs = P.qk_norm ? qscale * rnorm(q_sq) : qscale;
-    bf16x8 qp[KK];
+    bf16x8 qp[KK], qr[KK];
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-        uint32_t w[4];
+        uint32_t w[4], r[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             qf[kk][i >> 1][(2 * i) & 3] *= qs;
             qf[kk][i >> 1][(2 * i + 1) & 3] *= qs;
-            w[i] = bf16_part<PARTS>(qf[kk][i >> 1][(2 * i) & 3], qf[kk][i >> 1][(2 * i + 1) & 3], part);
+            w[i] = bf16_part<GRP>(qf[kk][i >> 1][(2 * i) & 3], qf[kk][i >> 1][(2 * i + 1) & 3], part, r[i]);
         }
         qp[kk] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+        qr[kk] = __builtin_bit_cast(bf16x8, u32x4{r[0], r[1], r[2], r[3]});
     }
     // ---- the token of this step: an LDS entry of its own (m = its score, l = 1, o = its V row), by the last wavefront, which
     // ---- has no step of its own in the shortest chunks
@@ -353,9 +355,11 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-            for (int blk = 0; blk < NBLK; ++blk)
-                sacc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    *reinterpret_cast<ETC_AS_LDS const bf16x8 *>(k_out + blk * 16 * VS + kk * 64), qp[kk], sacc[blk], 0, 0, 0);
+            for (int blk = 0; blk < NBLK; ++blk) {
+                const bf16x8 kf = *reinterpret_cast<ETC_AS_LDS const bf16x8 *>(k_out + blk * 16 * VS + kk * 64);
+                sacc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qp[kk], sacc[blk], 0, 0, 0);
+                if constexpr (REST) sacc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qr[kk], sacc[blk], 0, 0, 0);
+            }
         // The registers: rows in flight 64, output 32, queries 16; a refill waits until the fragments read back from the tile are
         // used up, so that nothing a caller keeps in registers has to be saved.
         __builtin_amdgcn_sched_barrier(0);
@@ -383,12 +387,12 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
         const float ref = fmaxf(nm, -1e30f);         // scores of -inf alone: exp2(-inf - ref) = 0 instead of exp2(nan)
         const float sc = exp2_f(mrun - ref);
         float psum = 0.f;
-        uint32_t pw[2 * NBLK];
+        uint32_t pw[2 * NBLK], pr[2 * NBLK];
 #pragma unroll
         for (int j = 0; j < 4 * NBLK; j += 2) {
             const float p0 = exp2_f(sv[j] - ref), p1 = exp2_f(sv[j + 1] - ref);
             psum += p0 + p1;
-            pw[j >> 1] = bf16_part<PARTS>(p0, p1, part);
+            pw[j >> 1] = bf16_part<GRP>(p0, p1, part, pr[j >> 1]);
         }
         lrun = lrun * sc + psum;
         mrun = nm;
@@ -407,11 +411,13 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<ETC_AS_LDS s16x4 *>(v_out + db * 32));
             if constexpr (NBLK == 1) {
                 oacc[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, u32x2{pw[0], pw[1]}), lo, oacc[db], 0, 0, 0);
+                if constexpr (REST) oacc[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, u32x2{pr[0], pr[1]}), lo, oacc[db], 0, 0, 0);
             } else {
                 const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<ETC_AS_LDS s16x4 *>(v_out + 16 * VS + db * 32));
                 const u32x2 a = __builtin_bit_cast(u32x2, lo), c = __builtin_bit_cast(u32x2, hi);
-                oacc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u32x4{pw[0], pw[1], pw[2], pw[3]}),
-                                                                   __builtin_bit_cast(bf16x8, u32x4{a.x, a.y, c.x, c.y}), oacc[db], 0, 0, 0);
+                const bf16x8 vf = __builtin_bit_cast(bf16x8, u32x4{a.x, a.y, c.x, c.y});
+                oacc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u32x4{pw[0], pw[1], pw[2], pw[3]}), vf, oacc[db], 0, 0, 0);
+                if constexpr (REST) oacc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u32x4{pr[0], pr[1], pr[2], pr[3]}), vf, oacc[db], 0, 0, 0);
             }
             if (db % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
