@@ -349,16 +349,16 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
         if (more) row_offsets(base + kWaves * STEP, true);
         to_tile(kr);
         __builtin_amdgcn_sched_barrier(0);
-        f32x4 sacc[NBLK];
+        f32x4 sacc[NBLK], srest[NBLK];
 #pragma unroll
-        for (int blk = 0; blk < NBLK; ++blk) sacc[blk] = f32x4{0, 0, 0, 0};
+        for (int blk = 0; blk < NBLK; ++blk) sacc[blk] = srest[blk] = f32x4{0, 0, 0, 0};
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
             for (int blk = 0; blk < NBLK; ++blk) {
                 const bf16x8 kf = *reinterpret_cast<ETC_AS_LDS const bf16x8 *>(k_out + blk * 16 * VS + kk * 64);
                 sacc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qp[kk], sacc[blk], 0, 0, 0);
-                if constexpr (REST) sacc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qr[kk], sacc[blk], 0, 0, 0);
+                if constexpr (REST) srest[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qr[kk], srest[blk], 0, 0, 0);
             }
         // The registers: rows in flight 64, output 32, queries 16; a refill waits until the fragments read back from the tile are
         // used up, so that nothing a caller keeps in registers has to be saved.
@@ -375,7 +375,11 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
 #pragma unroll
         for (int j = 0; j < 4 * NBLK; ++j) {
             const int key = base + (j >> 2) * 16 + kg * 4 + (j & 3);
-            float v = sacc[j >> 2][j & 3];
+            // An infinite element of a key decides its score (-inf: weight 0) through the leading parts of a query; the lower ones, zero
+            // or of the other sign, would make it a NaN.
+            float v = sacc[j >> 2][j & 3], low = v;
+            if constexpr (REST) low += srest[j >> 2][j & 3];
+            v = part == 0 ? v : (__builtin_isfinite(low) ? low : 0.f);
             v += dpp_f32<0x128>(v);                  // the columns of a head: rotations of the row by 8, 4, 2, 1
             if constexpr (GRP <= 4) v += dpp_f32<0x124>(v);
             if constexpr (GRP <= 2) v += dpp_f32<0x122>(v);

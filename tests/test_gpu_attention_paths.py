@@ -109,3 +109,49 @@ def test_pages_of_many_tokens(page):
         outs.append(out)
         dec.close()
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("d,grp,norm", SHAPES)
+@pytest.mark.parametrize("lens,kv_chunk", [([20, 127, 100], 128), ([300, 511, 500], 512), ([16, 300, 511] * 6, 512)])
+def test_infinite_keys(d, grp, norm, lens, kv_chunk):
+    """Keys with an infinite element whose score is -inf for every head of the group have weight 0, whichever lane, step or wavefront
+    meets them, be it a whole step; a NaN in a key stays a NaN, in its own sequence."""
+    import torch
+    import oracle
+    import paper_2604_13327_amd as etc
+    s = synth.ModelShape(f"inf-d{d}-g{grp}", 1, 256, 2 * grp, 2, d, 512, qk_norm=norm)
+    n_pool, seed = int(sum(synth.pages_needed(n, s.page) for n in lens)) + 2, 41
+    step = fixed_step(s, len(lens), lens, n_pool, seed=5)
+    w, x0 = synth.layer_weights_f32(s, seed, 0), synth.hidden_f32(s, seed, 0, len(lens))
+    model = GpuModel(s, seed, n_pool)
+    k, v = synth.kv_pool_f32(s, seed, 0, n_pool)
+    _, dbg = oracle.layer(oracle.shape_of(s), x0.copy(), w, k.copy(), v.copy(), step.kv_len, step.page_indptr, step.page_ids, debug=True)
+    q, hit = dbg["q_rot"].reshape(len(lens), 2, grp, d), 0
+    for b, n in enumerate(lens):
+        for h in range(2):
+            same = np.flatnonzero(np.abs(np.sign(q[b, h]).sum(0)) == grp)
+            if len(same) == 0:
+                continue
+            for j in {0, 5, n // 2, n - 1} | set(range(16, min(n - 1, 64))):
+                e = same[j % len(same)]
+                page = step.page_ids[step.page_indptr[b] + j // s.page]
+                k[page, j % s.page, h, e] = -np.sign(q[b, h, 0, e]) * np.inf
+                hit += 1
+    assert hit > 0
+    bad = len(lens) - 1
+    k[step.page_ids[step.page_indptr[bad]], 3, 0, 1] = np.nan
+    model.kpool.copy_(torch.from_numpy(k[None]))
+    dec = etc.Decoder(s, kv_chunk_tokens=kv_chunk, sampled_batches=[len(lens)], max_kv_len=max(lens) + 1,
+                      debug_flags=etc.DEBUG_LAYER_HIDDEN, spin_budget=SPIN)
+    model.bind(dec)
+    x = model.hidden(0, len(lens))
+    dec.bind_step(step)
+    dec.launch(x, torch.empty_like(x))
+    torch.cuda.synchronize()
+    got = dec.layer_hidden(0)
+    dec.close()
+    ref = oracle.decode_step(s, 1, x0, lambda l: w, lambda l: (k, v), step)["layers"][0]
+    for b in range(bad):
+        assert np.isfinite(ref[b]).all()
+        assert rel_err(got[b], ref[b]) <= TOL_LAYER, f"sequence {b}"
+    assert np.isnan(ref[bad]).all() and np.isnan(got[bad]).all()
