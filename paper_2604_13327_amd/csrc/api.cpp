@@ -44,6 +44,7 @@ struct DevPlan {          // one instantiated plan (one sampled batch size), hos
     int attn_grid = 1;    // attention task slots of a KV head
     int k_slices_o = 0, k_slices_d = 0;   // slices of K of this plan's O / down projection tasks
     bool all_staged = false;              // every projection task of this plan fits the staged path
+    bool slots_by_xcd = false;            // MoE layer: its row-tile slots go round the XCDs
     Plan host;
     Counters ctr;         // its task records are dropped once they are on the device
     Task *d_queue_tasks = nullptr, *d_tasks = nullptr;
@@ -301,6 +302,7 @@ void fill_launch_params(etc_ctx *c, Params &P)
     P.k_slices_o = dp.k_slices_o;
     P.k_slices_d = dp.k_slices_d;
     P.all_staged = dp.all_staged ? 1 : 0;
+    P.slots_by_xcd = dp.slots_by_xcd ? 1 : 0;
     P.kv_len = c->d_kv_len;
     P.page_indptr = c->d_page_indptr;
     P.page_ids = c->d_page_ids;
@@ -746,6 +748,7 @@ etc_status etc_moe_layer_create(const etc_model_desc *m, const etc_tile_desc *t,
         int syms[4] = {dp.sampled_batch, 0, 0, 0};
         std::string err = build_moe_layer_graph(d, dp.sampled_batch, c->n_queues, &c->graph);
         if (!err.empty()) { c->err = err; return bail(ETC_EINVAL); }
+        dp.slots_by_xcd = c->graph.slots_by_xcd;
         err = instantiate(c->graph, syms, c->n_queues, s->kind == ETC_SCHED_UNFUSED, &dp.host);
         if (!err.empty()) { c->err = err; return bail(ETC_EINVAL); }
         st = upload_plan(c, dp);

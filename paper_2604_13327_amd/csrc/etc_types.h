@@ -184,6 +184,7 @@ struct Params {
     float *ey;                         // expert outputs fp32 [maxB*topk, H]
     int32_t moel;                      // 1: stand-alone MoE layer over a block of B tokens
     int32_t row_merge;                 // stand-alone MoE layer: row tiles a GroupGEMM row block takes at most
+    int32_t slots_by_xcd;              // ... 1: the plan's row-tile slots go round the XCDs (moe_slots_by_xcd)
     uint16_t *x_copy;                  // stand-alone MoE layer: the tokens as they came, bf16 [T, H]
     int32_t *moel_hist;                // [token blocks of 64][E] pairs of the block routed to the expert
     int32_t *moel_base;                // [token blocks][E] first grouped row of the block's pairs of the expert

@@ -616,7 +616,8 @@ std::string build_moe_layer_graph(const ModelDims &m, int Ts, int n_queues, Grap
     const DimExpr one = dim_const(1);
     const int n_blk = (Ts + 63) / 64, n_ht = m.H / 16, n_ft = m.moeF / 8;
     const int r_max = moe_max_row_tiles(m.E, m.topk, Ts, m.tile_m);
-    const int row_block = m.tile_m * moe_row_merge(m.tile_m, m.H, m.moeF);
+    const int row_merge = moe_row_merge(m.tile_m, m.H, m.moeF), row_block = m.tile_m * row_merge;
+    g.slots_by_xcd = moe_slots_by_xcd(m.E, m.topk, Ts, row_merge);
     const int r_g = moe_tiles_per_task(m, Ts, row_block, n_ft, m.H, n_queues);
     const int r_d = moe_tiles_per_task(m, Ts, row_block, n_ht, m.moeF, n_queues);
     const RouterTask rl = router_task(m, Ts, n_queues);
@@ -674,7 +675,7 @@ std::string build_moe_layer_graph(const ModelDims &m, int Ts, int n_queues, Grap
         c.fn = FN_MOE_GATEUP; c.stage = stage++;     // task record: (row-tile slot, first tile, tiles)
         c.rank = 2; c.shape[0] = dim_const(r_max); c.shape[1] = dim_const(n_ft / r_g);
         c.c_mul[1] = r_g; c.c_fill[2] = r_g;
-        c.first_dim_by_xcd = true;
+        c.first_dim_by_xcd = g.slots_by_xcd;
         c.flags = TF_DYN_ROWTILE;
         c.in = {edge_const0(e_group)};
         c.out = {edge_dim(e_eact, 0)};
@@ -685,7 +686,7 @@ std::string build_moe_layer_graph(const ModelDims &m, int Ts, int n_queues, Grap
         c.fn = FN_MOE_DOWN; c.stage = stage++;
         c.rank = 2; c.shape[0] = dim_const(r_max); c.shape[1] = dim_const(n_ht / r_d);
         c.c_mul[1] = r_d; c.c_fill[2] = r_d;
-        c.first_dim_by_xcd = true;
+        c.first_dim_by_xcd = g.slots_by_xcd;
         c.flags = TF_DYN_ROWTILE;
         c.in = {edge_dim(e_eact, 0)};
         c.out = {edge_const0(e_y)};

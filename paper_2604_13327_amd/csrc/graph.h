@@ -62,6 +62,7 @@ struct GraphDecl {
     std::vector<CallDecl> calls;
     int k_slices_o = 0, k_slices_d = 0;   // decoder graphs: slices of K of the O / down projection tasks (0: whole K)
     bool all_staged = false;              // dense decoder graphs: every projection task fits the staged path
+    bool slots_by_xcd = false;            // stand-alone MoE layer: moe_slots_by_xcd
     int add_event(std::initializer_list<DimExpr> shape);
 };
 
@@ -129,6 +130,17 @@ inline int moe_max_row_tiles(int n_experts, int top_k, int batch, int tile_m)
 inline int moe_row_merge(int tile_m, int hidden, int moe_ffn)
 {
     return tile_m > 32 && hidden <= kMaxBufLd && moe_ffn <= kMaxBufLd ? 128 / tile_m : 1;
+}
+
+// Row-tile slots of the stand-alone MoE layer by XCD (first_dim_by_xcd; moel_scan puts the row blocks there): the tasks of a block find
+// its operand, and two blocks of an expert its weights, in one L2.  Worth it where blocks are long: merged row tiles and 48 pairs an
+// expert.  Shorter ones share little, and live tasks that do not follow one another spill into a round of their own.
+// Qwen3-30B-A3B shape, slots in order against by XCD: row tiles of 64, 15 / 16 / 128 / 640 tokens 181 / 187 / 278 / 321 -> 216 / 223 /
+// 279 / 320 us, 800 / 1600 / 2000 / 4001 tokens 377 / 523 / 628 / 1088 -> 373 / 509 / 610 / 1054; of 48, 800 / 2500 tokens 385 / 944 ->
+// 373 / 926; of 24 (not merged), 1024 / 1600 / 3000 tokens 904 / 1290 / 2102 -> 866 / 1329 / 2245; of 16, 2000 tokens 1976 -> 2070.
+inline bool moe_slots_by_xcd(int n_experts, int top_k, int tokens, int row_merge)
+{
+    return row_merge > 1 && (long long)tokens * top_k >= 48LL * n_experts;
 }
 
 // Row tiles of the weights a GroupGEMM task streams, of `per_slot` in all (K elements each): what a queue takes longest

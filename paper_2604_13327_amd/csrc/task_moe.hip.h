@@ -476,9 +476,9 @@ __device__ __noinline__ void moel_scan(const Params &P, float *sm)
     ETC_AS_LDS int32_t *expp = tokp + kRow, *clsp = expp + kRow;                       //   (then their exclusive sums, the total last)
     // A GroupGEMM task takes a row BLOCK of up to row_merge row tiles of one expert: the weights are streamed once for all its columns.
     // Static grids: the blocks fill the first slots, the longest first (by what they cost: more than 64, 32, 16 columns and the
-    // others), so that what a queue gets last is short; the other slots are left without rows.  Where enough slots are left
-    // over, neighbours in that order go in pairs to every eighth slot: the tasks of a slot go to the workgroups of one XCD
-    // (first_dim_by_xcd), so that two blocks of an expert find its weights in one L2, as the tasks of a block do their operand.
+    // others), so that what a queue gets last is short; the other slots are left without rows.  Where the grid is by XCD
+    // (moe_slots_by_xcd) and enough slots are left over, neighbours in that order go in pairs to every eighth slot: the tasks of a
+    // slot go to the workgroups of one XCD (first_dim_by_xcd).
     // Qwen3-30B-A3B layer of 2000 / 4001 tokens: 670 / 1160 us with the blocks in the experts' order and everywhere, 635 / 1162 by XCD, 630 / 1117 now.
     // Dynamic scheduler: an expert's tasks are released as the slots of its row tiles, so its blocks take the first of them.
     const int MB = M * P.row_merge;
@@ -545,7 +545,7 @@ __device__ __noinline__ void moel_scan(const Params &P, float *sm)
         n_blocks += clsp[c * kRow + E];
     }
     const int n_tiles = expp[E];
-    const bool by_xcd = (n_blocks + 2 * kXcds - 1) / (2 * kXcds) * (2 * kXcds) <= n_tiles;
+    const bool by_xcd = P.slots_by_xcd != 0 && (n_blocks + 2 * kXcds - 1) / (2 * kXcds) * (2 * kXcds) <= n_tiles;
     if (!P.moe_dd)
         for (int r = threadIdx.x; r < n_tiles; r += kWgThreads) {
             const int depth = r / kXcds, q = by_xcd ? 2 * (depth / 2 * kXcds + r % kXcds) + depth % 2 : r;

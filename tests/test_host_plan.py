@@ -641,3 +641,24 @@ def test_moe_layer_descriptor_validation():
         etc.moe_layer_plan_build(synth.TINY_MOE, 64, 8, moe_tile_m=65)
     with pytest.raises(etc.EtcError):
         etc.moe_layer_plan_build(dataclasses.replace(synth.TINY_MOE, n_experts=20), 64, 8)
+
+
+@pytest.mark.parametrize("tokens,tile_m,by_xcd", [(15, 64, False), (16, 16, False), (767, 64, False), (768, 64, True), (768, 40, True),
+                                                  (2000, 32, False), (3000, 16, False), (4001, 64, True)])
+def test_queues_of_moe_layer_slots(tokens, tile_m, by_xcd):
+    """Short row blocks: the tasks of the first n slots, the live ones, are spread over the queues as evenly as can be, for every n (16
+    tokens reach about 82 of 128 experts, three tasks each: one round of 256 queues).  Long ones: the queues of a slot share an XCD."""
+    t = etc.moe_layer_plan_build(synth.QWEN3_30B_A3B, tokens, 256, moe_tile_m=tile_m)["tasks"]
+    for fn in (12, 13):
+        calls = t[t["fn"] == fn]
+        slot, queue = calls["c0"], calls["id"] % 256
+        if by_xcd:
+            whole = slot < (slot.max() + 1) // 8 * 8           # the last few go round on their own
+            assert (queue % 8 == (calls["id"].min() + slot) % 8)[whole].all()
+            continue
+        order = np.argsort(slot, kind="stable")
+        assert (np.diff(calls["id"][order]) == 1).all()
+        per_slot = len(calls) // (slot.max() + 1)
+        for n in (1, 5, 82, 85, 86, slot.max() + 1):
+            live = np.bincount(queue[slot < n], minlength=256)
+            assert live.max() == -(-min(n, slot.max() + 1) * per_slot // 256)
