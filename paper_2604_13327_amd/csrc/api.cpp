@@ -35,8 +35,6 @@ std::string g_create_error;
 // Switch for the dynamic-scheduler kernel (off: launching it is refused; the static and unfused schedulers
 // are unaffected).
 constexpr bool kDynamicEnabled = true;
-// Plans of at most this many event counters give each a 128-byte line of its own (A | B and the dispatch counters: 32 MB then).
-constexpr size_t kLineCountersMax = 65536;
 const char *kDynamicOffMsg = "the dynamic scheduler is switched off in this build";
 
 struct DevPlan {          // one instantiated plan (one sampled batch size), host + device copies
@@ -209,11 +207,9 @@ etc_status alloc_events_and_queue(etc_ctx *c)
 {
     size_t n_ev = 1, n_tasks = 1;
     for (const DevPlan &dp : c->plans) {
-        n_ev = std::max(n_ev, dp.ctr.init.size());
+        n_ev = std::max(n_ev, dp.ctr.init.size() << dp.ctr.shift);
         n_tasks = std::max(n_tasks, dp.host.tasks.size());
     }
-    c->base.ev_shift = n_ev <= kLineCountersMax ? 5 : 0;
-    n_ev <<= c->base.ev_shift;
     c->n_events_max = (int)n_ev;
     HIP_TRY(c, dev_alloc(&c->d_events, 2 * n_ev, c->plan_owned));
     HIP_TRY(c, dev_alloc(&c->d_disp, 2 * n_ev, c->plan_owned));
@@ -240,7 +236,7 @@ etc_status arm_on_stream(etc_ctx *c, hipStream_t s)
         a.ev_cur = c->d_events + (c->parity ? N : 0);
         a.ev_init = dp.d_ev_init;
         a.n_events = (int)dp.ctr.init.size();
-        a.ev_shift = c->base.ev_shift;
+        a.ev_shift = dp.ctr.shift;
         a.disp_init = dp.d_disp_init;
         a.disp_cur = c->d_disp + (c->parity ? N : 0);
         a.pending = c->d_pending;
@@ -267,6 +263,7 @@ void fill_launch_params(etc_ctx *c, Params &P)
     P.ev_init = dp.d_ev_init;
     P.ev_next = c->d_events + (c->parity ? 0 : N);
     P.n_events = (int)dp.ctr.init.size();
+    P.ev_shift = dp.ctr.shift;
     P.tasks = dp.d_queue_tasks;
     P.queue_begin = dp.d_queue_begin;
     P.n_queues = c->n_queues;
@@ -896,12 +893,12 @@ etc_status etc_read_debug(etc_ctx *c, int32_t kind, int32_t layer, void *dst, si
     case ETC_DBG_EVENT_COUNTERS: {
         if (c->cur_plan < 0) return fail(c, ETC_ESTATE, "nothing bound");
         const DevPlan &dp = c->plans[c->cur_plan];
-        std::vector<int32_t> events(dp.host.ev_init.size(), 0), raw(dp.ctr.init.size() << P.ev_shift);
+        std::vector<int32_t> events(dp.host.ev_init.size(), 0), raw(dp.ctr.init.size() << dp.ctr.shift);
         if (bytes > events.size() * sizeof(int32_t)) return fail(c, ETC_EINVAL, "more bytes requested than the item holds");
         // the buffer the last launch consumed is the one the next launch re-arms... it was `cur` before the flip
         HIP_TRY(c, hipMemcpy(raw.data(), c->d_events + (c->parity ? 0 : N), raw.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
         for (size_t i = 0; i < dp.ctr.init.size(); ++i) {      // of a spread event: what its counters are off zero, in all
-            const int32_t v = raw[i << P.ev_shift];
+            const int32_t v = raw[i << dp.ctr.shift];
             int32_t &e = events[dp.ctr.event[i]];
             e = (i > 0 && dp.ctr.event[i - 1] == dp.ctr.event[i]) || (i + 1 < dp.ctr.init.size() && dp.ctr.event[i + 1] == dp.ctr.event[i]) ? e + std::abs(v) : v;
         }

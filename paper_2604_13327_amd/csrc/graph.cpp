@@ -216,6 +216,9 @@ Counters place_counters(const Plan &p, bool dynamic)
         if (dynamic && t.fn == FN_MOE_DOWN) wide[t.wait0] = 0;
     }
     for (int e = 0; e < p.dd_n_events; ++e) wide[p.dd_event_base + e] = 0;
+    const long long n_wide = std::count(wide.begin(), wide.end(), 1), all = n + (kEvSpreadN - 1) * n_wide;
+    if (all <= kLinesAnyway || (all <= kLinesMost && 8 * kEvSpreadN * n_wide >= all)) c.shift = 5;
+    else std::fill(wide.begin(), wide.end(), 0);
     std::vector<int32_t> first((size_t)n, 0), seen((size_t)n, 0), notify(p.tasks.size(), -1);
     for (int e = 0; e < n; ++e) {
         first[e] = (int32_t)c.init.size();

@@ -91,7 +91,12 @@ struct Plan {
 // decoder batch 1 374 -> 324; fewest producers 32 instead of 16: the two-layer decoder of hidden 256 takes 71 us instead of 67.
 // Not spread: events a task waits for eight at a time (its wavefront's lanes poll those), events whose count is known at run time
 // only, and under the dynamic scheduler those of row-tile slots, which the routing may cancel one by one.
+// A line each is worth it for counters that many wait for, and costs a miss each: of 2048 / 4096 / 16384 / 60000 events with four producers
+// and one consumer a launch takes 55.3 / 103 / 439 / 1749 us with counters side by side and 54.0 / 106 / 458 / 1856 with lines (256:
+// 11.1 and 8.3).  So a plan of more than kLinesAnyway counters has lines only if an eighth of them are of spread events (decoders: half
+// and more; 16 counters side by side are no better than one, so without lines nothing is spread), and at most kLinesMost (8 MB a buffer).
 struct Counters {
+    int shift = 0;                     // counter i sits at word i << shift: 5, a line each, or 0
     std::vector<int32_t> init;         // initial count of every counter
     std::vector<int32_t> event;        // counter -> event
     std::vector<int32_t> wait;         // event -> what a wait for it names: its first counter, kEvSpread
@@ -99,7 +104,7 @@ struct Counters {
     // dynamic scheduler, by first counter: producers not dispatched, consumers (CSR)
     std::vector<int32_t> disp_init, consumers;
 };
-constexpr int kSpreadMinProducers = 16;
+constexpr int kSpreadMinProducers = 16, kLinesAnyway = 2048, kLinesMost = 65536;
 Counters place_counters(const Plan &p, bool dynamic);
 
 // Binds the symbols and materialises the plan.  unfused: ignore the declared edges and put one

@@ -1,5 +1,6 @@
-"""Where events count on the device: an event of 16 or more producers has 16 counters among which they are divided, and a plan of at
-most 65536 counters keeps each in a line of its own.  Row sums of small whole numbers are exact, whatever the layout."""
+"""Where events count on the device: an event of 16 or more producers has 16 counters among which they are divided, and counters have
+lines of their own, unless a plan has many of them and few of such events.  Row sums of small whole numbers are exact, whatever the
+layout."""
 import numpy as np
 import pytest
 
@@ -34,6 +35,30 @@ def _buffers(g, n, seed):
     return A, C
 
 
+@pytest.mark.parametrize("kind", [0, 1])
+def test_plans_around_the_number_of_counters_that_have_lines(kind):
+    """n row blocks with an event of four producers each and, with `common`, one event of all final sums: its 16 counters are too few
+    for lines above 2048 counters, and 2032 + 16 of them the last plan that has them anyway."""
+    import torch
+    import paper_2604_13327_amd as etc
+    from paper_2604_13327_amd import binding as b
+    for common in (False, True):
+        g = etc.EventGraph(kind=kind, debug_flags=etc.DEBUG_EXEC_COUNT, spin_budget=SPIN)
+        n = g.dim(sym=0, mul=1, add=0)
+        ev, last = g.add_event([n]), g.add_event([g.dim(add=1)])
+        g.add_call(b.FN_ROWSUM_PARTIAL, [n, g.dim(add=4)], out_edges=[g.edge(ev, [(b.MAP_DIM, 0, 1)])])
+        g.add_call(b.FN_ROWSUM_FINAL, [n], in_edges=[g.edge(ev, [(b.MAP_DIM, 0, 1)])], out_edges=[g.edge(last, [(b.MAP_CONST, 0, 0)])] if common else [])
+        for blocks in (2031, 2032, 2033, 2047, 2048, 100):
+            A, C = _buffers(g, blocks, blocks)
+            for rep in range(2):
+                C.fill_(float("nan"))
+                g.launch()
+                torch.cuda.synchronize()
+                assert torch.equal(C, A.sum(1)), (blocks, rep)
+                assert (g.event_counters() == 0).all() and (g.exec_counts() == rep + 1).all(), (blocks, rep)
+        g.close()
+
+
 @pytest.mark.parametrize("kind", [0, 1, 2])
 def test_events_around_the_number_of_producers_that_spreads_them(kind):
     import torch
@@ -52,7 +77,7 @@ def test_events_around_the_number_of_producers_that_spreads_them(kind):
 
 
 def test_more_counters_than_lines():
-    """65600 row blocks with an event each: more counters than get a line of their own."""
+    """65600 row blocks with an event each: counters side by side; then a plan with lines."""
     import torch
     import paper_2604_13327_amd as etc
     from paper_2604_13327_amd import binding as b
