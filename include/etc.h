@@ -338,7 +338,7 @@ etc_status etc_graph_add_call(etc_ctx *ctx, int32_t device_fn, const etc_dim_exp
  * may use slots 0..7 as they like (3..5 keep their meaning when the graph has data-dependent edges).
  * bytes = size of the allocation, checked against the bound shape at launch. */
 etc_status etc_graph_bind_buffer(etc_ctx *ctx, int32_t slot, void *device_ptr, size_t bytes);
-/* Instantiates the template for concrete symbol values (values[4], host). */
+/* Instantiates the template for concrete symbol values (values[4], host).  ETC_EINVAL for 2^24 tasks and more, or 2^30 events. */
 etc_status etc_graph_bind_shape(etc_ctx *ctx, const int32_t *values);
 etc_status etc_graph_launch(etc_ctx *ctx, void *hip_stream);
 

@@ -150,7 +150,7 @@ etc_status fail(etc_ctx *c, etc_status s, const std::string &msg)
 etc_status upload_plan(etc_ctx *c, DevPlan &dp)
 {
     dp.ctr = place_counters(dp.host, c->sched.kind == ETC_SCHED_DYNAMIC);
-    if (dp.ctr.init.size() >= (1u << kEvNthShift)) return fail(c, ETC_EINVAL, "more than 2^24 event counters in one plan");
+    if (dp.ctr.init.size() > (size_t)kEvIndex) return fail(c, ETC_EINVAL, "2^30 events or more in one plan");
     HIP_TRY(c, dev_upload(&dp.d_queue_tasks, dp.ctr.queue_tasks, c->plan_owned));
     HIP_TRY(c, dev_upload(&dp.d_tasks, dp.ctr.tasks, c->plan_owned));
     std::vector<Task>().swap(dp.ctr.queue_tasks);

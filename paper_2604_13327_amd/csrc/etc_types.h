@@ -84,10 +84,13 @@ enum Fn : uint8_t {
 
 // The event indices of a device task record name counters.  A wait: `index` alone, or, with kEvSpread set, the kEvSpreadN counters
 // from `index` on, among which the event's producers are divided; the event has fired when all of them are zero.  A notify: the
-// event's first counter, and above kEvNthShift which one from there the producer decrements.
+// event's counter, or, with kEvSpread set, the first one (below 2^kEvNthShift) and above it which one from there the producer decrements.
 constexpr int kEvSpread = 1 << 30, kEvIndex = kEvSpread - 1, kEvSpreadN = 16, kEvNthShift = 24;
-constexpr int notify_event(int notify) { return notify & ((1 << kEvNthShift) - 1); }
-constexpr int notify_counter(int notify) { return notify_event(notify) + (notify >> kEvNthShift); }
+constexpr int notify_event(int notify) { return (notify & kEvSpread) ? notify & ((1 << kEvNthShift) - 1) : notify; }
+constexpr int notify_counter(int notify)
+{
+    return (notify & kEvSpread) ? notify_event(notify) + ((notify & kEvIndex) >> kEvNthShift) : notify;
+}
 
 // Control words of the ready queue (int32 each, in lines of their own: every workgroup takes a ticket and counts a task done
 // around every task, and one line takes an atomic every 16 ns).

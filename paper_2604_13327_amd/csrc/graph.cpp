@@ -240,7 +240,7 @@ Counters place_counters(const Plan &p, bool dynamic)
             const int e = t.notify0;
             // counted by slot, not by id: the slots a routing cancels are the last ones (ev_drop_producers)
             const int nth = t.fn == FN_MOE_DOWN ? t.c0 * per_slot[t.layer] + t.c1 / std::max(1, t.c2) : seen[e]++;
-            notify[t.id] = first[e] | (wide[e] ? (nth % kEvSpreadN) << kEvNthShift : 0);
+            notify[t.id] = first[e] | (wide[e] ? kEvSpread | (nth % kEvSpreadN) << kEvNthShift : 0);
         }
     auto place = [&](Task t) {
         if (t.wait0 >= 0) t.wait0 = c.wait[t.wait0];

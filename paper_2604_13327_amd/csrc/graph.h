@@ -105,6 +105,7 @@ struct Counters {
     std::vector<int32_t> disp_init, consumers;
 };
 constexpr int kSpreadMinProducers = 16, kLinesAnyway = 2048, kLinesMost = 65536;
+static_assert(kLinesMost < 1 << kEvNthShift, "the first counter of a spread event fits a notify");
 Counters place_counters(const Plan &p, bool dynamic);
 
 // Binds the symbols and materialises the plan.  unfused: ignore the declared edges and put one

@@ -17,10 +17,11 @@ static void check(bool ok, const char *what, int at = 0)
     exit(1);
 }
 
-// n tasks with an event each, and n final tasks that notify one more event
-static Plan rows(int n, int producers, bool common)
+// n tasks with an event each, and n final tasks that notify one more event; events nobody notifies in front of them
+static Plan rows(int n, int producers, bool common, int in_front = 0)
 {
     GraphDecl g;
+    if (in_front) g.add_event({dim_const(in_front)});
     const int ev = g.add_event({dim_const(n)}), last = g.add_event({dim_const(1)});
     CallDecl a, b;
     a.fn = FN_ROWSUM_PARTIAL; a.rank = 2; a.shape[0] = dim_const(n); a.shape[1] = dim_const(producers);
@@ -81,6 +82,10 @@ int main()
             const bool lines = n < 4096;             // (and the counter of the event nobody notifies)
             check(c.shift == (lines ? 5 : 0) && spread(c) == (lines ? n : 0), "spread events", n);
         }
+    }
+    for (int in_front : {(1 << 24) - 2, (1 << 24) + 5}) {      // counters that take more than 24 bits
+        const Counters c = placed(rows(20, 17, true, in_front), false);
+        check(c.shift == 0 && spread(c) == 0 && (int)c.init.size() == in_front + 21, "many events", in_front);
     }
     // the decoders' plans have lines, at every batch
     struct { ModelDims d; int batch, kv; } models[] = {

@@ -8,12 +8,12 @@ pytestmark = pytest.mark.gpu
 SPIN = 400000
 
 
-def _coarse_graph(etc, kind, consumers_first=False, **kw):
-    """partial_sum (n, 4) -> one event -> final_sum (n) -> another event; an event nobody notifies lies in front of them."""
+def _coarse_graph(etc, kind, consumers_first=False, in_front=3, **kw):
+    """partial_sum (n, 4) -> one event -> final_sum (n) -> another event; events nobody notifies lie in front of them."""
     from paper_2604_13327_amd import binding as b
     g = etc.EventGraph(kind=kind, **kw)
     n, one = g.dim(sym=0, mul=1, add=0), g.dim(add=1)
-    g.add_event([g.dim(add=3)])
+    g.add_event([g.dim(add=in_front)])
     e1, e2 = g.add_event([one]), g.add_event([one])
     whole = lambda e: g.edge(e, [(b.MAP_CONST, 0, 0)])
     calls = [lambda: g.add_call(b.FN_ROWSUM_PARTIAL, [n, g.dim(add=4)], out_edges=[whole(e1)]),
@@ -94,6 +94,20 @@ def test_more_counters_than_lines():
             torch.cuda.synchronize()
             assert torch.equal(C, A.sum(1))
             assert (g.event_counters() == 0).all()
+    g.close()
+
+
+def test_more_events_than_24_bits_count():
+    import torch
+    import paper_2604_13327_amd as etc
+    g = _coarse_graph(etc, 0, in_front=(1 << 24) + 5, spin_budget=SPIN)
+    A, C = _buffers(g, 20, 3)
+    for _ in range(2):
+        C.fill_(float("nan"))
+        g.launch()
+        torch.cuda.synchronize()
+        assert torch.equal(C, A.sum(1)) and (g.event_counters() == 0).all()
+    assert g.step_info().n_events == (1 << 24) + 7
     g.close()
 
 
