@@ -8,6 +8,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/etc.h"
@@ -44,10 +45,10 @@ struct DevPlan {          // one instantiated plan (one sampled batch size), hos
     bool all_staged = false;              // every projection task of this plan fits the staged path
     bool slots_by_xcd = false;            // MoE layer: its row-tile slots go round the XCDs
     Plan host;
-    Counters ctr;         // its task records are dropped once they are on the device
+    Counters ctr;
     Task *d_queue_tasks = nullptr, *d_tasks = nullptr;
-    int32_t *d_queue_begin = nullptr, *d_ev_init = nullptr, *d_disp_init = nullptr, *d_ev_consumers = nullptr, *d_consumer_ids = nullptr,
-            *d_seed = nullptr;
+    int32_t *d_queue_begin = nullptr, *d_ev_init = nullptr;      // one allocation
+    int32_t *d_disp_init = nullptr, *d_ev_consumers = nullptr, *d_consumer_ids = nullptr, *d_seed = nullptr;   // dynamic scheduler: as well
     // MoE plans: per layer the flat ids of the event of row-tile slot 0 and of the combine event; static grid sizes
     std::vector<int32_t> moe_layer_events;
     int32_t *d_moe_layer_events = nullptr;
@@ -149,18 +150,21 @@ etc_status fail(etc_ctx *c, etc_status s, const std::string &msg)
 
 etc_status upload_plan(etc_ctx *c, DevPlan &dp)
 {
-    dp.ctr = place_counters(dp.host, c->sched.kind == ETC_SCHED_DYNAMIC);
+    const bool dynamic = c->sched.kind == ETC_SCHED_DYNAMIC;
+    dp.ctr = place_counters(dp.host, dynamic);
     if (dp.ctr.init.size() > (size_t)kEvIndex) return fail(c, ETC_EINVAL, "2^30 events or more in one plan");
-    HIP_TRY(c, dev_upload(&dp.d_queue_tasks, dp.ctr.queue_tasks, c->plan_owned));
-    HIP_TRY(c, dev_upload(&dp.d_tasks, dp.ctr.tasks, c->plan_owned));
-    std::vector<Task>().swap(dp.ctr.queue_tasks);
-    std::vector<Task>().swap(dp.ctr.tasks);
-    HIP_TRY(c, dev_upload(&dp.d_queue_begin, dp.host.queue_begin, c->plan_owned));
-    HIP_TRY(c, dev_upload(&dp.d_ev_init, dp.ctr.init, c->plan_owned));
-    HIP_TRY(c, dev_upload(&dp.d_ev_consumers, dp.ctr.consumers, c->plan_owned));
-    HIP_TRY(c, dev_upload(&dp.d_disp_init, dp.ctr.disp_init, c->plan_owned));
-    HIP_TRY(c, dev_upload(&dp.d_consumer_ids, dp.host.consumer_ids, c->plan_owned));
-    HIP_TRY(c, dev_upload(&dp.d_seed, dp.host.seed_tasks, c->plan_owned));
+    HIP_TRY(c, dev_upload(&dp.d_queue_tasks, dp.host.queue_tasks, c->plan_owned));
+    HIP_TRY(c, dev_upload(&dp.d_tasks, dp.host.tasks, c->plan_owned));
+    // The integer tables in one allocation and one copy: each of their own takes 15 to 25 us (create and bind of a small graph).
+    const std::pair<const std::vector<int32_t> *, int32_t **> tables[] = {
+        {&dp.host.queue_begin, &dp.d_queue_begin}, {&dp.ctr.init, &dp.d_ev_init}, {&dp.ctr.disp_init, &dp.d_disp_init},
+        {&dp.ctr.consumers, &dp.d_ev_consumers}, {&dp.host.consumer_ids, &dp.d_consumer_ids}, {&dp.host.seed_tasks, &dp.d_seed}};
+    const int n_tables = dynamic ? 6 : 2;
+    std::vector<int32_t> words;
+    for (int i = 0; i < n_tables; ++i) words.insert(words.end(), tables[i].first->begin(), tables[i].first->end());
+    int32_t *at = nullptr;
+    HIP_TRY(c, dev_upload(&at, words, c->plan_owned));
+    for (int i = 0; i < n_tables; at += tables[i++].first->size()) *tables[i].second = at;
     // what the data-dependent MoE events need to know of the static grids (dynamic scheduler, Sec. 2.4)
     int n_layers = 0;
     for (const Task &t : dp.host.tasks) n_layers = std::max(n_layers, (int)t.layer + 1);
@@ -168,8 +172,8 @@ etc_status upload_plan(etc_ctx *c, DevPlan &dp)
     dp.moe_rmax = dp.moe_groups_gu = dp.moe_groups_down = 0;
     for (const Task &t : dp.host.tasks) {
         if (t.fn == FN_MOE_DOWN && t.c0 == 0) {
-            dp.moe_layer_events[2 * t.layer] = dp.ctr.wait[t.wait0];
-            dp.moe_layer_events[2 * t.layer + 1] = dp.ctr.wait[t.notify0];
+            dp.moe_layer_events[2 * t.layer] = t.wait0;
+            dp.moe_layer_events[2 * t.layer + 1] = dp.ctr.wait[dp.ctr.event[notify_event(t.notify0)]];
             if (t.layer == 0) dp.moe_groups_down++;
         }
         if (t.fn == FN_MOE_GATEUP && t.layer == 0) {
@@ -212,11 +216,14 @@ etc_status alloc_events_and_queue(etc_ctx *c)
     }
     c->n_events_max = (int)n_ev;
     HIP_TRY(c, dev_alloc(&c->d_events, 2 * n_ev, c->plan_owned));
-    HIP_TRY(c, dev_alloc(&c->d_disp, 2 * n_ev, c->plan_owned));
-    HIP_TRY(c, dev_alloc(&c->d_pending, n_tasks, c->plan_owned));
     c->n_tasks_max = n_tasks;
     if (c->sched.debug_flags & ETC_DEBUG_EXEC_COUNT) HIP_TRY(c, dev_alloc(&c->base.exec_count, n_tasks + 65536, c->plan_owned));
     if (c->sched.debug_flags & ETC_DEBUG_TRACE) HIP_TRY(c, dev_alloc(&c->base.trace, n_tasks * 8, c->plan_owned));
+    c->d_disp = c->d_pending = nullptr;
+    c->base.q_slots = nullptr;
+    if (c->sched.kind != ETC_SCHED_DYNAMIC) return ETC_OK;       // the other schedulers have no use for the rest
+    HIP_TRY(c, dev_alloc(&c->d_disp, 2 * n_ev, c->plan_owned));
+    HIP_TRY(c, dev_alloc(&c->d_pending, n_tasks, c->plan_owned));
     c->base.q_capacity = (int)(n_tasks + 65536 + c->n_queues);
     HIP_TRY(c, dev_alloc(&c->base.q_slots, (size_t)c->base.q_capacity, c->plan_owned));
     return ETC_OK;
@@ -238,7 +245,7 @@ etc_status arm_on_stream(etc_ctx *c, hipStream_t s)
         a.n_events = (int)dp.ctr.init.size();
         a.ev_shift = dp.ctr.shift;
         a.disp_init = dp.d_disp_init;
-        a.disp_cur = c->d_disp + (c->parity ? N : 0);
+        a.disp_cur = c->d_disp ? c->d_disp + (c->parity ? N : 0) : nullptr;
         a.pending = c->d_pending;
         a.n_pending = (int)c->n_tasks_max;
         a.exp_event = c->base.exp_event;
@@ -270,8 +277,10 @@ void fill_launch_params(etc_ctx *c, Params &P)
     P.dyn_tasks = dp.d_tasks;
     P.ev_consumers = dp.d_ev_consumers;
     P.consumer_ids = dp.d_consumer_ids;
-    P.ev_disp_cur = c->d_disp + (c->parity ? N : 0);
-    P.ev_disp_next = c->d_disp + (c->parity ? 0 : N);
+    if (c->d_disp) {
+        P.ev_disp_cur = c->d_disp + (c->parity ? N : 0);
+        P.ev_disp_next = c->d_disp + (c->parity ? 0 : N);
+    }
     P.ev_disp_init = dp.d_disp_init;
     P.task_pending = c->d_pending;
     P.moe_dd = (c->sched.kind == ETC_SCHED_DYNAMIC && dp.moe_rmax > 0) ? 1 : 0;
@@ -1141,7 +1150,7 @@ etc_status etc_graph_bind_shape(etc_ctx *c, const int32_t *values)
     c->plans.clear();
     etc_status st = upload_plan(c, dp);
     if (st != ETC_OK) return st;
-    c->plans.push_back(dp);
+    c->plans.push_back(std::move(dp));
     c->cur_plan = 0;
     st = alloc_events_and_queue(c);
     if (st != ETC_OK) return st;

@@ -160,11 +160,11 @@ std::string instantiate(const GraphDecl &g, const int *sym, int n_queues, bool u
     // static queues: round-robin over the task enumeration (Sec. 3.1).  Every queue is a
     // subsequence of one topological order (calls are listed producers first), so the globally
     // oldest unfinished task always sits at some queue head with its events fired: no deadlock.
-    std::vector<std::vector<Task>> q(n_queues);
-    for (const Task &t : p.tasks) q[t.id % n_queues].push_back(t);
+    const int n_tasks = (int)p.tasks.size(), full = n_tasks / n_queues, rest = n_tasks % n_queues;
+    p.queue_tasks.reserve((size_t)n_tasks);
     p.queue_begin.assign(1, 0);
     for (int i = 0; i < n_queues; ++i) {
-        p.queue_tasks.insert(p.queue_tasks.end(), q[i].begin(), q[i].end());
+        for (int k = 0; k < full + (i < rest ? 1 : 0); ++k) p.queue_tasks.push_back(p.tasks[(size_t)k * n_queues + i]);
         p.queue_begin.push_back((int32_t)p.queue_tasks.size());
     }
 
@@ -172,9 +172,9 @@ std::string instantiate(const GraphDecl &g, const int *sym, int n_queues, bool u
     // waits on has been dispatched, so it is listed under each of those events (events nobody notifies count
     // as passed, as for a wait); an entry of a task that waits on n > 1 events carries n in its top byte.
     if (p.tasks.size() >= (1u << 24)) return "more than 2^24 tasks in one plan";
-    std::vector<std::vector<int32_t>> cons(n_events);
-    for (const Task &t : p.tasks) {
-        int trig[kWaves + 1], n = 0;
+    int trig[kWaves + 1];
+    auto triggers = [&](const Task &t) {
+        int n = 0;
         auto add = [&](int e) {
             if (e < 0 || p.ev_init[e] <= 0) return;
             for (int k = 0; k < n; ++k)
@@ -186,70 +186,89 @@ std::string instantiate(const GraphDecl &g, const int *sym, int n_queues, bool u
             for (int w = 0; w < span; ++w) add(t.wait0 + w);
         }
         add(t.wait1);
+        return n;
+    };
+    p.ev_consumers.assign((size_t)n_events + 1, 0);        // counted, summed up, and moved on to each event's end while the ids are dealt
+    for (const Task &t : p.tasks)
+        for (int n = triggers(t), k = 0; k < n; ++k) ++p.ev_consumers[trig[k] + 1];
+    for (int e = 0; e < n_events; ++e) p.ev_consumers[e + 1] += p.ev_consumers[e];
+    p.consumer_ids.resize((size_t)p.ev_consumers[n_events]);
+    for (const Task &t : p.tasks) {
+        const int n = triggers(t);
         if (n == 0 && !(t.flags & TF_TRIGGERED)) p.seed_tasks.push_back(t.id);
-        for (int k = 0; k < n; ++k) cons[trig[k]].push_back(t.id | (n > 1 ? n << 24 : 0));
+        for (int k = 0; k < n; ++k) p.consumer_ids[p.ev_consumers[trig[k]]++] = t.id | (n > 1 ? n << 24 : 0);
     }
-    p.ev_consumers.assign(1, 0);
+    for (int e = n_events; e > 0; --e) p.ev_consumers[e] = p.ev_consumers[e - 1];
+    p.ev_consumers[0] = 0;
     for (int e = 0; e < n_events; ++e) {
         // GroupGEMM-1 tasks in the order of their row-tile slots, whatever the order of their ids: an expert releases a range of slots
-        if (!cons[e].empty() && p.tasks[cons[e][0] & 0xFFFFFF].fn == FN_MOE_GATEUP)
-            std::sort(cons[e].begin(), cons[e].end(), [&](int32_t a, int32_t b) {
+        const auto first = p.consumer_ids.begin() + p.ev_consumers[e], last = p.consumer_ids.begin() + p.ev_consumers[e + 1];
+        if (first != last && p.tasks[*first & 0xFFFFFF].fn == FN_MOE_GATEUP)
+            std::sort(first, last, [&](int32_t a, int32_t b) {
                 const Task &x = p.tasks[a & 0xFFFFFF], &y = p.tasks[b & 0xFFFFFF];
                 return x.c0 != y.c0 ? x.c0 < y.c0 : x.c1 < y.c1;
             });
-        p.consumer_ids.insert(p.consumer_ids.end(), cons[e].begin(), cons[e].end());
-        p.ev_consumers.push_back((int32_t)p.consumer_ids.size());
     }
     return "";
 }
 
-Counters place_counters(const Plan &p, bool dynamic)
+Counters place_counters(Plan &p, bool dynamic)
 {
     Counters c;
     const int n = (int)p.ev_init.size();
     std::vector<uint8_t> wide((size_t)n, 0);
     for (int e = 0; e < n; ++e) wide[e] = p.ev_init[e] >= kSpreadMinProducers;
+    std::vector<int> per_slot(kMaxLayers, 0);        // GroupGEMM-2 tasks of a row-tile slot
     for (const Task &t : p.tasks) {
+        if (t.fn == FN_MOE_DOWN && t.c0 == 0) ++per_slot[t.layer];
         if (t.wait0 < 0) continue;
         if (t.flags & TF_WAIT0_PER_WAVE)
             for (int w = 0; w < kWaves && t.wait0 + w < n; ++w) wide[t.wait0 + w] = 0;
         if (dynamic && t.fn == FN_MOE_DOWN) wide[t.wait0] = 0;
     }
     for (int e = 0; e < p.dd_n_events; ++e) wide[p.dd_event_base + e] = 0;
-    const long long n_wide = std::count(wide.begin(), wide.end(), 1), all = n + (kEvSpreadN - 1) * n_wide;
-    if (all <= kLinesAnyway || (all <= kLinesMost && 8 * kEvSpreadN * n_wide >= all)) c.shift = 5;
+    const long long n_wide = std::count(wide.begin(), wide.end(), 1), most = n + (kEvSpreadN - 1) * n_wide;
+    if (most <= kLinesAnyway || (most <= kLinesMost && 8 * kEvSpreadN * n_wide >= most)) c.shift = 5;
     else std::fill(wide.begin(), wide.end(), 0);
-    std::vector<int32_t> first((size_t)n, 0), seen((size_t)n, 0), notify(p.tasks.size(), -1);
+    const size_t all = c.shift ? (size_t)most : (size_t)n;
+    c.wait.reserve((size_t)n);
+    c.init.reserve(all);
+    c.event.reserve(all);
+    if (dynamic) {
+        c.disp_init.reserve(all);
+        c.consumers.reserve(all + 1);
+    }
     for (int e = 0; e < n; ++e) {
-        first[e] = (int32_t)c.init.size();
         const int k = wide[e] ? kEvSpreadN : 1;
+        c.wait.push_back((int32_t)c.init.size() | (wide[e] ? kEvSpread : 0));
         for (int i = 0; i < k; ++i) {       // producer j decrements counter j % k
             c.init.push_back((p.ev_init[e] + k - 1 - i) / k);
             c.event.push_back(e);
+            if (!dynamic) continue;
             c.disp_init.push_back(i == 0 ? p.ev_init[e] : 0);
             c.consumers.push_back(p.ev_consumers[i == 0 ? e : e + 1]);
         }
-        c.wait.push_back(first[e] | (wide[e] ? kEvSpread : 0));
     }
-    c.consumers.push_back(p.ev_consumers.back());
-    std::vector<int> per_slot(kMaxLayers, 0);        // GroupGEMM-2 tasks of a row-tile slot
-    for (const Task &t : p.tasks)
-        if (t.fn == FN_MOE_DOWN && t.c0 == 0) ++per_slot[t.layer];
-    for (const Task &t : p.tasks)
+    if (dynamic) c.consumers.push_back(p.ev_consumers.back());
+    std::vector<uint8_t> seen((size_t)n, 0);         // producers of an event so far, modulo kEvSpreadN
+    for (Task &t : p.tasks) {
         if (t.notify0 >= 0) {
             const int e = t.notify0;
-            // counted by slot, not by id: the slots a routing cancels are the last ones (ev_drop_producers)
-            const int nth = t.fn == FN_MOE_DOWN ? t.c0 * per_slot[t.layer] + t.c1 / std::max(1, t.c2) : seen[e]++;
-            notify[t.id] = first[e] | (wide[e] ? kEvSpread | (nth % kEvSpreadN) << kEvNthShift : 0);
+            t.notify0 = c.wait[e];
+            if (wide[e]) {
+                // counted by slot, not by id: the slots a routing cancels are the last ones (ev_drop_producers)
+                const int nth = t.fn == FN_MOE_DOWN ? t.c0 * per_slot[t.layer] + t.c1 / std::max(1, t.c2) : seen[e]++;
+                t.notify0 |= (nth % kEvSpreadN) << kEvNthShift;
+            }
         }
-    auto place = [&](Task t) {
         if (t.wait0 >= 0) t.wait0 = c.wait[t.wait0];
         if (t.wait1 >= 0) t.wait1 = c.wait[t.wait1];
-        t.notify0 = notify[t.id];
-        return t;
-    };
-    for (const Task &t : p.tasks) c.tasks.push_back(place(t));
-    for (const Task &t : p.queue_tasks) c.queue_tasks.push_back(place(t));
+    }
+    for (Task &t : p.queue_tasks) {
+        if (t.notify0 >= 0) t.notify0 = wide[t.notify0] ? p.tasks[t.id].notify0 : c.wait[t.notify0];
+        if (t.wait0 >= 0) t.wait0 = c.wait[t.wait0];
+        if (t.wait1 >= 0) t.wait1 = c.wait[t.wait1];
+    }
     return c;
 }
 

@@ -100,13 +100,12 @@ struct Counters {
     std::vector<int32_t> init;         // initial count of every counter
     std::vector<int32_t> event;        // counter -> event
     std::vector<int32_t> wait;         // event -> what a wait for it names: its first counter, kEvSpread
-    std::vector<Task> tasks, queue_tasks;   // the plan's records with counters in place of events
-    // dynamic scheduler, by first counter: producers not dispatched, consumers (CSR)
-    std::vector<int32_t> disp_init, consumers;
+    std::vector<int32_t> disp_init, consumers;   // dynamic scheduler, by first counter: producers not dispatched, consumers (CSR)
 };
 constexpr int kSpreadMinProducers = 16, kLinesAnyway = 2048, kLinesMost = 65536;
 static_assert(kLinesMost < 1 << kEvNthShift, "the first counter of a spread event fits a notify");
-Counters place_counters(const Plan &p, bool dynamic);
+// The plan's task records name counters in place of events afterwards.
+Counters place_counters(Plan &p, bool dynamic);
 
 // Binds the symbols and materialises the plan.  unfused: ignore the declared edges and put one
 // coarse event between consecutive stages (Sec. 4.5 baseline).  Returns "" or an error text.

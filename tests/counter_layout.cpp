@@ -41,11 +41,13 @@ static Plan rows(int n, int producers, bool common, int in_front = 0)
 
 static Counters placed(const Plan &p, bool dynamic)
 {
-    Counters c = place_counters(p, dynamic);
+    Plan q = p;
+    Counters c = place_counters(q, dynamic);
     std::vector<int32_t> left = c.init;
-    check(c.tasks.size() == p.tasks.size(), "tasks");
-    for (const Task &t : c.tasks) {
+    check(q.tasks.size() == p.tasks.size() && q.queue_tasks.size() == p.queue_tasks.size(), "tasks");
+    for (const Task &t : q.tasks) {
         const int32_t e = p.tasks[t.id].notify0;
+        for (auto w : {&Task::wait0, &Task::wait1}) check(t.*w == (p.tasks[t.id].*w < 0 ? -1 : c.wait[p.tasks[t.id].*w]), "a wait", t.id);
         check((e < 0) == (t.notify0 < 0), "a notify lost", t.id);
         if (e < 0) continue;
         const int32_t at = notify_counter(t.notify0);
@@ -54,7 +56,10 @@ static Counters placed(const Plan &p, bool dynamic)
         --left[at];
     }
     for (size_t i = 0; i < left.size(); ++i) check(left[i] == 0, "a counter that does not end at zero", (int)i);
-    for (const Task &t : c.queue_tasks) check(!memcmp(&t, &c.tasks[t.id], sizeof(Task)), "queue record", t.id);
+    for (size_t i = 0; i < q.queue_tasks.size(); ++i) {
+        const Task &t = q.queue_tasks[i];
+        check(t.id == p.queue_tasks[i].id && !memcmp(&t, &q.tasks[t.id], sizeof(Task)), "queue record", t.id);
+    }
     return c;
 }
 

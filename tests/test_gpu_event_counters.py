@@ -125,3 +125,21 @@ def test_a_wait_that_gives_up_names_the_event():
     with pytest.raises(etc.EtcError):
         g.event_counters()
     g.close()
+
+
+def test_only_the_dynamic_scheduler_holds_dispatch_counters():
+    """4000 events of 17 producers: two buffers of 64000 lines, 16 MB, and as much again for the counts of producers not dispatched."""
+    import torch
+    import paper_2604_13327_amd as etc
+    from paper_2604_13327_amd import binding as b
+    held = []
+    for kind in (0, 1):
+        g = etc.EventGraph(kind=kind)
+        n = g.dim(sym=0, mul=1, add=0)
+        ev = g.add_event([n])
+        g.add_call(b.FN_ROWSUM_PARTIAL, [n, g.dim(add=17)], out_edges=[g.edge(ev, [(b.MAP_DIM, 0, 1)])])
+        before = torch.cuda.mem_get_info()[0]
+        g.bind_shape([4000])
+        held.append(before - torch.cuda.mem_get_info()[0])
+        g.close()
+    assert 16 << 20 <= held[0] <= 24 << 20 and held[1] >= 32 << 20, held
