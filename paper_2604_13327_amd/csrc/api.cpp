@@ -271,6 +271,7 @@ void fill_launch_params(etc_ctx *c, Params &P)
     P.ev_next = c->d_events + (c->parity ? 0 : N);
     P.n_events = (int)dp.ctr.init.size();
     P.ev_shift = dp.ctr.shift;
+    P.plan = c->cur_plan;
     P.tasks = dp.d_queue_tasks;
     P.queue_begin = dp.d_queue_begin;
     P.n_queues = c->n_queues;
@@ -319,12 +320,14 @@ void fill_launch_params(etc_ctx *c, Params &P)
     for (int i = 0; i < 4; ++i) P.gsym[i] = c->sym_values[i];
 }
 
-// The error word; of a wait that gave up the device names the counter, the caller gets the event.
+// The error word; of a wait that gave up the device names the counter and the plan it ran, the caller gets the event.
 etc_status read_error_word(etc_ctx *c, int32_t (&w)[4])
 {
     HIP_TRY(c, hipMemcpy(w, c->base.error_word, sizeof(w), hipMemcpyDeviceToHost));
-    if (w[0] == ERR_WAIT_TIMEOUT && c->cur_plan >= 0 && w[2] >= 0 && w[2] < (int)c->plans[c->cur_plan].ctr.event.size())
-        w[2] = c->plans[c->cur_plan].ctr.event[w[2]];
+    const size_t plan = (size_t)(w[1] >> 8);
+    w[1] &= 255;
+    if (w[0] == ERR_WAIT_TIMEOUT && plan < c->plans.size() && w[2] >= 0 && w[2] < (int)c->plans[plan].ctr.event.size())
+        w[2] = c->plans[plan].ctr.event[w[2]];
     return ETC_OK;
 }
 

@@ -156,12 +156,13 @@ __device__ __forceinline__ void buf_st_4B(__amdgpu_buffer_rsrc_t b, uint32_t lan
 
 __device__ __forceinline__ int ev_peek(const int32_t *p) { return ld_i32(p); }
 
-// Records the first error; later waits see it and give up at once, so the kernel always drains.
+// Records the first error; later waits see it and give up at once, so the kernel always drains.  The plan the launch ran goes with
+// it: the host may have bound another one by the time it looks.
 __device__ __forceinline__ void raise_error(const Params &P, int code, int fn, int ev)
 {
     int expected = 0;
     if (__hip_atomic_compare_exchange_strong(as_global(P.error_word), &expected, code, __ATOMIC_RELAXED, __ATOMIC_RELAXED, ETC_SCOPE)) {
-        st_i32(P.error_word + 1, fn);
+        st_i32(P.error_word + 1, fn | P.plan << 8);
         st_i32(P.error_word + 2, ev);
         st_i32(P.error_word + 3, (int)blockIdx.x);
         // mirrored to pinned host memory: the host sees it without a device call (one store over the bus, error case only)

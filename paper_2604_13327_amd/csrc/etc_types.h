@@ -236,7 +236,8 @@ struct Params {
     uint32_t debug_flags;
     int32_t *exec_count;
     float *layer_hidden;               // [n_layers, maxB, H]
-    int32_t *error_word;               // [4]
+    int32_t plan;                      // which of the context's plans this is, for the error word
+    int32_t *error_word;               // [4]: code, task function | plan << 8, counter or ticket, queue
     int32_t *error_host;               // pinned host word the first error code is mirrored to (or null)
     uint64_t *trace;                   // [n_tasks][8] wall-clock marks, or null
     // generic-graph buffers (row-sum example)

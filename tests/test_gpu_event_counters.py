@@ -127,6 +127,40 @@ def test_a_wait_that_gives_up_names_the_event():
     g.close()
 
 
+def test_a_wait_that_gives_up_names_the_event_of_the_plan_it_ran():
+    """A launch of one plan gives up (nearly every task heads a queue of its own, with a budget of one look), and another plan is
+    bound before anybody looks: the error word names an event that tasks of its function wait for in the plan that was launched."""
+    import torch
+    import synth
+    from harness import GpuModel, fixed_step
+    import paper_2604_13327_amd as etc
+    from paper_2604_13327_amd import binding as b
+    s = synth.ModelShape("give-up", 2, 256, 4, 2, 64, 512)
+    model = GpuModel(s, seed=3, n_pool_pages=128)
+    for launched, bound in [(1, 64), (64, 1)] * 3:
+        dec = etc.Decoder(s, kv_chunk_tokens=32, sampled_batches=[1, 64], max_kv_len=32, spin_budget=1)
+        model.bind(dec)
+        first, then = (fixed_step(s, n, [9] * n, 128, seed=5) for n in (launched, bound))
+        dec.bind_step(first)
+        tasks = b.plan_build(s, 32, launched, dec.step_info().n_queues, 32)["tasks"]
+        x = model.hidden(0, launched)
+        out = torch.empty_like(x)
+        work = torch.zeros(8192, 8192, device="cuda")
+        side = torch.cuda.Stream()               # (the first launch copies weight tables and waits for the default stream)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for _ in range(8):                   # in front of the launch on its stream: it has not run when the other step is bound
+                work = work @ work
+        dec.launch(x, out, stream=side)
+        dec.bind_step(then)
+        torch.cuda.synchronize()
+        word = dec.error_word()
+        mine = tasks[tasks["fn"] == word[1]]
+        waits = set(mine["wait1"]) | {w + i for w, f in zip(mine["wait0"], mine["flags"]) for i in range(8 if f & 1 else 1)}
+        assert word[0] == 1 and word[2] in waits - {-1}, (launched, np.asarray(word), sorted(waits))
+        dec.close()
+
+
 def test_only_the_dynamic_scheduler_holds_dispatch_counters():
     """4000 events of 17 producers: two buffers of 64000 lines, 16 MB, and as much again for the counts of producers not dispatched."""
     import torch
