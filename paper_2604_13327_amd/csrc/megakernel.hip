@@ -548,9 +548,16 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
 #define ETC_ATTN(DD, GG)                                                                   \
     if (!ran && P.d == DD && grp == GG) {                                                  \
         ran = true;                                                                        \
-        if (chunk <= 16 * kWaves) attn_chunk<DD, GG, 1, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, nullptr);       \
-        else if constexpr (STAGED_ONLY) attn_chunk<DD, GG, 1, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, nullptr); \
-        else attn_chunk<DD, GG, 2, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, &anchor);                            \
+        const bool one_step = chunk <= 16 * kWaves;                                        \
+        if constexpr (GG == 1) {                                                           \
+            if (one_step) attn_chunk_one_head<DD, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);                     \
+            else if constexpr (STAGED_ONLY) attn_chunk_one_head<DD, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);    \
+        } else {                                                                           \
+            if (one_step) attn_chunk<DD, GG, 1, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, nullptr);              \
+            else if constexpr (STAGED_ONLY) attn_chunk<DD, GG, 1, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, nullptr); \
+        }                                                                                  \
+        if constexpr (!STAGED_ONLY)                                                        \
+            if (!one_step) attn_chunk<DD, GG, 2, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, &anchor);              \
     }
             ETC_ATTN_SHAPES(ETC_ATTN)
 #undef ETC_ATTN

@@ -478,6 +478,189 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
     attn_finish<D, GRP>(P, b, kvh, ch, chunk, n_keys, j1 == n_keys ? kWaves + 1 : kWaves, sm, task_id);
 }
 
+// One head per KV head, in fp32 on the vector units: D / 8 lanes to a key, 16 keys of a wavefront at a time.  On the matrix cores one
+// column in 16 of a product has work there, and a step of 16 keys is bound by the chain through it (two LDS round trips, products, row
+// swaps: a microsecond), where vector code needs a sum over 16 lanes and no LDS.  So it takes what goes in steps of 16: chunks of at
+// most 128 keys and all of the staged-only instances.  Eight layers, hidden 2048, 16 heads, batch 1 of 8192 / 8 of 500 / 8 of 2048 / 32 of
+// 120 keys: 435 / 429 / 532 / 779 us on the matrix cores, 407 / 395 / 502 / 751 here; in steps of 32, batch 32 / 64 of 2048 keys: 1275 /
+// 2026 there, 1347 / 2195 with vector code, so those stay.
+// Everything else is as in attn_chunk: windows of page ids, rows requested ahead of the wait, the new token from its fp32 row.
+template <int D, bool LOOP>
+__device__ __noinline__ void attn_chunk_one_head(const Params &P, int layer, int b, int kvh, int ch, int chunk, float *sm, int ev0, int ev1, int task_id)
+{
+    constexpr int LPK = D / 8, KPL = 64 / LPK, BATCH = 4, STEP = KPL * BATCH;      // lanes per key, keys per load, loads and keys of a step
+    static_assert((kAttnOff<1> + kAttnEnt * D) * 4 + 4 <= kAttnScratch && kAttnScratch + kAttnPages * 4 <= kLdsBytes, "LDS");
+    task_id = __builtin_amdgcn_readfirstlane(task_id);
+    layer = __builtin_amdgcn_readfirstlane(layer);       // uniform arguments back into scalar registers
+    b = __builtin_amdgcn_readfirstlane(b);
+    kvh = __builtin_amdgcn_readfirstlane(kvh);
+    ch = __builtin_amdgcn_readfirstlane(ch);
+    chunk = __builtin_amdgcn_readfirstlane(chunk);
+    ev0 = __builtin_amdgcn_readfirstlane(ev0);
+    ev1 = __builtin_amdgcn_readfirstlane(ev1);
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id()), lane = lane_id(), tq = lane / LPK, dl = lane % LPK;
+    const int n_keys = __builtin_amdgcn_readfirstlane(gld_i32(P.kv_len + b)) + 1;
+    const int j0 = ch * chunk;
+    const int j1 = j0 + min(n_keys - j0, chunk);
+    const int jc1 = min(j1, n_keys - 1);                 // cached keys of the chunk: [j0, jc1)
+    const int32_t *pages = P.page_ids + __builtin_amdgcn_readfirstlane(gld_i32(P.page_indptr + b));
+    const size_t lbase = (size_t)layer * (size_t)P.pool_layer_stride + (size_t)kvh * D;
+    const float qscale = 1.44269504088896f / sqrtf((float)D);      // and log2(e)
+    const int psh = P.page_shift, pmask = P.page - 1;
+    ETC_AS_LDS float *s_m = as_lds(sm), *s_l = s_m + kAttnEnt, *s_o = s_m + kAttnOff<1>;      // [kAttnEnt], [kAttnEnt], [kAttnEnt][D]
+    uint32_t pg_base = (uint32_t)(uintptr_t)(reinterpret_cast<ETC_AS_LDS char *>(as_lds(sm)) + kAttnScratch);
+    asm volatile("" : "+v"(pg_base));                    // computed once (see attn_chunk)
+    ETC_AS_LDS int *s_pg = reinterpret_cast<ETC_AS_LDS int *>(pg_base);
+
+    int w0 = j0, w1 = LOOP ? attn_window_end(j0, jc1, psh) : jc1;
+    auto load_pages = [&](int first) {
+        for (int i = first + (int)threadIdx.x; i < attn_window_pages(w0, w1, psh); i += kWgThreads) s_pg[i] = gld_i32(pages + (w0 >> psh) + i);
+    };
+    // rows of a step: this lane has piece dl of the rows of the keys base + u * KPL + tq; beyond the window: its last key again, weight 0
+    u32x4 kr[BATCH], vr[BATCH];
+    const uint32_t row_len = (uint32_t)__builtin_amdgcn_readfirstlane(P.nkv * D);
+    auto request = [&](int base, bool from_lds) {
+        int jc[BATCH], page[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int j = base + u * KPL + tq;
+            jc[u] = j < w1 ? j : max(w1 - 1, w0);            // (a chunk of the new token alone: that token's place, not used)
+            page[u] = from_lds ? s_pg[(jc[u] - w0) >> psh] : gld_i32(pages + (jc[u] >> psh));
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const size_t off = lbase + (size_t)(((uint32_t)page[u] << psh) + (uint32_t)(jc[u] & pmask)) * row_len + dl * 8;
+            kr[u] = gld_16B(P.kpool + off);
+            vr[u] = gld_16B(P.vpool + off);
+        }
+    };
+    auto widen = [](u32x4 r, float (&f)[8]) {
+        const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { f[2 * i] = bf16_low(w[i]); f[2 * i + 1] = bf16_high(w[i]); }
+    };
+    int page_id = 0;
+    if (LOOP) page_id = gld_i32(pages + (w0 >> psh) + min((int)threadIdx.x, max((w1 - w0 - 1) >> psh, 0)));
+    request(w0 + wave * STEP, false);
+    if (LOOP) {
+        s_pg[threadIdx.x] = page_id;
+        load_pages(kWgThreads);
+    }
+    if (ev0 < 0 && ev1 < 0) __syncthreads();             // the wait has a barrier
+    wg_wait(P, ev0, ev1, FN_ATTN);
+    trace_mark(P, task_id, 1);
+
+    // ---- the query, and for the step's own token its K and V row: one round trip ----------------------------------
+    const bool takes_new = j1 == n_keys && wave == 0;
+    float q[8], kn[8], vn[8], q_sq[D / 16], k_sq[D / 16];
+    auto row_of = [&](const float *p, float (&f)[8]) {
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) ld_f32x2(p + dl * 8 + i, f[i], f[i + 1]);
+    };
+    auto sum_of_squares = [&](int hd, float (&t)[D / 16]) {      // qk_norm models: the sums the head's projection tasks left
+#pragma unroll
+        for (int i = 0; i < D / 16; ++i) t[i] = ld_f32(P.qk_ssq + ((size_t)b * (P.nq + P.nkv) + hd) * (size_t)(D / 16) + i);
+    };
+    auto rnorm = [&](const float (&t)[D / 16]) {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < D / 16; ++i) s += t[i];
+        return 1.0f / sqrtf(s / (float)D + P.eps);
+    };
+    row_of(P.qbuf + ((size_t)b * P.nq + kvh) * D, q);
+    if (P.qk_norm) sum_of_squares(kvh, q_sq);
+    if (takes_new) {
+        row_of(P.knew + ((size_t)b * P.nkv + kvh) * D, kn);
+        row_of(P.vnew + ((size_t)b * P.nkv + kvh) * D, vn);
+        if (P.qk_norm) sum_of_squares(P.nq + kvh, k_sq);
+    }
+    const float qs = P.qk_norm ? qscale * rnorm(q_sq) : qscale;
+    float m = -INFINITY, l = 0.f, o[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { q[i] *= qs; o[i] = 0.f; }
+    if (takes_new) {                                     // the first key of lane group 0 of wavefront 0: weight 1
+        const float rk = P.qk_norm ? rnorm(k_sq) : 1.f;
+        float sc = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { kn[i] *= rk; sc += q[i] * kn[i]; }
+        sc = lanes_sum<LPK>(sc);
+        if (tq == 0) {
+            m = sc;
+            l = 1.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o[i] = vn[i];
+            if (P.qk_norm)       // K-Norm + RoPE + CacheAppend (Sec. 4.3): the key's norm is complete here, and so is its cache row
+                *as_global(reinterpret_cast<u32x4 *>(P.kpool + lbase + (size_t)gld_i32(P.kv_slot + b) * row_len + dl * 8)) =
+                    u32x4{pack_bf16(kn[0], kn[1]), pack_bf16(kn[2], kn[3]), pack_bf16(kn[4], kn[5]), pack_bf16(kn[6], kn[7])};
+        }
+    }
+
+    // ---- the wavefront's steps: all scores, one new maximum and one rescale, then the weighted rows ------------------
+    auto fold = [&](int base) {
+        float p[BATCH], nm = m;
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            float kf[8], sc = 0.f;
+            widen(kr[u], kf);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sc += q[i] * kf[i];
+            sc = lanes_sum<LPK>(sc);
+            p[u] = base + u * KPL + tq < w1 ? sc : -INFINITY;
+            nm = fmaxf(nm, p[u]);
+        }
+        const float ref = fmaxf(nm, -1e30f);             // scores of -inf alone: exp2(-inf - ref) = 0 instead of exp2(nan)
+        const float sc = exp2_f(m - ref);
+        l *= sc;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] *= sc;
+        m = nm;
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            float vf[8];
+            widen(vr[u], vf);
+            p[u] = exp2_f(p[u] - ref);
+            l += p[u];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o[i] += p[u] * vf[i];
+        }
+    };
+    for (;;) {
+        int base = w0 + wave * STEP;
+        if (base < w1) fold(base);                       // uniform per wavefront
+        if constexpr (LOOP)
+            for (base += kWaves * STEP; base < w1; base += kWaves * STEP) {
+                request(base, true);
+                fold(base);
+            }
+        if (!LOOP || w1 >= jc1) break;                   // uniform
+        w0 = w1;
+        w1 = attn_window_end(w0, jc1, psh);
+        __syncthreads();                                 // every wavefront is done with the page ids
+        load_pages(0);
+        __syncthreads();
+        request(w0 + wave * STEP, true);
+    }
+    trace_mark(P, task_id, 2);
+
+    // ---- the wavefront's partial result: its lane groups saw different keys; entry `wave` of the LDS table ----
+#pragma unroll
+    for (int off = LPK; off < 64; off <<= 1) {
+        const float om = __shfl_xor(m, off, 64), ol = __shfl_xor(l, off, 64), nm = fmaxf(m, om), ref = fmaxf(nm, -1e30f);
+        const float sa = exp2_f(m - ref), sb = exp2_f(om - ref);
+        l = l * sa + ol * sb;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] = o[i] * sa + __shfl_xor(o[i], off, 64) * sb;
+        m = nm;
+    }
+    if (tq == 0) {
+        if (dl == 0) { s_m[wave] = m; s_l[wave] = l; }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s_o[(size_t)wave * D + dl * 8 + i] = o[i];
+    }
+    __syncthreads();
+    attn_finish<D, 1>(P, b, kvh, ch, chunk, n_keys, kWaves, sm, task_id);
+}
+
 // Merge of the chunk partials of (sequence b, KV head kvh): ascending chunk order, whoever runs it.
 template <int D, int GRP>
 __device__ __forceinline__ void attn_merge_chunks(const Params &P, int b, int kvh, int nc)

@@ -48,7 +48,7 @@ def _check(shape, lens, kv_chunk, max_len, kind=0):
     dec.close()
 
 
-SHAPES = [(128, 1, False), (128, 4, False), (128, 8, True), (64, 2, True), (64, 4, False)]
+SHAPES = [(128, 1, False), (128, 1, True), (128, 4, False), (128, 8, True), (64, 2, True), (64, 4, False)]
 
 
 def _shape(d, grp, norm, page=16):
@@ -68,7 +68,7 @@ def test_steps_and_chunks(d, grp, norm, lens, kv_chunk):
 
 
 @pytest.mark.parametrize("batch", [2, 17])
-@pytest.mark.parametrize("d,grp", [(128, 8), (64, 4)])
+@pytest.mark.parametrize("d,grp", [(128, 1), (128, 8), (64, 4)])
 def test_more_pages_than_the_window_holds(d, grp, batch):
     """Pages of one token, chunks of 8192 keys: two windows of page ids, the second one key, 200 keys and 904 keys long."""
     lens = ([4097, 5000] if batch == 2 else [4097, 4296, 5000, 4096, 4095] + [7] * (batch - 5))
