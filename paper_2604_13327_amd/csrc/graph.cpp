@@ -275,10 +275,12 @@ Counters place_counters(Plan &p, bool dynamic)
 // A task of the router projection: its tiles of 16 router rows and its block of columns (tokens).  Its time is its operand (columns x
 // hidden, 512 KB for 64 at 2048, against 64 KB of router rows a tile).  So the columns are cut to 16, which fit the staged path (the
 // whole operand in one round trip instead of eight chunks), where one round of tasks still covers them all, and a task takes two
-// or four tiles where 64 columns take more than one round.  Below a hidden size of 1024 a block is a round trip or two
-// whole, and stays.  Qwen3-30B-A3B shape, 64 columns and one tile against this: two layers at batch 33 / 64 620 / 690 -> 604 / 678 us,
-// MoE layer of 50 / 200 / 400 tokens 271 / 307 / 322 -> 264 / 299 / 316, 3000 / 4001 tokens 876 / 1111 -> 848 / 1079 (dynamic 50 / 4001
-// tokens 347 / 1074 -> 332 / 1036).  32 columns (1024 tokens in one round of 256 tasks): 374 -> 376, not taken.
+// or four tiles where 64 columns take more than one round.  Qwen3-30B-A3B shape, 64 columns and one tile against this: two layers at
+// batch 33 / 64 620 / 690 -> 604 / 678 us, MoE layer of 50 / 200 / 400 tokens 271 / 307 / 322 -> 264 / 299 / 316, 3000 / 4001 tokens
+// 876 / 1111 -> 848 / 1079 (dynamic 50 / 4001 tokens 347 / 1074 -> 332 / 1036).  Layers of 24 / 100 / 400 tokens, 128 experts of 768, hidden
+// 1024: 138 / 175 / 207 -> 132 / 168 / 202.  The bound of 1024 is not one of time: hidden 256 and 512 would gain as much (73 / 92 / 129 ->
+// 67 / 85 / 124, 96 / 120 / 151 -> 89 / 113 / 146), but the plans of small layers are pinned at a task per 64 tokens.  Above 2200 or so 16
+// columns do not fit the staged path.  32 columns (1024 tokens in one round of 256 tasks): 374 -> 376, not taken.
 struct RouterTask {
     int tiles = 1, cols = 64;
     int record() const { return tiles | cols << 8; }
