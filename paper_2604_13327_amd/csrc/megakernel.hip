@@ -549,15 +549,11 @@ __device__ __forceinline__ void run_task(const Params &P, const Params &PL, cons
     if (!ran && P.d == DD && grp == GG) {                                                  \
         ran = true;                                                                        \
         const bool one_step = chunk <= 16 * kWaves;                                        \
-        if constexpr (GG == 1) {                                                           \
-            if (one_step) attn_chunk_one_head<DD, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);                     \
-            else if constexpr (STAGED_ONLY) attn_chunk_one_head<DD, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);    \
-        } else {                                                                           \
-            if (one_step) attn_chunk<DD, GG, 1, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, nullptr);              \
-            else if constexpr (STAGED_ONLY) attn_chunk<DD, GG, 1, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, nullptr); \
-        }                                                                                  \
-        if constexpr (!STAGED_ONLY)                                                        \
-            if (!one_step) attn_chunk<DD, GG, 2, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, &anchor);              \
+        if (GG == 1 && one_step) attn_chunk_one_head<DD, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id);                  \
+        else if (GG == 1 && (STAGED_ONLY || n_keys - ch * chunk <= kOneHeadKeys)) attn_chunk_one_head<DD, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id); \
+        else if (GG > 1 && one_step) attn_chunk<DD, GG, 1, false>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, nullptr);       \
+        else if constexpr (!STAGED_ONLY) attn_chunk<DD, GG, 2, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, &anchor);    \
+        else if constexpr (GG > 1) attn_chunk<DD, GG, 1, true>(PL, t.layer, b, kvh, ch, chunk, sm, w0, w1, t.id, nullptr);          \
     }
             ETC_ATTN_SHAPES(ETC_ATTN)
 #undef ETC_ATTN

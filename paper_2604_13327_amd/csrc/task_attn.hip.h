@@ -480,11 +480,13 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
 
 // One head per KV head, in fp32 on the vector units: D / 8 lanes to a key, 16 keys of a wavefront at a time.  On the matrix cores one
 // column in 16 of a product has work there, and a step of 16 keys is bound by the chain through it (two LDS round trips, products, row
-// swaps: a microsecond), where vector code needs a sum over 16 lanes and no LDS.  So it takes what goes in steps of 16: chunks of at
-// most 128 keys and all of the staged-only instances.  Eight layers, hidden 2048, 16 heads, batch 1 of 8192 / 8 of 500 / 8 of 2048 / 32 of
-// 120 keys: 435 / 429 / 532 / 779 us on the matrix cores, 407 / 395 / 502 / 751 here; in steps of 32, batch 32 / 64 of 2048 keys: 1275 /
-// 2026 there, 1347 / 2195 with vector code, so those stay.
+// swaps: a microsecond), where vector code needs a sum over 16 lanes and no LDS.  So it takes what goes in steps of 16, chunks of at
+// most 128 keys and all of the staged-only instances, and chunks of at most kOneHeadKeys, which are one step of 32 there.  Eight layers,
+// hidden 2048, 16 heads, batch 1 of 8192 / 8 of 500 / 8 of 2048 / 32 of 120 keys: 435 / 429 / 532 / 779 us on the matrix cores, 407 / 395 /
+// 502 / 751 here.  In steps of 32, batch 64 of 250 / 500 / 1000 / 2048 keys at most: 1159 / 1260 / 1496 / 2026 there, 1123 here, 1247 /
+// 1575 / 2195 with vector code for all.
 // Everything else is as in attn_chunk: windows of page ids, rows requested ahead of the wait, the new token from its fp32 row.
+constexpr int kOneHeadKeys = 256;
 template <int D, bool LOOP>
 __device__ __noinline__ void attn_chunk_one_head(const Params &P, int layer, int b, int kvh, int ch, int chunk, float *sm, int ev0, int ev1, int task_id)
 {
