@@ -661,7 +661,7 @@ __global__ void __launch_bounds__(kWgThreads) megakernel_static(const Params P)
 // ---- dynamic scheduler ------------------------------------------------------------------------
 // Ready queue: q_slots[ticket] = (epoch << 32) | (task id + 1).  push: reserve tickets with an atomic
 // add on tail, then publish each slot; pop: take a ticket with an atomic add on head, then wait for
-// that slot to carry this launch's epoch.  Control words: head, tail, -, tasks completed.  A popper
+// that slot to carry this launch's epoch.  Control words: head, tail and tasks completed, a line each.  A popper
 // that finds its slot empty leaves once every task of the step has counted itself completed.
 // Slots and control words follow the rule of all cross-task data here: device-scope stores and loads,
 // no cache-wide fence.

@@ -137,7 +137,8 @@ __device__ __forceinline__ float groups_sum(float v)
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// A chunk on the matrix cores.  A wavefront takes 32 (NBLK = 1: 16) keys per step:
+// A chunk on the matrix cores (one head per KV head: long ones only, see attn_chunk_one_head).  A wavefront takes 32 (NBLK = 1: 16)
+// keys per step:
 //   scores   S^T[key][column] = K[key][:] . Q[column][:]   A = K rows, read as fragments (lane (key % 16, kg): 16 bytes of its
 //            key's row) from a wavefront-private LDS tile, B = the queries as sums of bf16 parts.  The 16 columns hold the parts side by
 //            side: column n is part n / GRP of head n % GRP (three parts, all 24 bits of a query), so one product per
@@ -238,7 +239,7 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
 #pragma unroll
         for (int i = 0; i < NI; ++i) *reinterpret_cast<ETC_AS_LDS u32x4 *>(vt + (i * RPI + lr) * VS + lp * 16) = r[i];
     };
-    // In front of the wait: page ids, the first step's K rows and in the shortest chunks its V rows.  (The poll queues behind what
+    // In front of the wait: page ids, the first step's K rows and, in steps of 16 keys, its V rows.  (The poll queues behind what
     // its wavefront has requested, so no more than that; nor may it wait for a page id behind the rows.)
     int page_id = 0;
     if (LOOP) page_id = gld_i32(pages + (w0 >> psh) + min((int)threadIdx.x, max((w1 - w0 - 1) >> psh, 0)));
@@ -334,7 +335,7 @@ __device__ __noinline__ void attn_chunk(const Params &P, int layer, int b, int k
         request(P.vpool, vr);
     }
 
-    // ---- the wavefront's steps: 32 keys each -------------------------------------------------------------------
+    // ---- the wavefront's steps: 16 NBLK keys each -------------------------------------------------------------------
     f32x4 oacc[DB];                                      // O[row kg * 4 + r][db * 16 + n16]
 #pragma unroll
     for (int db = 0; db < DB; ++db) oacc[db] = f32x4{0, 0, 0, 0};
